@@ -98,6 +98,12 @@ void set_gemm_config(int config) { g_gemm_config = config; }
 double gemm_sharing() { return g_gemm_sharing; }
 void set_gemm_sharing(double share) { g_gemm_sharing = share < 0.0 ? 0.0 : (share > 1.0 ? 1.0 : share); }
 
+// Rounds of 256 CUs that a launch of `tiles` workgroups pays for: whole ones alone on the chip; next to kernels of other
+// lanes the CUs that its last round leaves idle are not lost, so the count moves towards tiles / 256.
+double rounds_of(long tiles) {
+  return g_gemm_sharing * (double)tiles / 256.0 + (1.0 - g_gemm_sharing) * (double)((tiles + 255) / 256);
+}
+
 // Tile choice for the direct-to-LDS kernels by a cost model fitted to timings on MI355X: a launch
 // runs ceil(tiles / 256 CUs) rounds; a round costs one K tile's time per 32 columns of K (0.84 us for
 // 256 x 256 with 8 wavefronts, 0.53 us for 256 x 128 (one wavefront per SIMD, three-stage ring; measured on a chip in
@@ -106,13 +112,14 @@ void set_gemm_sharing(double share) { g_gemm_sharing = share < 0.0 ? 0.0 : (shar
 // tile).  Large tiles reuse operands better; small ones waste less of the last round, which matters
 // less the more the chip is shared with other streams' kernels (set_gemm_sharing).  Returns -1 if no
 // configuration takes every problem.
-int choose_dma_config(const GemmArgs* gs, int count) {
-  if (g_gemm_config >= 0 && g_gemm_config != 3) {
+int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
+  *cost_us = 0.0;
+  if (g_gemm_config >= 0 && g_gemm_config != 3 && g_gemm_config < 12) {
     for (int i = 0; i < count; ++i)
       if (!gemm_dma_supported(gs[i], g_gemm_config)) return -1;
     return g_gemm_config;
   }
-  if (g_gemm_config != -1) return -1;
+  if (g_gemm_config != -1) return -1;  // 3, 12, 13
   static const struct { int config; double per_ktile, epilogue, start; } kTiles[] = {
       {6, 0.79, 3.0, 7.0}, {2, 0.53, 2.0, 4.5}, {4, 0.295, 2.3, 3.3}};
   int best = -1;
@@ -130,12 +137,10 @@ int choose_dma_config(const GemmArgs* gs, int count) {
       ktiles += (double)ti * (gs[i].K / 32);
     }
     if (!ok || tiles == 0) continue;
-    // Alone on the chip a launch pays for whole rounds; next to kernels of other lanes the CUs its
-    // last round leaves idle are not lost, so the count moves towards tiles / 256.
-    const double rounds = g_gemm_sharing * (double)tiles / 256.0 + (1.0 - g_gemm_sharing) * (double)((tiles + 255) / 256);
-    const double cost = t.start + rounds * ((ktiles / tiles) * t.per_ktile + t.epilogue);
+    const double cost = t.start + rounds_of(tiles) * ((ktiles / tiles) * t.per_ktile + t.epilogue);
     if (best < 0 || cost < best_cost) best = t.config, best_cost = cost;
   }
+  *cost_us = best_cost;
   // The same tile with 64-wide K tiles (half the barriers per unit of work) where K allows it.  The 256 x 128 tile
   // and, for a launch of at most one tile per CU alone on the chip, the 128 x 128 tile take a ring of three such
   // stages: with one wavefront per SIMD nothing else covers a load that is late, and one more tile of look-ahead
@@ -155,12 +160,49 @@ int choose_dma_config(const GemmArgs* gs, int count) {
   return best;
 }
 
+// Tile edge of the wavefront-split kernel for these problems, 0 if it does not take them or another kernel is better.
+// The same cost model, in us: a round costs the K tiles of its tiles plus an epilogue.  bf16: 0.178 us per 64 of K for
+// 64 x 64 (four rounds of 4096 x 1024: 19 us at K = 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix
+// instructions (256 flop per clock and CU): a 32 x 32 tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
+int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
+  if (g_gemm_config >= 0 && g_gemm_config < 12) return 0;
+  for (int i = 0; i < count; ++i)
+    if (!gemm_wave_supported(dtype, gs[i])) return 0;
+  if (g_gemm_config >= 12) return g_gemm_config == 12 ? 64 : 32;
+  static const struct { int edge; double per_k, epilogue, start; } kTiles[2][2] = {
+      {{64, 0.178 / 64, 1.0, 3.0}, {32, 0.075 / 64, 0.6, 2.5}}, {{64, 0.0154, 1.0, 3.0}, {32, 0.0044, 0.6, 2.5}}};
+  int best = 0;
+  double best_cost = 0.0;
+  for (const auto& t : kTiles[dtype == HANAYO_BF16 ? 0 : 1]) {
+    long tiles = 0;
+    double k = 0.0;
+    for (int i = 0; i < count; ++i) {
+      const long ti = (long)((gs[i].M + t.edge - 1) / t.edge) * ((gs[i].N + t.edge - 1) / t.edge);
+      tiles += ti;
+      k += (double)ti * gs[i].K;
+    }
+    const double cost = t.start + rounds_of(tiles) * (k / tiles * t.per_k + t.epilogue);
+    if (!best || cost < best_cost) best = t.edge, best_cost = cost;
+  }
+  if (dtype != HANAYO_BF16) return best;
+  double dma_cost;
+  if (choose_dma_config(gs, count, &dma_cost) >= 0) return dma_cost <= best_cost ? 0 : best;
+  // a ragged problem that fills the chip with 256 x 256 tiles of the staged kernel (2040 x 8192 x 2048: 83 us against 101)
+  if (count == 1 && gs[0].M % 8 == 0) {
+    const long tiles = (long)((gs[0].M + 255) / 256) * ((gs[0].N + 255) / 256);
+    if (tiles >= 256 && 8.0 + rounds_of(tiles) * (2.3 * gs[0].K / 64 + 12.0) < best_cost) return 0;
+  }
+  return best;
+}
+
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
   if (g.M < 1 || g.N < 1 || g.K < 1) return set_error(HANAYO_EINVAL, "gemm: empty problem");
   if (g.colsum && (!g.b_t || !g.colsum_scratch)) return set_error(HANAYO_EINVAL, "gemm: colsum needs b_t and scratch");
+  if (const int edge = choose_wave_edge(dtype, &g, 1)) return gemm_wave_group(dtype, &g, 1, edge, stream);
   if (dtype == HANAYO_BF16) {
     // the direct-to-LDS kernels fold the column sums into the GEMM
-    const int config = choose_dma_config(&g, 1);
+    double cost;
+    const int config = choose_dma_config(&g, 1, &cost);
     if (config >= 0) return gemm_dma(g, config, stream);
   }
   int rc;
@@ -172,7 +214,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
 
 int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
   if (count < 1 || count > 4) return set_error(HANAYO_EINVAL, "gemm_group: %d problems", count);
-  bool alike = dtype == HANAYO_BF16;
+  bool alike = true;
   for (int i = 0; i < count; ++i) {
     const GemmArgs& g = gs[i];
     if (g.M < 1 || g.N < 1 || g.K < 1) return set_error(HANAYO_EINVAL, "gemm: empty problem");
@@ -180,7 +222,11 @@ int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
     alike = alike && g.a_t == gs[0].a_t && g.b_t == gs[0].b_t && g.epi == gs[0].epi;
   }
   if (alike) {
-    const int config = choose_dma_config(gs, count);
+    if (const int edge = choose_wave_edge(dtype, gs, count)) return gemm_wave_group(dtype, gs, count, edge, stream);
+  }
+  if (alike && dtype == HANAYO_BF16) {
+    double cost;
+    const int config = choose_dma_config(gs, count, &cost);
     if (config >= 0) return gemm_dma_group(gs, count, config, stream);
   }
   for (int i = 0; i < count; ++i) {

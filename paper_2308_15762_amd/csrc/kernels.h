@@ -106,7 +106,12 @@ bool gemm_dma_supported(const GemmArgs& g, int config);
 void gemm_dma_tile(int config, int& bm, int& bn);
 int gemm_dma(const GemmArgs& g, int config, hipStream_t stream);
 int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream);
-// -1 = automatic choice; 0, 1, 2, 4 .. 11 = force that direct-to-LDS configuration where it applies; 3 = staged kernel only
+// Tiles of edge x edge (64 or 32) whose contraction is split over the wavefronts of a workgroup: few tiles, ragged
+// extents, fp32.  Up to 4 problems of one layout and epilogue per launch; column sums are folded in.
+bool gemm_wave_supported(int dtype, const GemmArgs& g);
+int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream);
+// -1 = automatic choice; 0, 1, 2, 4 .. 11 = force that direct-to-LDS configuration where it applies; 3 = staged kernel only;
+// 12 / 13 = the wavefront-split kernel with 64 x 64 / 32 x 32 tiles where it applies
 void set_gemm_config(int config);
 // How much of the chip the calling thread's GEMM launches share with kernels of other streams: 0 = a launch
 // runs alone (choose the tile for the shortest launch), 1 = idle CUs are always taken by other work (choose

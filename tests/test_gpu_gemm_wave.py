@@ -1,0 +1,84 @@
+"""The GEMM kernel that splits the contraction over a workgroup's wavefronts (gemm config 12: 64 x 64 tiles, 13: 32 x 32),
+at the edges of its tiles and its K tile, against fp64.
+
+Bound: a sum of K products in fp32 is off by at most (K + 4) 2^-24 sum |a b|, whatever its order; the fp32 epilogue
+(bias, residual, GELU) adds a few roundings of the result, and bf16 storage 2^-8 of it."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import block as OB
+from paper_2308_15762_amd import hanayo as hn
+from paper_2308_15762_amd import synth
+from helpers import dev, host
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = {"fwd": (False, True), "dx": (False, False), "dw": (True, True)}
+EPIS = {"fwd": [hn.EPI_BIAS, hn.EPI_BIAS_GELU, hn.EPI_BIAS_RES], "dx": [hn.EPI_NONE, hn.EPI_MUL_DGELU, hn.EPI_ADD], "dw": [hn.EPI_ACCUM_F32]}
+
+
+@pytest.fixture(params=[12, 13])
+def config(request):
+    hn.hanayo_op_gemm_config(request.param)
+    yield request.param
+    hn.hanayo_op_gemm_config(-1)
+
+
+# (M, N, K): M is ragged for fwd and dx, K (the tokens) for dw; the rest are multiples of 8
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("layout", list(LAYOUTS))
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (63, 64, 64), (65, 72, 136), (129, 56, 320), (64, 128, 1024), (777, 104, 264), (333, 520, 96)])
+def test_wave_gemm_edges(config, dtype, layout, M, N, K):
+    if layout == "dw":
+        M, N, K = K, N, M
+    a_t, b_t = LAYOUTS[layout]
+    rng = np.random.default_rng(M * 7 + N * 3 + K)
+    rnd = lambda *s: synth.bf16_round(rng.normal(size=s)) if dtype == "bf16" else rng.normal(size=s).astype(np.float32)
+    A, B, bias, aux = rnd(M, K), rnd(K, N), rnd(N), rnd(M, N)
+    ref = A.astype(np.float64) @ B
+    sums = np.abs(A).astype(np.float64) @ np.abs(B)
+    Ad, Bd = dev(A.T.copy() if a_t else A, dtype), dev(B if b_t else B.T.copy(), dtype)
+    for epi in EPIS[layout]:
+        gain = 1.0                              # what the epilogue multiplies the product's error by
+        if epi == hn.EPI_ACCUM_F32:
+            C = torch.from_numpy(aux.astype(np.float32)).cuda()
+            want = aux + ref
+        else:
+            C = torch.empty((M, N), dtype=Ad.dtype, device="cuda")
+            if epi == hn.EPI_MUL_DGELU:
+                gain = 1.2                      # |GELU'| < 1.13
+            want = {hn.EPI_NONE: ref, hn.EPI_BIAS: ref + bias, hn.EPI_BIAS_GELU: OB.gelu(ref + bias), hn.EPI_BIAS_RES: ref + bias + aux,
+                    hn.EPI_MUL_DGELU: ref * OB.gelu_grad(aux.astype(np.float64)), hn.EPI_ADD: ref + aux}[epi]
+            gain = 1.2 if epi == hn.EPI_BIAS_GELU else gain
+        pre = torch.empty((M, N), dtype=Ad.dtype, device="cuda")
+        cs = torch.zeros(N, dtype=torch.float32, device="cuda") if epi == hn.EPI_ACCUM_F32 else None
+        scratch = torch.empty(64 * N, dtype=torch.float32, device="cuda") if cs is not None else None
+        hn.hanayo_op_gemm(hn.BF16 if dtype == "bf16" else hn.FP32, Ad, Bd, C, M, N, K, M if a_t else K, N if b_t else K, N, a_t, b_t, epi,
+                          dev(bias, dtype), dev(aux, dtype), pre, cs, scratch)
+        torch.cuda.synchronize()
+        store = 2.0 ** -8 if dtype == "bf16" and epi != hn.EPI_ACCUM_F32 else 0.0
+        bound = (K + 4) * 2.0 ** -24 * gain * sums + (store + 2.0 ** -20) * (np.abs(want) + np.abs(ref) + 1.0)
+        assert (np.abs(host(C) - want) <= bound).all(), "epilogue %d" % epi
+        if epi == hn.EPI_BIAS_GELU:
+            assert (np.abs(host(pre) - (ref + bias)) <= bound + (store + 2.0 ** -20) * np.abs(ref + bias)).all()
+        if cs is not None:
+            assert (np.abs(cs.cpu().numpy() - B.astype(np.float64).sum(0)) <= (K + 4) * 2.0 ** -24 * np.abs(B).sum(0) + 1e-30).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_wave_gemm_group(config, dtype):
+    """Four weight gradients of different sizes and an odd token count in one launch."""
+    rng = np.random.default_rng(5)
+    K, probs, want = 201, [], []
+    for M, N in [(72, 136), (136, 72), (8, 264), (200, 8)]:
+        A, B = (synth.bf16_round(rng.normal(size=(K, n))) for n in (M, N))
+        probs.append(dict(A=dev(A, dtype), B=dev(B, dtype), C=torch.ones((M, N), device="cuda"), M=M, N=N, K=K, lda=M, ldb=N, ldc=N,
+                          colsum=torch.zeros(N, device="cuda"), colsum_scratch=torch.empty(64 * N, device="cuda")))
+        want.append((1.0 + A.astype(np.float64).T @ B, np.abs(A).astype(np.float64).T @ np.abs(B), B.astype(np.float64).sum(0), np.abs(B).sum(0)))
+    hn.hanayo_op_gemm_group(hn.BF16 if dtype == "bf16" else hn.FP32, True, True, hn.EPI_ACCUM_F32, probs)
+    torch.cuda.synchronize()
+    for p, (c, ca, s, sa) in zip(probs, want):
+        assert (np.abs(p["C"].cpu().numpy() - c) <= (K + 4) * 2.0 ** -24 * (ca + 1.0)).all()
+        assert (np.abs(p["colsum"].cpu().numpy() - s) <= (K + 4) * 2.0 ** -24 * sa).all()
