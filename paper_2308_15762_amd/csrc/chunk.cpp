@@ -237,13 +237,11 @@ int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
 }
 
 int attn_forward(int dtype, const AttnArgs& a, hipStream_t stream) {
-  if (dtype == HANAYO_BF16 && attn_mfma_supported(a)) return attn_forward_mfma(a, stream);
-  return attn_forward_alu(dtype, a, stream);
+  return dtype == HANAYO_BF16 ? attn_forward_mfma(a, stream) : attn_forward_f32(a, stream);
 }
 
 int attn_backward(int dtype, const AttnArgs& a, hipStream_t stream) {
-  if (dtype == HANAYO_BF16 && attn_mfma_supported(a)) return attn_backward_mfma(a, stream);
-  return attn_backward_alu(dtype, a, stream);
+  return dtype == HANAYO_BF16 ? attn_backward_mfma(a, stream) : attn_backward_f32(a, stream);
 }
 
 }  // namespace k

@@ -93,8 +93,8 @@ int attn_backward(int dtype, const AttnArgs& a, hipStream_t stream);
 
 // Implementations behind the dispatchers above.
 int gemm_alu(int dtype, const GemmArgs& g, hipStream_t stream);
-int attn_forward_alu(int dtype, const AttnArgs& a, hipStream_t stream);
-int attn_backward_alu(int dtype, const AttnArgs& a, hipStream_t stream);
+int attn_forward_f32(const AttnArgs& a, hipStream_t stream);  // fp32 storage
+int attn_backward_f32(const AttnArgs& a, hipStream_t stream);
 int attn_delta(int dtype, const AttnArgs& a, hipStream_t stream);  // delta = rowsum(dctx * ctx)
 bool gemm_mfma_supported(const GemmArgs& g);
 int gemm_mfma(const GemmArgs& g, hipStream_t stream);  // bf16 only
