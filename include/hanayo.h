@@ -590,13 +590,11 @@ int hanayo_op_gemm_group(int dtype, int a_t, int b_t, int epilogue, const hanayo
  */
 int hanayo_op_copy(void* dst, const void* src, size_t bytes, void* hip_stream);
 
-/* Tuning knob for measurements: which bf16 MFMA GEMM kernel hanayo_op_gemm and the chunk calls use.
-   -1 (default) = chosen from the shape by a fitted cost model; 0 / 1 / 2 / 4 / 5 / 6 = direct-to-LDS
-   kernel with 256x256 / 128x128 (8-deep load ring) / 256x128 / 128x128 (4-deep ring, two workgroups per
-   CU) / 128x128 (8 wavefronts that split a K tile's MFMA steps) / 256x256 (8 wavefronts) tiles wherever
-   the shape is a whole number of tiles; 7 / 8 / 9 = 256x256 (8 wavefronts) / 256x128 / 128x128 with two stages
-   of 64-wide K tiles instead of four of 32 (K a multiple of 64); 10 / 11 = 256x128 / 128x128 with three such
-   stages; 3 = register-staged kernel only.
+/* Tuning knob for measurements: which matrix-instruction GEMM kernel hanayo_op_gemm and the chunk calls use.
+   -1 (default) = chosen from the shape by a fitted cost model; 7 / 10 / 9 / 11 = bf16 direct-to-LDS kernel with
+   256x256 (8 wavefronts) / 256x128 (three stages of 64-wide K tiles) / 128x128 (two stages) / 128x128 (three stages)
+   tiles; 0 / 1 = the kernel whose wavefronts split the contraction, with 64x64 / 32x32 tiles (bf16 and fp32); each
+   where the shape allows it.  The other numbers name kernels that no longer exist and mean -1.
    HANAYO_EINVAL outside -1..11.
    The setting belongs to the calling thread: it changes what this thread's later hanayo_op_gemm*, hanayo_chunk_*
    and executor calls dispatch, and nothing for other threads. */

@@ -105,25 +105,27 @@ double rounds_of(long tiles) {
 }
 
 // Tile choice for the direct-to-LDS kernels by a cost model fitted to timings on MI355X: a launch
-// runs ceil(tiles / 256 CUs) rounds; a round costs one K tile's time per 32 columns of K (0.84 us for
-// 256 x 256 with 8 wavefronts, 0.53 us for 256 x 128 (one wavefront per SIMD, three-stage ring; measured on a chip in
-// its sustained clock state with operands that do not stay in the Infinity Cache), 0.295 us for 128 x 128 with two workgroups
+// runs ceil(tiles / 256 CUs) rounds; a round costs one K tile's time per 64 columns of K (1.58 us for
+// 256 x 256 with 8 wavefronts, 1.06 us for 256 x 128 (one wavefront per SIMD, three-stage ring; measured on a chip in
+// its sustained clock state with operands that do not stay in the Infinity Cache), 0.59 us for 128 x 128 with two workgroups
 // sharing a CU) plus an epilogue, and the launch a fixed start-up (pipeline fill grows with the
 // tile).  Large tiles reuse operands better; small ones waste less of the last round, which matters
-// less the more the chip is shared with other streams' kernels (set_gemm_sharing).  Returns -1 if no
-// configuration takes every problem.
+// less the more the chip is shared with other streams' kernels (set_gemm_sharing), and less of ragged edges.
+// Returns -1 if no configuration takes every problem.  *cost_us is the time to expect of the chosen one, for the
+// comparison with other kernels: the times above are those of a chip whose every CU multiplies and whose clock is down;
+// a launch that leaves CUs idle runs at a higher clock (2048 x 2560 x 2560 in 160 tiles of 256 x 128: 0.75 us per K tile).
 int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
   *cost_us = 0.0;
-  if (g_gemm_config >= 0 && g_gemm_config != 3 && g_gemm_config < 12) {
+  if (gemm_dma_config_exists(g_gemm_config)) {
     for (int i = 0; i < count; ++i)
       if (!gemm_dma_supported(gs[i], g_gemm_config)) return -1;
     return g_gemm_config;
   }
-  if (g_gemm_config != -1) return -1;  // 3, 12, 13
-  static const struct { int config; double per_ktile, epilogue, start; } kTiles[] = {
-      {6, 0.79, 3.0, 7.0}, {2, 0.53, 2.0, 4.5}, {4, 0.295, 2.3, 3.3}};
+  static const struct { int config; double per_ktile, per_ktile_idle, epilogue, start; } kTiles[] = {
+      {7, 1.58, 1.04, 3.0, 7.0}, {10, 1.06, 0.63, 2.0, 4.5}, {9, 0.59, 0.38, 2.3, 3.3}};
   int best = -1;
   double best_cost = 0.0;
+  long best_tiles = 0;
   for (const auto& t : kTiles) {
     int bm, bn;
     gemm_dma_tile(t.config, bm, bn);
@@ -132,31 +134,27 @@ int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
     bool ok = true;
     for (int i = 0; i < count && ok; ++i) {
       ok = gemm_dma_supported(gs[i], t.config);
-      const long ti = (long)(gs[i].M / bm) * (gs[i].N / bn);
+      const long ti = (long)((gs[i].M + bm - 1) / bm) * ((gs[i].N + bn - 1) / bn);
       tiles += ti;
-      ktiles += (double)ti * (gs[i].K / 32);
+      ktiles += (double)ti * ((gs[i].K + 63) / 64);
     }
     if (!ok || tiles == 0) continue;
     const double cost = t.start + rounds_of(tiles) * ((ktiles / tiles) * t.per_ktile + t.epilogue);
-    if (best < 0 || cost < best_cost) best = t.config, best_cost = cost;
+    if (best >= 0 && cost >= best_cost) continue;
+    best = t.config, best_cost = cost, best_tiles = tiles;
+    const double used = tiles / (256.0 * (double)((tiles + 255) / 256));  // share of the CUs over the launch's rounds
+    double per_ktile = t.per_ktile_idle + (t.per_ktile - t.per_ktile_idle) * used * used;
+    if (t.config == 9 && tiles > 256) per_ktile *= 0.75;  // two tiles in one CU overlap (1536 x 3072 x 768: 14.8 us)
+    if (g_gemm_sharing > 0.0) per_ktile = t.per_ktile;
+    *cost_us = t.start + rounds_of(tiles) * ((ktiles / tiles) * per_ktile + t.epilogue);
   }
-  *cost_us = best_cost;
-  // The same tile with 64-wide K tiles (half the barriers per unit of work) where K allows it.  The 256 x 128 tile
-  // and, for a launch of at most one tile per CU alone on the chip, the 128 x 128 tile take a ring of three such
-  // stages: with one wavefront per SIMD nothing else covers a load that is late, and one more tile of look-ahead
+  // The 256 x 128 tile and, for a launch of at most one tile per CU alone on the chip, the 128 x 128 tile take a ring of
+  // three stages: with one wavefront per SIMD nothing else covers a load that is late, and one more tile of look-ahead
   // is worth 11 - 21 % on the 2048 x 4096 outputs with K = 4096 .. 16384 (270 us instead of 338 for the input gradient
   // of FC1 at H = 4096) and 4 - 6 % on the 4096 x 1024 outputs.  The 128 x 128 tile with two stages only where a CU
   // holds two workgroups at a time (more than 256 tiles, or a chip shared with other lanes): measured alone on the
   // chip, 2048 x 2560 x 2560 takes 35 us instead of 44, but 4096 x 1024 x 4096, one workgroup per CU, 42 instead of 38.
-  if (best == 6 || best == 2 || best == 4) {
-    long tiles = 0;
-    for (int i = 0; i < count; ++i) tiles += (long)(gs[i].M / 128) * (gs[i].N / 128);
-    const bool one_per_cu = best == 4 && tiles <= 256 && g_gemm_sharing <= 0.0;
-    const int wide_config = best == 6 ? 7 : best == 2 ? 10 : one_per_cu ? 11 : 9;
-    bool wide = true;
-    for (int i = 0; i < count; ++i) wide = wide && gemm_dma_supported(gs[i], wide_config);
-    if (wide) best = wide_config;
-  }
+  if (best == 9 && best_tiles <= 256 && g_gemm_sharing <= 0.0) best = 11;
   return best;
 }
 
@@ -165,10 +163,10 @@ int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
 // 64 x 64 (four rounds of 4096 x 1024: 19 us at K = 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix
 // instructions (256 flop per clock and CU): a 32 x 32 tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
 int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
-  if (g_gemm_config >= 0 && g_gemm_config < 12) return 0;
+  if (gemm_dma_config_exists(g_gemm_config)) return 0;
   for (int i = 0; i < count; ++i)
     if (!gemm_wave_supported(dtype, gs[i])) return 0;
-  if (g_gemm_config >= 12) return g_gemm_config == 12 ? 64 : 32;
+  if (g_gemm_config == 0 || g_gemm_config == 1) return g_gemm_config == 0 ? 64 : 32;
   static const struct { int edge; double per_k, epilogue, start; } kTiles[2][2] = {
       {{64, 0.178 / 64, 1.0, 3.0}, {32, 0.075 / 64, 0.6, 2.5}}, {{64, 0.0154, 1.0, 3.0}, {32, 0.0044, 0.6, 2.5}}};
   int best = 0;
@@ -186,13 +184,7 @@ int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
   }
   if (dtype != HANAYO_BF16) return best;
   double dma_cost;
-  if (choose_dma_config(gs, count, &dma_cost) >= 0) return dma_cost <= best_cost ? 0 : best;
-  // a ragged problem that fills the chip with 256 x 256 tiles of the staged kernel (2040 x 8192 x 2048: 83 us against 101)
-  if (count == 1 && gs[0].M % 8 == 0) {
-    const long tiles = (long)((gs[0].M + 255) / 256) * ((gs[0].N + 255) / 256);
-    if (tiles >= 256 && 8.0 + rounds_of(tiles) * (2.3 * gs[0].K / 64 + 12.0) < best_cost) return 0;
-  }
-  return best;
+  return choose_dma_config(gs, count, &dma_cost) >= 0 && dma_cost <= best_cost ? 0 : best;
 }
 
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
@@ -205,9 +197,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
     const int config = choose_dma_config(&g, 1, &cost);
     if (config >= 0) return gemm_dma(g, config, stream);
   }
-  int rc;
-  if (dtype == HANAYO_BF16 && gemm_mfma_supported(g)) rc = gemm_mfma(g, stream);
-  else rc = gemm_alu(dtype, g, stream);
+  const int rc = gemm_alu(dtype, g, stream);
   if (rc || !g.colsum) return rc;
   return colsum_add(dtype, g.B, g.K, g.N, g.colsum, g.colsum_scratch, stream);  // B is stored [K][ldb = N]
 }

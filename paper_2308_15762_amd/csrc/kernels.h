@@ -96,12 +96,9 @@ int gemm_alu(int dtype, const GemmArgs& g, hipStream_t stream);
 int attn_forward_f32(const AttnArgs& a, hipStream_t stream);  // fp32 storage
 int attn_backward_f32(const AttnArgs& a, hipStream_t stream);
 int attn_delta(int dtype, const AttnArgs& a, hipStream_t stream);  // delta = rowsum(dctx * ctx)
-bool gemm_mfma_supported(const GemmArgs& g);
-int gemm_mfma(const GemmArgs& g, hipStream_t stream);  // bf16 only
-// Direct-to-LDS multi-stage kernel for tile-aligned shapes; config 0 = 256x256, 1 = 128x128 (8-deep ring),
-// 2 = 256x128, 4 = 128x128 (4-deep ring), 5 = 128x128 with 8 wavefronts, 6 = 256x256 with 8 wavefronts,
-// 7 / 8 / 9 = 256x256 (8 wavefronts) / 256x128 / 128x128 with two stages of 64-wide K tiles (K a multiple of 64),
-// 10 / 11 = 256x128 / 128x128 with three such stages.
+// Direct-to-LDS kernels in large tiles, bf16: config 7 = 256 x 256 (8 wavefronts), 9 / 11 = 128 x 128 with two / three
+// stages, 10 = 256 x 128.  Any extents made of whole 16-byte vectors.
+bool gemm_dma_config_exists(int config);
 bool gemm_dma_supported(const GemmArgs& g, int config);
 void gemm_dma_tile(int config, int& bm, int& bn);
 int gemm_dma(const GemmArgs& g, int config, hipStream_t stream);
@@ -110,8 +107,8 @@ int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream
 // extents, fp32.  Up to 4 problems of one layout and epilogue per launch; column sums are folded in.
 bool gemm_wave_supported(int dtype, const GemmArgs& g);
 int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream);
-// -1 = automatic choice; 0, 1, 2, 4 .. 11 = force that direct-to-LDS configuration where it applies; 3 = staged kernel only;
-// 12 / 13 = the wavefront-split kernel with 64 x 64 / 32 x 32 tiles where it applies
+// 7, 9, 10, 11 = force that direct-to-LDS configuration where it applies; 0 / 1 = the wavefront-split kernel with
+// 64 x 64 / 32 x 32 tiles where it applies; anything else = automatic choice
 void set_gemm_config(int config);
 // How much of the chip the calling thread's GEMM launches share with kernels of other streams: 0 = a launch
 // runs alone (choose the tile for the shortest launch), 1 = idle CUs are always taken by other work (choose

@@ -1,23 +1,20 @@
-// bf16 GEMM for shapes that are whole multiples of the tile: operand tiles go from
-// global memory straight into LDS (global_load_lds_dwordx4, no VGPR staging and no
-// LDS write instructions), through a ring of NSTAGE LDS buffers, so that loads
-// for tile t+NSTAGE-1 are in flight while tile t is multiplied.  One workgroup
-// barrier per K tile (32 elements; 64 in the two-stage form).
+// bf16 GEMM in large tiles: operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, no VGPR
+// staging and no LDS write instructions), through a ring of NSTAGE LDS buffers of 64-wide K tiles, so that loads for
+// tiles t+1 .. t+NSTAGE-1 are in flight while tile t is multiplied.  One workgroup barrier per K tile.
 //
-// LDS layouts are unpadded and XOR-swizzled in units of 16 bytes ("slots"); a
-// direct load writes 64 consecutive slots per wavefront instruction, so the
-// swizzle is applied by choosing which global vector each lane fetches:
-//   * contraction-contiguous operand, tile [rows][32]: 4 slots per row,
-//       slot' = slot ^ ((row >> 2) & 3)          (16-byte fragment reads of 16
-//       consecutive rows then cover all 64 banks);
-//     tile [rows][64] (two-stage form): 8 slots per row, slot' = slot ^ ((row >> 1) & 7)
-//   * contraction-strided operand, tile [32 or 64][cols]: cols/8 slots per row,
-//       slot' = slot ^ ((row & 3) << 2)          (the 4 rows x 4 slots one half
-//       wavefront touches in a transpose read cover all 64 banks)
-// MFMA and fragment orientation are those of the staged kernel (kernels_gemm_mfma.hip).
-// The epilogue goes through LDS (the idle load ring) so that stores are whole rows; a
-// launch may carry several problems of one layout (DmaGemmGroup); workgroups take their
-// tiles in an XCD-aware order (xcd_tile).
+// LDS layouts are unpadded and XOR-swizzled in units of 16 bytes ("slots"); a direct load writes 64 consecutive slots
+// per wavefront instruction, so the swizzle is applied by choosing which global vector each lane fetches:
+//   * contraction-contiguous operand, tile [rows][64]: 8 slots per row, slot' = slot ^ ((row >> 1) & 7)
+//       (16-byte fragment reads of 16 consecutive rows then cover all 64 banks)
+//   * contraction-strided operand, tile [64][cols]: cols/8 slots per row, slot' = slot ^ ((row & 3) << 2)
+//       (the 4 rows x 4 slots one half wavefront touches in a transpose read cover all 64 banks)
+// The MFMAs compute the transposed tile, so a lane holds 4 consecutive columns of one row.  The epilogue goes through
+// LDS (the idle load ring) so that stores are whole rows; a launch may carry several problems of one layout
+// (DmaGemmGroup); workgroups take their tiles in an XCD-aware order (xcd_tile).
+//
+// EDGE kernels take any extents whose rows are whole 16-byte vectors: rows and columns outside the operands are read
+// from inside instead (their products reach only outputs that are not stored), and what lies past K in the last K
+// tile is overwritten with zeros in LDS by the wavefront that loaded it, before the barrier that admits the tile.
 #include <type_traits>
 
 #include "device_util.h"
@@ -55,7 +52,8 @@ struct DmaGemmGroup {
   int count;
 };
 
-constexpr int kBK = 32;
+constexpr int kBK = 64;       // K tile
+constexpr int KS = kBK / 16;  // MFMA steps per K tile
 
 // One wavefront-wide 16-byte-per-lane load from global memory into LDS: lane L's
 // vector lands at lds_byte_addr + 16 L.  `voff` is the lane's byte offset from `base`.
@@ -91,45 +89,51 @@ __device__ __forceinline__ void wait_tiles(int tiles_in_flight) {
   }
 }
 
-// Operand tile description.  T = contraction strided in memory (tile is [BK][EXT]); BK = 32 or 64.
-template <int EXT, bool T, int NW, int BK>
+// Operand tile description.  T = contraction strided in memory (tile is [kBK][EXT]).
+template <int EXT, bool T, int NW>
 struct Operand {
-  static constexpr int kSlotsPerRow = T ? EXT / 8 : BK / 8;
-  static constexpr int kRows = T ? BK : EXT;
+  static constexpr int kSlotsPerRow = T ? EXT / 8 : kBK / 8;
+  static constexpr int kRows = T ? kBK : EXT;
   static constexpr int kBytes = kRows * kSlotsPerRow * 16;
   static constexpr int kInstr = kBytes / 1024;      // wavefront-wide loads per tile
   static constexpr int kPerWave = kInstr / NW;      // issued by each wavefront
-  static constexpr int kRowsPerInstr = 64 / kSlotsPerRow == 0 ? 1 : 64 / kSlotsPerRow;
   static_assert(kInstr % NW == 0, "tile loads must divide evenly over the wavefronts");
-  // row_base(q) is taken from the per-wavefront index i: valid when a wavefront's first
-  // instruction starts at a multiple of 4 rows
-  static_assert(!T || ((kPerWave * 64) / kSlotsPerRow) % 4 == 0, "wavefront's share must start on a 4-row boundary");
 
-  // contraction-contiguous rows are 64 bytes (BK = 32: four rows per 256 bytes of banks, slot ^ (row / 4 mod 4)) or
-  // 128 bytes (BK = 64: two rows, slot ^ (row / 2 mod 8)): 16 consecutive rows at one logical slot cover all banks
-  __device__ static int swizzle(int row, int slot) {
-    return T ? slot ^ ((row & 3) << 2) : (BK == 32 ? slot ^ ((row >> 2) & 3) : slot ^ ((row >> 1) & 7));
+  __device__ static int swizzle(int row, int slot) { return T ? slot ^ ((row & 3) << 2) : slot ^ ((row >> 1) & 7); }
+  // Tile row and logical slot of the vector that lands in LDS slot 64 q + lane.
+  __device__ static void where(int q, int lane, int& row, int& slot) {
+    const int at = q * 64 + lane;
+    row = at / kSlotsPerRow;
+    slot = swizzle(row, at % kSlotsPerRow);
   }
-
-  // Byte offset, from the first element an instruction covers, of the vector that lane `lane`
-  // fetches.  `row_base` = the bits of the instruction's first tile row that the swizzle looks at: the
-  // swizzle depends on the absolute row, and an instruction may start at a row that is not a multiple of
-  // the swizzle's period (it covers 64 / slots-per-row rows).
-  __device__ static unsigned lane_offset(int lane, int ld, int row_base) {
-    const int row = lane / kSlotsPerRow, sp = lane % kSlotsPerRow;
-    return (unsigned)((row * ld + swizzle(row_base + row, sp) * 8) * 2);
+  // Byte offset of that vector from the tile's first element; EDGE: `inside` rows (columns) of the operand are left
+  // from there on.
+  template <bool EDGE>
+  __device__ static unsigned offset(int q, int lane, int ld, int inside) {
+    int row, slot;
+    where(q, lane, row, slot);
+    if (EDGE) {
+      if (T) slot = slot * 8 < inside ? slot : 0;
+      else row = row < inside ? row : inside - 1;
+    }
+    return (unsigned)((row * ld + slot * 8) * 2);
   }
-  // row_base of instruction q: the bits of its first tile row that the swizzle looks at (a contraction-contiguous
-  // tile's swizzle has period 16 rows; an instruction covers 16 rows of 64 bytes or 8 rows of 128 bytes)
-  __device__ static constexpr int row_base(int q) { return T ? ((q * 64) / kSlotsPerRow) & 3 : ((q * 64) / kSlotsPerRow) & 15; }
-  static_assert(T || ((kPerWave * 64) / kSlotsPerRow) % 16 == 0, "wavefront's share must start on a 16-row boundary");
+  // Is the vector past the last of k_left contraction elements?  Then it is fetched from the K tile's first row (slot).
+  __device__ static bool past_k(int q, int lane, int k_left) {
+    int row, slot;
+    where(q, lane, row, slot);
+    return (T ? row : slot * 8) >= k_left;
+  }
+  __device__ static unsigned k_part(int q, int lane, int ld) {
+    int row, slot;
+    where(q, lane, row, slot);
+    return (unsigned)((T ? row * ld : slot * 8) * 2);
+  }
 };
 
-template <int PITCH_SLOTS>
 __device__ __forceinline__ bf16x8 frag_k(const char* lds, int r0, int kk, int lane) {
   const int row = r0 + (lane & 31), slot = 2 * kk + (lane >> 5);
-  const int swz = PITCH_SLOTS == 4 ? (row >> 2) & 3 : (row >> 1) & 7;
-  return *reinterpret_cast<const bf16x8*>(lds + (row * PITCH_SLOTS + (slot ^ swz)) * 16);
+  return *reinterpret_cast<const bf16x8*>(lds + (row * (kBK / 8) + (slot ^ ((row >> 1) & 7))) * 16);
 }
 
 template <int SPR>
@@ -147,53 +151,36 @@ __device__ __forceinline__ bf16x8 frag_t(const char* lds, int c0, int kk, int la
   return u.v;
 }
 
-// MODE 0: fragments are read one MFMA step ahead (large wavefront tiles).
-// MODE 1: fragments are read a whole K tile ahead (small wavefront tiles, where one MFMA step is
-//         shorter than the LDS latency); a tile's LDS buffer is then free one iteration earlier,
-//         so all NSTAGE buffers can be in flight.
-// MODE 2: as 1, with twice the wavefronts: the first WGM*WGN take MFMA step 0 of every K tile, the
-//         second WGM*WGN take step 1, and the two partial tiles are added through LDS at the end.
-//         A SIMD then holds two wavefronts that fill each other's stalls, and twice as many
-//         wavefronts issue LDS reads (the per-wavefront LDS request rate limits the 4-wavefront form).
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MODE, bool A_T, bool B_T, int EPI>
-__global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_kernel(DmaGemmGroup grp) {
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup grp) {
   int gi = 0;
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
     if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
   const DmaGemm p = grp.prob[gi];
   const int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
-  constexpr bool FDEEP = MODE == 1 || MODE == 2;
-  constexpr bool WIDE = NSTAGE == 2 || MODE == 3;  // 64-wide K tiles (MODE 3: in a ring of NSTAGE >= 2 stages)
-  constexpr int NSP = WGM * WGN;                 // wavefronts that tile the output
-  constexpr int NW = NSP * (MODE == 2 ? 2 : 1);  // wavefronts in the workgroup
+  constexpr int NW = WGM * WGN;                    // wavefronts in the workgroup
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
-  // A ring of two stages holds 64-wide K tiles (the same bytes in flight as four stages of 32, half as many
-  // barriers and waits per unit of work, whole 128-byte lines per row of a contraction-contiguous operand).
-  constexpr int BK = WIDE ? 64 : 32;
-  constexpr int KS = BK / 16;  // MFMA steps per K tile
-  using OpA = Operand<BM, A_T, NW, BK>;
-  using OpB = Operand<BN, B_T, NW, BK>;
+  using OpA = Operand<BM, A_T, NW>;
+  using OpB = Operand<BN, B_T, NW>;
   constexpr int STAGE_BYTES = OpA::kBytes + OpB::kBytes;
   constexpr int LOADS = OpA::kPerWave + OpB::kPerWave;  // per thread per tile
   static_assert((NSTAGE - 1) * LOADS <= 63, "vmcnt range");
-  static_assert(NSTAGE >= 3 || (NSTAGE == 2 && MODE == 0), "two stages: the 64-wide pipeline of MODE 0 only");
-  static_assert(MODE != 3 || NSTAGE >= 2, "the 64-wide pipeline needs at least two stages");
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // LDS byte address of the ring (address-space-3 offset, what M0 takes)
   const unsigned lds0 = (unsigned)(unsigned long)((__attribute__((address_space(3))) char*)smem);
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int khalf = wave / NSP;  // MODE 2: which MFMA step of a K tile this wavefront owns
-  const int wm = (wave % NSP) / WGN, wn = (wave % NSP) % WGN;
-  const int tiles_m = p.M / BM, tiles_n = p.N / BN;
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int tiles_m = EDGE ? (p.M + BM - 1) / BM : p.M / BM, tiles_n = EDGE ? (p.N + BN - 1) / BN : p.N / BN;
   int tile_m, tile_n;
   xcd_tile(wg, tiles_m, tiles_n, tile_m, tile_n);
   tile_m = __builtin_amdgcn_readfirstlane(tile_m);
   tile_n = __builtin_amdgcn_readfirstlane(tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int nk = p.K / BK;
+  const int nk = EDGE ? (p.K + kBK - 1) / kBK : p.K / kBK;
+  const int k_tail = EDGE ? p.K - (nk - 1) * kBK : kBK;  // contraction elements of the last K tile
 
   // Direct loads of one K tile.  The wavefront's i-th instruction for an operand covers the 64
   // slots q = wave * kPerWave + i of the tile; which rows that is goes into the lane's byte
@@ -201,37 +188,57 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
   // shares one uniform base pointer that just advances by a K tile.
   unsigned voff_a[OpA::kPerWave], voff_b[OpB::kPerWave];
 #pragma unroll
-  for (int i = 0; i < OpA::kPerWave; ++i) {
-    const int q = wave * OpA::kPerWave + i;
-    const unsigned first = A_T ? (unsigned)((((q * 64) / OpA::kSlotsPerRow) * p.lda + ((q * 64) % OpA::kSlotsPerRow) * 8) * 2)
-                               : (unsigned)((q * (64 / OpA::kSlotsPerRow) * p.lda) * 2);
-    voff_a[i] = first + OpA::lane_offset(lane, p.lda, OpA::row_base(i));
-  }
+  for (int i = 0; i < OpA::kPerWave; ++i)
+    voff_a[i] = OpA::template offset<EDGE>(wave * OpA::kPerWave + i, lane, p.lda, p.M - m0);
 #pragma unroll
-  for (int i = 0; i < OpB::kPerWave; ++i) {
-    const int q = wave * OpB::kPerWave + i;
-    const unsigned first = B_T ? (unsigned)((((q * 64) / OpB::kSlotsPerRow) * p.ldb + ((q * 64) % OpB::kSlotsPerRow) * 8) * 2)
-                               : (unsigned)((q * (64 / OpB::kSlotsPerRow) * p.ldb) * 2);
-    voff_b[i] = first + OpB::lane_offset(lane, p.ldb, OpB::row_base(i));
-  }
+  for (int i = 0; i < OpB::kPerWave; ++i)
+    voff_b[i] = OpB::template offset<EDGE>(wave * OpB::kPerWave + i, lane, p.ldb, p.N - n0);
   // uniform running state of the loader: next tile's base pointers and LDS buffer
   const bf16* a_next = A_T ? p.A + m0 : p.A + (size_t)m0 * p.lda;
   const bf16* b_next = B_T ? p.B + n0 : p.B + (size_t)n0 * p.ldb;
-  const size_t a_step = A_T ? (size_t)BK * p.lda : (size_t)BK;
-  const size_t b_step = B_T ? (size_t)BK * p.ldb : (size_t)BK;
+  const size_t a_step = A_T ? (size_t)kBK * p.lda : (size_t)kBK;
+  const size_t b_step = B_T ? (size_t)kBK * p.ldb : (size_t)kBK;
   unsigned stage_next = 0;  // buffer index the next issued tile goes to
   const unsigned wave_lds_a = lds0 + wave * OpA::kPerWave * 1024;
   const unsigned wave_lds_b = lds0 + OpA::kBytes + wave * OpB::kPerWave * 1024;
+  int to_start = 0;  // EDGE: number of the next tile to start (only the last one can be partial)
   // the i-th of the LOADS direct loads of the next tile (i is a compile-time constant at every call)
   auto issue_part = [&](int i) {
     const unsigned st = stage_next * STAGE_BYTES;
-    if (i < OpA::kPerWave) dma16(a_next, voff_a[i], wave_lds_a + st + i * 1024);
-    else dma16(b_next, voff_b[i - OpA::kPerWave], wave_lds_b + st + (i - OpA::kPerWave) * 1024);
+    const bool partial = EDGE && k_tail < kBK && to_start == nk - 1;
+    if (i < OpA::kPerWave) {
+      unsigned v = voff_a[i];
+      const int q = wave * OpA::kPerWave + i;
+      if (partial && OpA::past_k(q, lane, k_tail)) v -= OpA::k_part(q, lane, p.lda);
+      dma16(a_next, v, wave_lds_a + st + i * 1024);
+    } else {
+      unsigned v = voff_b[i - OpA::kPerWave];
+      const int q = wave * OpB::kPerWave + i - OpA::kPerWave;
+      if (partial && OpB::past_k(q, lane, k_tail)) v -= OpB::k_part(q, lane, p.ldb);
+      dma16(b_next, v, wave_lds_b + st + (i - OpA::kPerWave) * 1024);
+    }
+  };
+  // EDGE: zeros over what this wavefront loaded from past K into the stage of the last tile
+  auto clear_past_k = [&]() {
+    if (!EDGE || k_tail == kBK) return;
+    char* st = smem + ((nk - 1) % NSTAGE) * STAGE_BYTES;
+    const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < OpA::kPerWave; ++i) {
+      const int q = wave * OpA::kPerWave + i;
+      if (OpA::past_k(q, lane, k_tail)) *reinterpret_cast<f32x4*>(st + (q * 64 + lane) * 16) = z;
+    }
+#pragma unroll
+    for (int i = 0; i < OpB::kPerWave; ++i) {
+      const int q = wave * OpB::kPerWave + i;
+      if (OpB::past_k(q, lane, k_tail)) *reinterpret_cast<f32x4*>(st + OpA::kBytes + (q * 64 + lane) * 16) = z;
+    }
   };
   auto issue_done = [&]() {
     a_next += a_step;
     b_next += b_step;
     stage_next = stage_next + 1 == NSTAGE ? 0 : stage_next + 1;
+    if (EDGE) ++to_start;
   };
   auto issue = [&]() {
 #pragma unroll
@@ -266,14 +273,14 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
 #pragma unroll
     for (int i = 0; i < TM; ++i)
       f[i] = A_T ? frag_t<OpA::kSlotsPerRow>(a_lds, wm * WM + i * 32, kk, lane)
-                 : frag_k<OpA::kSlotsPerRow>(a_lds, wm * WM + i * 32, kk, lane);
+                 : frag_k(a_lds, wm * WM + i * 32, kk, lane);
   };
   auto read_b = [&](int kt, int kk, bf16x8 (&f)[TN]) {
     const char* b_lds = smem + (kt % NSTAGE) * STAGE_BYTES + OpA::kBytes;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       f[j] = B_T ? frag_t<OpB::kSlotsPerRow>(b_lds, wn * WN + j * 32, kk, lane)
-                 : frag_k<OpB::kSlotsPerRow>(b_lds, wn * WN + j * 32, kk, lane);
+                 : frag_k(b_lds, wn * WN + j * 32, kk, lane);
   };
   auto mfma_step = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
 #pragma unroll
@@ -283,9 +290,9 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
   };
 
   // Column sums of B (bias gradient): the workgroup of tile row 0 sums every K tile of its tile column from
-  // the B tiles that pass through LDS anyway (each thread adds 4 columns x (BK / kColRowGroups) rows per
+  // the B tiles that pass through LDS anyway (each thread adds 4 columns x (kBK / kColRowGroups) rows per
   // tile).  One workgroup per column and a fixed order of additions: the sums are the same bits every run.
-  constexpr int kColGroups = BN / 4, kColRowGroups = NW * 64 / kColGroups, kColRows = BK / kColRowGroups;
+  constexpr int kColGroups = BN / 4, kColRowGroups = NW * 64 / kColGroups, kColRows = kBK / kColRowGroups;
   float csum[4] = {0.f, 0.f, 0.f, 0.f};
   const bool sums_columns = B_T && p.colsum && tile_m == 0;
   auto colsum_tile = [&](int kt) {
@@ -305,7 +312,7 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
     }
   };
 
-  if constexpr (WIDE) {
+  {
     // NSTAGE 64-wide stages (two, or three where the tile leaves room: one more tile of look-ahead for launches
     // that have a single wavefront per SIMD and nothing else to cover a late load).  Per K tile (KS = 4 MFMA steps):
     //   steps 0 .. KS-2 of tile kt    | LDS reads: the following step of tile kt
@@ -317,6 +324,7 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
       if (t < nk) issue();
     bf16x8 fa[2][TM], fb[2][TN];
     wait_tiles<LOADS>(min(NSTAGE - 1, nk - 1));
+    if (nk == 1) clear_past_k();
     __syncthreads();
     colsum_tile(0);
     read_a(0, 0, fa[0]);
@@ -345,10 +353,10 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
               const int f = m * kFr + u;
               if (f < TM)
                 fa[1][f] = A_T ? frag_t<OpA::kSlotsPerRow>(a_cur, wm * WM + f * 32, 1, lane)
-                               : frag_k<OpA::kSlotsPerRow>(a_cur, wm * WM + f * 32, 1, lane);
+                               : frag_k(a_cur, wm * WM + f * 32, 1, lane);
               else if (f < TM + TN)
                 fb[1][f - TM] = B_T ? frag_t<OpB::kSlotsPerRow>(b_cur, wn * WN + (f - TM) * 32, 1, lane)
-                                    : frag_k<OpB::kSlotsPerRow>(b_cur, wn * WN + (f - TM) * 32, 1, lane);
+                                    : frag_k(b_cur, wn * WN + (f - TM) * 32, 1, lane);
             }
             if (m < kRest && pending) issue_part(kFirst + m);
             __builtin_amdgcn_sched_barrier(0);
@@ -396,10 +404,10 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
             const int f = m * kFr + u;
             if (f < TM)
               fa[0][f] = A_T ? frag_t<OpA::kSlotsPerRow>(a_nx, wm * WM + f * 32, 0, lane)
-                             : frag_k<OpA::kSlotsPerRow>(a_nx, wm * WM + f * 32, 0, lane);
+                             : frag_k(a_nx, wm * WM + f * 32, 0, lane);
             else if (f < TM + TN)
               fb[0][f - TM] = B_T ? frag_t<OpB::kSlotsPerRow>(b_nx, wn * WN + (f - TM) * 32, 0, lane)
-                                  : frag_k<OpB::kSlotsPerRow>(b_nx, wn * WN + (f - TM) * 32, 0, lane);
+                                  : frag_k(b_nx, wn * WN + (f - TM) * 32, 0, lane);
           }
 #pragma unroll
           for (int u = 0; u < kPer; ++u)
@@ -414,6 +422,7 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
     for (; kt + 1 < nk; ++kt) {
       steps_before_barrier(kt);
       wait_tiles<LOADS>(min(NSTAGE - 2, nk - 2 - kt));
+      if (kt + 2 == nk) clear_past_k();
       __syncthreads();
       colsum_tile(kt + 1);
       __builtin_amdgcn_sched_barrier(0);
@@ -432,151 +441,6 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
       __builtin_amdgcn_sched_barrier(0);
     }
     mfma_step(fa[(KS - 1) & 1], fb[(KS - 1) & 1]);
-  } else if constexpr (!FDEEP) {
-#pragma unroll
-    for (int t = 0; t < NSTAGE - 1; ++t)
-      if (t < nk) issue();
-    bf16x8 fa[2][TM], fb[2][TN];
-    // Tile 0 has landed once only tiles 1 .. NSTAGE-2 are outstanding.
-    wait_tiles<LOADS>(min(NSTAGE - 2, nk - 1));
-    __syncthreads();
-    colsum_tile(0);
-    read_a(0, 0, fa[0]);
-    read_b(0, 0, fb[0]);
-    // Steady state, per K tile (two MFMA steps of 16):
-    //   step 0 of tile kt   | LDS reads: step 1 of tile kt
-    //   wait until tile kt+1 has landed; barrier (also: everyone has finished tile kt-1)
-    //   start the loads of tile kt+NSTAGE-1 into the buffer tile kt-1 occupied
-    //   step 1 of tile kt   | LDS reads: step 0 of tile kt+1
-    // so the barrier never drains the fragment pipeline.
-    for (int kt = 0; kt + 1 < nk; ++kt) {
-      read_a(kt, 1, fa[1]);
-      read_b(kt, 1, fb[1]);
-      mfma_step(fa[0], fb[0]);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      if (kt + NSTAGE - 1 < nk) {  // steady state: a fixed number of tiles stays in flight
-        wait_vmcnt<(NSTAGE - 3) * LOADS>();
-        __syncthreads();
-        issue();
-      } else {
-        wait_tiles<LOADS>(min(NSTAGE - 3, nk - 2 - kt));
-        __syncthreads();
-      }
-      colsum_tile(kt + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      read_a(kt + 1, 0, fa[0]);
-      read_b(kt + 1, 0, fb[0]);
-      mfma_step(fa[1], fb[1]);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    read_a(nk - 1, 1, fa[1]);
-    read_b(nk - 1, 1, fb[1]);
-    mfma_step(fa[0], fb[0]);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(fa[1], fb[1]);
-  } else {
-    // All NSTAGE buffers are filled up front.  In iteration kt the fragments of tile kt are already
-    // in registers (read during iteration kt-1), so after the barrier its buffer takes tile kt+NSTAGE.
-#pragma unroll
-    for (int t = 0; t < NSTAGE; ++t)
-      if (t < nk) issue();
-    bf16x8 fa[2][2][TM], fb[2][2][TN];  // [tile parity][step]; MODE 2 uses step slot 0 only
-    wait_tiles<LOADS>(min(NSTAGE - 1, nk - 1));
-    __syncthreads();
-    colsum_tile(0);
-    if constexpr (MODE == 1) {
-      read_a(0, 0, fa[0][0]);
-      read_b(0, 0, fb[0][0]);
-      read_a(0, 1, fa[0][1]);
-      read_b(0, 1, fb[0][1]);
-    } else {
-      read_a(0, khalf, fa[0][0]);
-      read_b(0, khalf, fb[0][0]);
-    }
-    auto tile_iter = [&](int kt, auto parity, auto more) {
-      constexpr int P = decltype(parity)::value;
-      if constexpr (decltype(more)::value) {
-        // tile kt+1 has landed, for everyone after the barrier; tile kt's buffer is free then
-        if (kt + NSTAGE < nk) {  // steady state
-          wait_vmcnt<(NSTAGE - 2) * LOADS>();
-          __syncthreads();
-          issue();
-        } else {
-          wait_tiles<LOADS>(min(NSTAGE - 2, nk - 2 - kt));
-          __syncthreads();
-        }
-        colsum_tile(kt + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (MODE == 1) {
-          read_a(kt + 1, 0, fa[P ^ 1][0]);
-          read_b(kt + 1, 0, fb[P ^ 1][0]);
-          mfma_step(fa[P][0], fb[P][0]);
-          interleave();
-          __builtin_amdgcn_sched_barrier(0);
-          read_a(kt + 1, 1, fa[P ^ 1][1]);
-          read_b(kt + 1, 1, fb[P ^ 1][1]);
-          mfma_step(fa[P][1], fb[P][1]);
-          interleave();
-        } else {
-          read_a(kt + 1, khalf, fa[P ^ 1][0]);
-          read_b(kt + 1, khalf, fb[P ^ 1][0]);
-          mfma_step(fa[P][0], fb[P][0]);
-          interleave();
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-        mfma_step(fa[P][0], fb[P][0]);
-        if constexpr (MODE == 1) mfma_step(fa[P][1], fb[P][1]);
-      }
-    };
-    using P0 = std::integral_constant<int, 0>;
-    using P1 = std::integral_constant<int, 1>;
-    int kt = 0;
-    for (; kt + 2 < nk; kt += 2) {
-      tile_iter(kt, P0{}, std::true_type{});
-      tile_iter(kt + 1, P1{}, std::true_type{});
-    }
-    if (kt + 1 < nk) {
-      tile_iter(kt, P0{}, std::true_type{});
-      tile_iter(kt + 1, P1{}, std::false_type{});
-    } else {
-      tile_iter(kt, P0{}, std::false_type{});
-    }
-  }
-
-  if constexpr (MODE == 2) {
-    // add the step-1 group's partial tile to the step-0 group's: through LDS, 16 KiB per pair
-    __syncthreads();  // every wavefront is done with the load ring
-    float* xch = reinterpret_cast<float*>(smem) + (size_t)(wave % NSP) * (TM * TN * 16 * 64);
-    if (khalf == 1) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e];
-            *reinterpret_cast<f32x4*>(xch + (((i * TN + j) * 4 + q) * 64 + lane) * 4) = v;
-          }
-    }
-    __syncthreads();
-    if (khalf == 0) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(xch + (((i * TN + j) * 4 + q) * 64 + lane) * 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
-          }
-    }
   }
 
   if constexpr (B_T) {
@@ -587,7 +451,7 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
 #pragma unroll
       for (int e = 0; e < 4; ++e) red[rg * BN + c + e] = csum[e];
       __syncthreads();
-      if (threadIdx.x < BN) {
+      if (threadIdx.x < BN && (!EDGE || n0 + (int)threadIdx.x < p.N)) {
         float t = 0.f;
 #pragma unroll
         for (int g = 0; g < kColRowGroups; ++g) t += red[g * BN + threadIdx.x];
@@ -638,13 +502,14 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
     const int m = m0 + (br >> 5) * WM + i * 32 + (br & 31);
     n = n0 + c;
     at = (size_t)m * p.ldc + n;
+    return !EDGE || (m < p.M && n < p.N);
   };
   auto prefetch = [&](int i, int buf) {
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
       int br, c, n;
       size_t at;
-      where(i, u, br, c, at, n);
+      if (!where(i, u, br, c, at, n)) at = (size_t)m0 * p.ldc + n0;  // not used
       if constexpr (kReadsAux) pre_aux[buf][u] = *reinterpret_cast<const bf16x8*>(p.aux + at);
       if constexpr (kReadsC) {
         pre_c[buf][u][0] = *reinterpret_cast<const f32x4*>(p.Cf + at);
@@ -672,7 +537,7 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
         }
       }
     }
-    if (MODE != 2 || khalf == 0) {
+    {
       float* dst = stage + (wm * 32 + (lane & 31)) * EP + wn * WN + 4 * (lane >> 5);
 #pragma unroll
       for (int j = 0; j < TN; ++j)
@@ -692,7 +557,7 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
     for (int u = 0; u < VPT; ++u) {
       int br, c, n;
       size_t at;
-      where(i, u, br, c, at, n);
+      if (!where(i, u, br, c, at, n)) continue;
       float v[8];
       load8(stage + br * EP + c, v);
       if constexpr (EPI == EPI_ACCUM_F32) {
@@ -731,14 +596,11 @@ __global__ __launch_bounds__(WGM* WGN*(MODE == 2 ? 2 : 1) * 64) void gemm_dma_ke
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MODE, bool A_T, bool B_T, int EPI>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 int launch(DmaGemmGroup& grp, hipStream_t stream) {
-  constexpr int NW = WGM * WGN * (MODE == 2 ? 2 : 1);
-  constexpr int BK = (NSTAGE == 2 || MODE == 3) ? 64 : 32;  // as in the kernel
-  using OpA = Operand<BM, A_T, NW, BK>;
-  using OpB = Operand<BN, B_T, NW, BK>;
-  constexpr size_t lds = (size_t)NSTAGE * (OpA::kBytes + OpB::kBytes);
-  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, MODE, A_T, B_T, EPI>;
+  constexpr int NW = WGM * WGN;
+  constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes);
+  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>;
   static thread_local bool raised = false;
   if (lds > 64 * 1024 && !raised) {
     const hipError_t e =
@@ -749,7 +611,7 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   long tiles = 0;
   for (int i = 0; i < grp.count; ++i) {
     grp.first[i] = (int)tiles;
-    tiles += (long)(grp.prob[i].N / BN) * (grp.prob[i].M / BM);
+    tiles += (long)((grp.prob[i].N + BN - 1) / BN) * ((grp.prob[i].M + BM - 1) / BM);
   }
   for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
   if (tiles > 0x7fffffffL) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: too many tiles");
@@ -757,42 +619,46 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   return check_launch("gemm_dma");
 }
 
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int MODE>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool EDGE>
 int launch_layout(const GemmArgs& g, DmaGemmGroup& grp, hipStream_t stream) {
   if (!g.a_t && g.b_t) {
     switch (g.epi) {
-      case EPI_NONE: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, true, EPI_NONE>(grp, stream);
-      case EPI_BIAS: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, true, EPI_BIAS>(grp, stream);
-      case EPI_BIAS_GELU: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, true, EPI_BIAS_GELU>(grp, stream);
-      case EPI_BIAS_RES: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, true, EPI_BIAS_RES>(grp, stream);
-      case EPI_STORE_F32: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, true, EPI_STORE_F32>(grp, stream);
+      case EPI_NONE: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_NONE, EDGE>(grp, stream);
+      case EPI_BIAS: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_BIAS, EDGE>(grp, stream);
+      case EPI_BIAS_GELU: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_BIAS_GELU, EDGE>(grp, stream);
+      case EPI_BIAS_RES: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_BIAS_RES, EDGE>(grp, stream);
+      case EPI_STORE_F32: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_STORE_F32, EDGE>(grp, stream);
       default: break;
     }
   } else if (!g.a_t && !g.b_t) {
     switch (g.epi) {
-      case EPI_NONE: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, false, EPI_NONE>(grp, stream);
-      case EPI_MUL_DGELU: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, false, EPI_MUL_DGELU>(grp, stream);
-      case EPI_ADD: return launch<BM, BN, WGM, WGN, NSTAGE, MODE, false, false, EPI_ADD>(grp, stream);
+      case EPI_NONE: return launch<BM, BN, WGM, WGN, NSTAGE, false, false, EPI_NONE, EDGE>(grp, stream);
+      case EPI_MUL_DGELU: return launch<BM, BN, WGM, WGN, NSTAGE, false, false, EPI_MUL_DGELU, EDGE>(grp, stream);
+      case EPI_ADD: return launch<BM, BN, WGM, WGN, NSTAGE, false, false, EPI_ADD, EDGE>(grp, stream);
       default: break;
     }
   } else if (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32) {
-    return launch<BM, BN, WGM, WGN, NSTAGE, MODE, true, true, EPI_ACCUM_F32>(grp, stream);
+    return launch<BM, BN, WGM, WGN, NSTAGE, true, true, EPI_ACCUM_F32, EDGE>(grp, stream);
   }
   return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: layout/epilogue combination not built");
 }
 
+bool whole_tiles(const GemmArgs& g, int config) {
+  int bm, bn;
+  gemm_dma_tile(config, bm, bn);
+  return g.M % bm == 0 && g.N % bn == 0 && g.K % kBK == 0;
+}
+
 }  // namespace
 
-// Tile configurations: 0 = 256 x 256, 1 = 128 x 128 with an 8-deep buffer ring, 2 = 256 x 128,
-// 4 = 128 x 128 with a 4-deep ring (two workgroups fit a CU), 5 = as 4 with 8 wavefronts that split
-// the MFMA steps of a K tile, 6 = 256 x 256 with 8 wavefronts (2 x 4, 128 x 64 each: two per SIMD
-// that cover each other's stalls), 7, 8 and 9 = the tiles of 6, 2 and 4 with a ring of two 64-wide K tiles
-// instead of four 32-wide ones (same bytes in flight, one barrier per 64 of K); 10 and 11 = the tiles of 2 and 4 with
-// three 64-wide stages (one workgroup per CU: for launches whose single wavefront per SIMD has nothing else to cover
-// a late load).  The others use 4 wavefronts.
+// Tile configurations: 7 = 256 x 256 with 8 wavefronts (2 x 4, 128 x 64 each: two per SIMD that cover each other's
+// stalls), two stages; 9 = 128 x 128, two stages (64 KiB: two workgroups per CU); 10 = 256 x 128, three stages; 11 = 128 x
+// 128, three stages (96 KiB, one workgroup per CU: for launches whose single wavefront per SIMD has nothing else to cover
+// a late load).  9, 10 and 11 use 4 wavefronts.
+bool gemm_dma_config_exists(int config) { return config == 7 || (config >= 9 && config <= 11); }
 void gemm_dma_tile(int config, int& bm, int& bn) {
-  bm = (config == 1 || config == 4 || config == 5 || config == 9 || config == 11) ? 128 : 256;
-  bn = (config == 0 || config == 6 || config == 7) ? 256 : 128;  // 2, 8 and 10: 256 x 128
+  bm = config == 9 || config == 11 ? 128 : 256;
+  bn = config == 7 ? 256 : 128;
 }
 
 bool gemm_dma_supported(const GemmArgs& g, int config) {
@@ -800,13 +666,16 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
                                              g.epi == EPI_STORE_F32)) ||
                      (!g.a_t && !g.b_t && (g.epi == EPI_NONE || g.epi == EPI_MUL_DGELU || g.epi == EPI_ADD)) ||
                      (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32);
+  if (!combo || !gemm_dma_config_exists(config)) return false;
   int bm, bn;
   gemm_dma_tile(config, bm, bn);
   // lane offsets are 32-bit byte offsets from the tile origin
-  const int bk = config >= 7 ? 64 : kBK;
-  const long span_a = (long)(g.a_t ? bk : bm) * g.lda * 2, span_b = (long)(g.b_t ? bk : bn) * g.ldb * 2;
-  return combo && g.M % bm == 0 && g.N % bn == 0 && g.K % bk == 0 && g.K >= bk && g.lda % 8 == 0 && g.ldb % 8 == 0 &&
-         g.ldc % 4 == 0 && span_a < (1L << 31) && span_b < (1L << 31);
+  const long span_a = (long)(g.a_t ? kBK : bm) * g.lda * 2, span_b = (long)(g.b_t ? kBK : bn) * g.ldb * 2;
+  if (g.lda % 8 || g.ldb % 8 || g.ldc % 4 || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
+  if (whole_tiles(g, config)) return true;
+  // edges: whole 16-byte vectors along every row, on 16-byte boundaries
+  const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
+  return bits % 16 == 0 && (g.a_t ? g.M : g.K) % 8 == 0 && (g.b_t ? g.N : g.K) % 8 == 0 && g.N % 8 == 0;
 }
 
 // The problems of a group share layout and epilogue (those of gs[0]); each must pass gemm_dma_supported.
@@ -814,10 +683,12 @@ int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream
   if (count < 1 || count > kMaxGroup) return set_error(HANAYO_EINVAL, "gemm_dma: group of %d", count);
   DmaGemmGroup grp{};
   grp.count = count;
+  bool edge = false;
   for (int i = 0; i < count; ++i) {
     const GemmArgs& g = gs[i];
     if (!gemm_dma_supported(g, config) || g.a_t != gs[0].a_t || g.b_t != gs[0].b_t || g.epi != gs[0].epi)
       return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: shape not supported");
+    edge = edge || !whole_tiles(g, config);
     DmaGemm& p = grp.prob[i];
     p.A = (const bf16*)g.A; p.B = (const bf16*)g.B; p.C = (bf16*)g.C; p.Cf = (float*)g.C;
     p.bias = (const bf16*)g.bias; p.aux = (const bf16*)g.aux; p.aux_out = (bf16*)g.aux_out;
@@ -826,17 +697,10 @@ int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream
   }
   const GemmArgs& g = gs[0];
   switch (config) {
-    case 0: return launch_layout<256, 256, 2, 2, 4, 0>(g, grp, stream);
-    case 1: return launch_layout<128, 128, 2, 2, 8, 1>(g, grp, stream);  // 128 KiB LDS: one workgroup per CU
-    case 4: return launch_layout<128, 128, 2, 2, 4, 1>(g, grp, stream);  // 64 KiB LDS: two per CU
-    case 5: return launch_layout<128, 128, 2, 2, 4, 2>(g, grp, stream);
-    case 6: return launch_layout<256, 256, 2, 4, 4, 0>(g, grp, stream);  // 8 wavefronts, 128 x 64 each
-    case 7: return launch_layout<256, 256, 2, 4, 2, 0>(g, grp, stream);  // as 6 with two stages of 64-wide K tiles
-    case 8: return launch_layout<256, 128, 2, 2, 2, 0>(g, grp, stream);  // as 2 with two stages of 64-wide K tiles
-    case 9: return launch_layout<128, 128, 2, 2, 2, 0>(g, grp, stream);  // 128 x 128 likewise (two workgroups per CU)
-    case 10: return launch_layout<256, 128, 2, 2, 3, 3>(g, grp, stream);  // as 8 with three stages (144 KiB): one more tile of look-ahead
-    case 11: return launch_layout<128, 128, 2, 2, 3, 3>(g, grp, stream);  // 128 x 128, three 64-wide stages (96 KiB, one workgroup per CU)
-    default: return launch_layout<256, 128, 2, 2, 4, 0>(g, grp, stream);
+    case 7: return edge ? launch_layout<256, 256, 2, 4, 2, true>(g, grp, stream) : launch_layout<256, 256, 2, 4, 2, false>(g, grp, stream);
+    case 9: return edge ? launch_layout<128, 128, 2, 2, 2, true>(g, grp, stream) : launch_layout<128, 128, 2, 2, 2, false>(g, grp, stream);
+    case 10: return edge ? launch_layout<256, 128, 2, 2, 3, true>(g, grp, stream) : launch_layout<256, 128, 2, 2, 3, false>(g, grp, stream);
+    default: return edge ? launch_layout<128, 128, 2, 2, 3, true>(g, grp, stream) : launch_layout<128, 128, 2, 2, 3, false>(g, grp, stream);
   }
 }
 

@@ -1,5 +1,5 @@
-"""The GEMM kernel that splits the contraction over a workgroup's wavefronts (gemm config 12: 64 x 64 tiles, 13: 32 x 32),
-at the edges of its tiles and its K tile, against fp64.
+"""The GEMM kernels at the edges of their tiles and of their K tile, against fp64: the one that splits the contraction over
+a workgroup's wavefronts (gemm config 0: 64 x 64 tiles, 1: 32 x 32) and the direct-to-LDS kernels (7, 9, 10, 11; bf16 only).
 
 Bound: a sum of K products in fp32 is off by at most (K + 4) 2^-24 sum |a b|, whatever its order; the fp32 epilogue
 (bias, residual, GELU) adds a few roundings of the result, and bf16 storage 2^-8 of it."""
@@ -19,7 +19,7 @@ LAYOUTS = {"fwd": (False, True), "dx": (False, False), "dw": (True, True)}
 EPIS = {"fwd": [hn.EPI_BIAS, hn.EPI_BIAS_GELU, hn.EPI_BIAS_RES], "dx": [hn.EPI_NONE, hn.EPI_MUL_DGELU, hn.EPI_ADD], "dw": [hn.EPI_ACCUM_F32]}
 
 
-@pytest.fixture(params=[12, 13])
+@pytest.fixture(params=[0, 1, 7, 9, 10, 11])
 def config(request):
     hn.hanayo_op_gemm_config(request.param)
     yield request.param
@@ -29,8 +29,8 @@ def config(request):
 # (M, N, K): M is ragged for fwd and dx, K (the tokens) for dw; the rest are multiples of 8
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("layout", list(LAYOUTS))
-@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (63, 64, 64), (65, 72, 136), (129, 56, 320), (64, 128, 1024), (777, 104, 264), (333, 520, 96)])
-def test_wave_gemm_edges(config, dtype, layout, M, N, K):
+@pytest.mark.parametrize("M,N,K", [(1, 8, 8), (63, 64, 64), (65, 72, 136), (129, 56, 320), (64, 128, 1024), (777, 104, 264), (333, 520, 96), (513, 264, 200), (256, 384, 72)])
+def test_gemm_edges(config, dtype, layout, M, N, K):
     if layout == "dw":
         M, N, K = K, N, M
     a_t, b_t = LAYOUTS[layout]
@@ -68,7 +68,7 @@ def test_wave_gemm_edges(config, dtype, layout, M, N, K):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
-def test_wave_gemm_group(config, dtype):
+def test_gemm_group_edges(config, dtype):
     """Four weight gradients of different sizes and an odd token count in one launch."""
     rng = np.random.default_rng(5)
     K, probs, want = 201, [], []
