@@ -95,7 +95,6 @@ thread_local int g_gemm_config = -1;  // measurement knob: of the calling thread
 thread_local double g_gemm_sharing = 0.0;
 }
 void set_gemm_config(int config) { g_gemm_config = config; }
-double gemm_sharing() { return g_gemm_sharing; }
 void set_gemm_sharing(double share) { g_gemm_sharing = share < 0.0 ? 0.0 : (share > 1.0 ? 1.0 : share); }
 
 // Rounds of 256 CUs that a launch of `tiles` workgroups pays for: whole ones alone on the chip; next to kernels of other
@@ -197,6 +196,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
     const int config = choose_dma_config(&g, 1, &cost);
     if (config >= 0) return gemm_dma(g, config, stream);
   }
+  if (g.live) return set_error(HANAYO_EUNSUPPORTED, "gemm: rows counted on the device need 16-byte vectors");
   const int rc = gemm_alu(dtype, g, stream);
   if (rc || !g.colsum) return rc;
   return colsum_add(dtype, g.B, g.K, g.N, g.colsum, g.colsum_scratch, stream);  // B is stored [K][ldb = N]

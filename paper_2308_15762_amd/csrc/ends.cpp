@@ -25,18 +25,33 @@ namespace {
 
 bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) != 0; }
 
+// The head works on the labelled rows only (a bidirectional model labels about one position in seven): their hidden
+// states are gathered, and the three GEMMs, the loss and their gradients run over `live` rows, a number that stays on
+// the device.  Measured (MI355X), bidirectional, T = 4096, H = 1024, V = 30592, 460 labelled rows: 828 us over all rows,
+// 211 over these (of which 72 add to d_head, 250 MB read and written); all rows labelled, V = 50304: no slower than before
+// (the row list, the gather and the scatter take 5 us each of 1.5 ms).
 struct HeadLayout {
   size_t hn;       // [T][H]  LN_f(y)
+  size_t hc;       // [live][H] the labelled rows of hn (of y without LN_f)
   size_t d_hn;     // [T][H]  gradient w.r.t. hn
   size_t stats;    // [T] float2
-  size_t nll;      // [T] float
-  size_t count;    // float
+  size_t nll;      // [live] float
+  size_t live;     // int
+  size_t list;     // [live] int
+  size_t slot;     // [T] int
   size_t partial;  // [kMaxPartialRows][2H] float
-  size_t logits;   // [T][V]
-  size_t split;    // [kHeadSplit][T][H] float: partial products of the d_hn GEMM when its K (= V) is split
+  size_t logits;   // [live][V]
+  size_t product;  // gradient w.r.t. hc: [live][H], or the fp32 slices of a split contraction
   size_t bytes;
 };
-constexpr int kHeadSplit = 4;
+
+// d_hc[live][H] = dlogits[live][V] head[V][H] has few output tiles and a contraction over the whole vocabulary: in bf16, from
+// 64 K tiles on, it is cut into slices (split_plan); returns the launch's workgroups, 0 = not split.
+int split_grid(const Shape& sh, int vocab) {
+  if (sh.dtype != HANAYO_BF16 || vocab < 64 * 64) return 0;
+  const int tiles = (sh.T + 255) / 256 * ((sh.H + 255) / 256);
+  return tiles > k::kSplitGrid ? tiles : k::kSplitGrid;
+}
 
 HeadLayout head_layout(const Shape& sh, int vocab) {
   HeadLayout L{};
@@ -48,13 +63,20 @@ HeadLayout head_layout(const Shape& sh, int vocab) {
   };
   const size_t act = (size_t)sh.T * sh.H * sh.esz;
   L.hn = take(act);
+  L.hc = take(act);
   L.d_hn = take(act);
   L.stats = take((size_t)sh.T * sizeof(float2));
   L.nll = take((size_t)sh.T * sizeof(float));
-  L.count = take(sizeof(float));
+  L.live = take(sizeof(int));
+  L.list = take((size_t)sh.T * sizeof(int));
+  L.slot = take((size_t)sh.T * sizeof(int));
   L.partial = take((size_t)kMaxPartialRows * 2 * sh.H * sizeof(float));
   L.logits = take((size_t)sh.T * vocab * sh.esz);
-  L.split = take((size_t)kHeadSplit * sh.T * sh.H * sizeof(float));
+  // slices x live x H <= slices x tiles x 256 x 256 <= grid x 256 x 256, and at most kMaxSlices x T x H
+  const int grid = split_grid(sh, vocab);
+  size_t slices = (size_t)k::kMaxSlices * sh.T * sh.H * sizeof(float);
+  if (slices > (size_t)grid * 256 * 256 * sizeof(float)) slices = (size_t)grid * 256 * 256 * sizeof(float);
+  L.product = take(grid ? slices : act);
   L.bytes = at;
   return L;
 }
@@ -88,7 +110,9 @@ int head_loss(const Shape& sh, const hanayo_ends_desc* e, const void* lnf, const
   const HeadLayout L = head_layout(sh, e->vocab);
   char* ws = static_cast<char*>(workspace);
   const int T = sh.T, H = sh.H, V = e->vocab;
-  float* count = reinterpret_cast<float*>(ws + L.count);
+  int* live = reinterpret_cast<int*>(ws + L.live);
+  int32_t* list = reinterpret_cast<int32_t*>(ws + L.list);
+  int32_t* slot = reinterpret_cast<int32_t*>(ws + L.slot);
   float* nll = reinterpret_cast<float*>(ws + L.nll);
   float2* stats = reinterpret_cast<float2*>(ws + L.stats);
   const void* hn = y;
@@ -97,66 +121,39 @@ int head_loss(const Shape& sh, const hanayo_ends_desc* e, const void* lnf, const
     TRY(k::ln_forward(sh.dtype, y, gamma, gamma + (size_t)H * sh.esz, ws + L.hn, stats, nullptr, T, H, sh.eps, st));
     hn = ws + L.hn;
   }
-  TRY(k::count_labels(labels, T, V, count, st));
-  // The vocabulary is rarely a multiple of the largest GEMM tile (256): for the logits the rows of the table up to
-  // the last such multiple go out as one launch that may use it, the few rows left as a second, small one.
-  const int v_main = V >= 512 ? V / 256 * 256 : V, v_rest = V - v_main;
-  const char* head_rest = static_cast<const char*>(head) + (size_t)v_main * H * sh.esz;
-  // logits[T][V] = hn[T][H] head[V][H]^T
+  TRY(k::list_labelled(labels, T, V, live, list, slot, st));
+  TRY(k::gather_rows(sh.dtype, hn, live, list, ws + L.hc, T, H, st));
+  // logits[live][V] = hc[live][H] head[V][H]^T
   k::GemmArgs g{};
-  g.A = hn; g.B = head; g.C = ws + L.logits;
-  g.M = T; g.N = v_main; g.K = H; g.lda = H; g.ldb = H; g.ldc = V;
+  g.A = ws + L.hc; g.B = head; g.C = ws + L.logits;
+  g.M = T; g.N = V; g.K = H; g.lda = H; g.ldb = H; g.ldc = V;
   g.a_t = false; g.b_t = false; g.epi = k::EPI_NONE;
+  g.live = live; g.live_dim = k::LIVE_M;
   TRY(k::gemm(sh.dtype, g, st));
-  if (v_rest) {
-    g.B = head_rest; g.C = ws + L.logits + (size_t)v_main * sh.esz; g.N = v_rest;
-    TRY(k::gemm(sh.dtype, g, st));
-  }
   // in place: logits -> gradient of loss_scale * loss w.r.t. the logits
-  TRY(k::softmax_xent(sh.dtype, ws + L.logits, labels, count, loss_scale, nll, T, V, st));
-  TRY(k::loss_finish(nll, count, T, loss, st));
-  // d_head[V][H] += dlogits[T][V]^T hn[T][H]
+  TRY(k::softmax_xent(sh.dtype, ws + L.logits, labels, live, list, loss_scale, nll, T, V, st));
+  TRY(k::loss_finish(nll, live, loss, st));
+  // d_head[V][H] += dlogits[live][V]^T hc[live][H]
   k::GemmArgs gw{};
-  gw.A = ws + L.logits; gw.B = hn; gw.C = d_head;
+  gw.A = ws + L.logits; gw.B = ws + L.hc; gw.C = d_head;
   gw.M = V; gw.N = H; gw.K = T; gw.lda = V; gw.ldb = H; gw.ldc = H;
   gw.a_t = true; gw.b_t = true; gw.epi = k::EPI_ACCUM_F32;
-  // Alone on the chip one launch of small tiles is fastest here (measured: V / 256 x H / 256 large tiles leave a
-  // quarter of the last round idle); next to other lanes' kernels idle CUs are not lost and the large tile's
-  // better use of a CU wins, so the rows split as for the logits.
-  if (v_rest && k::gemm_sharing() > 0.0) {
-    gw.M = v_main;
-    TRY(k::gemm(sh.dtype, gw, st));
-    gw.A = ws + L.logits + (size_t)v_main * sh.esz; gw.C = d_head + (size_t)v_main * H; gw.M = v_rest;
-  }
+  gw.live = live; gw.live_dim = k::LIVE_K;
   TRY(k::gemm(sh.dtype, gw, st));
-  // d_hn[T][H] = dlogits[T][V] head[V][H]
+  // d_hc[live][H] = dlogits[live][V] head[V][H], then back to its rows
   k::GemmArgs gx{};
-  gx.A = ws + L.logits; gx.B = head; gx.C = e->final_ln ? static_cast<void*>(ws + L.d_hn) : dy;
+  gx.A = ws + L.logits; gx.B = head; gx.C = ws + L.product;
   gx.M = T; gx.N = H; gx.K = V; gx.lda = V; gx.ldb = H; gx.ldc = H;
   gx.a_t = false; gx.b_t = true; gx.epi = k::EPI_NONE;
-  // The output has T H / 256^2 tiles (64 for 4096 x 1024) and the contraction runs over the whole vocabulary:
-  // where the largest tile would leave most of the chip idle, K is cut into kHeadSplit slices that go out as one
-  // grouped launch into fp32 partial products, summed by a small kernel.
-  const int slice = (V / kHeadSplit) / 64 * 64;  // the last slice takes the rest
-  const long tiles256 = (long)(T / 256) * (H / 256);
-  bool split = sh.dtype == HANAYO_BF16 && slice >= 1024 && T % 256 == 0 && H % 256 == 0 && tiles256 * kHeadSplit <= 256;
-  k::GemmArgs part[kHeadSplit];
-  for (int i = 0; i < kHeadSplit && split; ++i) {
-    const int k0 = i * slice, kn = i + 1 < kHeadSplit ? slice : V - k0;
-    part[i] = gx;
-    part[i].A = ws + L.logits + (size_t)k0 * sh.esz;
-    part[i].B = static_cast<const char*>(head) + (size_t)k0 * H * sh.esz;
-    part[i].C = ws + L.split + (size_t)i * T * H * sizeof(float);
-    part[i].K = kn;
-    part[i].epi = k::EPI_STORE_F32;
-    split = k::gemm_dma_supported(part[i], 7);  // 256 x 256 tiles, 64-wide K tiles
-  }
-  if (split) {
-    TRY(k::gemm_dma_group(part, kHeadSplit, 7, st));
-    TRY(k::sum_slices(sh.dtype, reinterpret_cast<const float*>(ws + L.split), kHeadSplit, (size_t)T * H, gx.C, st));
+  gx.live = live; gx.live_dim = k::LIVE_M;
+  const int grid = split_grid(sh, V);
+  if (grid) {
+    gx.epi = k::EPI_STORE_F32; gx.live_dim = k::LIVE_M_SPLIT;
+    TRY(k::gemm_dma_group(&gx, 1, 7, st));
   } else {
     TRY(k::gemm(sh.dtype, gx, st));
   }
+  TRY(k::scatter_rows(sh.dtype, ws + L.product, live, slot, grid, V, e->final_ln ? static_cast<void*>(ws + L.d_hn) : dy, T, H, st));
   if (e->final_ln)
     TRY(k::ln_backward(sh.dtype, ws + L.d_hn, y, lnf, stats, nullptr, dy, d_lnf, d_lnf + H,
                        reinterpret_cast<float*>(ws + L.partial), T, H, st));

@@ -69,7 +69,26 @@ struct GemmArgs {
   // kernels that cannot fold the sums into the GEMM itself.
   float* colsum;
   float* colsum_scratch;
+  // Optional: *live (device) is the number of rows of C (LIVE_M) or of contraction elements (LIVE_K) that count, at most
+  // M or K; workgroups past it leave at once.  LIVE_M_SPLIT (EPI_STORE_F32, gemm_dma_group only, one problem): as LIVE_M, with
+  // the contraction cut into slices, one partial product each, by split_plan.
+  const int* live;
+  int live_dim;
 };
+enum { LIVE_NONE = 0, LIVE_M, LIVE_K, LIVE_M_SPLIT };
+// How a grid of `grid` workgroups covers `live` rows x tiles_n 256-column tiles with K cut into slices of `per` elements
+// (whole K tiles, at least 8 each): as many slices as the grid holds.  Evaluated on the device, by the GEMM and by the
+// kernel that adds the slices.
+constexpr int kMaxSlices = 16, kSplitGrid = 256;  // workgroups of a LIVE_M_SPLIT launch: this many, or one per 256 x 256 tile
+__host__ __device__ inline int split_plan(int live, int tiles_n, int K, int grid, int& per) {
+  const int tiles = (live + 255) / 256 * tiles_n, ktiles = (K + 63) / 64;
+  int slices = tiles > 0 ? grid / tiles : 1;
+  if (slices > kMaxSlices) slices = kMaxSlices;
+  if (slices > ktiles / 8) slices = ktiles / 8;
+  if (slices < 1) slices = 1;
+  per = (ktiles + slices - 1) / slices * 64;
+  return (K + per - 1) / per;
+}
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream);
 // Up to 4 independent problems of one layout and epilogue; one launch where the tiled kernels allow
 // it (small problems then fill the chip together), otherwise one after the other.
@@ -114,7 +133,6 @@ void set_gemm_config(int config);
 // runs alone (choose the tile for the shortest launch), 1 = idle CUs are always taken by other work (choose
 // for the least CU time).  The executor sets it from its lane count while it enqueues a list.
 void set_gemm_sharing(double share);
-double gemm_sharing();
 bool attn_mfma_supported(const AttnArgs& a);
 int attn_forward_mfma(const AttnArgs& a, hipStream_t stream);
 int attn_backward_mfma(const AttnArgs& a, hipStream_t stream);
@@ -126,14 +144,17 @@ int embed_forward(int dtype, const void* wte, const void* wpe, const int32_t* to
 // d_wte[tokens[n][i]][:] += dx[n][i][:] (fixed order, no atomics); d_wpe[i][:] += sum_n dx[n][i][:].
 int embed_backward(int dtype, const int32_t* tokens, const void* dx, float* d_wte, float* d_wpe, int b, int s, int H,
                    int vocab, hipStream_t stream);
-// count[0] = number of labels inside [0, vocab).
-int count_labels(const int32_t* labels, int rows, int vocab, float* count, hipStream_t stream);
-// In place on logits [rows][V]: the gradient of loss_scale * (mean over counted rows of the negative
-// log-likelihood); nll[row] = the row's negative log-likelihood (0 if its label is outside [0, V)).
-int softmax_xent(int dtype, void* logits, const int32_t* labels, const float* count, float loss_scale, float* nll,
-                 int rows, int V, hipStream_t stream);
-// loss[0] = sum(nll) / count[0] (0 if count is 0).
-int loss_finish(const float* nll, const float* count, int rows, float* loss, hipStream_t stream);
+// The rows whose label lies inside [0, vocab), in order: live[0] = their number n, list[0..n) = the rows, slot[row] =
+// the row's place in the list or -1.
+int list_labelled(const int32_t* labels, int rows, int vocab, int* live, int32_t* list, int32_t* slot, hipStream_t stream);
+// out[i][:] = in[list[i]][:] for i < live[0]
+int gather_rows(int dtype, const void* in, const int* live, const int32_t* list, void* out, int rows, int H, hipStream_t stream);
+// In place on logits [live][V], whose row i belongs to label labels[list[i]]: the gradient of loss_scale * (mean of the
+// rows' negative log-likelihoods); nll[i] = the row's negative log-likelihood.
+int softmax_xent(int dtype, void* logits, const int32_t* labels, const int* live, const int32_t* list, float loss_scale,
+                 float* nll, int rows, int V, hipStream_t stream);
+// loss[0] = sum(nll[0..live)) / live (0 if live is 0).
+int loss_finish(const float* nll, const int* live, float* loss, hipStream_t stream);
 struct AdamArgs {
   void* params;   // storage type, updated
   float* master;  // bf16 storage: fp32 copy of the parameters, updated; ignored for fp32 storage
@@ -151,8 +172,10 @@ struct AdamArgs {
 };
 int adam(int dtype, const AdamArgs& a, hipStream_t stream);
 
-// out[i] = sum over s < slices of parts[s * count + i]  (the partial products of a K split; count multiple of 8)
-int sum_slices(int dtype, const float* parts, int slices, size_t count, void* out, hipStream_t stream);
+// out[row][:] = row slot[row] of the [live][H] product (zeros where slot is -1).  grid > 0: the product is the sum of the
+// fp32 slices of split_plan(live, tiles_n, K, grid), else it is stored whole in the storage type.
+int scatter_rows(int dtype, const void* product, const int* live, const int32_t* slot, int grid, int K, void* out, int rows, int H,
+                 hipStream_t stream);
 
 // ---- misc ------------------------------------------------------------------------
 // max_workgroups > 0 caps the grid: a copy that uses only a few CUs and so runs at a chosen fraction of the

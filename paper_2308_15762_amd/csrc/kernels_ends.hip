@@ -173,38 +173,63 @@ __global__ __launch_bounds__(256) void embed_bwd_pos_kernel(const T* __restrict_
   store8(d_wpe + (size_t)i * H + c, acc);
 }
 
-// count[0] = number of labels inside [0, vocab).  One workgroup; integer counting, so exact in any order.
-__global__ __launch_bounds__(256) void count_labels_kernel(const int32_t* __restrict__ labels, int rows, int vocab,
-                                                           float* __restrict__ count) {
-  __shared__ int total;
-  if (threadIdx.x == 0) total = 0;
-  __syncthreads();
-  int mine = 0;
-  for (int t = threadIdx.x; t < rows; t += 256) mine += (labels[t] >= 0 && labels[t] < vocab) ? 1 : 0;
-  atomicAdd(&total, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) count[0] = (float)total;
+// The labelled rows in order (see kernels.h).  One workgroup: ballots and prefix counts over 1024 rows at a time.
+__global__ __launch_bounds__(1024) void list_labelled_kernel(const int32_t* __restrict__ labels, int rows, int vocab,
+                                                             int* __restrict__ live, int32_t* __restrict__ list,
+                                                             int32_t* __restrict__ slot) {
+  __shared__ int cnt[2][16];  // double-buffered: one barrier per 1024 rows
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int total = 0;
+  for (int base = 0, it = 0; base < rows; base += 1024, ++it) {
+    const int t = base + (int)threadIdx.x;
+    const int label = t < rows ? labels[t] : -1;
+    const bool hit = label >= 0 && label < vocab;
+    const unsigned long long mask = __ballot(hit);
+    if (lane == 0) cnt[it & 1][wave] = __popcll(mask);
+    __syncthreads();
+    int before = total;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const int c = cnt[it & 1][w];
+      if (w < wave) before += c;
+      total += c;
+    }
+    const int at = before + __popcll(mask & ((1ull << lane) - 1ull));
+    if (hit) list[at] = t;
+    if (t < rows) slot[t] = hit ? at : -1;
+  }
+  if (threadIdx.x == 0) live[0] = total;
 }
 
-// One workgroup per row of logits [rows][V]: the row's log-sum-exp by an online max / sum pass, then a
+// One wavefront per listed row.
+template <typename T>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const T* __restrict__ in, const int* __restrict__ live,
+                                                          const int32_t* __restrict__ list, T* __restrict__ out, int H) {
+  const int lane = threadIdx.x & 63, i = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
+  if (i >= live[0]) return;
+  const T* src = in + (size_t)list[i] * H;
+  T* dst = out + (size_t)i * H;
+  for (int c = lane * 8; c < H; c += 64 * 8) {
+    float v[8];
+    load8(src + c, v);
+    store8(dst + c, v);
+  }
+}
+
+// One workgroup per row of logits [live][V]: the row's log-sum-exp by an online max / sum pass, then a
 // second pass (the row is still in cache) that overwrites the logits with the gradient of
 // loss_scale * mean negative log-likelihood:  (softmax - onehot(label)) * loss_scale / count.
-// nll[row] = lse - logit[label]; a row whose label is outside [0, V) gets nll 0 and a zero gradient.
+// nll[row] = lse - logit[label].
 template <typename T>
 __global__ __launch_bounds__(256) void xent_kernel(T* __restrict__ logits, const int32_t* __restrict__ labels,
-                                                   const float* __restrict__ count, float loss_scale,
-                                                   float* __restrict__ nll, int V) {
+                                                   const int* __restrict__ live, const int32_t* __restrict__ list,
+                                                   float loss_scale, float* __restrict__ nll, int V) {
   __shared__ float red_m[4], red_s[4];
-  const int row = blockIdx.x;
+  const int row = blockIdx.x, n = live[0];
+  if (row >= n) return;
   T* lr = logits + (size_t)row * V;
-  const int label = labels[row];
+  const int label = labels[list[row]];
   const int vecs = V / 8;
-  if (label < 0 || label >= V) {
-    const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int i = threadIdx.x; i < vecs; i += 256) store8(lr + i * 8, zero);
-    if (threadIdx.x == 0) nll[row] = 0.f;
-    return;
-  }
   float m = -INFINITY, sum = 0.f;
   for (int i = threadIdx.x; i < vecs; i += 256) {
     float v[8];
@@ -231,8 +256,7 @@ __global__ __launch_bounds__(256) void xent_kernel(T* __restrict__ logits, const
 #pragma unroll
   for (int w = 0; w < 4; ++w) gs += red_m[w] == -INFINITY ? 0.f : red_s[w] * __expf(red_m[w] - gm);
   const float lse = gm + __logf(gs);
-  const float n = count[0];
-  const float scale = n > 0.f ? loss_scale / n : 0.f;
+  const float scale = loss_scale / (float)n;
   for (int i = threadIdx.x; i < vecs; i += 256) {
     float v[8], g[8];
     load8(lr + i * 8, v);
@@ -250,19 +274,14 @@ __global__ __launch_bounds__(256) void xent_kernel(T* __restrict__ logits, const
 // in registers, so the logits are read from memory once.
 template <int NV>
 __global__ __launch_bounds__(1024) void xent_row_kernel(bf16* __restrict__ logits, const int32_t* __restrict__ labels,
-                                                        const float* __restrict__ count, float loss_scale,
-                                                        float* __restrict__ nll, int V) {
+                                                        const int* __restrict__ live, const int32_t* __restrict__ list,
+                                                        float loss_scale, float* __restrict__ nll, int V) {
   __shared__ float red_m[16], red_s[16];
-  const int row = blockIdx.x;
+  const int row = blockIdx.x, n = live[0];
+  if (row >= n) return;
   bf16* lr = logits + (size_t)row * V;
-  const int label = labels[row];
+  const int label = labels[list[row]];
   const int vecs = V / 8;
-  if (label < 0 || label >= V) {
-    const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int i = threadIdx.x; i < vecs; i += 1024) store8(lr + i * 8, zero);
-    if (threadIdx.x == 0) nll[row] = 0.f;
-    return;
-  }
   bf16x8 v[NV];
   float m = -INFINITY;
 #pragma unroll
@@ -295,8 +314,7 @@ __global__ __launch_bounds__(1024) void xent_row_kernel(bf16* __restrict__ logit
 #pragma unroll
   for (int w = 0; w < 16; ++w) gs += red_s[w];
   const float lse = gm + __logf(gs);
-  const float n = count[0];
-  const float scale = n > 0.f ? loss_scale / n : 0.f;
+  const float scale = loss_scale / (float)n;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int i = k * 1024 + threadIdx.x;
@@ -314,10 +332,11 @@ __global__ __launch_bounds__(1024) void xent_row_kernel(bf16* __restrict__ logit
   }
 }
 
-// loss[0] = sum(nll) / count (0 if nothing was counted).  One workgroup, fixed summation order.
-__global__ __launch_bounds__(256) void loss_finish_kernel(const float* __restrict__ nll, const float* __restrict__ count,
-                                                          int rows, float* __restrict__ loss) {
+// loss[0] = sum(nll) / live (0 if no row counts).  One workgroup, fixed summation order.
+__global__ __launch_bounds__(256) void loss_finish_kernel(const float* __restrict__ nll, const int* __restrict__ live,
+                                                          float* __restrict__ loss) {
   __shared__ float part[256];
+  const int rows = live[0];
   float mine = 0.f;
   for (int t = threadIdx.x; t < rows; t += 256) mine += nll[t];
   part[threadIdx.x] = mine;
@@ -326,24 +345,30 @@ __global__ __launch_bounds__(256) void loss_finish_kernel(const float* __restric
     if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) loss[0] = count[0] > 0.f ? part[0] / count[0] : 0.f;
+  if (threadIdx.x == 0) loss[0] = rows > 0 ? part[0] / (float)rows : 0.f;
 }
 
-// out[i] = sum over the slices of parts[s][i], 8 elements per thread.
-template <typename T>
-__global__ __launch_bounds__(256) void sum_slices_kernel(const float* __restrict__ parts, int slices, size_t count,
-                                                         T* __restrict__ out) {
-  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
-  if (i >= count) return;
-  float acc[8];
-  load8(parts + i, acc);
-  for (int s = 1; s < slices; ++s) {
-    float v[8];
-    load8(parts + (size_t)s * count + i, v);
+// One wavefront per row of `out` (see scatter_rows in kernels.h); slices are added in order.
+template <typename T, typename S>
+__global__ __launch_bounds__(256) void scatter_rows_kernel(const S* __restrict__ product, const int* __restrict__ live,
+                                                           const int32_t* __restrict__ slot, int grid, int K, T* __restrict__ out,
+                                                           int rows, int H) {
+  const int lane = threadIdx.x & 63, row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
+  if (row >= rows) return;
+  const int at = slot[row], n = live[0];
+  int per;
+  const int slices = at < 0 ? 0 : grid > 0 ? split_plan(n, (H + 255) / 256, K, grid, per) : 1;
+  for (int c = lane * 8; c < H; c += 64 * 8) {
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int s = 0; s < slices; ++s) {
+      float v[8];
+      load8(product + ((size_t)s * n + at) * H + c, v);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += v[j];
+      for (int j = 0; j < 8; ++j) acc[j] += v[j];
+    }
+    store8(out + (size_t)row * H + c, acc);
   }
-  store8(out + i, acc);
 }
 
 // Adam with bias correction and decoupled weight decay on 4-element vectors.  The moments and, for
@@ -455,41 +480,52 @@ int embed_backward(int dtype, const int32_t* tokens, const void* dx, float* d_wt
                               : embed_backward_t<float>(tokens, dx, d_wte, d_wpe, b, s, H, vocab, stream);
 }
 
-int count_labels(const int32_t* labels, int rows, int vocab, float* count, hipStream_t stream) {
-  if (rows < 1 || vocab < 1) return set_error(HANAYO_EINVAL, "count_labels: bad shape");
-  hipLaunchKernelGGL(count_labels_kernel, dim3(1), dim3(256), 0, stream, labels, rows, vocab, count);
-  return check_launch("count_labels");
+int list_labelled(const int32_t* labels, int rows, int vocab, int* live, int32_t* list, int32_t* slot, hipStream_t stream) {
+  if (rows < 1 || vocab < 1) return set_error(HANAYO_EINVAL, "list_labelled: bad shape");
+  hipLaunchKernelGGL(list_labelled_kernel, dim3(1), dim3(1024), 0, stream, labels, rows, vocab, live, list, slot);
+  return check_launch("list_labelled");
 }
 
-int softmax_xent(int dtype, void* logits, const int32_t* labels, const float* count, float loss_scale, float* nll,
-                 int rows, int V, hipStream_t stream) {
+int gather_rows(int dtype, const void* in, const int* live, const int32_t* list, void* out, int rows, int H, hipStream_t stream) {
+  if (rows < 1 || H < 8 || H % 8) return set_error(HANAYO_EINVAL, "gather_rows: bad shape");
+  const dim3 grid((rows + kRowsPerBlock - 1) / kRowsPerBlock);
+  if (dtype == HANAYO_BF16)
+    hipLaunchKernelGGL(gather_rows_kernel<bf16>, grid, dim3(256), 0, stream, (const bf16*)in, live, list, (bf16*)out, H);
+  else
+    hipLaunchKernelGGL(gather_rows_kernel<float>, grid, dim3(256), 0, stream, (const float*)in, live, list, (float*)out, H);
+  return check_launch("gather_rows");
+}
+
+int scatter_rows(int dtype, const void* product, const int* live, const int32_t* slot, int grid, int K, void* out, int rows, int H,
+                 hipStream_t stream) {
+  if (rows < 1 || H < 8 || H % 8) return set_error(HANAYO_EINVAL, "scatter_rows: bad shape");
+  const dim3 g((rows + kRowsPerBlock - 1) / kRowsPerBlock);
+  if (dtype != HANAYO_BF16)
+    hipLaunchKernelGGL((scatter_rows_kernel<float, float>), g, dim3(256), 0, stream, (const float*)product, live, slot, grid, K, (float*)out, rows, H);
+  else if (grid > 0)
+    hipLaunchKernelGGL((scatter_rows_kernel<bf16, float>), g, dim3(256), 0, stream, (const float*)product, live, slot, grid, K, (bf16*)out, rows, H);
+  else
+    hipLaunchKernelGGL((scatter_rows_kernel<bf16, bf16>), g, dim3(256), 0, stream, (const bf16*)product, live, slot, grid, K, (bf16*)out, rows, H);
+  return check_launch("scatter_rows");
+}
+
+int softmax_xent(int dtype, void* logits, const int32_t* labels, const int* live, const int32_t* list, float loss_scale,
+                 float* nll, int rows, int V, hipStream_t stream) {
   if (rows < 1 || V < 8 || V % 8) return set_error(HANAYO_EINVAL, "softmax_xent: bad shape");
   if (dtype == HANAYO_BF16 && V > 2048 && V <= 1024 * 8 * 8) {
     const int nv = (V / 8 + 1023) / 1024;
     auto kern = nv <= 2 ? xent_row_kernel<2> : nv <= 4 ? xent_row_kernel<4> : nv <= 6 ? xent_row_kernel<6> : xent_row_kernel<8>;
-    hipLaunchKernelGGL(kern, dim3(rows), dim3(1024), 0, stream, (bf16*)logits, labels, count, loss_scale, nll, V);
+    hipLaunchKernelGGL(kern, dim3(rows), dim3(1024), 0, stream, (bf16*)logits, labels, live, list, loss_scale, nll, V);
   } else if (dtype == HANAYO_BF16)
-    hipLaunchKernelGGL(xent_kernel<bf16>, dim3(rows), dim3(256), 0, stream, (bf16*)logits, labels, count, loss_scale, nll, V);
+    hipLaunchKernelGGL(xent_kernel<bf16>, dim3(rows), dim3(256), 0, stream, (bf16*)logits, labels, live, list, loss_scale, nll, V);
   else
-    hipLaunchKernelGGL(xent_kernel<float>, dim3(rows), dim3(256), 0, stream, (float*)logits, labels, count, loss_scale, nll, V);
+    hipLaunchKernelGGL(xent_kernel<float>, dim3(rows), dim3(256), 0, stream, (float*)logits, labels, live, list, loss_scale, nll, V);
   return check_launch("softmax_xent");
 }
 
-int loss_finish(const float* nll, const float* count, int rows, float* loss, hipStream_t stream) {
-  if (rows < 1) return set_error(HANAYO_EINVAL, "loss_finish: bad shape");
-  hipLaunchKernelGGL(loss_finish_kernel, dim3(1), dim3(256), 0, stream, nll, count, rows, loss);
+int loss_finish(const float* nll, const int* live, float* loss, hipStream_t stream) {
+  hipLaunchKernelGGL(loss_finish_kernel, dim3(1), dim3(256), 0, stream, nll, live, loss);
   return check_launch("loss_finish");
-}
-
-int sum_slices(int dtype, const float* parts, int slices, size_t count, void* out, hipStream_t stream) {
-  if (slices < 1 || count == 0 || count % 8) return set_error(HANAYO_EINVAL, "sum_slices: bad shape");
-  const size_t blocks = (count / 8 + 255) / 256;
-  if (blocks > 0x7fffffffu) return set_error(HANAYO_EUNSUPPORTED, "sum_slices: too many elements");
-  if (dtype == HANAYO_BF16)
-    hipLaunchKernelGGL(sum_slices_kernel<bf16>, dim3((unsigned)blocks), dim3(256), 0, stream, parts, slices, count, (bf16*)out);
-  else
-    hipLaunchKernelGGL(sum_slices_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, parts, slices, count, (float*)out);
-  return check_launch("sum_slices");
 }
 
 int adam(int dtype, const AdamArgs& g, hipStream_t stream) {

@@ -40,6 +40,8 @@ struct DmaGemm {
   int M, N, K;
   int lda, ldb, ldc;
   float* colsum;  // see GemmArgs; folded into the kernel (B_T only)
+  const int* live;  // see GemmArgs; EDGE kernels only
+  int live_dim;
 };
 
 // One launch covers up to kMaxGroup independent problems of one layout and epilogue: workgroups
@@ -157,8 +159,30 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
     if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
-  const DmaGemm p = grp.prob[gi];
-  const int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
+  DmaGemm p = grp.prob[gi];
+  int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
+  if (EDGE && p.live) {
+    const int live = __builtin_amdgcn_readfirstlane(*p.live);
+    if (live < 1) return;
+    if (p.live_dim == LIVE_K) {
+      p.K = live;
+    } else {
+      p.M = live;
+      const int tiles_n = (p.N + BN - 1) / BN, tiles = (live + BM - 1) / BM * tiles_n;
+      if (EPI == EPI_STORE_F32 && p.live_dim == LIVE_M_SPLIT) {
+        int per;
+        const int slices = split_plan(live, tiles_n, p.K, grp.first[kMaxGroup], per), slice = wg / tiles;
+        if (slice >= slices) return;
+        wg -= slice * tiles;
+        p.A += A_T ? (size_t)slice * per * p.lda : (size_t)slice * per;
+        p.B += B_T ? (size_t)slice * per * p.ldb : (size_t)slice * per;
+        p.Cf += (size_t)slice * live * p.ldc;
+        p.K = min(per, p.K - slice * per);
+      } else if (wg >= tiles) {
+        return;
+      }
+    }
+  }
   constexpr int NW = WGM * WGN;                    // wavefronts in the workgroup
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
   using OpA = Operand<BM, A_T, NW>;
@@ -612,6 +636,7 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   for (int i = 0; i < grp.count; ++i) {
     grp.first[i] = (int)tiles;
     tiles += (long)((grp.prob[i].N + BN - 1) / BN) * ((grp.prob[i].M + BM - 1) / BM);
+    if (grp.prob[i].live_dim == LIVE_M_SPLIT && tiles < kSplitGrid) tiles = kSplitGrid;
   }
   for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
   if (tiles > 0x7fffffffL) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: too many tiles");
@@ -694,6 +719,10 @@ int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream
     p.bias = (const bf16*)g.bias; p.aux = (const bf16*)g.aux; p.aux_out = (bf16*)g.aux_out;
     p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
     p.colsum = g.b_t ? g.colsum : nullptr;
+    p.live = g.live; p.live_dim = g.live_dim;
+    edge = edge || g.live;
+    if (g.live && g.live_dim == LIVE_M_SPLIT && (config != 7 || count != 1 || g.epi != EPI_STORE_F32))
+      return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: a split contraction takes one problem of 256 x 256 tiles");
   }
   const GemmArgs& g = gs[0];
   switch (config) {

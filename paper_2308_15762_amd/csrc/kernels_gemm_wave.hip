@@ -52,6 +52,8 @@ struct WaveGemm {
   int M, N, K;
   int lda, ldb, ldc;
   float* colsum;  // see GemmArgs
+  const int* live;
+  int live_dim;
 };
 template <typename T>
 struct WaveGemmGroup {
@@ -205,7 +207,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(WaveGemmGroup<T> grp
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
     if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
-  const WaveGemm<T> p = grp.prob[gi];
+  WaveGemm<T> p = grp.prob[gi];
+  if (p.live) {
+    const int live = __builtin_amdgcn_readfirstlane(*p.live);
+    if (live < 1) return;
+    if (p.live_dim == LIVE_K) p.K = live;
+    else p.M = live;
+    if ((int)blockIdx.x - grp.first[gi] >= (p.M + BM - 1) / BM * ((p.N + BN - 1) / BN)) return;
+  }
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const unsigned lds0 = (unsigned)(unsigned long)((__attribute__((address_space(3))) char*)smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -488,6 +497,7 @@ int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream) {
     p.bias = (const T*)g.bias; p.aux = (const T*)g.aux; p.aux_out = (T*)g.aux_out;
     p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
     p.colsum = g.epi == EPI_ACCUM_F32 ? g.colsum : nullptr;
+    p.live = g.live; p.live_dim = g.live_dim;
     grp.first[i] = (int)tiles;
     tiles += tiles_of(&g, 1, edge);
   }
@@ -506,7 +516,7 @@ bool gemm_wave_supported(int dtype, const GemmArgs& g) {
   const bool combo = (!g.a_t && g.b_t && (g.epi == EPI_NONE || g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU || g.epi == EPI_BIAS_RES)) ||
                      (!g.a_t && !g.b_t && (g.epi == EPI_NONE || g.epi == EPI_MUL_DGELU || g.epi == EPI_ADD)) ||
                      (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32);
-  if (!combo || (g.colsum && g.epi != EPI_ACCUM_F32)) return false;
+  if (!combo || (g.colsum && g.epi != EPI_ACCUM_F32) || (g.live && g.live_dim == LIVE_M_SPLIT)) return false;
   const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
   return bits % 16 == 0 && (g.a_t ? g.M : g.K) % vec == 0 && (g.b_t ? g.N : g.K) % vec == 0 && g.N % vec == 0 && g.lda % vec == 0 &&
          g.ldb % vec == 0 && g.ldc % 4 == 0 && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
