@@ -104,11 +104,10 @@ double rounds_of(long tiles) {
 }
 
 // Tile choice for the direct-to-LDS kernels by a cost model fitted to timings on MI355X: a launch
-// runs ceil(tiles / 256 CUs) rounds; a round costs one K tile's time per 64 columns of K (1.58 us for
-// 256 x 256 with 8 wavefronts, 1.06 us for 256 x 128 (one wavefront per SIMD, three-stage ring; measured on a chip in
-// its sustained clock state with operands that do not stay in the Infinity Cache), 0.59 us for 128 x 128 with two workgroups
-// sharing a CU) plus an epilogue, and the launch a fixed start-up (pipeline fill grows with the
-// tile).  Large tiles reuse operands better; small ones waste less of the last round, which matters
+// runs ceil(tiles / 256 CUs) rounds; a round costs one K tile's time per 64 columns of K (1.60 us for
+// 256 x 256, 0.90 us for 256 x 128, 0.54 us for 128 x 128 with two workgroups sharing a CU, measured on a chip in
+// its sustained clock state with operands that do not stay in the Infinity Cache) plus an epilogue, and the launch a
+// fixed start-up (pipeline fill grows with the tile).  Large tiles reuse operands better; small ones waste less of the last round, which matters
 // less the more the chip is shared with other streams' kernels (set_gemm_sharing), and less of ragged edges.
 // Returns -1 if no configuration takes every problem.  *cost_us is the time to expect of the chosen one, for the
 // comparison with other kernels: the times above are those of a chip whose every CU multiplies and whose clock is down;
@@ -121,7 +120,7 @@ int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
     return g_gemm_config;
   }
   static const struct { int config; double per_ktile, per_ktile_idle, epilogue, start; } kTiles[] = {
-      {7, 1.58, 1.04, 3.0, 7.0}, {10, 1.06, 0.63, 2.0, 4.5}, {9, 0.59, 0.38, 2.3, 3.3}};
+      {7, 1.60, 1.04, 3.0, 7.0}, {10, 0.90, 0.63, 2.0, 4.5}, {9, 0.54, 0.38, 2.3, 3.3}};
   int best = -1;
   double best_cost = 0.0;
   long best_tiles = 0;
@@ -147,12 +146,10 @@ int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
     if (g_gemm_sharing > 0.0) per_ktile = t.per_ktile;
     *cost_us = t.start + rounds_of(tiles) * ((ktiles / tiles) * per_ktile + t.epilogue);
   }
-  // The 256 x 128 tile and, for a launch of at most one tile per CU alone on the chip, the 128 x 128 tile take a ring of
-  // three stages: with one wavefront per SIMD nothing else covers a load that is late, and one more tile of look-ahead
-  // is worth 11 - 21 % on the 2048 x 4096 outputs with K = 4096 .. 16384 (270 us instead of 338 for the input gradient
-  // of FC1 at H = 4096) and 4 - 6 % on the 4096 x 1024 outputs.  The 128 x 128 tile with two stages only where a CU
-  // holds two workgroups at a time (more than 256 tiles, or a chip shared with other lanes): measured alone on the
-  // chip, 2048 x 2560 x 2560 takes 35 us instead of 44, but 4096 x 1024 x 4096, one workgroup per CU, 42 instead of 38.
+  // For a launch of at most one tile per CU alone on the chip the 128 x 128 tile takes a ring of three stages: with one
+  // wavefront per SIMD nothing else covers a load that is late (4096 x 1024 x 4096: 37.0 us, 45.4 with two stages).  Two
+  // stages only where a CU holds two workgroups at a time (more than 256 tiles, or a chip shared with other lanes):
+  // 2048 x 2560 x 2560 in 320 tiles takes 37.9 us instead of 43.2.
   if (best == 9 && best_tiles <= 256 && g_gemm_sharing <= 0.0) best = 11;
   return best;
 }
@@ -189,6 +186,12 @@ int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
   if (g.M < 1 || g.N < 1 || g.K < 1) return set_error(HANAYO_EINVAL, "gemm: empty problem");
   if (g.colsum && (!g.b_t || !g.colsum_scratch)) return set_error(HANAYO_EINVAL, "gemm: colsum needs b_t and scratch");
+  if (g.colsum && g.epi != EPI_ACCUM_F32) {  // only the weight-gradient kernels fold column sums in
+    GemmArgs plain = g;
+    plain.colsum = nullptr;
+    const int rc = gemm(dtype, plain, stream);
+    return rc ? rc : colsum_add(dtype, g.B, g.K, g.N, g.colsum, g.colsum_scratch, stream);
+  }
   if (const int edge = choose_wave_edge(dtype, &g, 1)) return gemm_wave_group(dtype, &g, 1, edge, stream);
   if (dtype == HANAYO_BF16) {
     // the direct-to-LDS kernels fold the column sums into the GEMM

@@ -6,8 +6,13 @@
 // per wavefront instruction, so the swizzle is applied by choosing which global vector each lane fetches:
 //   * contraction-contiguous operand, tile [rows][64]: 8 slots per row, slot' = slot ^ ((row >> 1) & 7)
 //       (16-byte fragment reads of 16 consecutive rows then cover all 64 banks)
-//   * contraction-strided operand, tile [64][cols]: cols/8 slots per row, slot' = slot ^ ((row & 3) << 2)
-//       (the 4 rows x 4 slots one half wavefront touches in a transpose read cover all 64 banks)
+//   * contraction-strided operand, tile [64][cols]: cols/8 slots per row, slot' = slot ^ ((row & 3) << 2 | (row >> 3 & 1) << 1)
+//       (the 8 rows x 2 slots one half wavefront touches in a transpose read cover all 64 banks)
+//
+// The matrix instruction is the 16x16x32 one.  What bounds the large launches is the chip's power: on random operands in
+// registers, eight wavefronts per CU, 16x16x32 sustains 2055 TFLOP/s and 32x32x16 1823 (both issue 2500 at full clock).
+// With 32x32x16 in this kernel: 8192^3 1340 TFLOP/s, now 1425; 4096 x 1024 x 4096 40.2 -> 34.5 us, 2048 x 10240 x 2560
+// (160 tiles) 134 -> 132 us, 2048 x 16384 x 4096 233 -> 224 us, one after the other on one chip in its sustained state.
 // The MFMAs compute the transposed tile, so a lane holds 4 consecutive columns of one row.  The epilogue goes through
 // LDS (the idle load ring) so that stores are whole rows; a launch may carry several problems of one layout
 // (DmaGemmGroup); workgroups take their tiles in an XCD-aware order (xcd_tile).
@@ -28,6 +33,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+typedef __attribute__((address_space(3))) const bf16x8* lds_bf16x8_ptr;
 
 struct DmaGemm {
   const bf16* A;
@@ -39,7 +45,7 @@ struct DmaGemm {
   bf16* aux_out;
   int M, N, K;
   int lda, ldb, ldc;
-  float* colsum;  // see GemmArgs; folded into the kernel (B_T only)
+  float* colsum;  // see GemmArgs; folded into the weight-gradient kernels
   const int* live;  // see GemmArgs; EDGE kernels only
   int live_dim;
 };
@@ -55,7 +61,7 @@ struct DmaGemmGroup {
 };
 
 constexpr int kBK = 64;       // K tile
-constexpr int KS = kBK / 16;  // MFMA steps per K tile
+constexpr int KS = kBK / 32;  // MFMA steps per K tile
 
 // One wavefront-wide 16-byte-per-lane load from global memory into LDS: lane L's
 // vector lands at lds_byte_addr + 16 L.  `voff` is the lane's byte offset from `base`.
@@ -101,7 +107,9 @@ struct Operand {
   static constexpr int kPerWave = kInstr / NW;      // issued by each wavefront
   static_assert(kInstr % NW == 0, "tile loads must divide evenly over the wavefronts");
 
-  __device__ static int swizzle(int row, int slot) { return T ? slot ^ ((row & 3) << 2) : slot ^ ((row >> 1) & 7); }
+  __device__ static int swizzle(int row, int slot) {
+    return T ? slot ^ ((row & 3) << 2 | (row >> 3 & 1) << 1) : slot ^ ((row >> 1) & 7);
+  }
   // Tile row and logical slot of the vector that lands in LDS slot 64 q + lane.
   __device__ static void where(int q, int lane, int& row, int& slot) {
     const int at = q * 64 + lane;
@@ -131,30 +139,36 @@ struct Operand {
     where(q, lane, row, slot);
     return (unsigned)((T ? row * ld : slot * 8) * 2);
   }
+  // What a lane feeds to one 16x16x32 MFMA step: row (column) 16 i + lane % 16 of the wavefront's share, contraction
+  // elements 32 kk + 8 (lane / 16) .. + 7.  lane_at is where that is for i = kk = 0, in bytes from the tile's start, which
+  // is a multiple of 1024; i and kk then only flip or add bits, so one register addresses every fragment of the operand.
+  __device__ static unsigned lane_at(int first, int lane) {
+    if (T) {
+      const int row = 8 * (lane >> 4) + ((lane & 15) >> 2), col = first + (lane & 3) * 4;
+      return (unsigned)((row * kSlotsPerRow + swizzle(row, col >> 3)) * 16 + (col & 7) * 2);
+    }
+    const int row = first + (lane & 15);
+    return (unsigned)((row * kSlotsPerRow + swizzle(row, lane >> 4)) * 16);
+  }
+  __device__ static bf16x8 frag(unsigned at, int i, int kk) {
+    if constexpr (T) {
+      const unsigned p = (at ^ (unsigned)(i * 32)) + kk * 32 * kSlotsPerRow * 16;
+      union {
+        struct { s16x4 lo, hi; } s;
+        bf16x8 v;
+      } u;
+      u.s.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p);
+      u.s.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * kSlotsPerRow * 16));  // same swizzle
+      return u.v;
+    } else {
+      return *(lds_bf16x8_ptr)((at ^ (unsigned)(kk * 64)) + i * 16 * kSlotsPerRow * 16);
+    }
+  }
 };
 
-__device__ __forceinline__ bf16x8 frag_k(const char* lds, int r0, int kk, int lane) {
-  const int row = r0 + (lane & 31), slot = 2 * kk + (lane >> 5);
-  return *reinterpret_cast<const bf16x8*>(lds + (row * (kBK / 8) + (slot ^ ((row >> 1) & 7))) * 16);
-}
-
-template <int SPR>
-__device__ __forceinline__ bf16x8 frag_t(const char* lds, int c0, int kk, int lane) {
-  const int krow = kk * 16 + 8 * (lane >> 5) + ((lane & 15) >> 2);
-  const int col = c0 + 16 * ((lane >> 4) & 1) + (lane & 3) * 4;
-  const int slot = (col >> 3) ^ ((krow & 3) << 2);
-  const char* p = lds + (krow * SPR + slot) * 16 + (col & 7) * 2;
-  union {
-    struct { s16x4 lo, hi; } s;
-    bf16x8 v;
-  } u;
-  u.s.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-  u.s.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * SPR * 16));
-  return u.v;
-}
 
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup grp) {
+__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(DmaGemmGroup grp) {
   int gi = 0;
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
@@ -184,7 +198,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
     }
   }
   constexpr int NW = WGM * WGN;                    // wavefronts in the workgroup
-  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
+  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   using OpA = Operand<BM, A_T, NW>;
   using OpB = Operand<BN, B_T, NW>;
   constexpr int STAGE_BYTES = OpA::kBytes + OpB::kBytes;
@@ -225,21 +239,24 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
   unsigned stage_next = 0;  // buffer index the next issued tile goes to
   const unsigned wave_lds_a = lds0 + wave * OpA::kPerWave * 1024;
   const unsigned wave_lds_b = lds0 + OpA::kBytes + wave * OpB::kPerWave * 1024;
-  int to_start = 0;  // EDGE: number of the next tile to start (only the last one can be partial)
   // the i-th of the LOADS direct loads of the next tile (i is a compile-time constant at every call)
   auto issue_part = [&](int i) {
     const unsigned st = stage_next * STAGE_BYTES;
-    const bool partial = EDGE && k_tail < kBK && to_start == nk - 1;
-    if (i < OpA::kPerWave) {
-      unsigned v = voff_a[i];
+    if (i < OpA::kPerWave) dma16(a_next, voff_a[i], wave_lds_a + st + i * 1024);
+    else dma16(b_next, voff_b[i - OpA::kPerWave], wave_lds_b + st + (i - OpA::kPerWave) * 1024);
+  };
+  // EDGE, before the first load of the last tile (nothing is started after it): what lies past K is fetched from inside
+  auto stay_inside_k = [&](bool last) {
+    if (!EDGE || !last || k_tail == kBK) return;
+#pragma unroll
+    for (int i = 0; i < OpA::kPerWave; ++i) {
       const int q = wave * OpA::kPerWave + i;
-      if (partial && OpA::past_k(q, lane, k_tail)) v -= OpA::k_part(q, lane, p.lda);
-      dma16(a_next, v, wave_lds_a + st + i * 1024);
-    } else {
-      unsigned v = voff_b[i - OpA::kPerWave];
-      const int q = wave * OpB::kPerWave + i - OpA::kPerWave;
-      if (partial && OpB::past_k(q, lane, k_tail)) v -= OpB::k_part(q, lane, p.ldb);
-      dma16(b_next, v, wave_lds_b + st + (i - OpA::kPerWave) * 1024);
+      if (OpA::past_k(q, lane, k_tail)) voff_a[i] -= OpA::k_part(q, lane, p.lda);
+    }
+#pragma unroll
+    for (int i = 0; i < OpB::kPerWave; ++i) {
+      const int q = wave * OpB::kPerWave + i;
+      if (OpB::past_k(q, lane, k_tail)) voff_b[i] -= OpB::k_part(q, lane, p.ldb);
     }
   };
   // EDGE: zeros over what this wavefront loaded from past K into the stage of the last tile
@@ -262,7 +279,6 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
     a_next += a_step;
     b_next += b_step;
     stage_next = stage_next + 1 == NSTAGE ? 0 : stage_next + 1;
-    if (EDGE) ++to_start;
   };
   auto issue = [&]() {
 #pragma unroll
@@ -270,64 +286,33 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
     issue_done();
   };
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // issue order of one step: the LDS reads go out one per MFMA at the start of the step, so the
-  // last of them has a good part of the step to complete
-  auto interleave = [&]() {
-    constexpr int kDs = (A_T ? 2 : 1) * TM + (B_T ? 2 : 1) * TN;
-    constexpr int kMfma = TM * TN;
-    constexpr int kDsEach = kMfma >= kDs ? 1 : (kDs + kMfma - 1) / kMfma;
-    constexpr int kGroups = kMfma >= kDs ? kDs : kMfma;
-#pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-      __builtin_amdgcn_sched_group_barrier(0x100, kDsEach, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-    if (kMfma > kGroups) __builtin_amdgcn_sched_group_barrier(0x008, kMfma - kGroups, 0);
-  };
-  auto read_a = [&](int kt, int kk, bf16x8 (&f)[TM]) {
-    const char* a_lds = smem + (kt % NSTAGE) * STAGE_BYTES;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-      f[i] = A_T ? frag_t<OpA::kSlotsPerRow>(a_lds, wm * WM + i * 32, kk, lane)
-                 : frag_k(a_lds, wm * WM + i * 32, kk, lane);
-  };
-  auto read_b = [&](int kt, int kk, bf16x8 (&f)[TN]) {
-    const char* b_lds = smem + (kt % NSTAGE) * STAGE_BYTES + OpA::kBytes;
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-      f[j] = B_T ? frag_t<OpB::kSlotsPerRow>(b_lds, wn * WN + j * 32, kk, lane)
-                 : frag_k(b_lds, wn * WN + j * 32, kk, lane);
-  };
-  auto mfma_step = [&](const bf16x8 (&a)[TM], const bf16x8 (&b)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-  };
+  const unsigned at_a = lds0 + OpA::lane_at(wm * WM, lane), at_b = lds0 + OpA::kBytes + OpB::lane_at(wn * WN, lane);
+  static_assert(WM <= 128 && WN <= 128 && STAGE_BYTES % 1024 == 0, "frag flips address bits below 256");
 
   // Column sums of B (bias gradient): the workgroup of tile row 0 sums every K tile of its tile column from
   // the B tiles that pass through LDS anyway (each thread adds 4 columns x (kBK / kColRowGroups) rows per
   // tile).  One workgroup per column and a fixed order of additions: the sums are the same bits every run.
   constexpr int kColGroups = BN / 4, kColRowGroups = NW * 64 / kColGroups, kColRows = kBK / kColRowGroups;
   float csum[4] = {0.f, 0.f, 0.f, 0.f};
-  const bool sums_columns = B_T && p.colsum && tile_m == 0;
+  constexpr bool kColsum = EPI == EPI_ACCUM_F32;  // nothing else asks for them
+  const bool sums_columns = kColsum && p.colsum && tile_m == 0;
   auto colsum_tile = [&](int kt) {
-    if constexpr (B_T) {
+    if constexpr (kColsum) {
       if (sums_columns) {
         const char* b_lds = smem + (kt % NSTAGE) * STAGE_BYTES + OpA::kBytes;
         const int c = (threadIdx.x % kColGroups) * 4, rg = threadIdx.x / kColGroups;
 #pragma unroll
         for (int r = 0; r < kColRows; ++r) {
           const int row = rg * kColRows + r;
-          const int slot = (c >> 3) ^ ((row & 3) << 2);
+          const int slot = OpB::swizzle(row, c >> 3);
           const bf16x4 v = *reinterpret_cast<const bf16x4*>(b_lds + (row * OpB::kSlotsPerRow + slot) * 16 + (c & 7) * 2);
 #pragma unroll
           for (int e = 0; e < 4; ++e) csum[e] += (float)v[e];
@@ -336,138 +321,110 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
     }
   };
 
-  {
-    // NSTAGE 64-wide stages (two, or three where the tile leaves room: one more tile of look-ahead for launches
-    // that have a single wavefront per SIMD and nothing else to cover a late load).  Per K tile (KS = 4 MFMA steps):
-    //   steps 0 .. KS-2 of tile kt    | LDS reads: the following step of tile kt
-    //   every fragment of tile kt is in registers; wait until tile kt+1 has landed; barrier (everyone is there)
-    //   start the loads of tile kt+NSTAGE into the buffer tile kt occupied
-    //   step KS-1 of tile kt          | LDS reads: step 0 of tile kt+1
+  // Main loop over K tiles of two MFMA steps.  A wavefront holds the A fragments of one step, each replaced by the next
+  // step's as soon as its row of MFMAs is out, and the B fragments of two:
+  //   step 0                | LDS reads: the fragments of step 1
+  //   step 1, kHead rows    | these cover the last of those reads
+  //   everything of the tile is in registers: wait until the next tile has landed; barrier (everyone is there)
+  //   step 1, other rows    | start the loads of tile kt + NSTAGE into the buffer of tile kt; LDS reads: step 0 of tile kt + 1
+  // Behind each MFMA goes its share of the reads and loads, one or two instructions, held there by scheduling barriers:
+  // every wavefront leaves the barrier in the same phase, so a run of loads between two MFMAs idles the matrix pipe of all
+  // four SIMDs at once.  With three stages the second half of a tile's direct loads goes out in step 0 of the next tile
+  // (with two it would have less than a tile's time to land).
+  constexpr int kHead = 2, kLate = (TM - kHead) * TN, kMf = TM * TN;
+  constexpr int kFirst = NSTAGE < 3 ? LOADS : LOADS / 2, kRest = LOADS - kFirst;
+  static_assert(KS == 2 && kLate >= TN + kHead && kFirst <= 2 * kLate && kRest <= kMf, "slots for every read and load");
+  bf16x8 fa[TM], fb[2][TN];
+  // Loads [n0, n1) of the next tile that belong behind slot m of `slots`: evenly spread.
+  auto issue_slot = [&](int m, int slots, int n0, int n1) {
 #pragma unroll
-    for (int t = 0; t < NSTAGE; ++t)
-      if (t < nk) issue();
-    bf16x8 fa[2][TM], fb[2][TN];
-    wait_tiles<LOADS>(min(NSTAGE - 1, nk - 1));
+    for (int u = 0; u < LOADS; ++u)
+      if (n0 + u < n1 && u * slots / (n1 - n0) == m) issue_part(n0 + u);
+  };
+  // One K tile.  ISSUE: start the loads of tile kt + NSTAGE; `rest`: the previous tile left half of its loads; NEXT: there is
+  // a tile kt + 1, admitted once at most `in_flight` younger tiles are outstanding.
+  auto k_tile = [&](auto issue_tag, auto next_tag, int kt, bool rest, int in_flight) {
+    constexpr bool ISSUE = decltype(issue_tag)::value, NEXT = decltype(next_tag)::value;
+    const unsigned cur = (kt % NSTAGE) * STAGE_BYTES, nxt = ((kt + 1) % NSTAGE) * STAGE_BYTES;
+    unsigned a_cur = at_a + cur, b_cur = at_b + cur, a_nxt = at_a + nxt, b_nxt = at_b + nxt;
+    // left to itself the compiler keeps a register per fragment address and spills
+    asm volatile("" : "+v"(a_cur), "+v"(b_cur));
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][j], fa[i], acc[i][j], 0, 0, 0);
+        if (i == 0) fb[1][j] = OpB::frag(b_cur, j, 1);
+        if (j == TN - 1) fa[i] = OpA::frag(a_cur, i, 1);
+        if (kRest > 0 && NEXT && rest) issue_slot(i * TN + j, kMf, kFirst, LOADS);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    if (kRest > 0 && NEXT && rest) issue_done();
+#pragma unroll
+    for (int i = 0; i < kHead; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[1][j], fa[i], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NEXT) {
+      asm volatile("" : "+v"(a_nxt), "+v"(b_nxt));
+      // the buffer of tile kt is overwritten right after the barrier: its last fragments must have arrived
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if constexpr (ISSUE) wait_vmcnt<(NSTAGE - 2) * LOADS>();
+      else wait_tiles<LOADS>(in_flight);
+      if (!ISSUE && kt + 2 == nk) clear_past_k();
+      __syncthreads();
+      if constexpr (ISSUE) stay_inside_k(kt + NSTAGE == nk - 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = kHead; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int m = (i - kHead) * TN + j;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[1][j], fa[i], acc[i][j], 0, 0, 0);
+        if constexpr (NEXT) {
+          if (m < TN) fb[0][m] = OpB::frag(b_nxt, m, 0);
+          else if (m < TN + kHead) fa[m - TN] = OpA::frag(a_nxt, m - TN, 0);
+          if (j == TN - 1) fa[i] = OpA::frag(a_nxt, i, 0);
+        }
+        if constexpr (ISSUE) issue_slot(m, kLate, 0, kFirst);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    if constexpr (ISSUE && kRest == 0) issue_done();
+    if constexpr (NEXT) colsum_tile(kt + 1);
+  };
+  {
+#pragma unroll
+    for (int t = 0; t < NSTAGE - (kRest > 0); ++t)
+      if (t < nk) {
+        stay_inside_k(t == nk - 1);
+        issue();
+      }
+    if (kRest > 0 && nk >= NSTAGE) {
+      stay_inside_k(NSTAGE == nk);
+#pragma unroll
+      for (int i = 0; i < kFirst; ++i) issue_part(i);
+      wait_vmcnt<(NSTAGE - 1) * LOADS - kRest>();
+    } else {
+      wait_tiles<LOADS>(min(NSTAGE - 1, nk - 1));
+    }
     if (nk == 1) clear_past_k();
     __syncthreads();
     colsum_tile(0);
-    read_a(0, 0, fa[0]);
-    read_b(0, 0, fb[0]);
-    // A tile's direct loads go out one behind each MFMA: the first kFirst in the step after the barrier, the rest
-    // (a 4-wavefront tile has more loads per wavefront than MFMAs per step) in step 0 of the next tile; `pending`
-    // says that this rest is still to be issued.
-    // (Only with three stages: with two, the rest would have less than a tile's time to land.)
-    constexpr int kMf = TM * TN, kFirst = (LOADS < kMf || NSTAGE < 3) ? LOADS : kMf, kRest = LOADS - kFirst;
-    constexpr int kPer = (kFirst + kMf - 1) / kMf;
-    static_assert(kRest <= kMf, "at most two steps' worth of loads per tile");
-    bool pending = false;
-    auto steps_before_barrier = [&](int kt) {
-      {  // step 0, one slot per MFMA: behind it, its share of step 1's fragment reads and of the pending loads
-        const char* a_cur = smem + (kt % NSTAGE) * STAGE_BYTES;
-        const char* b_cur = a_cur + OpA::kBytes;
-        constexpr int kFr = (TM + TN + kMf - 1) / kMf;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int j = 0; j < TN; ++j) fb[0][j] = OpB::frag(at_b, j, 0);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int m = i * TN + j;
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[0][j], fa[0][i], acc[i][j], 0, 0, 0);
-#pragma unroll
-            for (int u = 0; u < kFr; ++u) {
-              const int f = m * kFr + u;
-              if (f < TM)
-                fa[1][f] = A_T ? frag_t<OpA::kSlotsPerRow>(a_cur, wm * WM + f * 32, 1, lane)
-                               : frag_k(a_cur, wm * WM + f * 32, 1, lane);
-              else if (f < TM + TN)
-                fb[1][f - TM] = B_T ? frag_t<OpB::kSlotsPerRow>(b_cur, wn * WN + (f - TM) * 32, 1, lane)
-                                    : frag_k(b_cur, wn * WN + (f - TM) * 32, 1, lane);
-            }
-            if (m < kRest && pending) issue_part(kFirst + m);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        if (kRest > 0 && pending) {
-          issue_done();
-          pending = false;
-        }
-      }
-#pragma unroll
-      for (int st = 1; st + 1 < KS; ++st) {
-        read_a(kt, st + 1, fa[(st + 1) & 1]);
-        read_b(kt, st + 1, fb[(st + 1) & 1]);
-        mfma_step(fa[st & 1], fb[st & 1]);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // the buffer of tile kt is overwritten right after the barrier: its last fragments must have arrived
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    };
+    for (int i = 0; i < TM; ++i) fa[i] = OpA::frag(at_a, i, 0);
+    const std::true_type yes;
+    const std::false_type no;
     int kt = 0;
-    // Steady state: tiles kt+2 .. kt+NSTAGE-1 may still be in flight at the barrier, and tile kt+NSTAGE is started
-    // after it.  Every wavefront of the workgroup leaves the barrier in the same phase, so whatever stands between
-    // the barrier and the next MFMA is time the matrix pipe idles on all four SIMDs at once.  The last step's
-    // fragments are in registers: its MFMAs start at once, and behind each of them goes its share of the tile's
-    // direct loads and of the first fragment reads of tile kt+1, one or two instructions, held there by
-    // scheduling barriers.  (Left to the scheduler the loads, each with its M0 set-up, go out in runs of four
-    // between two MFMAs; both wavefronts of a SIMD do that at the same moment and the pipe idles meanwhile.)
-    for (; kt + NSTAGE < nk; ++kt) {
-      steps_before_barrier(kt);
-      wait_vmcnt<(NSTAGE - 2) * LOADS>();
-      __syncthreads();
-      __builtin_amdgcn_sched_barrier(0);
-      constexpr int kFr = (TM + TN + kMf - 1) / kMf;
-      const char* a_nx = smem + ((kt + 1) % NSTAGE) * STAGE_BYTES;
-      const char* b_nx = a_nx + OpA::kBytes;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int m = i * TN + j;  // one slot per MFMA: its share of the fragment reads and of the direct loads
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[(KS - 1) & 1][j], fa[(KS - 1) & 1][i], acc[i][j], 0, 0, 0);
-#pragma unroll
-          for (int u = 0; u < kFr; ++u) {
-            const int f = m * kFr + u;
-            if (f < TM)
-              fa[0][f] = A_T ? frag_t<OpA::kSlotsPerRow>(a_nx, wm * WM + f * 32, 0, lane)
-                             : frag_k(a_nx, wm * WM + f * 32, 0, lane);
-            else if (f < TM + TN)
-              fb[0][f - TM] = B_T ? frag_t<OpB::kSlotsPerRow>(b_nx, wn * WN + (f - TM) * 32, 0, lane)
-                                  : frag_k(b_nx, wn * WN + (f - TM) * 32, 0, lane);
-          }
-#pragma unroll
-          for (int u = 0; u < kPer; ++u)
-            if (m * kPer + u < kFirst) issue_part(m * kPer + u);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      if (kRest > 0) pending = true;  // the rest goes out in step 0 of tile kt+1, which advances the loader's state
-      else issue_done();
-      colsum_tile(kt + 1);
-    }
+    for (; kt + NSTAGE < nk; ++kt) k_tile(yes, yes, kt, true, 0);
     // The last tiles: nothing left to start.
-    for (; kt + 1 < nk; ++kt) {
-      steps_before_barrier(kt);
-      wait_tiles<LOADS>(min(NSTAGE - 2, nk - 2 - kt));
-      if (kt + 2 == nk) clear_past_k();
-      __syncthreads();
-      colsum_tile(kt + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      read_a(kt + 1, 0, fa[0]);
-      read_b(kt + 1, 0, fb[0]);
-      mfma_step(fa[(KS - 1) & 1], fb[(KS - 1) & 1]);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int st = 0; st + 1 < KS; ++st) {
-      read_a(nk - 1, st + 1, fa[(st + 1) & 1]);
-      read_b(nk - 1, st + 1, fb[(st + 1) & 1]);
-      mfma_step(fa[st & 1], fb[st & 1]);
-      interleave();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    mfma_step(fa[(KS - 1) & 1], fb[(KS - 1) & 1]);
+    for (; kt + 1 < nk; ++kt) k_tile(no, yes, kt, kt + NSTAGE == nk, min(NSTAGE - 2, nk - 2 - kt));
+    k_tile(no, no, kt, false, 0);
   }
 
-  if constexpr (B_T) {
+  if constexpr (kColsum) {
     if (sums_columns) {  // combine the row groups through LDS (the ring is idle now); this workgroup alone owns the columns
       __syncthreads();
       float* red = reinterpret_cast<float*>(smem);
@@ -491,6 +448,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
   // taken out again with each thread owning 8 consecutive columns, so every global access of the
   // epilogue is a run of full rows: 16 bytes per lane, whole 128-byte lines.
   constexpr int EP = BN + 4;  // fp32 row pitch in LDS: +4 keeps the register-layout writes conflict-free
+  constexpr int kBands = WM / 32;
   float* stage = reinterpret_cast<float*>(smem);
   constexpr int kBandRows = WGM * 32, kVecPerRow = BN / 8, kVecs = kBandRows * kVecPerRow;
   static_assert((size_t)kBandRows * EP * 4 <= (size_t)NSTAGE * STAGE_BYTES, "epilogue band must fit the load ring");
@@ -543,7 +501,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
   };
   if constexpr (kReadsAux || kReadsC) prefetch(0, 0);
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
+  for (int i = 0; i < kBands; ++i) {
     __syncthreads();  // the ring (first band) or the previous band is no longer being read
     if constexpr (kGelu) {
       if (i == 0) {
@@ -562,19 +520,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_dma_kernel(DmaGemmGroup gr
       }
     }
     {
-      float* dst = stage + (wm * 32 + (lane & 31)) * EP + wn * WN + 4 * (lane >> 5);
+      float* dst = stage + (wm * 32 + (lane & 15)) * EP + wn * WN + 4 * (lane >> 4);
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f32x4 v;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e];
-          *reinterpret_cast<f32x4*>(dst + j * 32 + 8 * q) = v;
-        }
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4*>(dst + h * 16 * EP + j * 16) = acc[2 * i + h][j];
     }
     if constexpr (kReadsAux || kReadsC) {
-      if (i + 1 < TM) prefetch(i + 1, (i + 1) & 1);
+      if (i + 1 < kBands) prefetch(i + 1, (i + 1) & 1);
     }
     __syncthreads();
 #pragma unroll
@@ -677,9 +630,10 @@ bool whole_tiles(const GemmArgs& g, int config) {
 }  // namespace
 
 // Tile configurations: 7 = 256 x 256 with 8 wavefronts (2 x 4, 128 x 64 each: two per SIMD that cover each other's
-// stalls), two stages; 9 = 128 x 128, two stages (64 KiB: two workgroups per CU); 10 = 256 x 128, three stages; 11 = 128 x
-// 128, three stages (96 KiB, one workgroup per CU: for launches whose single wavefront per SIMD has nothing else to cover
-// a late load).  9, 10 and 11 use 4 wavefronts.
+// stalls), two stages; 9 = 128 x 128 with 4 wavefronts, two stages (64 KiB: two workgroups per CU); 10 = 256 x 128 with 8
+// wavefronts (4 x 2, 64 x 64 each), three stages (with 4 wavefronts of 128 x 64 the same time where every CU has a tile and
+// 3 - 7 % more where some idle: 2048 x 2560 x 2560 34.1 us, here 31.6); 11 = 128 x 128 with 4 wavefronts, three stages (96
+// KiB, one workgroup per CU: for launches whose single wavefront per SIMD has nothing else to cover a late load).
 bool gemm_dma_config_exists(int config) { return config == 7 || (config >= 9 && config <= 11); }
 void gemm_dma_tile(int config, int& bm, int& bn) {
   bm = config == 9 || config == 11 ? 128 : 256;
@@ -691,7 +645,7 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
                                              g.epi == EPI_STORE_F32)) ||
                      (!g.a_t && !g.b_t && (g.epi == EPI_NONE || g.epi == EPI_MUL_DGELU || g.epi == EPI_ADD)) ||
                      (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32);
-  if (!combo || !gemm_dma_config_exists(config)) return false;
+  if (!combo || !gemm_dma_config_exists(config) || (g.colsum && g.epi != EPI_ACCUM_F32)) return false;
   int bm, bn;
   gemm_dma_tile(config, bm, bn);
   // lane offsets are 32-bit byte offsets from the tile origin
@@ -728,7 +682,7 @@ int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream
   switch (config) {
     case 7: return edge ? launch_layout<256, 256, 2, 4, 2, true>(g, grp, stream) : launch_layout<256, 256, 2, 4, 2, false>(g, grp, stream);
     case 9: return edge ? launch_layout<128, 128, 2, 2, 2, true>(g, grp, stream) : launch_layout<128, 128, 2, 2, 2, false>(g, grp, stream);
-    case 10: return edge ? launch_layout<256, 128, 2, 2, 3, true>(g, grp, stream) : launch_layout<256, 128, 2, 2, 3, false>(g, grp, stream);
+    case 10: return edge ? launch_layout<256, 128, 4, 2, 3, true>(g, grp, stream) : launch_layout<256, 128, 4, 2, 3, false>(g, grp, stream);
     default: return edge ? launch_layout<128, 128, 2, 2, 3, true>(g, grp, stream) : launch_layout<128, 128, 2, 2, 3, false>(g, grp, stream);
   }
 }
