@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libhanayo.so")
 SOURCES = [
     "schedule.cpp", "layout.cpp", "chunk.cpp", "executor.cpp", "ops.cpp", "ends.cpp", "kernels_ends.hip",
     "kernels_norm.hip", "kernels_generic.hip", "kernels_gemm_dma.hip", "kernels_gemm_wave.hip",
-    "kernels_attn_mfma.hip", "kernels_attn_f32.hip",
+    "kernels_attn_mfma.hip", "kernels_attn_split.hip", "kernels_attn_f32.hip",
 ]
 
 FLAGS = [

@@ -135,6 +135,8 @@ void set_gemm_config(int config);
 void set_gemm_sharing(double share);
 bool attn_mfma_supported(const AttnArgs& a);
 int attn_forward_mfma(const AttnArgs& a, hipStream_t stream);
+int attn_forward_split(const AttnArgs& a, hipStream_t stream);   // few rows; head dims 32, 64, 80, 96, 128 (called by attn_*_mfma)
+int attn_backward_split(const AttnArgs& a, hipStream_t stream);
 int attn_backward_mfma(const AttnArgs& a, hipStream_t stream);
 
 // ---- the model's ends and the optimizer --------------------------------------------

@@ -17,7 +17,7 @@
 // numbering, which makes the pairing exact.  All outputs come out transposed
 // (lane = row, registers = 4 consecutive columns), so stores are 8-byte vectors
 // and per-row softmax statistics are per-lane scalars.
-#include "device_util.h"
+#include "attn_tile.h"
 #include "kernels.h"
 
 namespace hanayo {
@@ -25,35 +25,13 @@ namespace k {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kPad = 8;  // LDS row padding in elements
-
-__device__ __forceinline__ f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = 0.f;
-  return z;
-}
-
-// Row of accumulator register r inside its 32-row tile.
-__device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
 // 16-byte fragment: row (r0 + lane % 32), contraction elements 16 kk + 8 (lane / 32) .. +7,
 // from a row-major LDS tile whose rows hold the contraction index contiguously.
 template <int PITCH>
 __device__ __forceinline__ bf16x8 frag_rows(const bf16* lds, int r0, int kk, int lane) {
   return *reinterpret_cast<const bf16x8*>(lds + (r0 + (lane & 31)) * PITCH + kk * 16 + 8 * (lane >> 5));
-}
-
-// The same fragment straight from global memory (row pointer given), zero outside [0, d).
-__device__ __forceinline__ bf16x8 frag_global(const bf16* row, bool row_ok, int kk, int lane, int d) {
-  const int c = kk * 16 + 8 * (lane >> 5);
-  bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-  return (row_ok && c < d) ? *reinterpret_cast<const bf16x8*>(row + c) : z;
 }
 
 // Transposed fragment: this lane's "row" is column (c0 + lane % 32) of the LDS tile, its 8
@@ -73,14 +51,6 @@ __device__ __forceinline__ bf16x8 frag_cols(const bf16* lds, int r0, int c0, int
   return u.v;
 }
 
-// Accumulator registers 8t .. 8t+7 as a bf16 MFMA operand.
-__device__ __forceinline__ bf16x8 pack_half(const f32x16& a, int t) {
-  bf16x8 o;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) o[j] = (bf16)a[8 * t + j];
-  return o;
-}
-
 // ROWS x DP tile (DP contiguous) from global rows row0.. with stride ld; zero outside rows < row_lim, cols < d.
 template <int ROWS, int DP>
 __device__ __forceinline__ void tile_to_lds(bf16* lds, const bf16* g, size_t ld, int row0, int row_lim, int d) {
@@ -91,23 +61,6 @@ __device__ __forceinline__ void tile_to_lds(bf16* lds, const bf16* g, size_t ld,
     const bf16x8 val = (row0 + r < row_lim && c < d) ? *reinterpret_cast<const bf16x8*>(g + (size_t)(row0 + r) * ld + c) : z;
     *reinterpret_cast<bf16x8*>(lds + r * (DP + kPad) + c) = val;
   }
-}
-
-struct AttnDev {
-  const bf16* qkv;
-  const int32_t* valid_len;
-  bf16* ctx;
-  float* lse;
-  const bf16* dctx;
-  bf16* dqkv;
-  float* delta;  // written by attn_delta or by the pipelined dQ kernel, read by the others
-  int s, heads, d, causal;
-};
-
-__device__ __forceinline__ int seq_len(const AttnDev& p, int n) {
-  if (!p.valid_len) return p.s;
-  const int v = p.valid_len[n];
-  return v < 1 ? 1 : (v > p.s ? p.s : v);
 }
 
 // ------------------------------------------------------------------ forward
@@ -380,113 +333,17 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(AttnDev p) {
 // Direct-to-LDS variants for head dims 64 and 128 (DP == d; 80 and 96 as partly filled DP = 128 rows): K/V (forward, dQ) or Q/dC (dK/dV)
 // tiles of 64 rows go global -> LDS with global_load_lds_dwordx4 through a ring of NST buffers,
 // so the loads of tile t+NST-1 are in flight while tile t is used; one barrier per tile.
-// LDS rows are unpadded and XOR-swizzled in 16-byte slots so that both access patterns are
-// bank-conflict free:
-//   16-byte fragment reads: 16 consecutive rows at one slot;
-//   transpose reads: 4 consecutive rows x 4 consecutive slots per half wavefront.
-// DP = 64 (8 slots/row, two rows per 256-byte bank line): slot' = slot ^ (r1<<2 | r3<<1 | r2)
-// DP = 128 (16 slots/row, one row per bank line):         slot' = slot ^ (r1<<3 | r0<<2 | r3<<1 | r2)
-// with r0..r3 the low bits of the row.
 // Softmax arithmetic is kept to one fma and one v_exp_f32 per score (scores stay unscaled, the
 // scale goes into the exponent), masks are applied only on tiles that cross the diagonal or the
 // end of the valid keys, and the output accumulator is rescaled only when a row maximum moved.
 // ======================================================================================
 
-__device__ __forceinline__ void dma16(const void* base, unsigned voff, unsigned lds_byte_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(base), "s"(lds_byte_addr)
-      : "memory");
-}
-__device__ __forceinline__ void dma4(const void* base, unsigned voff, unsigned lds_byte_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dword %0, %1"
-      :
-      : "v"(voff), "s"(base), "s"(lds_byte_addr)
-      : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 template <int LOADS>
 __device__ __forceinline__ void wait_tiles(int tiles_in_flight) {
   if (tiles_in_flight <= 0) wait_vmcnt<0>();
   else if (tiles_in_flight == 1) wait_vmcnt<LOADS>();
   else wait_vmcnt<2 * LOADS>();
 }
-
-template <int DP>
-struct SwTile {
-  static_assert(DP == 64 || DP == 128, "swizzled tiles exist for head dims 64 and 128");
-  static constexpr int SPR = DP / 8;
-  static constexpr int kRowsPerInstr = 64 / SPR;
-  static constexpr int kInstr = 64 / kRowsPerInstr;  // per 64-row tile
-  static constexpr int kPerWave = kInstr / 4;
-  static constexpr int kBytes = 64 * DP * 2;
-
-  __device__ static int swz(int row) {
-    return DP == 64 ? ((((row >> 1) & 1) << 2) | ((row >> 2) & 3)) : (((row & 3) << 2) | ((row >> 2) & 3));
-  }
-  // This wavefront's share of the tile whose first row is row0 (rows clamped to s-1).  D = the row
-  // length actually present in memory: for D < DP the slots past it are left as they are (every
-  // instruction still has active lanes, so the load counts per wavefront do not change); their
-  // contents only ever reach output columns >= D, which are not stored.
-  template <int D = DP>
-  __device__ static void issue(const bf16* gbase, int ld, int row0, int s, unsigned lds_addr, int wave, int lane) {
-    static_assert(D % 16 == 0 && D <= DP && D > DP / 2, "row length for this layout");
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-      const int q = wave * kPerWave + i;
-      const int lr = q * kRowsPerInstr + lane / SPR, sp = lane % SPR;
-      const int row = min(row0 + lr, s - 1);
-      const int src = sp ^ swz(lr);  // the global slot that lands in LDS slot sp of this row
-      if (D == DP || src < D / 8) dma16(gbase, (unsigned)((row * ld + (src << 3)) * 2), lds_addr + q * 1024);
-    }
-  }
-  // Per-lane byte offsets of every fragment read inside a tile, computed once per kernel.  The swizzle
-  // depends on the row's low four bits only, so a fragment that starts r0 rows further down (r0 a
-  // multiple of 16) is the same offset plus r0 * SPR * 16, an immediate in the LDS instruction.
-  struct Offsets {
-    unsigned rows[DP / 16];     // 16-byte fragment of contraction step kk (rows = lane % 32)
-    unsigned cols_lo[DP / 32];  // transpose reads of column tile dt: tile rows 4 (lane/32) + 0..3
-    unsigned cols_hi[DP / 32];  //                                   and those rows + 8
-  };
-  __device__ static void init(Offsets& f, int lane) {
-#pragma unroll
-    for (int kk = 0; kk < DP / 16; ++kk) {
-      const int row = lane & 31, slot = 2 * kk + (lane >> 5);
-      f.rows[kk] = (unsigned)((row * SPR + (slot ^ swz(row))) * 16);
-    }
-#pragma unroll
-    for (int dt = 0; dt < DP / 32; ++dt) {
-      const int row = 4 * (lane >> 5) + ((lane & 15) >> 2);
-      const int col = 32 * dt + 16 * ((lane >> 4) & 1) + (lane & 3) * 4;
-      const int slot = col >> 3, sub = (col & 7) * 2;
-      f.cols_lo[dt] = (unsigned)((row * SPR + (slot ^ swz(row))) * 16 + sub);
-      f.cols_hi[dt] = (unsigned)(((row + 8) * SPR + (slot ^ swz(row + 8))) * 16 + sub);
-    }
-  }
-  // rows r0 + lane % 32 (r0 multiple of 16), contraction step kk
-  __device__ static bf16x8 frag_rows(const char* lds, const Offsets& f, int r0, int kk) {
-    return *reinterpret_cast<const bf16x8*>(lds + f.rows[kk] + r0 * SPR * 16);
-  }
-  // columns 32 dt + lane % 32; contraction rows r0 + {0..3, 8..11} + 4 (lane / 32) (r0 multiple of 16)
-  __device__ static bf16x8 frag_cols(const char* lds, const Offsets& f, int r0, int dt) {
-    union {
-      struct { s16x4 lo, hi; } s;
-      bf16x8 v;
-    } u;
-    u.s.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds + f.cols_lo[dt] + r0 * SPR * 16));
-    u.s.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(lds + f.cols_hi[dt] + r0 * SPR * 16));
-    return u.v;
-  }
-};
 
 template <int DP, int NST, int D = DP>
 __global__ __launch_bounds__(256) void attn_fwd_dma_kernel(AttnDev p) {
@@ -1293,7 +1150,20 @@ int raise_lds(K kern, size_t lds) {
 
 // 32-bit lane offsets: the largest byte offset inside one sequence's rows must stay below 2^31
 bool dma_ok(const AttnArgs& a) {
-  return (a.d == 64 || a.d == 80 || a.d == 96 || a.d == 128) && (long)a.s * 3 * a.heads * a.d * 2 < (1L << 31);
+  return (a.d == 32 || a.d == 64 || a.d == 80 || a.d == 96 || a.d == 128) && (long)a.s * 3 * a.heads * a.d * 2 < (1L << 31);
+}
+
+// Few workgroups of 128 rows: 32-row workgroups whose wavefronts split the other side take over.  They do the same products
+// on four times the K and V traffic, so the line lies where the launch would fill most of the chip; half of a causal
+// launch's tile steps are masked away, so it lies higher there.  us forward / backward, 128-row and split kernels:
+//   causal d = 64:  64 workgroups (s = 512) 10.9 / 30.2 and 6.5 / 12.1; 192 (s = 512) 11.2 / 31.1 and 10.6 / 25.9, (s = 2048)
+//                   31.5 / 89.2 and 20.3 / 56.3; 256 (s = 512) 11.5 / 31.9 and 12.2 / 32.2
+//   causal d = 128: 128 (s = 1024) 30.9 / 106 and 19.8 / 55.2; 256 32.5 / 110 and 37.2 / 110;  d = 80: 256 34.3 / 82.2 and 35.4 / 96.2
+//   otherwise:      128 (d = 64, s = 512) 10.2 / 29.7 and 8.5 / 23.1, (d = 128) 18.1 / 62.6 and 18.2 / 52.7; 144 (s = 509)
+//                   11.5 / 36.2 and 13.3 / 28.4; 256 11.1 / 31.5 and 15.0 / 42.3
+bool split_rows(const AttnArgs& a, bool forward) {
+  const long workgroups = (long)a.heads * a.b * ((a.s + 127) / 128);
+  return dma_ok(a) && workgroups <= (a.causal ? 192 : forward ? 128 : 144);
 }
 
 AttnDev to_dev(const AttnArgs& a) {
@@ -1314,12 +1184,16 @@ bool attn_mfma_supported(const AttnArgs& a) { return a.d % 8 == 0 && a.d >= 8 &&
 
 int attn_forward_mfma(const AttnArgs& a, hipStream_t stream) {
   if (!attn_mfma_supported(a)) return set_error(HANAYO_EUNSUPPORTED, "attn_mfma: head dim %d", a.d);
+  if (split_rows(a, true)) return attn_forward_split(a, stream);
   const AttnDev p = to_dev(a);
   const dim3 grid(a.heads, a.b, (a.s + 127) / 128), block(256);
   if (dma_ok(a)) {
     if (a.d == 64) {
       constexpr size_t lds = 4 * 2 * SwTile<64>::kBytes;
       hipLaunchKernelGGL((attn_fwd_pipe_kernel<64, 4>), grid, block, lds, stream, p);
+    } else if (a.d == 32) {  // in the 64-wide LDS rows, half filled
+      constexpr size_t lds = 4 * 2 * SwTile<64>::kBytes;
+      hipLaunchKernelGGL((attn_fwd_pipe_wide_kernel<64, 4, 32>), grid, block, lds, stream, p);
     } else if (a.d == 80) {
       // one tile at a time, two stages, in the 128-wide LDS rows partly filled: 231 registers and 64 KiB, so two
       // workgroups share a CU.  (The pipelined body is no faster here alone, 39.2 against 39.8 us at s = 1024,
@@ -1350,6 +1224,7 @@ int attn_forward_mfma(const AttnArgs& a, hipStream_t stream) {
 
 int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
   if (!attn_mfma_supported(a)) return set_error(HANAYO_EUNSUPPORTED, "attn_mfma: head dim %d", a.d);
+  if (split_rows(a, false)) return attn_backward_split(a, stream);
   int rc;
   const AttnDev p = to_dev(a);
   const dim3 grid(a.heads, a.b, (a.s + 127) / 128), block(256);
@@ -1360,6 +1235,12 @@ int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
     hipLaunchKernelGGL((attn_bwd_dq_pipe_kernel<64, 4>), grid, block, 4 * 2 * SwTile<64>::kBytes, stream, p);
     hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<64, 4>), grid, block, lds_dkv, stream, p);
     return check_launch("attn_bwd_pipe");
+  }
+  if (dma_ok(a) && a.d == 32) {
+    constexpr size_t lds_dkv = 3 * (2 * SwTile<64>::kBytes + 512);
+    hipLaunchKernelGGL((attn_bwd_dq_dma2_kernel<64, 3, 32>), grid, block, 3 * 2 * SwTile<64>::kBytes, stream, p);
+    hipLaunchKernelGGL((attn_bwd_dkv_dma2_kernel<64, 3, 32>), grid, block, lds_dkv, stream, p);
+    return check_launch("attn_bwd_dma");
   }
   if (dma_ok(a)) {  // likewise: dQ first (it writes delta), then dK/dV
     {
