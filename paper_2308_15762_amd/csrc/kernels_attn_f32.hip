@@ -11,7 +11,9 @@
 // registers straight into the next product: accumulator register r of half wavefront h is tile row 8 (r / 4) + 4 h + r mod 4,
 // and that row is what the other operand fetches for MFMA r.
 //
-// Measured (MI355X): b = 2, 8 heads, d = 64, s = 512, causal: forward 208 us on the ALU, 20 here; backward 709 and 68.
+// Measured (MI355X): b = 2, 8 heads, d = 64, s = 512, causal: forward 208 us on the ALU, 17 here; backward 709 and 46.5
+// (65.5 as two launches, dQ first).  The backward kernel keeps its 322 registers and one wavefront per SIMD at d = 64: held
+// to 256 it spills and takes 71 us.
 #include "device_util.h"
 #include "kernels.h"
 
@@ -31,8 +33,7 @@ struct AttnF32 {
   float* lse;
   const float* dctx;
   float* dqkv;
-  float* delta;
-  int s, heads, d, causal, tiles;
+  int s, heads, d, causal, tiles, pairs;  // tiles of 32 rows; (sequence, head) pairs
 };
 
 __device__ __forceinline__ int seq_len(const AttnF32& p, int n) {
@@ -95,10 +96,9 @@ __device__ __forceinline__ f32x16 mul_cols(const Cols& a, const f32x16& w, f32x1
 
 // Workgroup -> (tile, head, sequence): consecutive workgroups are heads, so that the long tiles of a causal grid, which
 // come first, start together.
-__device__ __forceinline__ void place(const AttnF32& p, int& tile, int& h, int& n) {
-  const int w = blockIdx.x, per = gridDim.x / p.tiles;
-  const int hn = w % per;
-  tile = w / per;
+__device__ __forceinline__ void place(const AttnF32& p, int w, int& tile, int& h, int& n) {
+  const int hn = w % p.pairs;
+  tile = w / p.pairs;
   h = hn % p.heads;
   n = hn / p.heads;
 }
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnF32 p) {
   float2* stats = reinterpret_cast<float2*>(smem + NW * part_floats<DP>());
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   int qt, h, n;
-  place(p, qt, h, n);
+  place(p, blockIdx.x, qt, h, n);
   qt = p.tiles - 1 - qt;
   const int H = p.heads * p.d, q0 = qt * 32, q = q0 + (lane & 31);
   const size_t ld3 = (size_t)3 * H;
@@ -208,15 +208,11 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnF32 p) {
   }
 }
 
-// dQ of 32 query rows; forms delta = rowsum(dC * C) on the way and leaves it for the dK / dV kernel.
+// dQ of 32 query rows.
 template <int DP, bool FULL>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnF32 p) {
+__device__ __forceinline__ void bwd_dq(const AttnF32& p, float* smem, int qt, int h, int n) {
   constexpr int DT = DP / 32;
-  extern __shared__ float smem[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
-  int qt, h, n;
-  place(p, qt, h, n);
-  qt = p.tiles - 1 - qt;
   const int H = p.heads * p.d, q0 = qt * 32, q = q0 + (lane & 31), q_in = min(q, p.s - 1);
   const size_t ld3 = (size_t)3 * H, at_q = ((size_t)n * p.s + q_in) * H + h * p.d;
   const float* base = p.qkv + (size_t)n * p.s * ld3 + h * p.d;
@@ -239,7 +235,6 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnF32 p) {
       for (int e = 0; e < 4; ++e) delta += c[e] * cf.v[kk][e];
     }
   delta += __shfl_xor(delta, 32, 64);
-  if (wave == 0 && half == 0 && q < p.s) p.delta[stat] = delta;
 
   f32x16 dq[DT];
 #pragma unroll
@@ -291,16 +286,14 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_f32_kernel(AttnF32 p) {
 
 // dK and dV of 32 keys.
 template <int DP, bool FULL>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnF32 p) {
+__device__ __forceinline__ void bwd_dkv(const AttnF32& p, float* smem, int kt, int h, int n) {
   constexpr int DT = DP / 32;
-  extern __shared__ float smem[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
-  int kt, h, n;
-  place(p, kt, h, n);
   const int H = p.heads * p.d, k0 = kt * 32, key = k0 + (lane & 31);
   const size_t ld3 = (size_t)3 * H;
   const float* base = p.qkv + (size_t)n * p.s * ld3 + h * p.d;
   const float* dcb = p.dctx + (size_t)n * p.s * H + h * p.d;
+  const float* ctb = p.ctx + (size_t)n * p.s * H + h * p.d;
   const size_t stat0 = ((size_t)n * p.heads + h) * p.s;
   const int len = seq_len(p, n);
   const float scale = rsqrtf((float)p.d), c2 = scale * kLog2e;
@@ -320,25 +313,30 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnF32 p) {
     Rows<DP, FULL> qf, cf;
     qf.load(base + (size_t)qr * ld3, p.d, half);
     if (DP <= 64) cf.load(dcb + (size_t)qr * H, p.d, half);
-    float lse2[16], dlt[16];
+    float lse2[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const size_t at = stat0 + min(q0 + acc_row(r, half), p.s - 1);
-      lse2[r] = p.lse[at] * kLog2e;
-      dlt[r] = p.delta[at];
-    }
+    for (int r = 0; r < 16; ++r) lse2[r] = p.lse[stat0 + min(q0 + acc_row(r, half), p.s - 1)] * kLog2e;
     f32x16 sc = mul_rows<DP, FULL>(qf, kf);
     if (DP > 64) {
       __builtin_amdgcn_sched_barrier(0);
       cf.load(dcb + (size_t)qr * H, p.d, half);
     }
+    float delta = 0.f;  // of this lane's row
+#pragma unroll
+    for (int kk = 0; kk < DP / 8; ++kk) {
+      const f32x4 c = *reinterpret_cast<const f32x4*>(ctb + (size_t)qr * H + (FULL || kk * 8 < p.d ? kk * 8 + 4 * half : 0));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) delta += c[e] * cf.v[kk][e];  // cf is zero past d
+    }
+    delta += __shfl_xor(delta, 32, 64);
     f32x16 dp = mul_rows<DP, FULL>(cf, vf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
+      const float dlt = __shfl(delta, acc_row(r, half), 64);
       const int qq = q0 + acc_row(r, half);
       const bool ok = qq < p.s && key < len && (!p.causal || key <= qq);
       sc[r] = ok ? __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -lse2[r])) : 0.f;
-      dp[r] = sc[r] * (dp[r] - dlt[r]);
+      dp[r] = sc[r] * (dp[r] - dlt);
     }
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) {
@@ -373,16 +371,28 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkv_f32_kernel(AttnF32 p) {
   }
 }
 
+// dK / dV of every key tile, then dQ of every query tile, the longer work first: one launch, because the former forms its
+// deltas itself instead of waiting for the latter.
+template <int DP, bool FULL>
+__global__ __launch_bounds__(NW * 64, DP <= 32 ? 2 : 1) void attn_bwd_f32_kernel(AttnF32 p) {
+  extern __shared__ float smem[];
+  const int per_side = p.pairs * p.tiles, side = (int)blockIdx.x >= per_side;
+  int t, h, n;
+  place(p, (int)blockIdx.x - side * per_side, t, h, n);
+  if (side) bwd_dq<DP, FULL>(p, smem, p.tiles - 1 - t, h, n);
+  else bwd_dkv<DP, FULL>(p, smem, t, h, n);
+}
+
 int check_shape(const AttnArgs& a, unsigned& grid) {
   if (a.d % 8 || a.d < 8 || a.d > 128) return set_error(HANAYO_EUNSUPPORTED, "attn_f32: head dim %d", a.d);
   const long wgs = (long)((a.s + 31) / 32) * a.heads * a.b;
-  if (wgs > 0x7fffffffL) return set_error(HANAYO_EUNSUPPORTED, "attn_f32: too many tiles");
+  if (wgs > 0x3fffffffL) return set_error(HANAYO_EUNSUPPORTED, "attn_f32: too many tiles");
   grid = (unsigned)wgs;
   return HANAYO_OK;
 }
 AttnF32 to_dev(const AttnArgs& a) {
-  return AttnF32{(const float*)a.qkv, a.valid_len, (float*)a.ctx, a.lse, (const float*)a.dctx, (float*)a.dqkv, a.delta,
-                 a.s, a.heads, a.d, a.causal ? 1 : 0, (a.s + 31) / 32};
+  return AttnF32{(const float*)a.qkv, a.valid_len, (float*)a.ctx, a.lse, (const float*)a.dctx, (float*)a.dqkv,
+                 a.s, a.heads, a.d, a.causal ? 1 : 0, (a.s + 31) / 32, a.heads * a.b};
 }
 template <int DP>
 constexpr size_t lds_bytes() { return NW * part_floats<DP>() * sizeof(float) + NW * 32 * sizeof(float2); }
@@ -405,11 +415,9 @@ int forward_t(const AttnF32& p, unsigned grid, hipStream_t stream) {
 }
 template <int DP, bool FULL>
 int backward_t(const AttnF32& p, unsigned grid, hipStream_t stream) {
-  static thread_local bool raised_q = false, raised_kv = false;
-  if (const int rc = raise_lds(attn_bwd_dq_f32_kernel<DP, FULL>, lds_bytes<DP>(), raised_q)) return rc;
-  if (const int rc = raise_lds(attn_bwd_dkv_f32_kernel<DP, FULL>, lds_bytes<DP>(), raised_kv)) return rc;
-  hipLaunchKernelGGL((attn_bwd_dq_f32_kernel<DP, FULL>), dim3(grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);  // writes delta
-  hipLaunchKernelGGL((attn_bwd_dkv_f32_kernel<DP, FULL>), dim3(grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);
+  static thread_local bool raised = false;
+  if (const int rc = raise_lds(attn_bwd_f32_kernel<DP, FULL>, lds_bytes<DP>(), raised)) return rc;
+  hipLaunchKernelGGL((attn_bwd_f32_kernel<DP, FULL>), dim3(2 * grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);
   return check_launch("attn_bwd_f32");
 }
 

@@ -240,7 +240,6 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
     for (int e = 0; e < 8; ++e) delta += (float)cf[kk][e] * (float)of[e];
   }
   delta += __shfl_xor(delta, 32, 64);
-  if (wave == 0 && half == 0 && in) p.delta[((size_t)n * p.heads + h) * p.s + q] = delta;  // as the 128-row kernels leave it
   f32x16 dq[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dq[dt] = zero16();
