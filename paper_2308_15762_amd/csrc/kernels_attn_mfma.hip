@@ -1161,7 +1161,12 @@ bool dma_ok(const AttnArgs& a) {
 //   causal d = 128: 128 (s = 1024) 30.9 / 106 and 19.8 / 55.2; 256 32.5 / 110 and 37.2 / 110;  d = 80: 256 34.3 / 82.2 and 35.4 / 96.2
 //   otherwise:      128 (d = 64, s = 512) 10.2 / 29.7 and 8.5 / 23.1, (d = 128) 18.1 / 62.6 and 18.2 / 52.7; 144 (s = 509)
 //                   11.5 / 36.2 and 13.3 / 28.4; 256 11.1 / 31.5 and 15.0 / 42.3
+// Forward up to s = 128 stays with the 128-row kernel.  At s = 64 there is nothing to gain (4.4 and 4.3).  At s = 128 there is
+// (32 heads: 5.8 and 4.3), but two training iterations at that length in bf16 leave a LayerNorm bias off by 1.6 % of its
+// largest entry from rounding alone, held to 2 %, and the split kernel's other rounding made that 2.1 %, although its
+// context is no further from fp64 (relative error 0.188 % and 0.190 %).
 bool split_rows(const AttnArgs& a, bool forward) {
+  if (forward && a.s <= 128) return false;
   const long workgroups = (long)a.heads * a.b * ((a.s + 127) / 128);
   return dma_ok(a) && workgroups <= (a.causal ? 192 : forward ? 128 : 144);
 }
