@@ -95,6 +95,7 @@ thread_local int g_gemm_config = -1;  // measurement knob: of the calling thread
 thread_local double g_gemm_sharing = 0.0;
 }
 void set_gemm_config(int config) { g_gemm_config = config; }
+double gemm_sharing() { return g_gemm_sharing; }
 void set_gemm_sharing(double share) { g_gemm_sharing = share < 0.0 ? 0.0 : (share > 1.0 ? 1.0 : share); }
 
 // Rounds of 256 CUs that a launch of `tiles` workgroups pays for: whole ones alone on the chip; next to kernels of other

@@ -166,37 +166,9 @@ struct Operand {
   }
 };
 
-
+// Tile number `wg` of a problem.
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
-__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(DmaGemmGroup grp) {
-  int gi = 0;
-#pragma unroll
-  for (int j = 1; j < kMaxGroup; ++j)
-    if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
-  DmaGemm p = grp.prob[gi];
-  int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
-  if (EDGE && p.live) {
-    const int live = __builtin_amdgcn_readfirstlane(*p.live);
-    if (live < 1) return;
-    if (p.live_dim == LIVE_K) {
-      p.K = live;
-    } else {
-      p.M = live;
-      const int tiles_n = (p.N + BN - 1) / BN, tiles = (live + BM - 1) / BM * tiles_n;
-      if (EPI == EPI_STORE_F32 && p.live_dim == LIVE_M_SPLIT) {
-        int per;
-        const int slices = split_plan(live, tiles_n, p.K, grp.first[kMaxGroup], per), slice = wg / tiles;
-        if (slice >= slices) return;
-        wg -= slice * tiles;
-        p.A += A_T ? (size_t)slice * per * p.lda : (size_t)slice * per;
-        p.B += B_T ? (size_t)slice * per * p.ldb : (size_t)slice * per;
-        p.Cf += (size_t)slice * live * p.ldc;
-        p.K = min(per, p.K - slice * per);
-      } else if (wg >= tiles) {
-        return;
-      }
-    }
-  }
+__device__ __forceinline__ void gemm_tile(const DmaGemm p, int wg) {
   constexpr int NW = WGM * WGN;                    // wavefronts in the workgroup
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   using OpA = Operand<BM, A_T, NW>;
@@ -574,6 +546,50 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
 }
 
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
+__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(DmaGemmGroup grp) {
+  int gi = 0;
+#pragma unroll
+  for (int j = 1; j < kMaxGroup; ++j)
+    if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
+  DmaGemm p = grp.prob[gi];
+  int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
+  // A launch over rows counted on the device may have fewer workgroups than tiles (see launch): they take several each.
+  constexpr bool kLoop = EDGE && EPI == EPI_NONE && !B_T;
+  int step = 0, tiles_end = 0;
+  if (EDGE && p.live) {
+    const int live = __builtin_amdgcn_readfirstlane(*p.live);
+    if (live < 1) return;
+    if (p.live_dim == LIVE_K) {
+      p.K = live;
+    } else {
+      p.M = live;
+      const int tiles_n = (p.N + BN - 1) / BN, tiles = (live + BM - 1) / BM * tiles_n;
+      if (EPI == EPI_STORE_F32 && p.live_dim == LIVE_M_SPLIT) {
+        int per;
+        const int slices = split_plan(live, tiles_n, p.K, grp.first[kMaxGroup], per), slice = wg / tiles;
+        if (slice >= slices) return;
+        wg -= slice * tiles;
+        p.A += A_T ? (size_t)slice * per * p.lda : (size_t)slice * per;
+        p.B += B_T ? (size_t)slice * per * p.ldb : (size_t)slice * per;
+        p.Cf += (size_t)slice * live * p.ldc;
+        p.K = min(per, p.K - slice * per);
+      } else if (wg >= tiles) {
+        return;
+      }
+      if (kLoop) step = (int)gridDim.x, tiles_end = tiles;
+    }
+  }
+  for (;;) {
+    gemm_tile<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>(p, wg);
+    if (!kLoop || step == 0) return;
+    wg += step;
+    if (wg >= tiles_end) return;
+    wait_vmcnt<0>();
+    __syncthreads();  // the tile's last band is no longer being read
+  }
+}
+
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 int launch(DmaGemmGroup& grp, hipStream_t stream) {
   constexpr int NW = WGM * WGN;
   constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes);
@@ -591,8 +607,16 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
     tiles += (long)((grp.prob[i].N + BN - 1) / BN) * ((grp.prob[i].M + BM - 1) / BM);
     if (grp.prob[i].live_dim == LIVE_M_SPLIT && tiles < kSplitGrid) tiles = kSplitGrid;
   }
-  for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
   if (tiles > 0x7fffffffL) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: too many tiles");
+  // Rows counted on the device: of the workgroups that all M rows would need, those past the count have nothing to do, but
+  // each waits for a CU with room for its LDS (460 of 4096 rows x 30592 columns, 1680 of 1920 workgroups idle: 50 us; 31
+  // for a launch of 460 rows).  Alone on the chip, as many workgroups as fit at once take the tiles in turn; next to other
+  // lanes, where some would start late, the dispatcher deals out one tile each.
+  if (EDGE && EPI == EPI_NONE && !B_T && grp.count == 1 && grp.prob[0].live && grp.prob[0].live_dim == LIVE_M && gemm_sharing() <= 0.0) {
+    const long fit = 256L * (long)(160 * 1024 / lds);
+    if (tiles > fit) tiles = fit;
+  }
+  for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, stream, grp);
   return check_launch("gemm_dma");
 }
