@@ -28,7 +28,7 @@ bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) 
 // The head works on the labelled rows only (a bidirectional model labels about one position in seven): their hidden
 // states are gathered, and the three GEMMs, the loss and their gradients run over `live` rows, a number that stays on
 // the device.  Measured (MI355X), bidirectional, T = 4096, H = 1024, V = 30592, 460 labelled rows: 828 us over all rows,
-// 201 over these (of which 70 add to d_head, 250 MB read and written); all rows labelled, V = 50304: no slower than before
+// 212 over these (of which 70 add to d_head, 250 MB read and written); all rows labelled, V = 50304: no slower than before
 // (the row list, the gather and the scatter take 5 us each of 1.5 ms).
 struct HeadLayout {
   size_t hn;       // [T][H]  LN_f(y)
