@@ -160,7 +160,11 @@ int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
 // 64 x 64 (four rounds of 4096 x 1024: 19 us at K = 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix
 // instructions (256 flop per clock and CU): a 32 x 32 tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
 int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
-  if (gemm_dma_config_exists(g_gemm_config)) return 0;
+  if (dtype == HANAYO_BF16 && gemm_dma_config_exists(g_gemm_config)) {
+    bool forced = true;  // a kernel that does not take these problems (or fp32) forces nothing
+    for (int i = 0; i < count; ++i) forced = forced && gemm_dma_supported(gs[i], g_gemm_config);
+    if (forced) return 0;
+  }
   for (int i = 0; i < count; ++i)
     if (!gemm_wave_supported(dtype, gs[i])) return 0;
   if (g_gemm_config == 0 || g_gemm_config == 1) return g_gemm_config == 0 ? 64 : 32;

@@ -52,3 +52,33 @@ def test_head_on_labelled_rows(dtype, seq, mb, hidden, vocab, picked, final_ln):
     assert not host(dy).reshape(T, hidden)[other].any()
     if final_ln:
         assert perr(host(d_lnf), np.concatenate(w_lnf)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("config", [0, 1, 7, 9, 10, 11])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_head_under_a_forced_gemm_kernel(config, dtype):
+    """A kernel is forced only where it takes the problem: the direct-to-LDS ones take no fp32, whose results are then those of
+    the automatic choice, bit for bit."""
+    d, e = hn.make_desc(1, 64, 1, 64, 65, 3, hn.PRE_LN, hn.MASK_CAUSAL, hn.BF16 if dtype == "bf16" else hn.FP32), hn.EndsDesc(4104, 65, 0)
+    g = torch.Generator().manual_seed(3)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    y, head = torch.randn((3, 65, 64), generator=g).to(t), (0.02 * torch.randn((4104, 64), generator=g)).to(t)
+    labels = torch.randint(-2000, 4104, (3, 65), generator=g, dtype=torch.int32)
+
+    def run(config):
+        loss, d_head, dy = torch.zeros(1, device="cuda"), torch.zeros((4104, 64), device="cuda"), torch.empty_like(y, device="cuda")
+        hn.hanayo_op_gemm_config(config)
+        try:
+            hn.hanayo_head_loss(d, e, None, head.cuda(), y.cuda(), labels.cuda(), 1.0, loss, dy, None, d_head, dev_bytes(hn.hanayo_head_workspace_bytes(d, e)))
+        finally:
+            hn.hanayo_op_gemm_config(-1)
+        torch.cuda.synchronize()
+        return host(loss), host(dy), host(d_head)
+
+    got, auto = run(config), run(-1)
+    f = lambda a: a.double().numpy()
+    want = OE.head_loss(f(y), np.where(labels.numpy() < 0, -1, labels.numpy()), f(head), None, 1e-5, 1.0)
+    for a, b, w in zip(got, auto, want):
+        assert perr(a, w) <= TOL[dtype]
+        if dtype == "fp32" and config > 1:
+            assert (a == b).all()
