@@ -92,16 +92,23 @@ namespace k {
 
 namespace {
 thread_local int g_gemm_config = -1;  // measurement knob: of the calling thread only
+thread_local bool g_in_lanes = false;
 thread_local double g_gemm_sharing = 0.0;
 }
 void set_gemm_config(int config) { g_gemm_config = config; }
+bool in_lanes() { return g_in_lanes; }
 double gemm_sharing() { return g_gemm_sharing; }
-void set_gemm_sharing(double share) { g_gemm_sharing = share < 0.0 ? 0.0 : (share > 1.0 ? 1.0 : share); }
+void set_lanes(bool executor, double busy) {
+  // Measured: next to one other busy lane the shortest GEMM launch still wins, next to three the one with the least CU time.
+  const double share = (busy - 2.0) * 0.5;
+  g_in_lanes = executor;
+  g_gemm_sharing = !executor || share < 0.0 ? 0.0 : (share > 1.0 ? 1.0 : share);
+}
 
-// Rounds of 256 CUs that a launch of `tiles` workgroups pays for: whole ones alone on the chip; next to kernels of other
-// lanes the CUs that its last round leaves idle are not lost, so the count moves towards tiles / 256.
-double rounds_of(long tiles) {
-  return g_gemm_sharing * (double)tiles / 256.0 + (1.0 - g_gemm_sharing) * (double)((tiles + 255) / 256);
+// Rounds of 256 CUs that a launch of `tiles` workgroups pays for: whole ones alone on the chip (share 0); next to kernels of
+// other lanes the CUs that its last round leaves idle are not lost, so the count moves towards tiles / 256 (share 1).
+double rounds_of(long tiles, double share) {
+  return share * (double)tiles / 256.0 + (1.0 - share) * (double)((tiles + 255) / 256);
 }
 
 // Tile choice for the direct-to-LDS kernels by a cost model fitted to timings on MI355X: a launch
@@ -109,11 +116,11 @@ double rounds_of(long tiles) {
 // 256 x 256, 0.90 us for 256 x 128, 0.54 us for 128 x 128 with two workgroups sharing a CU, measured on a chip in
 // its sustained clock state with operands that do not stay in the Infinity Cache) plus an epilogue, and the launch a
 // fixed start-up (pipeline fill grows with the tile).  Large tiles reuse operands better; small ones waste less of the last round, which matters
-// less the more the chip is shared with other streams' kernels (set_gemm_sharing), and less of ragged edges.
+// less the more the chip is shared with other streams' kernels (`share`), and less of ragged edges.
 // Returns -1 if no configuration takes every problem.  *cost_us is the time to expect of the chosen one, for the
 // comparison with other kernels: the times above are those of a chip whose every CU multiplies and whose clock is down;
 // a launch that leaves CUs idle runs at a higher clock (2048 x 2560 x 2560 in 160 tiles of 256 x 128: 0.75 us per K tile).
-int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
+int choose_dma_config(const GemmArgs* gs, int count, double share, double* cost_us) {
   *cost_us = 0.0;
   if (gemm_dma_config_exists(g_gemm_config)) {
     for (int i = 0; i < count; ++i)
@@ -138,27 +145,54 @@ int choose_dma_config(const GemmArgs* gs, int count, double* cost_us) {
       ktiles += (double)ti * ((gs[i].K + 63) / 64);
     }
     if (!ok || tiles == 0) continue;
-    const double cost = t.start + rounds_of(tiles) * ((ktiles / tiles) * t.per_ktile + t.epilogue);
+    const double cost = t.start + rounds_of(tiles, share) * ((ktiles / tiles) * t.per_ktile + t.epilogue);
     if (best >= 0 && cost >= best_cost) continue;
     best = t.config, best_cost = cost, best_tiles = tiles;
     const double used = tiles / (256.0 * (double)((tiles + 255) / 256));  // share of the CUs over the launch's rounds
     double per_ktile = t.per_ktile_idle + (t.per_ktile - t.per_ktile_idle) * used * used;
     if (t.config == 9 && tiles > 256) per_ktile *= 0.75;  // two tiles in one CU overlap (1536 x 3072 x 768: 14.8 us)
-    if (g_gemm_sharing > 0.0) per_ktile = t.per_ktile;
-    *cost_us = t.start + rounds_of(tiles) * ((ktiles / tiles) * per_ktile + t.epilogue);
+    if (share > 0.0) per_ktile = t.per_ktile;
+    *cost_us = t.start + rounds_of(tiles, share) * ((ktiles / tiles) * per_ktile + t.epilogue);
   }
   // For a launch of at most one tile per CU alone on the chip the 128 x 128 tile takes a ring of three stages: with one
   // wavefront per SIMD nothing else covers a load that is late (4096 x 1024 x 4096: 37.0 us, 45.4 with two stages).  Two
   // stages only where a CU holds two workgroups at a time (more than 256 tiles, or a chip shared with other lanes):
   // 2048 x 2560 x 2560 in 320 tiles takes 37.9 us instead of 43.2.
-  if (best == 9 && best_tiles <= 256 && g_gemm_sharing <= 0.0) best = 11;
+  if (best == 9 && best_tiles <= 256 && share <= 0.0) best = 11;
   return best;
 }
 
-// Tile edge of the wavefront-split kernel for these problems, 0 if it does not take them or another kernel is better.
-// The same cost model, in us: a round costs the K tiles of its tiles plus an epilogue.  bf16: 0.178 us per 64 of K for
-// 64 x 64 (four rounds of 4096 x 1024: 19 us at K = 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix
-// instructions (256 flop per clock and CU): a 32 x 32 tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
+// The same cost model for the wavefront-split kernel: the better tile edge and, in us, what it costs.  A round costs the K
+// tiles of its tiles plus an epilogue.  bf16: 0.178 us per 64 of K for 64 x 64 (four rounds of 4096 x 1024: 19 us at K =
+// 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix instructions (256 flop per clock and CU): a 32 x 32
+// tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
+int wave_edge(int dtype, const GemmArgs* gs, int count, double share, double* cost_us) {
+  static const struct { int edge; double per_k, epilogue, start; } kTiles[2][2] = {
+      {{64, 0.178 / 64, 1.0, 3.0}, {32, 0.075 / 64, 0.6, 2.5}}, {{64, 0.0154, 1.0, 3.0}, {32, 0.0044, 0.6, 2.5}}};
+  int best = 0;
+  for (const auto& t : kTiles[dtype == HANAYO_BF16 ? 0 : 1]) {
+    long tiles = 0;
+    double k = 0.0;
+    for (int i = 0; i < count; ++i) {
+      const long ti = (long)((gs[i].M + t.edge - 1) / t.edge) * ((gs[i].N + t.edge - 1) / t.edge);
+      tiles += ti;
+      k += (double)ti * gs[i].K;
+    }
+    const double cost = t.start + rounds_of(tiles, share) * (k / tiles * t.per_k + t.epilogue);
+    if (!best || cost < *cost_us) best = t.edge, *cost_us = cost;
+  }
+  return best;
+}
+
+// Tile edge of the wavefront-split kernel for these problems, 0 if it does not take them or a direct-to-LDS kernel is better.
+// That kernel adds a contraction in another order than the direct-to-LDS ones, which among themselves (and its two tile
+// edges among themselves) give the same bits.  An executor's results do not depend on its lanes, nor on what its plan
+// expects of the other lanes, so between the two kinds the choice is made at one share for all of them.  Alone the split
+// kernel's many small tiles win up to K in the thousands; next to other lanes large tiles use the chip better.  us per
+// 16 x (forward, backward) of a block, share 0 / share 0.7, with 1, 2 and 4 lanes: H = 2048, T = 1024 8460 / 9248, 7996 /
+// 7507, 8343 / 7581; H = 1280, T = 1527 6445 / 6713, 5722 / 5373, 5994 / 5554; H = 512, T = 4096 4210 / 4202, 3274 / 3112,
+// 3404 / 3227.  Up to K = 1024 the time goes into start and epilogue, and nothing is won with lanes (H = 256, T = 2048:
+// 1597 / 1685, 1189 / 1201, 1241 / 1253).
 int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
   if (dtype == HANAYO_BF16 && gemm_dma_config_exists(g_gemm_config)) {
     bool forced = true;  // a kernel that does not take these problems (or fp32) forces nothing
@@ -168,24 +202,19 @@ int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
   for (int i = 0; i < count; ++i)
     if (!gemm_wave_supported(dtype, gs[i])) return 0;
   if (g_gemm_config == 0 || g_gemm_config == 1) return g_gemm_config == 0 ? 64 : 32;
-  static const struct { int edge; double per_k, epilogue, start; } kTiles[2][2] = {
-      {{64, 0.178 / 64, 1.0, 3.0}, {32, 0.075 / 64, 0.6, 2.5}}, {{64, 0.0154, 1.0, 3.0}, {32, 0.0044, 0.6, 2.5}}};
-  int best = 0;
-  double best_cost = 0.0;
-  for (const auto& t : kTiles[dtype == HANAYO_BF16 ? 0 : 1]) {
-    long tiles = 0;
-    double k = 0.0;
+  double wave_cost, dma_cost;
+  if (dtype == HANAYO_BF16) {
+    double k = 0.0, outputs = 0.0;
     for (int i = 0; i < count; ++i) {
-      const long ti = (long)((gs[i].M + t.edge - 1) / t.edge) * ((gs[i].N + t.edge - 1) / t.edge);
-      tiles += ti;
-      k += (double)ti * gs[i].K;
+      const double n = (double)gs[i].M * gs[i].N;
+      outputs += n;
+      k += n * gs[i].K;
     }
-    const double cost = t.start + rounds_of(tiles) * (k / tiles * t.per_k + t.epilogue);
-    if (!best || cost < best_cost) best = t.edge, best_cost = cost;
+    const double share = g_in_lanes && k > 1024.0 * outputs ? 0.7 : 0.0;
+    wave_edge(dtype, gs, count, share, &wave_cost);
+    if (choose_dma_config(gs, count, share, &dma_cost) >= 0 && dma_cost <= wave_cost) return 0;
   }
-  if (dtype != HANAYO_BF16) return best;
-  double dma_cost;
-  return choose_dma_config(gs, count, &dma_cost) >= 0 && dma_cost <= best_cost ? 0 : best;
+  return wave_edge(dtype, gs, count, g_gemm_sharing, &wave_cost);
 }
 
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
@@ -201,7 +230,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
   if (dtype == HANAYO_BF16) {
     // the direct-to-LDS kernels fold the column sums into the GEMM
     double cost;
-    const int config = choose_dma_config(&g, 1, &cost);
+    const int config = choose_dma_config(&g, 1, g_gemm_sharing, &cost);
     if (config >= 0) return gemm_dma(g, config, stream);
   }
   if (g.live) return set_error(HANAYO_EUNSUPPORTED, "gemm: rows counted on the device need 16-byte vectors");
@@ -224,7 +253,7 @@ int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
   }
   if (alike && dtype == HANAYO_BF16) {
     double cost;
-    const int config = choose_dma_config(gs, count, &cost);
+    const int config = choose_dma_config(gs, count, g_gemm_sharing, &cost);
     if (config >= 0) return gemm_dma_group(gs, count, config, stream);
   }
   for (int i = 0; i < count; ++i) {

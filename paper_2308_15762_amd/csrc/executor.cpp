@@ -403,9 +403,7 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
     for (int32_t j : lp.dep[i])
       if (j >= 0 && lp.lane[j] != lane) HIP_NOTE(rc, hipStreamWaitEvent(st, res->events[j], 0));
     if (rc) break;
-    // Measured: next to one other busy lane the shortest GEMM launch still wins, next to three the
-    // one with the least CU time does; the plan says how busy the other lanes are during this task.
-    k::set_gemm_sharing((lp.busy[i] - 2.0f) * 0.5f);
+    k::set_lanes(true, lp.busy[i]);
     void* entry = arena + (pl.chunk_base[tk.chunk] + (size_t)pl.slot[i]) * entry_bytes;
     const int32_t* vl = a->valid_len ? a->valid_len[tk.mb] : nullptr;
     // input-only stash: the lane's scratch entry takes what the forward materialises, then an output scratch
@@ -445,7 +443,7 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
     if (signals[i]) HIP_NOTE(rc, hipEventRecord(res->events[i], st));
     if (rc) break;
   }
-  k::set_gemm_sharing(0.0);
+  k::set_lanes(false, 1.0);
   // join, also after a failed enqueue or a failed event call: the caller's stream ends after every side lane
   for (int l = 1; l < lanes; ++l) {
     int jrc = 0;

@@ -129,10 +129,12 @@ int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStrea
 // 7, 9, 10, 11 = force that direct-to-LDS configuration where it applies; 0 / 1 = the wavefront-split kernel with
 // 64 x 64 / 32 x 32 tiles where it applies; anything else = automatic choice
 void set_gemm_config(int config);
-// How much of the chip the calling thread's GEMM launches share with kernels of other streams: 0 = a launch
-// runs alone (choose the tile for the shortest launch), 1 = idle CUs are always taken by other work (choose
-// for the least CU time).  The executor sets it from its lane count while it enqueues a list.
-void set_gemm_sharing(double share);
+// Whose launches the calling thread enqueues.  executor: a task of the executor, next to which its plan expects `busy` lanes
+// to run (itself among them); otherwise a caller's own, alone on the chip.  in_lanes() decides between kernels that add in
+// different orders (one choice whatever the lanes do, so that results do not depend on them); gemm_sharing() between tiles
+// that give the same bits: 0 = choose for the shortest launch, 1 = idle CUs are always taken by other work.
+void set_lanes(bool executor, double busy);
+bool in_lanes();
 double gemm_sharing();
 bool attn_mfma_supported(const AttnArgs& a);
 int attn_forward_mfma(const AttnArgs& a, hipStream_t stream);

@@ -125,6 +125,22 @@ def test_lanes_do_not_change_results(name):
             assert perr(b.cpu().numpy(), a.cpu().numpy()) <= 1e-5
 
 
+@pytest.mark.parametrize("hidden,heads,seq,mb,causal", [(1024, 16, 512, 4, True), (512, 8, 512, 1, False), (640, 8, 777, 2, True)])
+def test_kernel_choice_does_not_depend_on_lanes(hidden, heads, seq, mb, causal):
+    """The same at sizes where the expected load of the other lanes decides between GEMM tiles and where attention is near its
+    few-rows line: kernels that add in different orders must not be exchanged by it, nor when a backward task recomputes."""
+    wl = W["gpt_1024_bf16"].scaled(hidden=hidden, heads=heads, ffn=4 * hidden, seq=seq, mb=mb, n_blocks=1, P=4, W=1, M=8, causal=causal)
+    runs = []
+    for lanes, mode in ((1, hn.STASH_FULL), (2, hn.STASH_FULL), (4, hn.STASH_FULL), (4, hn.STASH_INPUT)):
+        gpu = GpuRank(wl, 0, lanes=lanes, stash_mode=mode)
+        gpu.run()
+        torch.cuda.synchronize()
+        runs.append([t.clone() for t in gpu.act_out + gpu.grad_out])
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("lanes", [1, 3])
 @pytest.mark.parametrize("name", ["tiny_gpt_fp32_rank0", "gpt_1024_sched_small", "bert_sched_small"])
 def test_input_only_stash_recomputes_to_the_same_result(name, lanes):
