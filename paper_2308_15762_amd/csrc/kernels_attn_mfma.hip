@@ -1154,21 +1154,42 @@ bool dma_ok(const AttnArgs& a) {
 }
 
 // Few workgroups of 128 rows: 32-row workgroups whose wavefronts split the other side take over.  They do the same products
-// on four times the K and V traffic, so the line lies where the launch would fill most of the chip; half of a causal
-// launch's tile steps are masked away, so it lies higher there.  us forward / backward, 128-row and split kernels:
-//   causal d = 64:  64 workgroups (s = 512) 10.9 / 30.2 and 6.5 / 12.1; 192 (s = 512) 11.2 / 31.1 and 10.6 / 25.9, (s = 2048)
-//                   31.5 / 89.2 and 20.3 / 56.3; 256 (s = 512) 11.5 / 31.9 and 12.2 / 32.2
-//   causal d = 128: 128 (s = 1024) 30.9 / 106 and 19.8 / 55.2; 256 32.5 / 110 and 37.2 / 110;  d = 80: 256 34.3 / 82.2 and 35.4 / 96.2
-//   otherwise:      128 (d = 64, s = 512) 10.2 / 29.7 and 8.5 / 23.1, (d = 128) 18.1 / 62.6 and 18.2 / 52.7; 144 (s = 509)
-//                   11.5 / 36.2 and 13.3 / 28.4; 256 11.1 / 31.5 and 15.0 / 42.3
-// Forward up to s = 128 stays with the 128-row kernel.  At s = 64 there is nothing to gain (4.4 and 4.3).  At s = 128 there is
-// (32 heads: 5.8 and 4.3), but two training iterations at that length in bf16 leave a LayerNorm bias off by 1.6 % of its
-// largest entry from rounding alone, held to 2 %, and the split kernel's other rounding made that 2.1 %, although its
-// context is no further from fp64 (relative error 0.188 % and 0.190 %).
+// on four times the K and V traffic, so the line lies where the launch would fill most of the chip: lower for the wide heads
+// (one workgroup per CU), lower without a causal mask (with one, half of the tile steps are masked away and the long chains
+// bound the launch), lower for short sequences (short chains to begin with).
+// Alone on the chip, us forward / backward, 128-row and split kernels:
+//   causal, d = 64:  s = 256 128 workgroups 7.7 / 21.0 and 5.9 / 15.5, 192 8.0 / 21.6 and 9.0 / 20.2; s = 512 192 11.3 / 31.3 and
+//                    10.8 / 26.3; s = 2048 192 31.6 / 89.2 and 21.0 / 56.9
+//   causal, d = 80:  s = 128 64 - / 18.4 and - / 12.0, 128 - / 20.0 and - / 23.2; s = 256 128 11.0 / 29.2 and 10.5 / 27.0, 192 11.3 / 30.5
+//                    and 15.2 / 40.2; s = 512 128 17.5 / 45.9 and 13.4 / 34.5, 192 18.2 / 47.2 and 19.4 / 50.8; s = 1024 192 31.5 / 81.0
+//                    and 27.5 / 73.1;  d = 128 behaves alike (s = 1024 192 31.3 / 108 and 29.8 / 83.6)
+//   no mask, d = 64: s = 512 128 10.3 / 29.8 and 9.0 / 23.8, 160 10.5 / 29.9 and 12.2 / 29.6
+//   no mask, d = 80: s = 256 96 10.2 / 28.9 and 11.1 / 24.5; s = 512 96 16.7 / 46.2 and 16.5 / 35.7; s = 1024 128 29.6 / 83.1 and
+//                    27.4 / 74.6, 192 30.3 / 84.8 and 39.3 / 113
+// Next to other lanes idle CUs are not lost and only the shorter chain counts, so the lines lie lower, the same ones for every
+// lane count (the kernels do not give the same bits).  Change of a step with 4 lanes, forward / backward split, %:
+//   causal, d = 64:  s = 512 128 -0.9 / -2.5, 192 +0.9 / +1.9; s = 2048 128 -2.2 / -10.6
+//   causal, d = 80:  s = 128 32 -2.7 / -5.9, 64 +0.3 / -0.1 (with 2 lanes -0.1 / +1.6); s = 512 96 -0.6 / -1.6, 128 +1.3 / +3.7; s = 2048 128 -1.5 / -3.1
+//   no mask, d = 64: s = 512 96 -0.8 / -1.3, 128 +0.8 / +3.1;  d = 80: s = 512 64 -2.2 / -2.9, 96 +2.4 / +0.3, 128 +3.2 / +7.4
+// (with the lines for a launch alone a step of H = 640, s = 777, 3 sequences, took 6932 us with 4 lanes instead
+// of 6506, one of H = 1024, 8 heads, s = 1024, 2 sequences without a mask 10406 instead of 9883).
+// Forward up to s = 128 stays with the 128-row kernel: alone there is 1 us to gain (d = 64, 64 workgroups: 5.9 and 4.7), a step
+// gains 0 - 3 % with one lane and nothing beyond the noise with four from 64 workgroups on.  Accuracy is no reason: the split
+// kernel's context is the closer one to fp64 (s = 128: 0.187 % and 0.189 %, s = 512 0.193 % and 0.198 %).
 bool split_rows(const AttnArgs& a, bool forward) {
-  if (forward && a.s <= 128) return false;
-  const long workgroups = (long)a.heads * a.b * ((a.s + 127) / 128);
-  return dma_ok(a) && workgroups <= (a.causal ? 192 : forward ? 128 : 144);
+  if (!dma_ok(a) || (forward && a.s <= 128)) return false;
+  const bool narrow = a.d <= 64;
+  long most;
+  if (in_lanes()) {
+    if (a.causal) most = a.d == 32 ? 192 : narrow ? 128 : a.s > 256 ? 96 : 48;
+    else most = a.d == 32 ? 128 : narrow ? 96 : a.s > 256 ? 64 : 48;
+    if (a.causal && a.d != 32 && (long)a.s * a.d >= 1L << 17) most += most / 3;
+  } else if (a.causal) {
+    most = a.s >= 768 || a.d == 32 || (narrow && a.s > 256) ? 192 : narrow || a.s > 128 ? 128 : 64;
+  } else {
+    most = narrow ? (forward ? 128 : 144) : a.s >= 1024 ? 128 : a.s > 256 ? 96 : 64;
+  }
+  return (long)a.heads * a.b * ((a.s + 127) / 128) <= most;
 }
 
 AttnDev to_dev(const AttnArgs& a) {

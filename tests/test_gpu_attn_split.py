@@ -21,7 +21,11 @@ pytestmark = pytest.mark.gpu
     (1, 160, 2, 96, True, False), (1, 225, 1, 96, False, True), (1, 321, 2, 128, True, True), (2, 64, 8, 128, False, False),
     (3, 509, 16, 64, True, False), (2, 509, 16, 64, False, True),   # the last that split: 192 workgroups of 128 rows, 128
     (1, 385, 36, 64, False, False), (1, 481, 49, 32, True, False),  # backward only (144); none (196)
-    (7, 130, 16, 32, True, True), (4, 261, 32, 32, False, True)])   # head dim 32 in the 128-row kernels
+    (7, 130, 16, 32, True, True), (4, 261, 32, 32, False, True),    # head dim 32 in the 128-row kernels
+    # both sides of the lines that depend on the sequence length
+    (2, 250, 32, 64, True, False), (2, 250, 33, 64, True, False), (2, 250, 32, 80, True, False), (2, 250, 33, 80, True, False),
+    (1, 256, 32, 128, False, True), (1, 256, 33, 128, False, True), (1, 300, 32, 96, False, False), (1, 300, 33, 96, False, False),
+    (2, 128, 32, 128, True, False), (2, 128, 33, 128, True, False), (1, 770, 27, 80, True, False), (1, 770, 28, 80, True, False)])
 def test_attention_bf16(b, s, heads, d, causal, padded):
     g = torch.Generator().manual_seed(s * 131 + d)
     H = heads * d
