@@ -185,7 +185,8 @@ size_t hanayo_act_bytes(const hanayo_chunk_desc* d);       /* one [b][s][H] boun
  *   weights      device, packed parameters (read)
  *   x            device [b][s][H] storage type (read)
  *   valid_len    device int32 [b] or NULL: keys j >= valid_len[n] of sequence n are
- *                masked for every query row; each must be in [1, s]
+ *                masked for every query row; each must be in [1, s] (x has to be finite behind
+ *                them too, see hanayo_op_attention_forward)
  *   y            device [b][s][H] (fully overwritten; may not alias x)
  *   stash_entry  device, hanayo_stash_bytes(): written here, read-only in backward;
  *                holds a copy of x, so x may be reused once the call's work is done
@@ -624,7 +625,9 @@ int hanayo_op_colsum_add(int dtype, const void* in, int rows, int n, float* out,
 
 /* qkv [b*s][3H] (Q | K | V), ctx [b*s][H], lse [b][heads][s] fp32 (log-sum-exp of the
    scaled, masked scores).  Backward reads qkv, ctx, lse, dctx and writes all of
-   dqkv [b*s][3H]; delta is scratch [b][heads][s] fp32. */
+   dqkv [b*s][3H]; delta is scratch [b][heads][s] fp32.  What a mask keeps from a row does not reach
+   its results, whatever it holds, in fp32; in bf16 masked rows have to be finite (their probability
+   of zero is multiplied in). */
 int hanayo_op_attention_forward(int dtype, const void* qkv, const int32_t* valid_len, void* ctx, float* lse, int b,
                                 int s, int heads, int head_dim, int causal, void* hip_stream);
 int hanayo_op_attention_backward(int dtype, const void* qkv, const int32_t* valid_len, const void* ctx,

@@ -11,6 +11,10 @@
 // registers straight into the next product: accumulator register r of half wavefront h is tile row 8 (r / 4) + 4 h + r mod 4,
 // and that row is what the other operand fetches for MFMA r.
 //
+// Masked keys and rows have probability zero and count for nothing, whatever they hold; a product with zero lets infinities
+// and NaN through.  They can only reach a result as NaN, so a result that is not finite is worked out again by a wavefront
+// that skips what has probability zero (redo_*), and nothing else pays for it.
+//
 // Measured (MI355X): b = 2, 8 heads, d = 64, s = 512, causal: forward 208 us on the ALU, 17 here; backward 709 and 46.5
 // (65.5 as two launches, dQ first).  The backward kernel keeps its 322 registers and one wavefront per SIMD at d = 64: held
 // to 256 it spills and takes 71 us.
@@ -119,6 +123,122 @@ __device__ __forceinline__ void park(float* part, const f32x16 (&o)[DP / 32], in
 template <int DP>
 constexpr size_t part_floats() { return 32 * (DP + 4); }
 
+// ---- results that are not finite, again: one wavefront per row, a lane per key (query), then two columns per lane.  A NaN
+// among a row's probabilities makes all its columns NaN, so a model that has diverged does not go through every pair here.
+__device__ __forceinline__ bool finite4(const f32x4& v) {
+  const float m = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));  // fmaxf drops NaN: add it back
+  return m < INFINITY && v[0] + v[1] + v[2] + v[3] == v[0] + v[1] + v[2] + v[3];
+}
+__device__ __forceinline__ float dot(const float* a, const float* b, int d) {
+  float t = 0.f;
+  for (int c = 0; c < d; c += 4) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(a + c), y = *reinterpret_cast<const f32x4*>(b + c);
+    t += x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
+  }
+  return t;
+}
+// acc += sum over the 64 lanes' rows with w != 0 of w * row (this lane's columns: lane, lane + 64)
+__device__ __forceinline__ void add_rows(float w, const float* first, size_t ld, int d, int lane, float (&acc)[2]) {
+  for (int j = 0; j < 64; ++j) {
+    const float wj = __shfl(w, j, 64);
+    if (wj == 0.f) continue;
+    const float* row = first + (size_t)j * ld;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (lane + 64 * u < d) acc[u] += wj * row[lane + 64 * u];
+  }
+}
+__device__ __forceinline__ bool nan_row(float w, float (&acc)[2]) {
+  if (!__ballot(w != w)) return false;
+  acc[0] = acc[1] = NAN;
+  return true;
+}
+// Columns whose vector of four is in `vecs`.
+__device__ __forceinline__ void store_columns(float* row, unsigned vecs, int d, int lane, const float (&acc)[2], float scale) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int c = lane + 64 * u;
+    if (c < d && (vecs >> (c >> 2) & 1u)) row[c] = acc[u] * scale;
+  }
+}
+__device__ __forceinline__ void redo_ctx(const AttnF32& p, int n, int h, int q, unsigned vecs) {
+  const int lane = threadIdx.x & 63, H = p.heads * p.d, len = seq_len(p, n), end = p.causal ? min(len, q + 1) : len;
+  const size_t ld3 = (size_t)3 * H;
+  const float* base = p.qkv + (size_t)n * p.s * ld3 + h * p.d;
+  const float* qr = base + (size_t)q * ld3;
+  const float c2 = rsqrtf((float)p.d) * kLog2e;
+  auto score = [&](int j) { return j < end ? dot(qr, base + H + (size_t)j * ld3, p.d) : -INFINITY; };
+  float mx = -INFINITY, sum = 0.f, acc[2] = {0.f, 0.f};
+  for (int j0 = 0; j0 < end; j0 += 64) mx = fmaxf(mx, score(j0 + lane));
+  mx = wave_max(mx);
+  for (int j0 = 0; j0 < end; j0 += 64) {
+    const float t = score(j0 + lane), e = t == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((t - mx) * c2);
+    sum += e;
+    if (nan_row(e, acc)) break;
+    add_rows(e, base + 2 * H + (size_t)j0 * ld3, ld3, p.d, lane, acc);
+  }
+  sum = wave_sum(sum);
+  store_columns(p.ctx + ((size_t)n * p.s + q) * H + h * p.d, vecs, p.d, lane, acc, 1.f / sum);
+  if ((vecs & 1u) && lane == 0) p.lse[((size_t)n * p.heads + h) * p.s + q] = (mx * c2 + log2f(sum)) * kLn2;
+}
+// Probability and score gradient of (query i, key j), zero where the mask says so.
+__device__ __forceinline__ void redo_pair(const AttnF32& p, int n, int h, int i, int j, float& pr, float& ds) {
+  const int H = p.heads * p.d;
+  const size_t ld3 = (size_t)3 * H, at = ((size_t)n * p.s + i) * H + h * p.d;
+  const float* base = p.qkv + (size_t)n * p.s * ld3 + h * p.d;
+  const float c2 = rsqrtf((float)p.d) * kLog2e;
+  const float t = dot(base + (size_t)i * ld3, base + H + (size_t)j * ld3, p.d);
+  const float dp = dot(p.dctx + at, base + 2 * H + (size_t)j * ld3, p.d);
+  pr = __builtin_amdgcn_exp2f(fmaf(t, c2, -p.lse[((size_t)n * p.heads + h) * p.s + i] * kLog2e));
+  ds = pr * (dp - dot(p.dctx + at, p.ctx + at, p.d));
+}
+__device__ __forceinline__ void redo_dq(const AttnF32& p, int n, int h, int q, unsigned vecs) {
+  const int lane = threadIdx.x & 63, H = p.heads * p.d, len = seq_len(p, n), end = p.causal ? min(len, q + 1) : len;
+  const size_t ld3 = (size_t)3 * H, first = (size_t)n * p.s * ld3 + h * p.d;
+  float acc[2] = {0.f, 0.f};
+  for (int j0 = 0; j0 < end; j0 += 64) {
+    float pr = 0.f, ds = 0.f;
+    if (j0 + lane < end) redo_pair(p, n, h, q, j0 + lane, pr, ds);
+    if (pr == 0.f) ds = 0.f;
+    if (nan_row(ds, acc)) break;
+    add_rows(ds, p.qkv + first + H + (size_t)j0 * ld3, ld3, p.d, lane, acc);
+  }
+  store_columns(p.dqkv + first + (size_t)q * ld3, vecs, p.d, lane, acc, rsqrtf((float)p.d));
+}
+// dK (which = 0) or dV (1) of one key.
+__device__ __forceinline__ void redo_dkv(const AttnF32& p, int n, int h, int key, unsigned vecs, int which) {
+  const int lane = threadIdx.x & 63, H = p.heads * p.d;
+  const size_t ld3 = (size_t)3 * H, first = (size_t)n * p.s * ld3 + h * p.d;
+  const float* rows = which ? p.dctx + (size_t)n * p.s * H + h * p.d : p.qkv + first;
+  const size_t ld = which ? (size_t)H : ld3;
+  float acc[2] = {0.f, 0.f};
+  const int begin = p.causal ? key : 0, end = key < seq_len(p, n) ? p.s : 0;
+  for (int i0 = begin; i0 < end; i0 += 64) {
+    float pr = 0.f, ds = 0.f;
+    if (i0 + lane < end) redo_pair(p, n, h, i0 + lane, key, pr, ds);
+    const float w = which || pr == 0.f ? pr : ds;
+    if (nan_row(w, acc)) break;
+    add_rows(w, rows + (size_t)i0 * ld, ld, p.d, lane, acc);
+  }
+  store_columns(p.dqkv + first + (size_t)key * ld3 + (which + 1) * H, vecs, p.d, lane, acc, which ? 1.f : rsqrtf((float)p.d));
+}
+
+// Called by whole wavefronts: lanes with `bad` hold a vector (first column c) of `row` that has to be done again; redo(row,
+// vectors) does one row.
+template <typename Redo>
+__device__ __forceinline__ void redo_rows(bool bad, int row, int c, Redo redo) {
+  unsigned long long left = __ballot(bad);
+  while (left) {
+    const int r = __shfl(row, __ffsll(left) - 1, 64);
+    const bool mine = bad && row == r;
+    unsigned vecs = mine ? 1u << (c >> 2) : 0u;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) vecs |= __shfl_xor(vecs, o, 64);
+    redo(r, vecs);
+    left &= ~__ballot(mine);
+  }
+}
+
 template <int DP, bool FULL>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnF32 p) {
   constexpr int DT = DP / 32;
@@ -183,7 +303,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnF32 p) {
   park<DP>(smem + wave * part_floats<DP>(), o, lane);
   if (half == 0) stats[wave * 32 + lane] = make_float2(m, lsum);
   __syncthreads();
-  const int vecs = p.d / 4;
+  const int vecs = p.d / 4;  // 32 * vecs is a multiple of 64: whole wavefronts
   for (int i = threadIdx.x; i < 32 * vecs; i += NW * 64) {
     const int row = i / vecs, c = (i % vecs) * 4;
     float mx = -INFINITY, total = 0.f;
@@ -199,12 +319,15 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnF32 p) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += t[e] * f;
     }
-    if (q0 + row >= p.s) continue;
     const float inv = 1.f / total;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] *= inv;
-    *reinterpret_cast<f32x4*>(p.ctx + ((size_t)n * p.s + q0 + row) * H + h * p.d + c) = v;
-    if (c == 0) p.lse[((size_t)n * p.heads + h) * p.s + q0 + row] = (mx * c2 + log2f(total)) * kLn2;
+    const bool in = q0 + row < p.s, fine = finite4(v);
+    if (in && fine) {
+      *reinterpret_cast<f32x4*>(p.ctx + ((size_t)n * p.s + q0 + row) * H + h * p.d + c) = v;
+      if (c == 0) p.lse[((size_t)n * p.heads + h) * p.s + q0 + row] = (mx * c2 + log2f(total)) * kLn2;
+    }
+    redo_rows(in && !fine, row, c, [&](int r, unsigned which) { redo_ctx(p, n, h, q0 + r, which); });
   }
 }
 
@@ -270,7 +393,6 @@ __device__ __forceinline__ void bwd_dq(const AttnF32& p, float* smem, int qt, in
   const int vecs = p.d / 4;
   for (int i = threadIdx.x; i < 32 * vecs; i += NW * 64) {
     const int row = i / vecs, c = (i % vecs) * 4;
-    if (q0 + row >= p.s) continue;
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -280,7 +402,9 @@ __device__ __forceinline__ void bwd_dq(const AttnF32& p, float* smem, int qt, in
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] *= scale;
-    *reinterpret_cast<f32x4*>(p.dqkv + ((size_t)n * p.s + q0 + row) * ld3 + h * p.d + c) = v;
+    const bool in = q0 + row < p.s, fine = finite4(v);
+    if (in && fine) *reinterpret_cast<f32x4*>(p.dqkv + ((size_t)n * p.s + q0 + row) * ld3 + h * p.d + c) = v;
+    redo_rows(in && !fine, row, c, [&](int r, unsigned which) { redo_dq(p, n, h, q0 + r, which); });
   }
 }
 
@@ -355,7 +479,6 @@ __device__ __forceinline__ void bwd_dkv(const AttnF32& p, float* smem, int kt, i
     __syncthreads();
     for (int i = threadIdx.x; i < 32 * vecs; i += NW * 64) {
       const int row = i / vecs, c = (i % vecs) * 4;
-      if (k0 + row >= p.s) continue;
       f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
@@ -365,7 +488,9 @@ __device__ __forceinline__ void bwd_dkv(const AttnF32& p, float* smem, int kt, i
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] *= which ? 1.f : scale;
-      *reinterpret_cast<f32x4*>(p.dqkv + ((size_t)n * p.s + k0 + row) * ld3 + (which ? 2 : 1) * H + h * p.d + c) = v;
+      const bool in = k0 + row < p.s, fine = finite4(v);
+      if (in && fine) *reinterpret_cast<f32x4*>(p.dqkv + ((size_t)n * p.s + k0 + row) * ld3 + (which ? 2 : 1) * H + h * p.d + c) = v;
+      redo_rows(in && !fine, row, c, [&](int r, unsigned bad) { redo_dkv(p, n, h, k0 + r, bad, which); });
     }
     __syncthreads();
   }

@@ -58,3 +58,55 @@ def test_attention_fp32(b, s, heads, d, causal, padded):
     for i, name in enumerate(("dq", "dk", "dv")):
         got, ref = host(dqkv)[..., i * H:(i + 1) * H], dqkv_ref[..., i * H:(i + 1) * H]
         assert np.abs(got - ref).max() <= tol * max(np.abs(ref).max(), 1.0), name
+
+
+def run(qkv, vl, dc, heads, d, causal, ctx=None, lse=None):
+    b, s, _ = qkv.shape
+    H = heads * d
+    qd, vd = dev(qkv, "fp32"), None if vl is None else torch.from_numpy(vl).cuda()
+    if ctx is None:
+        ctx, lse = torch.full((b, s, H), 7.0, device="cuda"), torch.full((b, heads, s), 7.0, device="cuda")
+        hn.hanayo_op_attention_forward(hn.FP32, qd, vd, ctx, lse, b, s, heads, d, causal)
+    dqkv, delta = torch.full((b, s, 3 * H), 7.0, device="cuda"), torch.empty((b, heads, s), device="cuda")
+    hn.hanayo_op_attention_backward(hn.FP32, qd, vd, ctx, lse, dev(dc, "fp32"), dqkv, delta, b, s, heads, d, causal)
+    torch.cuda.synchronize()
+    return ctx, lse, host(dqkv)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("s,heads,d", [(40, 1, 24), (97, 2, 64), (161, 1, 96), (130, 2, 128)])
+def test_masked_rows_may_hold_anything(s, heads, d, bad):
+    """Keys behind valid_len and, under the causal mask, later tokens have probability zero: what their rows hold reaches no
+    result that the mask keeps from them."""
+    rng = np.random.default_rng(s + d)
+    H, b = heads * d, 2
+    qkv, dc = rng.normal(size=(b, s, 3 * H)).astype(np.float32), rng.normal(size=(b, s, H)).astype(np.float32)
+    tol = 4 * (d + s + 32) * 2.0 ** -24
+    close = lambda got, ref: np.abs(got - ref).max() <= tol * max(np.abs(ref).max(), 1.0)
+    # keys and values of padding
+    vl = np.array([s - 9, 1], np.int32)
+    for n in range(b):
+        qkv[n, vl[n]:, H:] = 0.0
+    ref = reference(qkv, vl, dc, heads, d, False)
+    for n in range(b):
+        qkv[n, vl[n]:, H:] = bad
+    ctx, lse, dqkv = run(qkv, vl, dc, heads, d, False)
+    assert close(host(ctx), ref[0]) and close(lse.cpu().numpy(), ref[1]) and close(dqkv, ref[2])
+    # token j and those after it, as seen by the tokens before it
+    qkv, j = rng.normal(size=(b, s, 3 * H)).astype(np.float32), s - 21
+    clean = reference(qkv, None, dc, heads, d, True)
+    poisoned = qkv.copy()
+    poisoned[:, j] = bad
+    ctx, lse, dqkv = run(poisoned, None, dc, heads, d, True)
+    assert close(host(ctx)[:, :j], clean[0][:, :j]) and close(lse.cpu().numpy()[:, :, :j], clean[1][:, :, :j])
+    assert close(dqkv[:, :j, :H], clean[2][:, :j, :H])
+    assert np.isnan(host(ctx)[:, j:]).any(axis=-1).all()            # and those that see it do not come out clean
+    # a query and its upstream gradient, as seen by the keys behind it
+    ctx, lse, _ = run(qkv, None, dc, heads, d, True)
+    poisoned, dcp = qkv.copy(), dc.copy()
+    poisoned[:, j, :H] = bad
+    dcp[:, j] = bad
+    _, _, dqkv = run(poisoned, None, dcp, heads, d, True, ctx, lse)
+    assert close(dqkv[:, j + 1:], clean[2][:, j + 1:])
+    assert close(dqkv[:, :j, :H], clean[2][:, :j, :H])
+    assert not np.isfinite(dqkv[:, :j + 1, H:]).any()
