@@ -233,7 +233,6 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
     const int config = choose_dma_config(&g, 1, g_gemm_sharing, &cost);
     if (config >= 0) return gemm_dma(g, config, stream);
   }
-  if (g.live) return set_error(HANAYO_EUNSUPPORTED, "gemm: rows counted on the device need 16-byte vectors");
   const int rc = gemm_alu(dtype, g, stream);
   if (rc || !g.colsum) return rc;
   return colsum_add(dtype, g.B, g.K, g.N, g.colsum, g.colsum_scratch, stream);  // B is stored [K][ldb = N]

@@ -46,9 +46,10 @@ struct HeadLayout {
 };
 
 // d_hc[live][H] = dlogits[live][V] head[V][H] has few output tiles and a contraction over the whole vocabulary: in bf16, from
-// 64 K tiles on, it is cut into slices (split_plan); returns the launch's workgroups, 0 = not split.
+// 64 K tiles on, it is cut into slices (split_plan); returns the launch's workgroups, 0 = not split.  Not from 2^22 columns
+// on, where 256 rows of logits reach past the 2 GiB of that kernel's 32-bit lane offsets.
 int split_grid(const Shape& sh, int vocab) {
-  if (sh.dtype != HANAYO_BF16 || vocab < 64 * 64) return 0;
+  if (sh.dtype != HANAYO_BF16 || vocab < 64 * 64 || vocab >= 1 << 22) return 0;
   const int tiles = (sh.T + 255) / 256 * ((sh.H + 255) / 256);
   return tiles > k::kSplitGrid ? tiles : k::kSplitGrid;
 }

@@ -12,17 +12,29 @@ namespace {
 // ---------------------------------------------------------------- GEMM 64x64x16
 template <typename T, int EPI>
 __global__ __launch_bounds__(256) void gemm_alu_kernel(const T* __restrict__ A, const T* __restrict__ B, int M, int N,
-                                                       int K, int lda, int ldb, bool a_t, bool b_t, EpiParams<T> ep) {
+                                                       int K, int lda, int ldb, bool a_t, bool b_t,
+                                                       const int* __restrict__ live, int live_dim, EpiParams<T> ep) {
   __shared__ float As[16][64 + 4];
   __shared__ float Bs[16][64 + 4];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  float acc[4][4];
+  const int tiles_n = (N + 63) / 64, m0 = (int)(blockIdx.x / tiles_n) * 64, n0 = (int)(blockIdx.x % tiles_n) * 64;
+  if (live) {
+    (live_dim == LIVE_K ? K : M) = live[0];
+    if (live[0] < 1 || m0 >= M) return;
+  }
+  float acc[4][4], sum[4][4];  // of the last 65536 contraction elements, of all before: in one sum over a vocabulary of millions
+                               // the later terms would be lost
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+    for (int j = 0; j < 4; ++j) acc[i][j] = sum[i][j] = 0.f;
   for (int k0 = 0; k0 < K; k0 += 16) {
+    if (k0 && k0 % 65536 == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[i][j] += acc[i][j], acc[i][j] = 0.f;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int idx = threadIdx.x + i * 256;
@@ -59,7 +71,7 @@ __global__ __launch_bounds__(256) void gemm_alu_kernel(const T* __restrict__ A, 
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) epilogue_one<T, EPI>(ep, m, n, acc[i][j]);
+      if (m < M && n < N) epilogue_one<T, EPI>(ep, m, n, sum[i][j] + acc[i][j]);
     }
 }
 
@@ -98,11 +110,14 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const T* __restrict__ c
 template <typename T>
 int gemm_alu_t(const GemmArgs& g, hipStream_t stream) {
   EpiParams<T> ep{(T*)g.C, (float*)g.C, (const T*)g.bias, (const T*)g.aux, (T*)g.aux_out, g.ldc};
-  const dim3 grid((g.N + 63) / 64, (g.M + 63) / 64), block(256);
+  const long tiles = (long)((g.N + 63) / 64) * ((g.M + 63) / 64);  // in one dimension: the others end at 65535 workgroups
+  if (tiles >= 1L << 24) return set_error(HANAYO_EUNSUPPORTED, "gemm_alu: too many tiles");
+  if (g.live && g.live_dim == LIVE_M_SPLIT) return set_error(HANAYO_EUNSUPPORTED, "gemm_alu: split contraction");
+  const dim3 grid((unsigned)tiles), block(256);
 #define LAUNCH(E)                                                                                                    \
   case E:                                                                                                            \
     hipLaunchKernelGGL((gemm_alu_kernel<T, E>), grid, block, 0, stream, (const T*)g.A, (const T*)g.B, g.M, g.N, g.K, \
-                       g.lda, g.ldb, g.a_t, g.b_t, ep);                                                              \
+                       g.lda, g.ldb, g.a_t, g.b_t, g.live, g.live_dim, ep);                                                          \
     break
   switch (g.epi) {
     LAUNCH(EPI_NONE);

@@ -82,3 +82,23 @@ def test_head_under_a_forced_gemm_kernel(config, dtype):
         assert perr(a, w) <= TOL[dtype]
         if dtype == "fp32" and config > 1:
             assert (a == b).all()
+
+
+@pytest.mark.parametrize("dtype,vocab", [("bf16", (1 << 22) - 8), ("bf16", 1 << 22), ("fp32", 1 << 23)])
+def test_head_with_a_very_large_vocabulary(dtype, vocab):
+    """The last vocabulary whose contraction is cut into slices, the first that is not, and one whose rows are too long for the
+    32-bit offsets of the matrix-instruction kernels.  fp32: the contraction over the vocabulary runs in sums of 65536 terms,
+    4 sqrt(65536) 2^-24 < 6.2e-5, by the rule above."""
+    tol = 6.2e-5 if dtype == "fp32" else TOL[dtype]
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    d, e = hn.make_desc(1, 8, 1, 8, 3, 1, hn.PRE_LN, hn.MASK_CAUSAL, hn.BF16 if dtype == "bf16" else hn.FP32), hn.EndsDesc(vocab, 3, 0)
+    g = torch.Generator().manual_seed(11)
+    y, head = torch.randn((1, 3, 8), generator=g).to(t), torch.randn((vocab, 8), generator=g).to(t)
+    labels = torch.tensor([[vocab - 1, -1, 5]], dtype=torch.int32)
+    loss, d_head, dy = torch.zeros(1, device="cuda"), torch.zeros((vocab, 8), device="cuda"), torch.full_like(y, 7.0, device="cuda")
+    hn.hanayo_head_loss(d, e, None, head.cuda(), y.cuda(), labels.cuda(), 1.0, loss, dy, None, d_head, dev_bytes(hn.hanayo_head_workspace_bytes(d, e)))
+    torch.cuda.synchronize()
+    w_loss, w_dy, w_head, _ = OE.head_loss(y.double().numpy(), labels.numpy(), head.double().numpy(), None, 1e-5, 1.0)
+    assert abs(float(loss) - w_loss) <= tol * w_loss
+    assert perr(host(dy), w_dy) <= tol and perr(host(d_head), w_head) <= tol
+    assert not host(dy)[0, 1].any()
