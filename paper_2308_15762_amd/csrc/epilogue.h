@@ -17,6 +17,21 @@ struct EpiParams {
   int ldc;
 };
 
+// Eight elements of a row of C, aux or aux_out: rows start on 8-byte boundaries only where ldc is no multiple of 8.  (The
+// chip takes such 16-byte accesses; the type keeps the compiler from assuming more than there is.)
+typedef bf16x8 bf16x8_row __attribute__((aligned(8)));
+__device__ __forceinline__ void load8_row(const bf16* p, float (&v)[8]) {
+  const bf16x8 a = *reinterpret_cast<const bf16x8_row*>(p);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = (float)a[i];
+}
+__device__ __forceinline__ void store8_row(bf16* p, const float (&v)[8]) {
+  bf16x8 a;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = (bf16)v[i];
+  *reinterpret_cast<bf16x8_row*>(p) = a;
+}
+
 // One output element (m, n) with accumulator value `acc`.
 template <typename T, int EPI>
 __device__ __forceinline__ void epilogue_one(const EpiParams<T>& p, int m, int n, float acc) {

@@ -499,7 +499,7 @@ next_tile:
       int br, c, n;
       size_t at;
       if (!where(i, u, br, c, at, n)) at = (size_t)m0 * p.ldc + n0;  // not used
-      if constexpr (kReadsAux) pre_aux[buf][u] = *reinterpret_cast<const bf16x8*>(p.aux + at);
+      if constexpr (kReadsAux) pre_aux[buf][u] = *reinterpret_cast<const bf16x8_row*>(p.aux + at);
       if constexpr (kReadsC) {
         pre_c[buf][u][0] = *reinterpret_cast<const f32x4*>(p.Cf + at);
         pre_c[buf][u][1] = *reinterpret_cast<const f32x4*>(p.Cf + at + 4);
@@ -570,11 +570,11 @@ next_tile:
           for (int e = 0; e < 8; ++e) v[e] *= gelu_lookup((float)pre_aux[i & 1][u][e]);
         }
         if constexpr (EPI == EPI_BIAS_GELU) {
-          store8(p.aux_out + at, v);
+          store8_row(p.aux_out + at, v);
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] *= gelu_lookup(v[e]);
         }
-        store8(p.C + at, v);
+        store8_row(p.C + at, v);
       }
     }
   }
@@ -673,11 +673,12 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
   gemm_dma_tile(config, bm, bn);
   // lane offsets are 32-bit byte offsets from the tile origin
   const long span_a = (long)(g.a_t ? kBK : bm) * g.lda * 2, span_b = (long)(g.b_t ? kBK : bn) * g.ldb * 2;
-  if (g.lda % 8 || g.ldb % 8 || g.ldc % 4 || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
-  if (whole_tiles(g, config)) return true;
-  // edges: whole 16-byte vectors along every row, on 16-byte boundaries
+  // operands on 16-byte boundaries with every row of A and B on one too (those of C: see epilogue.h)
   const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
-  return bits % 16 == 0 && (g.a_t ? g.M : g.K) % 8 == 0 && (g.b_t ? g.N : g.K) % 8 == 0 && g.N % 8 == 0;
+  if (bits % 16 || g.lda % 8 || g.ldb % 8 || g.ldc % 4 || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
+  if (whole_tiles(g, config)) return true;
+  // edges: whole 16-byte vectors along every row
+  return (g.a_t ? g.M : g.K) % 8 == 0 && (g.b_t ? g.N : g.K) % 8 == 0 && g.N % 8 == 0;
 }
 
 // The problems of a group share layout and epilogue (those of gs[0]); each must pass gemm_dma_supported.

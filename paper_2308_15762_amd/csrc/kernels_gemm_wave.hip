@@ -170,14 +170,14 @@ __device__ __forceinline__ void storev(bf16* p, const float (&v)[4]) {
   for (int i = 0; i < 4; ++i) a[i] = (bf16)v[i];
   *reinterpret_cast<bf16x4*>(p) = a;
 }
-__device__ __forceinline__ void loadv(const bf16* p, float (&v)[8]) { load8(p, v); }
+__device__ __forceinline__ void loadv(const bf16* p, float (&v)[8]) { load8_row(p, v); }
 __device__ __forceinline__ void loadv(const float* p, float (&v)[8]) { load8(p, v); }
 __device__ __forceinline__ void loadv(const float* p, float (&v)[4]) {
   const f32x4 a = *reinterpret_cast<const f32x4*>(p);
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = a[i];
 }
-__device__ __forceinline__ void storev(bf16* p, const float (&v)[8]) { store8(p, v); }
+__device__ __forceinline__ void storev(bf16* p, const float (&v)[8]) { store8_row(p, v); }
 __device__ __forceinline__ void storev(float* p, const float (&v)[8]) { store8(p, v); }
 __device__ __forceinline__ void storev(float* p, const float (&v)[4]) {
   f32x4 a;
@@ -519,7 +519,8 @@ int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream) {
 
 }  // namespace
 
-// 16-byte vectors never straddle the end of a row and start on 16-byte boundaries; lane offsets are 32-bit.
+// 16-byte vectors never straddle the end of a row and, in A and B, start on 16-byte boundaries (in C: see epilogue.h); lane
+// offsets are 32-bit.
 bool gemm_wave_supported(int dtype, const GemmArgs& g) {
   const int vec = dtype == HANAYO_BF16 ? 8 : 4, esz = dtype == HANAYO_BF16 ? 2 : 4;
   const bool combo = (!g.a_t && g.b_t && (g.epi == EPI_NONE || g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU || g.epi == EPI_BIAS_RES)) ||

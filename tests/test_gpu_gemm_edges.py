@@ -82,3 +82,62 @@ def test_gemm_group_edges(config, dtype):
     for p, (c, ca, s, sa) in zip(probs, want):
         assert (np.abs(p["C"].cpu().numpy() - c) <= (K + 4) * 2.0 ** -24 * (ca + 1.0)).all()
         assert (np.abs(p["colsum"].cpu().numpy() - s) <= (K + 4) * 2.0 ** -24 * sa).all()
+
+
+def placed(a, pitch, dtype, shift=0, fill=float("nan")):
+    """`a` on the device with row pitch `pitch`, its first element `shift` elements behind an aligned address; the gaps hold `fill`."""
+    rows, cols = a.shape
+    flat = torch.full((shift + rows * pitch,), fill, device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    t = flat[shift:].view(rows, pitch)
+    t[:, :cols] = dev(np.ascontiguousarray(a), dtype)
+    return t
+
+
+def check_gemm(dtype, layout, epi, M, N, K, pads=(0, 0, 0), shifts=(0, 0, 0)):
+    """One product with pitches pads = (A, B, C) wider than the rows and bases off by shifts elements, against fp64."""
+    a_t, b_t = LAYOUTS[layout]
+    rng = np.random.default_rng(M * 5 + N * 3 + K + epi)
+    rnd = lambda *s: synth.bf16_round(rng.normal(size=s)) if dtype == "bf16" else rng.normal(size=s).astype(np.float32)
+    A, B, bias, aux = rnd(M, K), rnd(K, N), rnd(N), rnd(M, N)
+    ref, sums = A.astype(np.float64) @ B, np.abs(A).astype(np.float64) @ np.abs(B)
+    want = {hn.EPI_NONE: ref, hn.EPI_BIAS: ref + bias, hn.EPI_BIAS_GELU: OB.gelu(ref + bias), hn.EPI_BIAS_RES: ref + bias + aux,
+            hn.EPI_MUL_DGELU: ref * OB.gelu_grad(aux.astype(np.float64)), hn.EPI_ADD: ref + aux, hn.EPI_ACCUM_F32: ref + aux}[epi]
+    lda, ldb, ldc = (M if a_t else K) + pads[0], (N if b_t else K) + pads[1], N + pads[2]
+    Ad, Bd = placed(A.T if a_t else A, lda, dtype, shifts[0]), placed(B if b_t else B.T, ldb, dtype, shifts[1])
+    cdt = "fp32" if epi == hn.EPI_ACCUM_F32 else dtype
+    C = placed(aux if epi == hn.EPI_ACCUM_F32 else 0 * aux, ldc, cdt, shifts[2], 7.0)
+    auxd, pre = placed(aux, ldc, dtype, shifts[2]), placed(0 * aux, ldc, dtype, shifts[2], 7.0)
+    hn.hanayo_op_gemm(hn.BF16 if dtype == "bf16" else hn.FP32, Ad, Bd, C, M, N, K, lda, ldb, ldc, a_t, b_t, epi, dev(bias, dtype), auxd, pre)
+    torch.cuda.synchronize()
+    store = 2.0 ** -8 if cdt == "bf16" else 0.0
+    bound = (K + 4) * 2.0 ** -24 * 1.2 * sums + (store + 2.0 ** -20) * (np.abs(want) + np.abs(ref) + 1.0)
+    assert (np.abs(host(C)[:, :N] - want) <= bound).all()
+    if epi == hn.EPI_BIAS_GELU:
+        assert (np.abs(host(pre)[:, :N] - (ref + bias)) <= bound + (store + 2.0 ** -20) * np.abs(ref + bias)).all()
+    assert (host(C)[:, N:] == 7.0).all() and (host(pre)[:, N:] == 7.0).all()     # nothing past the rows
+
+
+ALL = [(layout, epi) for layout in LAYOUTS for epi in EPIS[layout]]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("layout,epi", ALL)
+@pytest.mark.parametrize("M,N,K,pads", [(256, 256, 128, (8, 16, 8)), (256, 256, 128, (0, 0, 4)), (72, 136, 96, (24, 8, 4))])
+def test_gemm_pitches(config, dtype, layout, epi, M, N, K, pads):
+    """Leading dimensions wider than the rows, also where those of C start on 8-byte boundaries only (bf16, ldc = 4 mod 8)."""
+    check_gemm(dtype, layout, epi, M, N, K, pads)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("layout,epi", ALL)
+@pytest.mark.parametrize("M,N,K,pads,shifts", [
+    (65, 33, 47, (0, 0, 0), (0, 0, 0)), (64, 64, 64, (1, 2, 3), (0, 0, 0)),                                # no whole vectors, odd pitches
+    (256, 256, 128, (0, 0, 0), (1, 0, 0)), (256, 256, 128, (0, 0, 0), (0, 2, 0)), (256, 256, 128, (0, 0, 0), (0, 0, 1))])   # bases off a boundary
+def test_gemm_on_the_alu(dtype, layout, epi, M, N, K, pads, shifts):
+    """What the matrix-instruction kernels do not take."""
+    check_gemm(dtype, layout, epi, M, N, K, pads, shifts)
+
+
+def test_gemm_on_the_alu_long_contraction():
+    """More than 65536 contraction elements: the running sum is put aside every 65536."""
+    check_gemm("fp32", "fwd", hn.EPI_NONE, 3, 5, 65536 + 65536 + 7)
