@@ -10,18 +10,6 @@ namespace k {
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-__device__ __forceinline__ f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = 0.f;
-  return z;
-}
-
-// Row of accumulator register r inside its 32-row tile.
-__device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
-
 // 16-byte fragment straight from global memory (row pointer given): contraction elements 16 kk + 8 (lane / 32) .. +7,
 // zero outside [0, d).
 __device__ __forceinline__ bf16x8 frag_global(const bf16* row, bool row_ok, int kk, int lane, int d) {
@@ -55,15 +43,6 @@ __device__ __forceinline__ int seq_len(const AttnDev& p, int n) {
   return v < 1 ? 1 : (v > p.s ? p.s : v);
 }
 
-__device__ __forceinline__ void dma16(const void* base, unsigned voff, unsigned lds_byte_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(base), "s"(lds_byte_addr)
-      : "memory");
-}
 __device__ __forceinline__ void dma4(const void* base, unsigned voff, unsigned lds_byte_addr) {
   asm volatile(
       "s_mov_b32 m0, %2\n\t"
@@ -72,10 +51,6 @@ __device__ __forceinline__ void dma4(const void* base, unsigned voff, unsigned l
       :
       : "v"(voff), "s"(base), "s"(lds_byte_addr)
       : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 // LDS rows are unpadded and XOR-swizzled in 16-byte slots so that both access patterns are
 // bank-conflict free:

@@ -80,6 +80,35 @@ __device__ __forceinline__ void xcd_tile(int w, int tiles_m, int tiles_n, int& t
   tn = r / rows;
 }
 
+// One wavefront-wide 16-byte-per-lane load from global memory into LDS: lane L's vector lands at lds_byte_addr + 16 L.
+// `voff` is the lane's byte offset from `base`.  M0 carries the LDS address; it is written and consumed inside the statement,
+// and nothing else in these kernels lives in M0 (gfx950 LDS instructions do not use it).
+__device__ __forceinline__ void dma16(const void* base, unsigned voff, unsigned lds_byte_addr) {
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %0, %1"
+      :
+      : "v"(voff), "s"(base), "s"(lds_byte_addr)
+      : "memory");
+}
+// Waits until at most N vector-memory operations of the wavefront are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.f;
+  return z;
+}
+// Row of accumulator register r of a 32 x 32 MFMA inside its tile, for half wavefront `half`.
+__device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
+
 // GELU(h) = h/2 (1 + erf(h / sqrt 2)) and its derivative Phi(h) + h phi(h).
 __device__ __forceinline__ float gelu_f(float h) { return 0.5f * h * (1.0f + erff(h * 0.70710678118654752f)); }
 __device__ __forceinline__ float gelu_grad_f(float h) {

@@ -1,4 +1,4 @@
-// GEMM epilogues, shared by the ALU and the MFMA GEMM kernels.
+// GEMM epilogues: the ALU kernel's, and the row access of the MFMA kernels'.
 #pragma once
 
 #include "device_util.h"
@@ -50,8 +50,6 @@ __device__ __forceinline__ void epilogue_one(const EpiParams<T>& p, int m, int n
     st(p.C + at, acc * gelu_grad_f(ld(p.aux + at)));
   } else if constexpr (EPI == EPI_ADD) {
     st(p.C + at, acc + ld(p.aux + at));
-  } else if constexpr (EPI == EPI_STORE_F32) {
-    p.Cf[at] = acc;
   } else {
     p.Cf[at] += acc;
   }

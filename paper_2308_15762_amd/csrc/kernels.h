@@ -114,7 +114,7 @@ int attn_backward(int dtype, const AttnArgs& a, hipStream_t stream);
 int gemm_alu(int dtype, const GemmArgs& g, hipStream_t stream);
 int attn_forward_f32(const AttnArgs& a, hipStream_t stream);  // fp32 storage
 int attn_backward_f32(const AttnArgs& a, hipStream_t stream);
-int attn_delta(int dtype, const AttnArgs& a, hipStream_t stream);  // delta = rowsum(dctx * ctx)
+int attn_delta(const AttnArgs& a, hipStream_t stream);  // bf16: delta = rowsum(dctx * ctx)
 // Direct-to-LDS kernels in large tiles, bf16: config 7 = 256 x 256 (8 wavefronts), 9 / 11 = 128 x 128 with two / three
 // stages, 10 = 256 x 128.  Any extents made of whole 16-byte vectors.
 bool gemm_dma_config_exists(int config);

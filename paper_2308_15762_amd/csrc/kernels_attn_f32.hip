@@ -26,8 +26,6 @@ namespace k {
 
 namespace {
 
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 constexpr int NW = 4;  // wavefronts per workgroup
 
 struct AttnF32 {
@@ -44,13 +42,6 @@ __device__ __forceinline__ int seq_len(const AttnF32& p, int n) {
   if (!p.valid_len) return p.s;
   const int v = p.valid_len[n];
   return v < 1 ? 1 : (v > p.s ? p.s : v);
-}
-__device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
-__device__ __forceinline__ f32x16 zero16() {
-  f32x16 z;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) z[r] = 0.f;
-  return z;
 }
 
 // Row fragments: this lane's row (lane % 32 of a tile), elements 8 kk + 4 (lane / 32) .. + 3 of it.

@@ -1296,7 +1296,7 @@ int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
     }
     return check_launch("attn_bwd_dma");
   }
-  rc = attn_delta(HANAYO_BF16, a, stream);
+  rc = attn_delta(a, stream);
   if (rc) return rc;
   if (a.d <= 64) {
     hipLaunchKernelGGL((attn_bwd_dkv_kernel<64>), grid, block, 0, stream, p);

@@ -63,37 +63,13 @@ struct DmaGemmGroup {
 constexpr int kBK = 64;       // K tile
 constexpr int KS = kBK / 32;  // MFMA steps per K tile
 
-// One wavefront-wide 16-byte-per-lane load from global memory into LDS: lane L's
-// vector lands at lds_byte_addr + 16 L.  `voff` is the lane's byte offset from `base`.
-// M0 carries the LDS address; it is written and consumed inside the statement, and nothing
-// else in these kernels lives in M0 (gfx950 LDS instructions do not use it).
-__device__ __forceinline__ void dma16(const void* base, unsigned voff, unsigned lds_byte_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(base), "s"(lds_byte_addr)
-      : "memory");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Waits until at most `tiles_in_flight` tiles (LOADS instructions each) are still outstanding.
+// Waits until at most `tiles_in_flight` tiles (0 to 2, LOADS instructions each) are still outstanding.
 template <int LOADS>
 __device__ __forceinline__ void wait_tiles(int tiles_in_flight) {
   switch (tiles_in_flight) {
     case 0: wait_vmcnt<0>(); break;
     case 1: wait_vmcnt<LOADS>(); break;
-    case 2: wait_vmcnt<2 * LOADS>(); break;
-    case 3: wait_vmcnt<3 * LOADS>(); break;
-    case 4: wait_vmcnt<(4 * LOADS > 63 ? 63 : 4 * LOADS)>(); break;
-    case 5: wait_vmcnt<(5 * LOADS > 63 ? 63 : 5 * LOADS)>(); break;
-    case 6: wait_vmcnt<(6 * LOADS > 63 ? 63 : 6 * LOADS)>(); break;
-    default: wait_vmcnt<(7 * LOADS > 63 ? 63 : 7 * LOADS)>(); break;
+    default: wait_vmcnt<2 * LOADS>(); break;
   }
 }
 
@@ -177,7 +153,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
   int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
   // A launch over rows counted on the device may have fewer workgroups than tiles (see launch): they take several each.
   // (By goto: with the tile's code in a function and a loop around it the other instances, which never loop, are scheduled
-  // worse and one spills: 2048 x 16384 x 4096 with GELU' 222 -> 229 us.)
+  // worse and one spills: 2048 x 16384 x 4096 with GELU' 222 -> 229 us.  With the goto only the 256 x 256 instance that loops
+  // spills, 10 registers, 44 bytes per lane; with the function it does not, and the head of 460 rows x 30592 columns takes 201
+  // us instead of 208.)
   constexpr bool kLoop = EDGE && EPI == EPI_NONE && !B_T;
   int step = 0, tiles_end = 0;
   if (EDGE && p.live) {
@@ -448,8 +426,8 @@ next_tile:
     }
   }
 
-  // Epilogue through LDS.  In registers a lane holds 4 consecutive columns of one row, and the 32
-  // lanes of a half wavefront hold 32 different rows: stores (and the reads of the residual or
+  // Epilogue through LDS.  In registers a lane holds 4 consecutive columns of one row, and 16
+  // consecutive lanes hold 16 different rows: stores (and the reads of the residual or
   // pre-activation operand) straight from that layout touch 16 bytes per row.  Instead, one band
   // of 32 rows per wavefront row (WGM * 32 rows x BN columns, fp32) at a time is parked in LDS and
   // taken out again with each thread owning 8 consecutive columns, so every global access of the
@@ -628,7 +606,9 @@ int launch_layout(const GemmArgs& g, DmaGemmGroup& grp, hipStream_t stream) {
       case EPI_BIAS: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_BIAS, EDGE>(grp, stream);
       case EPI_BIAS_GELU: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_BIAS_GELU, EDGE>(grp, stream);
       case EPI_BIAS_RES: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_BIAS_RES, EDGE>(grp, stream);
-      case EPI_STORE_F32: return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_STORE_F32, EDGE>(grp, stream);
+      case EPI_STORE_F32:  // the split contraction of LIVE_M_SPLIT only
+        if constexpr (BM == 256 && BN == 256 && EDGE) return launch<BM, BN, WGM, WGN, NSTAGE, false, true, EPI_STORE_F32, EDGE>(grp, stream);
+        break;
       default: break;
     }
   } else if (!g.a_t && !g.b_t) {
@@ -665,7 +645,7 @@ void gemm_dma_tile(int config, int& bm, int& bn) {
 
 bool gemm_dma_supported(const GemmArgs& g, int config) {
   const bool combo = (!g.a_t && g.b_t && (g.epi == EPI_NONE || g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU || g.epi == EPI_BIAS_RES ||
-                                             g.epi == EPI_STORE_F32)) ||
+                                             (g.epi == EPI_STORE_F32 && config == 7 && g.live && g.live_dim == LIVE_M_SPLIT))) ||
                      (!g.a_t && !g.b_t && (g.epi == EPI_NONE || g.epi == EPI_MUL_DGELU || g.epi == EPI_ADD)) ||
                      (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32);
   if (!combo || !gemm_dma_config_exists(config) || (g.colsum && g.epi != EPI_ACCUM_F32)) return false;

@@ -88,20 +88,6 @@ struct Prec<float> {
 };
 constexpr int kSteps = 4;
 
-// One wavefront-wide 16-byte-per-lane load from global memory into LDS (see kernels_gemm_dma.hip).
-__device__ __forceinline__ void dma16(const void* base, unsigned voff, unsigned lds_byte_addr) {
-  asm volatile(
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %0, %1"
-      :
-      : "v"(voff), "s"(base), "s"(lds_byte_addr)
-      : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 // Operand tile of EXT rows (columns, if the contraction is strided in memory: TR).
 template <typename T, int EXT, bool TR>
@@ -424,8 +410,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(WaveGemmGroup<T> grp
     if constexpr (kReadsC) {
 #pragma unroll
       for (int e = 0; e < OV; ++e) v[e] += pre[u][e];
-      storev(p.Cf + at, v);
-    } else if constexpr (EPI == EPI_STORE_F32) {
       storev(p.Cf + at, v);
     } else {
       if constexpr (kBias) {

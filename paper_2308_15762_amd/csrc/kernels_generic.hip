@@ -1,5 +1,5 @@
 // A GEMM on the ALU for the shapes that the matrix-instruction kernels do not take (extents or leading dimensions that
-// are no multiple of a 16-byte vector), and the row sums of the attention backward pass.
+// are no multiple of a 16-byte vector, unaligned bases), and the row sums of the bf16 attention backward pass.
 #include "device_util.h"
 #include "epilogue.h"
 #include "kernels.h"
@@ -80,8 +80,7 @@ __global__ __launch_bounds__(256) void gemm_alu_kernel(const T* __restrict__ A, 
 // vectors (d / 8 consecutive vectors make one (row, head) group); a workgroup takes kDeltaGroups
 // groups, parks the per-vector sums in LDS and adds each group up.
 constexpr int kDeltaGroups = 64;
-template <typename T>
-__global__ __launch_bounds__(256) void attn_delta_kernel(const T* __restrict__ ctx, const T* __restrict__ dctx,
+__global__ __launch_bounds__(256) void attn_delta_kernel(const bf16* __restrict__ ctx, const bf16* __restrict__ dctx,
                                                          float* __restrict__ delta, long groups, int s, int heads, int d) {
   __shared__ float part[kDeltaGroups * 16];
   const int vpg = d / 8;  // vectors per group, at most 16
@@ -127,19 +126,10 @@ int gemm_alu_t(const GemmArgs& g, hipStream_t stream) {
     LAUNCH(EPI_MUL_DGELU);
     LAUNCH(EPI_ADD);
     LAUNCH(EPI_ACCUM_F32);
-    LAUNCH(EPI_STORE_F32);
+    default: return set_error(HANAYO_EUNSUPPORTED, "gemm_alu: epilogue");
   }
 #undef LAUNCH
   return check_launch("gemm_alu");
-}
-
-template <typename T>
-int attn_delta_t(const AttnArgs& a, hipStream_t stream) {
-  if (a.d % 8 || a.d > 128) return set_error(HANAYO_EUNSUPPORTED, "attn_delta: head dim %d", a.d);
-  const long groups = (long)a.b * a.s * a.heads;
-  hipLaunchKernelGGL((attn_delta_kernel<T>), dim3((unsigned)((groups + kDeltaGroups - 1) / kDeltaGroups)), dim3(256), 0,
-                     stream, (const T*)a.ctx, (const T*)a.dctx, a.delta, groups, a.s, a.heads, a.d);
-  return check_launch("attn_delta");
 }
 
 }  // namespace
@@ -147,8 +137,12 @@ int attn_delta_t(const AttnArgs& a, hipStream_t stream) {
 int gemm_alu(int dtype, const GemmArgs& g, hipStream_t stream) {
   return dtype == HANAYO_BF16 ? gemm_alu_t<bf16>(g, stream) : gemm_alu_t<float>(g, stream);
 }
-int attn_delta(int dtype, const AttnArgs& a, hipStream_t stream) {
-  return dtype == HANAYO_BF16 ? attn_delta_t<bf16>(a, stream) : attn_delta_t<float>(a, stream);
+int attn_delta(const AttnArgs& a, hipStream_t stream) {
+  if (a.d % 8 || a.d > 128) return set_error(HANAYO_EUNSUPPORTED, "attn_delta: head dim %d", a.d);
+  const long groups = (long)a.b * a.s * a.heads;
+  hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((groups + kDeltaGroups - 1) / kDeltaGroups)), dim3(256), 0, stream,
+                     (const bf16*)a.ctx, (const bf16*)a.dctx, a.delta, groups, a.s, a.heads, a.d);
+  return check_launch("attn_delta");
 }
 
 }  // namespace k
