@@ -19,18 +19,22 @@ LAYOUTS = {"fwd": (False, True), "dx": (False, False), "dw": (True, True)}
 EPIS = {"fwd": [hn.EPI_BIAS, hn.EPI_BIAS_GELU, hn.EPI_BIAS_RES], "dx": [hn.EPI_NONE, hn.EPI_MUL_DGELU, hn.EPI_ADD], "dw": [hn.EPI_ACCUM_F32]}
 
 
-@pytest.fixture(params=[0, 1, 7, 9, 10, 11])
-def config(request):
-    hn.hanayo_op_gemm_config(request.param)
+# every kernel with the types it takes
+KERNELS = [(c, "bf16") for c in (0, 1, 7, 9, 10, 11)] + [(0, "fp32"), (1, "fp32")]
+
+
+@pytest.fixture(params=KERNELS, ids=lambda k: "%d-%s" % k)
+def kernel(request):
+    hn.hanayo_op_gemm_config(request.param[0])
     yield request.param
     hn.hanayo_op_gemm_config(-1)
 
 
 # (M, N, K): M is ragged for fwd and dx, K (the tokens) for dw; the rest are multiples of 8
-@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("layout", list(LAYOUTS))
 @pytest.mark.parametrize("M,N,K", [(1, 8, 8), (63, 64, 64), (65, 72, 136), (129, 56, 320), (64, 128, 1024), (777, 104, 264), (333, 520, 96), (513, 264, 200), (256, 384, 72)])
-def test_gemm_edges(config, dtype, layout, M, N, K):
+def test_gemm_edges(kernel, layout, M, N, K):
+    dtype = kernel[1]
     if layout == "dw":
         M, N, K = K, N, M
     a_t, b_t = LAYOUTS[layout]
@@ -67,9 +71,9 @@ def test_gemm_edges(config, dtype, layout, M, N, K):
             assert (np.abs(cs.cpu().numpy() - B.astype(np.float64).sum(0)) <= (K + 4) * 2.0 ** -24 * np.abs(B).sum(0) + 1e-30).all()
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
-def test_gemm_group_edges(config, dtype):
+def test_gemm_group_edges(kernel):
     """Four weight gradients of different sizes and an odd token count in one launch."""
+    dtype = kernel[1]
     rng = np.random.default_rng(5)
     K, probs, want = 201, [], []
     for M, N in [(72, 136), (136, 72), (8, 264), (200, 8)]:
@@ -120,12 +124,11 @@ def check_gemm(dtype, layout, epi, M, N, K, pads=(0, 0, 0), shifts=(0, 0, 0)):
 ALL = [(layout, epi) for layout in LAYOUTS for epi in EPIS[layout]]
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("layout,epi", ALL)
 @pytest.mark.parametrize("M,N,K,pads", [(256, 256, 128, (8, 16, 8)), (256, 256, 128, (0, 0, 4)), (72, 136, 96, (24, 8, 4))])
-def test_gemm_pitches(config, dtype, layout, epi, M, N, K, pads):
+def test_gemm_pitches(kernel, layout, epi, M, N, K, pads):
     """Leading dimensions wider than the rows, also where those of C start on 8-byte boundaries only (bf16, ldc = 4 mod 8)."""
-    check_gemm(dtype, layout, epi, M, N, K, pads)
+    check_gemm(kernel[1], layout, epi, M, N, K, pads)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])

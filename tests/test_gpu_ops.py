@@ -25,12 +25,12 @@ def rnd(rng, shape, dtype, scale=1.0):
 
 GEMM_SHAPES = [
     # M, N, K
-    (256, 256, 128),        # one or a few tiles
-    (384, 640, 192),        # several 128-tiles
+    (256, 256, 128),        # few tiles: the kernel whose wavefronts split the contraction
+    (384, 640, 192),
     (200, 136, 72),         # ragged in every dimension
-    (4096, 4096, 128),      # enough tiles for the 256 x 256 configuration
+    (4096, 4096, 128),      # bf16: enough tiles for the direct-to-LDS kernels
     (4104, 4120, 136),      # the same with ragged edges
-    (128, 256, 2048),       # long reduction (split K for the accumulate epilogue)
+    (128, 256, 2048),       # few tiles with a long contraction
 ]
 LAYOUTS = {"fwd": (False, True), "dx": (False, False), "dw": (True, True)}
 EPIS = {"fwd": [hn.EPI_BIAS, hn.EPI_BIAS_GELU, hn.EPI_BIAS_RES],
@@ -45,12 +45,33 @@ def gemm_config(request):
     hn.hanayo_op_gemm_config(-1)
 
 
-# every bf16 MFMA kernel variant on shapes that are whole numbers of its tile
-@pytest.mark.parametrize("gemm_config", [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11], indirect=True)
+# the automatic choice and every bf16 MFMA kernel by force, on whole tiles with K tiles that are whole and that are not
+@pytest.mark.parametrize("gemm_config", [-1, 0, 1, 7, 9, 10, 11], indirect=True)
 @pytest.mark.parametrize("layout", list(LAYOUTS))
 @pytest.mark.parametrize("shape", [(512, 768, 256), (256, 256, 32), (1024, 512, 96), (512, 512, 192), (256, 512, 64)])
 def test_gemm_kernel_variants(gemm_config, layout, shape):
     run_gemm_case("bf16", layout, shape)
+
+
+def test_retired_gemm_kernels_mean_the_automatic_choice():
+    """hanayo_op_gemm_config takes the numbers of kernels that no longer exist; results are those of -1, bit for bit."""
+    rng = np.random.default_rng(8)
+    M, N, K = 1024, 512, 96
+    A, B, bias = dev(rnd(rng, (M, K), "bf16"), "bf16"), dev(rnd(rng, (K, N), "bf16"), "bf16"), dev(rnd(rng, (N,), "bf16"), "bf16")
+
+    def run(config):
+        hn.hanayo_op_gemm_config(config)
+        C = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        hn.hanayo_op_gemm(hn.BF16, A, B, C, M, N, K, K, N, N, False, True, hn.EPI_BIAS, bias)
+        hn.hanayo_op_gemm_config(-1)
+        return C
+
+    auto = run(-1)
+    for config in (2, 3, 4, 5, 6, 8):
+        assert torch.equal(run(config), auto), config
+    for config in (-2, 12):
+        with pytest.raises(hn.HanayoError):
+            hn.hanayo_op_gemm_config(config)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
@@ -61,8 +82,9 @@ def test_gemm(dtype, layout, shape):
 
 
 @pytest.mark.parametrize("dtype,shapes", [
-    ("bf16", [(512, 384, 256), (128, 128, 256), (256, 1024, 256), (1024, 128, 256)]),   # one tiled launch
-    ("bf16", [(256, 256, 512), (200, 136, 96)]),                                        # ragged member: one by one
+    ("bf16", [(512, 384, 256), (128, 128, 256), (256, 1024, 256), (1024, 128, 256)]),   # whole tiles
+    ("bf16", [(256, 256, 512), (200, 136, 96)]),                                        # a ragged member
+    ("bf16", [(256, 256, 512), (135, 136, 96)]),                                        # one whose rows are no whole vectors: one by one
     ("fp32", [(96, 64, 80), (40, 72, 56), (64, 64, 64)]),
 ])
 def test_gemm_group_weight_gradients(dtype, shapes):
