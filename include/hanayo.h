@@ -223,7 +223,7 @@ int hanayo_chunk_backward(const hanayo_chunk_desc* d, const void* weights, float
  * Tables are row-major in the storage type, gradients fp32 and ADDED to.
  * ------------------------------------------------------------------------- */
 typedef struct hanayo_ends_desc {
-  int vocab;    /* V; multiple of 8 (multiples of 128 take the fast bf16 GEMM kernels) */
+  int vocab;    /* V; multiple of 8 */
   int max_pos;  /* rows of the position table wpe, >= seq */
   int final_ln; /* 1: LayerNorm (gamma[H] then beta[H], the chunk's ln_eps) in front of the head */
 } hanayo_ends_desc;
@@ -372,7 +372,8 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
  * the tasks hanayo_executor_plan lists for it; tasks of one lane run in list
  * order; the side lanes start after the work hip_stream already holds and
  * hip_stream ends after all of them, so the caller sees one ordered stream.
- * Results equal those of one lane (a chunk's gradient accumulations keep their
+ * Results equal those of one lane, bit for bit up to the order in which bias gradients are
+ * added inside a launch (a chunk's gradient accumulations keep their
  * list order).  Calls with lanes > 1 on one device are serialised on the host.
  *
  * The lanes are chosen by list scheduling with the schedule's own costs (forward 1, backward 2).
@@ -551,9 +552,9 @@ enum {
  * The forward linears use (a_t, b_t) = (0, 1), the input gradients (0, 0), the
  * weight gradients (1, 1) with HANAYO_EPI_ACCUM_F32.
  * colsum (device fp32 [N], may be NULL; needs b_t = 1 and ldb = N): colsum[n] += sum over k of B[k][n],
- * the bias gradient that belongs to a weight-gradient GEMM; the tiled bf16 MFMA kernels fold it into the
- * GEMM (the workgroups of the first tile row sum the B tiles they load anyway), the others run a
- * column-sum pass using colsum_scratch (device, at least 64 * N floats).  No atomics either way: the
+ * the bias gradient that belongs to a weight-gradient GEMM; with HANAYO_EPI_ACCUM_F32 the matrix-instruction
+ * kernels fold it into the GEMM (the workgroups of the first tile row sum the B tiles they load anyway), otherwise a
+ * column-sum pass follows, which uses colsum_scratch (device, at least 64 * N floats).  No atomics either way: the
  * sums are added in a fixed order and repeat bit for bit.
  */
 int hanayo_op_gemm(int dtype, const void* A, const void* B, void* C, int M, int N, int K, int lda, int ldb, int ldc,
@@ -562,7 +563,7 @@ int hanayo_op_gemm(int dtype, const void* A, const void* B, void* C, int M, int 
 
 /*
  * Up to 4 independent GEMMs of one layout and epilogue (arguments as for
- * hanayo_op_gemm) that go out as ONE launch where the tiled bf16 kernels take
+ * hanayo_op_gemm) that go out as ONE launch where a matrix-instruction kernel takes
  * every problem, else one after the other.  chunk_backward sends a block's four
  * weight-gradient GEMMs this way: none of them fills the chip alone.  The
  * problems must not write the same memory.
