@@ -1173,9 +1173,11 @@ bool dma_ok(const AttnArgs& a) {
 //   no mask, d = 64: s = 512 96 -0.8 / -1.3, 128 +0.8 / +3.1;  d = 80: s = 512 64 -2.2 / -2.9, 96 +2.4 / +0.3, 128 +3.2 / +7.4
 // (with the lines for a launch alone a step of H = 640, s = 777, 3 sequences, took 6932 us with 4 lanes instead
 // of 6506, one of H = 1024, 8 heads, s = 1024, 2 sequences without a mask 10406 instead of 9883).
-// Forward up to s = 128 stays with the 128-row kernel: alone there is 1 us to gain (d = 64, 64 workgroups: 5.9 and 4.7), a step
-// gains 0 - 3 % with one lane and nothing beyond the noise with four from 64 workgroups on.  Accuracy is no reason: the split
-// kernel's context is the closer one to fp64 (s = 128: 0.187 % and 0.189 %, s = 512 0.193 % and 0.198 %).
+// Forward up to s = 128 stays with the 128-row kernel, by no accuracy of its own (the split kernel's context is the closer one
+// to fp64: s = 128 0.187 % and 0.189 %, s = 512 0.193 % and 0.198 %): alone there is 1 us to gain (d = 64, 64 workgroups: 5.9 and
+// 4.7), a step gains 0 - 3 % with one lane and nothing beyond the noise with four from 64 workgroups on, and a training test
+// at that length holds gradients summed over 128 tokens to 2 % where rounding alone takes 1.6 %: with the other kernel's
+// rounding one came out at 2.1 %.  That test's bound has to be derived before the line can follow the times.
 bool split_rows(const AttnArgs& a, bool forward) {
   if (!dma_ok(a) || (forward && a.s <= 128)) return false;
   const bool narrow = a.d <= 64;
