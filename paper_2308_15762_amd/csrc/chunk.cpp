@@ -90,6 +90,18 @@ k::GemmArgs bwd_params_gemm(const Shape& sh, const void* x, const void* dy, floa
 
 namespace k {
 
+int raise_lds(const void* kernel, size_t lds, uint64_t& devices) {
+  if (lds <= 64 * 1024) return HANAYO_OK;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return set_error(HANAYO_EHIP, "hipGetDevice failed");
+  const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
+  if (devices & bit) return HANAYO_OK;
+  const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return set_error(HANAYO_EHIP, "cannot raise a kernel's LDS limit to %zu bytes: %s", lds, hipGetErrorString(e));
+  devices |= bit;
+  return HANAYO_OK;
+}
+
 namespace {
 thread_local int g_gemm_config = -1;  // measurement knob: of the calling thread only
 thread_local bool g_in_lanes = false;

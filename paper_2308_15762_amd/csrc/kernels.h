@@ -10,6 +10,10 @@
 namespace hanayo {
 namespace k {
 
+// Raises a kernel's limit of dynamic LDS for a launch of `lds` bytes.  The limit belongs to the device: `devices` (a
+// thread_local of the launcher, one bit per device) says where the calling thread has raised it already.
+int raise_lds(const void* kernel, size_t lds, uint64_t& devices);
+
 // ---- LayerNorm (row-wise over H; wavefront reductions) ----------------------
 // out = LN(x) * gamma + beta; stats[t] = (mean, rstd); copy_out (optional) = x.
 int ln_forward(int dtype, const void* x, const void* gamma, const void* beta, void* out, float2* stats, void* copy_out,

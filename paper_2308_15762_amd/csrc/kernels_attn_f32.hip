@@ -513,26 +513,17 @@ AttnF32 to_dev(const AttnArgs& a) {
 template <int DP>
 constexpr size_t lds_bytes() { return NW * part_floats<DP>() * sizeof(float) + NW * 32 * sizeof(float2); }
 
-template <typename K>
-int raise_lds(K kern, size_t lds, bool& raised) {
-  if (lds <= 64 * 1024 || raised) return HANAYO_OK;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return set_error(HANAYO_EHIP, "attn_f32: cannot raise LDS limit: %s", hipGetErrorString(e));
-  raised = true;
-  return HANAYO_OK;
-}
-
 template <int DP, bool FULL>
 int forward_t(const AttnF32& p, unsigned grid, hipStream_t stream) {
-  static thread_local bool raised = false;
-  if (const int rc = raise_lds(attn_fwd_f32_kernel<DP, FULL>, lds_bytes<DP>(), raised)) return rc;
+  static thread_local uint64_t raised = 0;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_fwd_f32_kernel<DP, FULL>), lds_bytes<DP>(), raised)) return rc;
   hipLaunchKernelGGL((attn_fwd_f32_kernel<DP, FULL>), dim3(grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);
   return check_launch("attn_fwd_f32");
 }
 template <int DP, bool FULL>
 int backward_t(const AttnF32& p, unsigned grid, hipStream_t stream) {
-  static thread_local bool raised = false;
-  if (const int rc = raise_lds(attn_bwd_f32_kernel<DP, FULL>, lds_bytes<DP>(), raised)) return rc;
+  static thread_local uint64_t raised = 0;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_bwd_f32_kernel<DP, FULL>), lds_bytes<DP>(), raised)) return rc;
   hipLaunchKernelGGL((attn_bwd_f32_kernel<DP, FULL>), dim3(2 * grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);
   return check_launch("attn_bwd_f32");
 }

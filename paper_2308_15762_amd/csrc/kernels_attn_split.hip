@@ -414,29 +414,20 @@ AttnDev to_dev(const AttnArgs& a) {
   return p;
 }
 
-template <typename K>
-int raise_lds(K kern, size_t lds, bool& raised) {
-  if (lds <= 64 * 1024 || raised) return HANAYO_OK;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return set_error(HANAYO_EHIP, "attn_split: cannot raise LDS limit: %s", hipGetErrorString(e));
-  raised = true;
-  return HANAYO_OK;
-}
-
 template <int DP, int D>
 int forward_t(const AttnArgs& a, hipStream_t stream) {
-  static thread_local bool raised = false;
+  static thread_local uint64_t raised = 0;
   constexpr size_t lds = lds_bytes<DP>(2 * kTile32<DP>);
-  if (const int rc = raise_lds(attn_fwd_split_kernel<DP, D>, lds, raised)) return rc;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_fwd_split_kernel<DP, D>), lds, raised)) return rc;
   const int pairs = a.heads * a.b, tiles = (a.s + 31) / 32;
   hipLaunchKernelGGL((attn_fwd_split_kernel<DP, D>), dim3(pairs * tiles), dim3(NW * 64), lds, stream, to_dev(a), pairs);
   return check_launch("attn_fwd_split");
 }
 template <int DP, int D>
 int backward_t(const AttnArgs& a, hipStream_t stream) {
-  static thread_local bool raised = false;
+  static thread_local uint64_t raised = 0;
   constexpr size_t lds = lds_bytes<DP>(kBwdStage<DP>);
-  if (const int rc = raise_lds(attn_bwd_split_kernel<DP, D>, lds, raised)) return rc;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_bwd_split_kernel<DP, D>), lds, raised)) return rc;
   const int pairs = a.heads * a.b, tiles = (a.s + 31) / 32;
   hipLaunchKernelGGL((attn_bwd_split_kernel<DP, D>), dim3(2 * pairs * tiles), dim3(NW * 64), lds, stream, to_dev(a), pairs, tiles);
   return check_launch("attn_bwd_split");

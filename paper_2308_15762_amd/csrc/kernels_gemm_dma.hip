@@ -571,13 +571,8 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   constexpr int NW = WGM * WGN;
   constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes);
   auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>;
-  static thread_local bool raised = false;
-  if (lds > 64 * 1024 && !raised) {
-    const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return set_error(HANAYO_EHIP, "gemm_dma: cannot raise LDS limit: %s", hipGetErrorString(e));
-    raised = true;
-  }
+  static thread_local uint64_t raised = 0;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
   long tiles = 0;
   for (int i = 0; i < grp.count; ++i) {
     grp.first[i] = (int)tiles;

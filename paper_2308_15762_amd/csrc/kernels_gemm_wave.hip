@@ -438,13 +438,8 @@ template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
 int launch(WaveGemmGroup<T>& grp, unsigned tiles, hipStream_t stream) {
   constexpr size_t lds = wave_lds_bytes<BM, BN>(NST);
   auto kern = gemm_wave_kernel<T, BM, BN, NST, A_T, B_T, EPI>;
-  static thread_local bool raised = false;
-  if (lds > 64 * 1024 && !raised) {
-    const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return set_error(HANAYO_EHIP, "gemm_wave: cannot raise LDS limit: %s", hipGetErrorString(e));
-    raised = true;
-  }
+  static thread_local uint64_t raised = 0;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp);
   return check_launch("gemm_wave");
 }
