@@ -107,8 +107,8 @@ def test_gradients_repeat_bit_for_bit(lanes):
 
 @pytest.mark.parametrize("name", ["gpt_1024_sched_small", "wave4_sched_small_rank3"])
 def test_lanes_do_not_change_results(name):
-    """Boundary outputs are bit-identical whatever the lane count; gradients differ only by the
-    order of the bias-gradient atomics."""
+    """Boundary outputs are bit-identical whatever the lane count; gradients differ only by the order in which tiles of
+    different shapes add up bias gradients."""
     wl, rank = CASES[name]
     runs = []
     for lanes in (1, 2, 4):
@@ -146,7 +146,7 @@ def test_kernel_choice_does_not_depend_on_lanes(hidden, heads, seq, mb, causal):
 def test_input_only_stash_recomputes_to_the_same_result(name, lanes):
     """Stash mode "input": entries hold the chunk input only and every backward recomputes its forward.
     The boundary outputs are bit-identical to the full-stash run, the gradients equal up to the order of
-    the bias-gradient atomics, and the arena is the plan's entry count times one activation tensor."""
+    the bias-gradient sums, and the arena is the plan's entry count times one activation tensor."""
     wl, rank = CASES[name]
     full = GpuRank(wl, rank, lanes=lanes)
     full.run()
