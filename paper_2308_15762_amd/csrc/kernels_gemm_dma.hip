@@ -60,6 +60,53 @@ struct DmaGemmGroup {
   int count;
 };
 
+// GELU in the epilogues: Phi (forward) and GELU' (input gradient of FC2) over [-8, 8) as kGeluN intervals of 1 / 128, each the
+// value at its left end and the rise to its right end; read with linear interpolation (error below 1e-5, far under bf16
+// rounding).  Computed by the compiler, Phi from one point to the next by its Taylor series about the left one (the term
+// after the last is below 1e-16), so that a workgroup only copies them into LDS, under the first K tiles.  Worked out with
+// erff by every workgroup between main loop and epilogue they cost 1.5 us of a tile: FC1 of 777 x 2560 x 640, 140 tiles,
+// 11.7 us a launch then and 10.1 now, 1527 x 3072 x 768 15.0 and 14.3; 1 us of 35 in 256 x 256 tiles, whose epilogue is
+// bound by what it stores.
+constexpr int kGeluN = 2048;
+struct GeluTable {
+  float at[kGeluN][2];
+};
+constexpr GeluTable gelu_table(bool grad) {
+  constexpr double h = 1.0 / 128.0;
+  // Phi and the density phi at k / 128, k = 0 .. 1024; phi(x + h) = phi(x) exp(-(x h + h h / 2))
+  double cdf[kGeluN / 2 + 1] = {0.5}, pdf[kGeluN / 2 + 1] = {0.39894228040143267794};
+  for (int k = 0; k < kGeluN / 2; ++k) {
+    const double x = k * h, e = -(x * h + 0.5 * h * h);
+    double term = 1.0, sum = 1.0;
+    for (int n = 1; n < 12; ++n) sum += term *= e / n;
+    pdf[k + 1] = pdf[k] * sum;
+    // derivatives of Phi: phi times the Hermite polynomials 1, -x, x^2 - 1, ...
+    double he0 = 1.0, he1 = x, step = h, rise = h, sign = -1.0;
+    for (int n = 2; n < 9; ++n) {
+      step *= h / n;
+      rise += sign * he1 * step;
+      sign = -sign;
+      const double he2 = x * he1 - (n - 1) * he0;
+      he0 = he1;
+      he1 = he2;
+    }
+    cdf[k + 1] = cdf[k] + pdf[k] * rise;
+  }
+  GeluTable t{};
+  float value[kGeluN + 1] = {};
+  for (int k = 0; k <= kGeluN; ++k) {
+    const int i = k - kGeluN / 2, a = i < 0 ? -i : i;
+    const double c = i < 0 ? 1.0 - cdf[a] : cdf[a];
+    value[k] = (float)(grad ? c + i * h * pdf[a] : c);
+  }
+  for (int k = 0; k < kGeluN; ++k) {
+    t.at[k][0] = value[k];
+    t.at[k][1] = value[k + 1] - value[k];
+  }
+  return t;
+}
+__device__ const GeluTable kPhiTable = gelu_table(false), kGeluGradTable = gelu_table(true);
+
 constexpr int kBK = 64;       // K tile
 constexpr int KS = kBK / 32;  // MFMA steps per K tile
 
@@ -204,6 +251,16 @@ next_tile:
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int nk = EDGE ? (p.K + kBK - 1) / kBK : p.K / kBK;
   const int k_tail = EDGE ? p.K - (nk - 1) * kBK : kBK;  // contraction elements of the last K tile
+
+  constexpr bool kGelu = EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU;
+  if constexpr (kGelu) {
+    const GeluTable* table = EPI == EPI_BIAS_GELU ? &kPhiTable : &kGeluGradTable;
+    constexpr int kParts = (int)sizeof(GeluTable) / 1024 / NW;
+    static_assert(kParts * NW * 1024 == (int)sizeof(GeluTable), "the table divides among the wavefronts");
+#pragma unroll
+    for (int i = 0; i < kParts; ++i)
+      dma16(table, (unsigned)((wave * kParts + i) * 1024 + lane * 16), lds0 + NSTAGE * STAGE_BYTES + (wave * kParts + i) * 1024);
+  }
 
   // Direct loads of one K tile.  The wavefront's i-th instruction for an operand covers the 64
   // slots q = wave * kPerWave + i of the tile; which rows that is goes into the lane's byte
@@ -437,16 +494,9 @@ next_tile:
   float* stage = reinterpret_cast<float*>(smem);
   constexpr int kBandRows = WGM * 32, kVecPerRow = BN / 8, kVecs = kBandRows * kVecPerRow;
   static_assert((size_t)kBandRows * EP * 4 <= (size_t)NSTAGE * STAGE_BYTES, "epilogue band must fit the load ring");
-  // GELU epilogues: Phi (forward) or GELU' (input gradient of FC2) comes from a table of kGeluN
-  // intervals over [-8, 8) built next to the staging band with erff, read with linear interpolation
-  // (error below 1e-5, far under bf16 rounding): 8 VALU operations and one LDS read per element
-  // instead of an exponential, a reciprocal and a polynomial, which at one workgroup per CU nothing
-  // else would overlap.
-  constexpr bool kGelu = EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU;
-  constexpr int kGeluN = 2048;
-  constexpr int kStageBytes = ((WGM * 32 * EP * 4 + 15) / 16) * 16;
-  static_assert(!kGelu || kStageBytes + kGeluN * 8 <= NSTAGE * STAGE_BYTES, "table does not fit behind the band");
-  float2* gelu_tab = reinterpret_cast<float2*>(smem + kStageBytes);
+  // GELU epilogues: 8 VALU operations and one LDS read per element instead of an exponential, a reciprocal and a
+  // polynomial, which at one workgroup per CU nothing else would overlap.
+  const float2* gelu_tab = reinterpret_cast<const float2*>(smem + NSTAGE * STAGE_BYTES);
   auto gelu_lookup = [&](float x) {
     const float t = fminf(fmaxf(fmaf(x, 128.f, 1024.f), 0.f), 2047.99f);
     const int k = (int)t;
@@ -474,9 +524,10 @@ next_tile:
   auto prefetch = [&](int i, int buf) {
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
-      int br, c, n;
-      size_t at;
-      if (!where(i, u, br, c, at, n)) at = (size_t)m0 * p.ldc + n0;  // not used
+      const int vi = threadIdx.x + u * NW * 64, br = vi / kVecPerRow;
+      int m = m0 + (br >> 5) * WM + i * 32 + (br & 31), n = n0 + (vi % kVecPerRow) * 8;
+      if (EDGE) m = min(m, p.M - 1), n = n < p.N ? n : n0;  // from inside: what is outside is not stored
+      const size_t at = (size_t)m * p.ldc + n;
       if constexpr (kReadsAux) pre_aux[buf][u] = *reinterpret_cast<const bf16x8_row*>(p.aux + at);
       if constexpr (kReadsC) {
         pre_c[buf][u][0] = *reinterpret_cast<const f32x4*>(p.Cf + at);
@@ -488,22 +539,6 @@ next_tile:
 #pragma unroll
   for (int i = 0; i < kBands; ++i) {
     __syncthreads();  // the ring (first band) or the previous band is no longer being read
-    if constexpr (kGelu) {
-      if (i == 0) {
-        for (int k = threadIdx.x; k < kGeluN; k += NW * 64) {
-          const float x0 = -8.f + (float)k * (1.f / 128.f), x1 = -8.f + (float)(k + 1) * (1.f / 128.f);
-          float f0, f1;
-          if constexpr (EPI == EPI_BIAS_GELU) {
-            f0 = 0.5f * (1.0f + erff(x0 * 0.70710678118654752f));
-            f1 = 0.5f * (1.0f + erff(x1 * 0.70710678118654752f));
-          } else {
-            f0 = gelu_grad_f(x0);
-            f1 = gelu_grad_f(x1);
-          }
-          gelu_tab[k] = make_float2(f0, f1 - f0);
-        }
-      }
-    }
     {
       float* dst = stage + (wm * 32 + (lane & 15)) * EP + wn * WN + 4 * (lane >> 4);
 #pragma unroll
@@ -569,7 +604,8 @@ next_tile:
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 int launch(DmaGemmGroup& grp, hipStream_t stream) {
   constexpr int NW = WGM * WGN;
-  constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes);
+  constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes) +
+                         (EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU ? sizeof(GeluTable) : 0);
   auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>;
   static thread_local uint64_t raised = 0;
   if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
