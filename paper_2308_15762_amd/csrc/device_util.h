@@ -67,8 +67,12 @@ __device__ __forceinline__ float wave_max(float v) {
 // (w / 8)-th.  Each XCD therefore gets one contiguous run of tile numbers, and tile numbers walk the
 // tile grid in bands of kTileBand tile rows, column by column within a band: the workgroups resident
 // on one XCD at a time then cover a compact patch of the output and share their operand panels in
-// that L2 instead of each XCD fetching every panel.  Any bijection is correct; this one is fast.
-constexpr int kXcds = 8, kTileBand = 8;
+// that L2 instead of each XCD fetching every panel.  Any bijection is correct; this one is fast.  A band
+// of 8 makes the patch of 32 workgroups 8 x 4 tiles; tiles twice as tall as wide take bands of 4, so that
+// the patch is as many rows as columns: 16 panels of a 2048 x 4096 x 16384 product then cross the fabric
+// instead of 20 per XCD (see kernels_gemm_dma.hip for what that measured).
+constexpr int kXcds = 8;
+template <int kTileBand = 8>
 __device__ __forceinline__ void xcd_tile(int w, int tiles_m, int tiles_n, int& tm, int& tn) {
   const int total = tiles_m * tiles_n, per = total / kXcds, rem = total % kXcds;
   const int xcd = w % kXcds;

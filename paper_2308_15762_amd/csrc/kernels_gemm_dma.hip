@@ -245,7 +245,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
 next_tile:
   const int tiles_m = EDGE ? (p.M + BM - 1) / BM : p.M / BM, tiles_n = EDGE ? (p.N + BN - 1) / BN : p.N / BN;
   int tile_m, tile_n;
-  xcd_tile(wg, tiles_m, tiles_n, tile_m, tile_n);
+  // 256 x 128: patches of 1024 x 1024 outputs per XCD instead of 2048 x 512.  Steps with four and two lanes: H = 4096 164.6 ->
+  // 164.0 ms, H = 2560 47.6 -> 46.2 ms (with band 8 in the same runs 164.5 and 47.5).
+  xcd_tile<BM == 2 * BN ? 4 : 8>(wg, tiles_m, tiles_n, tile_m, tile_n);
   tile_m = __builtin_amdgcn_readfirstlane(tile_m);
   tile_n = __builtin_amdgcn_readfirstlane(tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
