@@ -252,7 +252,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
 
 int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
   if (count < 1 || count > 4) return set_error(HANAYO_EINVAL, "gemm_group: %d problems", count);
-  bool alike = true;
+  bool alike = count == 1 || gs[0].epi == EPI_ACCUM_F32;  // the kernels take only weight gradients in groups
   for (int i = 0; i < count; ++i) {
     const GemmArgs& g = gs[i];
     if (g.M < 1 || g.N < 1 || g.K < 1) return set_error(HANAYO_EINVAL, "gemm: empty problem");

@@ -59,6 +59,9 @@ struct DmaGemmGroup {
   int first[kMaxGroup + 1];
   int count;
 };
+// What a launch passes: only weight gradients come in groups.
+template <int EPI>
+using DmaArgs = std::conditional_t<EPI == EPI_ACCUM_F32, DmaGemmGroup, DmaGemm>;
 
 // GELU in the epilogues: Phi (forward) and GELU' (input gradient of FC2) over [-8, 8) as kGeluN intervals of 1 / 128, each the
 // value at its left end and the rise to its right end; read with linear interpolation (error below 1e-5, far under bf16
@@ -191,13 +194,19 @@ struct Operand {
 
 
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
-__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(DmaGemmGroup grp) {
-  int gi = 0;
+__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(DmaArgs<EPI> args) {
+  DmaGemm p;
+  int wg = (int)blockIdx.x;  // tile number within the problem
+  if constexpr (EPI == EPI_ACCUM_F32) {
+    int gi = 0;
 #pragma unroll
-  for (int j = 1; j < kMaxGroup; ++j)
-    if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
-  DmaGemm p = grp.prob[gi];
-  int wg = (int)blockIdx.x - grp.first[gi];  // tile number within the problem
+    for (int j = 1; j < kMaxGroup; ++j)
+      if (j < args.count && wg >= args.first[j]) gi = j;
+    p = args.prob[gi];
+    wg -= args.first[gi];
+  } else {
+    p = args;
+  }
   // A launch over rows counted on the device may have fewer workgroups than tiles (see launch): they take several each.
   // (By goto: with the tile's code in a function and a loop around it the other instances, which never loop, are scheduled
   // worse and one spills: 2048 x 16384 x 4096 with GELU' 222 -> 229 us.  With the goto only the 256 x 256 instance that loops
@@ -215,7 +224,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
       const int tiles_n = (p.N + BN - 1) / BN, tiles = (live + BM - 1) / BM * tiles_n;
       if (EPI == EPI_STORE_F32 && p.live_dim == LIVE_M_SPLIT) {
         int per;
-        const int slices = split_plan(live, tiles_n, p.K, grp.first[kMaxGroup], per), slice = wg / tiles;
+        const int slices = split_plan(live, tiles_n, p.K, (int)gridDim.x, per), slice = wg / tiles;
         if (slice >= slices) return;
         wg -= slice * tiles;
         p.A += A_T ? (size_t)slice * per * p.lda : (size_t)slice * per;
@@ -627,7 +636,8 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
     if (tiles > fit) tiles = fit;
   }
   for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
-  hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, stream, grp);
+  if constexpr (EPI == EPI_ACCUM_F32) hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, stream, grp);
+  else hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, stream, grp.prob[0]);
   return check_launch("gemm_dma");
 }
 
@@ -697,6 +707,7 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
 // The problems of a group share layout and epilogue (those of gs[0]); each must pass gemm_dma_supported.
 int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream) {
   if (count < 1 || count > kMaxGroup) return set_error(HANAYO_EINVAL, "gemm_dma: group of %d", count);
+  if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: only weight gradients in groups");
   DmaGemmGroup grp{};
   grp.count = count;
   bool edge = false;

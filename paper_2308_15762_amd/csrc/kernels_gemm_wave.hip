@@ -61,6 +61,10 @@ struct WaveGemmGroup {
   int first[kMaxGroup + 1];  // workgroups first[i] .. first[i + 1] - 1 are the tiles of problem i
   int count;
 };
+// What a launch passes: only weight gradients come in groups.  A single problem is passed by itself: its fields are where
+// the kernel expects them without a search, and a quarter of the bytes goes through the launch (1 us of host time).
+template <typename T, int EPI>
+using WaveArgs = std::conditional_t<EPI == EPI_ACCUM_F32, WaveGemmGroup<T>, WaveGemm<T>>;
 
 // VEC = elements of a 16-byte vector, BK = elements of a K tile (4 MFMA steps), Frag = what a lane feeds per step:
 // VEC contraction elements, 2 VEC per step over the two halves of the wavefront.
@@ -182,30 +186,37 @@ constexpr size_t wave_lds_bytes(int nst) {
 // other's waits) for launches with more tiles than CUs, two for launches of at most one tile per CU.  Even with one
 // stage the next tile's loads run under the MFMAs of this one: its fragments are in registers by then.
 template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
-__global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(WaveGemmGroup<T> grp) {
+__global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(WaveArgs<T, EPI> args) {
   using P = Prec<T>;
   using OpA = WaveOperand<T, BM, A_T>;
   using OpB = WaveOperand<T, BN, B_T>;
   using Frag = typename P::Frag;
   constexpr int TM = BM / 32, TN = BN / 32, VEC = P::VEC, BK = P::BK;
   constexpr int STAGE = OpA::kBytes + OpB::kBytes, LOADS = OpA::kInstr + OpB::kInstr;
-  int gi = 0;
+  WaveGemm<T> p;
+  int wg = (int)blockIdx.x;
+  if constexpr (EPI == EPI_ACCUM_F32) {
+    int gi = 0;
 #pragma unroll
-  for (int j = 1; j < kMaxGroup; ++j)
-    if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
-  WaveGemm<T> p = grp.prob[gi];
+    for (int j = 1; j < kMaxGroup; ++j)
+      if (j < args.count && wg >= args.first[j]) gi = j;
+    p = args.prob[gi];
+    wg -= args.first[gi];
+  } else {
+    p = args;
+  }
   if (p.live) {
     const int live = __builtin_amdgcn_readfirstlane(*p.live);
     if (live < 1) return;
     if (p.live_dim == LIVE_K) p.K = live;
     else p.M = live;
-    if ((int)blockIdx.x - grp.first[gi] >= (p.M + BM - 1) / BM * ((p.N + BN - 1) / BN)) return;
+    if (wg >= (p.M + BM - 1) / BM * ((p.N + BN - 1) / BN)) return;
   }
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const unsigned lds0 = (unsigned)(unsigned long)((__attribute__((address_space(3))) char*)smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int tile_m, tile_n;
-  xcd_tile((int)blockIdx.x - grp.first[gi], (p.M + BM - 1) / BM, (p.N + BN - 1) / BN, tile_m, tile_n);
+  xcd_tile(wg, (p.M + BM - 1) / BM, (p.N + BN - 1) / BN, tile_m, tile_n);
   const int m0 = __builtin_amdgcn_readfirstlane(tile_m) * BM, n0 = __builtin_amdgcn_readfirstlane(tile_n) * BN;
   const int nk = (p.K + BK - 1) / BK, k_tail = p.K - (nk - 1) * BK;  // k_tail = BK: the last K tile is whole
 
@@ -440,7 +451,8 @@ int launch(WaveGemmGroup<T>& grp, unsigned tiles, hipStream_t stream) {
   auto kern = gemm_wave_kernel<T, BM, BN, NST, A_T, B_T, EPI>;
   static thread_local uint64_t raised = 0;
   if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
-  hipLaunchKernelGGL(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp);
+  if constexpr (EPI == EPI_ACCUM_F32) hipLaunchKernelGGL(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp);
+  else hipLaunchKernelGGL(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp.prob[0]);
   return check_launch("gemm_wave");
 }
 
@@ -516,6 +528,7 @@ int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStrea
   for (int i = 0; i < count; ++i)
     if (!gemm_wave_supported(dtype, gs[i]) || gs[i].a_t != gs[0].a_t || gs[i].b_t != gs[0].b_t || gs[i].epi != gs[0].epi)
       return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: shape not supported");
+  if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: only weight gradients in groups");
   return dtype == HANAYO_BF16 ? group_t<bf16>(gs, count, edge, stream) : group_t<float>(gs, count, edge, stream);
 }
 
