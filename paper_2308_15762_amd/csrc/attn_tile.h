@@ -37,6 +37,14 @@ struct AttnDev {
   int s, heads, d, causal;
 };
 
+// A kernel's parameters one by one and the block made of them: the first 14 words of them are in scalar registers when the
+// kernel starts (see the build flags), a struct would have to be read from memory first.
+#define ATTN_PARAMS                                                                                                    \
+  const bf16 *qkv, const int32_t *valid_len, float *lse, int s, int heads, int d, int causal, const bf16 *dctx, bf16 *ctx, \
+      bf16 *dqkv, float *delta
+#define ATTN_BLOCK AttnDev{qkv, valid_len, ctx, lse, dctx, dqkv, delta, s, heads, d, causal}
+#define ATTN_ARGS(p) p.qkv, p.valid_len, p.lse, p.s, p.heads, p.d, p.causal, p.dctx, p.ctx, p.dqkv, p.delta
+
 __device__ __forceinline__ int seq_len(const AttnDev& p, int n) {
   if (!p.valid_len) return p.s;
   const int v = p.valid_len[n];

@@ -37,6 +37,13 @@ struct AttnF32 {
   float* dqkv;
   int s, heads, d, causal, tiles, pairs;  // tiles of 32 rows; (sequence, head) pairs
 };
+// A kernel's parameters one by one and the block made of them: the first 14 words of them are in scalar registers when the
+// kernel starts (see the build flags), a struct would have to be read from memory first.
+#define ATTN_F32_PARAMS                                                                                                        \
+  const float *qkv, const int32_t *valid_len, float *lse, int s, int heads, int d, int causal, int tiles, int pairs, const float *dctx, \
+      float *ctx, float *dqkv
+#define ATTN_F32_BLOCK AttnF32{qkv, valid_len, ctx, lse, dctx, dqkv, s, heads, d, causal, tiles, pairs}
+#define ATTN_F32_ARGS(p) p.qkv, p.valid_len, p.lse, p.s, p.heads, p.d, p.causal, p.tiles, p.pairs, p.dctx, p.ctx, p.dqkv
 
 __device__ __forceinline__ int seq_len(const AttnF32& p, int n) {
   if (!p.valid_len) return p.s;
@@ -231,7 +238,8 @@ __device__ __forceinline__ void redo_rows(bool bad, int row, int c, Redo redo) {
 }
 
 template <int DP, bool FULL>
-__global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(AttnF32 p) {
+__global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(ATTN_F32_PARAMS) {
+  const AttnF32 p = ATTN_F32_BLOCK;
   constexpr int DT = DP / 32;
   extern __shared__ float smem[];  // [NW][32][DP + 4] partial outputs, then [NW][32] maxima and sums
   float2* stats = reinterpret_cast<float2*>(smem + NW * part_floats<DP>());
@@ -490,7 +498,8 @@ __device__ __forceinline__ void bwd_dkv(const AttnF32& p, float* smem, int kt, i
 // dK / dV of every key tile, then dQ of every query tile, the longer work first: one launch, because the former forms its
 // deltas itself instead of waiting for the latter.
 template <int DP, bool FULL>
-__global__ __launch_bounds__(NW * 64, DP <= 32 ? 2 : 1) void attn_bwd_f32_kernel(AttnF32 p) {
+__global__ __launch_bounds__(NW * 64, DP <= 32 ? 2 : 1) void attn_bwd_f32_kernel(ATTN_F32_PARAMS) {
+  const AttnF32 p = ATTN_F32_BLOCK;
   extern __shared__ float smem[];
   const int per_side = p.pairs * p.tiles, side = (int)blockIdx.x >= per_side;
   int t, h, n;
@@ -517,14 +526,14 @@ template <int DP, bool FULL>
 int forward_t(const AttnF32& p, unsigned grid, hipStream_t stream) {
   static thread_local uint64_t raised = 0;
   if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_fwd_f32_kernel<DP, FULL>), lds_bytes<DP>(), raised)) return rc;
-  hipLaunchKernelGGL((attn_fwd_f32_kernel<DP, FULL>), dim3(grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);
+  launch_kernel((attn_fwd_f32_kernel<DP, FULL>), dim3(grid), dim3(NW * 64), lds_bytes<DP>(), stream, ATTN_F32_ARGS(p));
   return check_launch("attn_fwd_f32");
 }
 template <int DP, bool FULL>
 int backward_t(const AttnF32& p, unsigned grid, hipStream_t stream) {
   static thread_local uint64_t raised = 0;
   if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_bwd_f32_kernel<DP, FULL>), lds_bytes<DP>(), raised)) return rc;
-  hipLaunchKernelGGL((attn_bwd_f32_kernel<DP, FULL>), dim3(2 * grid), dim3(NW * 64), lds_bytes<DP>(), stream, p);
+  launch_kernel((attn_bwd_f32_kernel<DP, FULL>), dim3(2 * grid), dim3(NW * 64), lds_bytes<DP>(), stream, ATTN_F32_ARGS(p));
   return check_launch("attn_bwd_f32");
 }
 

@@ -66,7 +66,8 @@ __device__ __forceinline__ void tile_to_lds(bf16* lds, const bf16* g, size_t ld,
 // ------------------------------------------------------------------ forward
 // Workgroup = 128 query rows of one (sequence, head); wavefront = 32 of them.
 template <int DP>
-__global__ __launch_bounds__(256) void attn_fwd_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_fwd_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   constexpr int PITCH = DP + kPad, BKV = 64, KS = DP / 16, DT = DP / 32;
   __shared__ __attribute__((aligned(16))) bf16 Ks[BKV * PITCH];
   __shared__ __attribute__((aligned(16))) bf16 Vs[BKV * PITCH];
@@ -162,7 +163,8 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(AttnDev p) {
 // ------------------------------------------------------------------ backward: dK, dV
 // Workgroup = 128 keys of one (sequence, head); wavefront = 32 keys; loops over 64-query tiles.
 template <int DP>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   constexpr int PITCH = DP + kPad, BQ = 64, KS = DP / 16, DT = DP / 32;
   __shared__ __attribute__((aligned(16))) bf16 Qs[BQ * PITCH];
   __shared__ __attribute__((aligned(16))) bf16 Cs[BQ * PITCH];
@@ -255,7 +257,8 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(AttnDev p) {
 // ------------------------------------------------------------------ backward: dQ
 // Workgroup = 128 query rows; wavefront = 32; loops over 64-key tiles.
 template <int DP>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   constexpr int PITCH = DP + kPad, BKV = 64, KS = DP / 16, DT = DP / 32;
   __shared__ __attribute__((aligned(16))) bf16 Ks[BKV * PITCH];
   __shared__ __attribute__((aligned(16))) bf16 Vs[BKV * PITCH];
@@ -346,7 +349,8 @@ __device__ __forceinline__ void wait_tiles(int tiles_in_flight) {
 }
 
 template <int DP, int NST, int D = DP>
-__global__ __launch_bounds__(256) void attn_fwd_dma_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_fwd_dma_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   using Tile = SwTile<DP>;
   constexpr int BKV = 64, KS = D / 16, DT = (D + 31) / 32;  // D = head dim in memory, DP = LDS row layout
   constexpr int STAGE = 2 * Tile::kBytes, LOADS = 2 * Tile::kPerWave;
@@ -613,11 +617,13 @@ __device__ __forceinline__ void attn_fwd_pipe_body(const AttnDev& p) {
 // Head dim 64: capped at 256 registers so that two workgroups share a CU.  Head dim 128: the output
 // accumulators and two score sets need more, one workgroup per CU.
 template <int DP, int NST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_pipe_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_pipe_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   attn_fwd_pipe_body<DP, NST>(p);
 }
 template <int DP, int NST, int D = DP>
-__global__ __launch_bounds__(256) void attn_fwd_pipe_wide_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_fwd_pipe_wide_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   attn_fwd_pipe_body<DP, NST, D>(p);
 }
 
@@ -741,12 +747,14 @@ __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
 }
 
 template <int DP, int NST, int D = DP>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_dma_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_bwd_dkv_dma_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   attn_bwd_dkv_dma_body<DP, NST, D>(p);
 }
 // The same under a cap of 256 registers, so that two workgroups share a CU.
 template <int DP, int NST, int D = DP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_dma2_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_dma2_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   attn_bwd_dkv_dma_body<DP, NST, D>(p);
 }
 
@@ -850,11 +858,13 @@ __device__ __forceinline__ void attn_bwd_dq_dma_body(const AttnDev& p) {
 }
 
 template <int DP, int NST, int D = DP>
-__global__ __launch_bounds__(256) void attn_bwd_dq_dma_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) void attn_bwd_dq_dma_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   attn_bwd_dq_dma_body<DP, NST, D>(p);
 }
 template <int DP, int NST, int D = DP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_dma2_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_dma2_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   attn_bwd_dq_dma_body<DP, NST, D>(p);
 }
 
@@ -862,7 +872,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // MFMAs of the next half tile (and this half's dP MFMAs) share a block with the exponentials, dS and
 // the dV / dK MFMAs of this one.  Arithmetic is that of attn_bwd_dkv_dma_kernel.
 template <int DP, int NST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_pipe_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_pipe_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   using Tile = SwTile<DP>;
   static_assert(NST >= 3, "tile t+1 is read while tile t+NST-1 is loaded");
   constexpr int BQ = 64, KS = DP / 16, DT = DP / 32;
@@ -1019,7 +1030,8 @@ store:
 // sets alternate; the barrier that admits tile t+1 sits between the two halves of tile t.
 // Arithmetic is that of attn_bwd_dq_dma_kernel.
 template <int DP, int NST>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_pipe_kernel(AttnDev p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_pipe_kernel(ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   using Tile = SwTile<DP>;
   static_assert(NST >= 3, "tile t+1 is read while tile t+NST-1 is loaded");
   constexpr int BKV = 64, KS = DP / 16, DT = DP / 32;
@@ -1218,17 +1230,17 @@ int attn_forward_mfma(const AttnArgs& a, hipStream_t stream) {
   if (dma_ok(a)) {
     if (a.d == 64) {
       constexpr size_t lds = 4 * 2 * SwTile<64>::kBytes;
-      hipLaunchKernelGGL((attn_fwd_pipe_kernel<64, 4>), grid, block, lds, stream, p);
+      launch_kernel((attn_fwd_pipe_kernel<64, 4>), grid, block, lds, stream, ATTN_ARGS(p));
     } else if (a.d == 32) {  // in the 64-wide LDS rows, half filled
       constexpr size_t lds = 4 * 2 * SwTile<64>::kBytes;
-      hipLaunchKernelGGL((attn_fwd_pipe_wide_kernel<64, 4, 32>), grid, block, lds, stream, p);
+      launch_kernel((attn_fwd_pipe_wide_kernel<64, 4, 32>), grid, block, lds, stream, ATTN_ARGS(p));
     } else if (a.d == 80) {
       // one tile at a time, two stages, in the 128-wide LDS rows partly filled: 231 registers and 64 KiB, so two
       // workgroups share a CU.  (The pipelined body is no faster here alone, 39.2 against 39.8 us at s = 1024,
       // 64 (sequence, head) pairs, and with its 128 KiB and one workgroup per CU it leaves less room for the
       // kernels of the executor's other lanes: 573.5 against 570.6 ms per step of the eight-chunk workload.)
       constexpr size_t lds = 2 * 2 * SwTile<128>::kBytes;
-      hipLaunchKernelGGL((attn_fwd_dma_kernel<128, 2, 80>), grid, block, lds, stream, p);
+      launch_kernel((attn_fwd_dma_kernel<128, 2, 80>), grid, block, lds, stream, ATTN_ARGS(p));
     } else {  // the pipelined body without the register cap (one workgroup per CU), four stages of K and V
               // (128 KiB); head dim 96 in the 128-wide LDS rows, partly filled
       constexpr size_t lds = 4 * 2 * SwTile<128>::kBytes;
@@ -1236,7 +1248,7 @@ int attn_forward_mfma(const AttnArgs& a, hipStream_t stream) {
   do {                                                                                         \
     const int rc = raise_lds(attn_fwd_pipe_wide_kernel<__VA_ARGS__>, lds);                     \
     if (rc) return rc;                                                                         \
-    hipLaunchKernelGGL((attn_fwd_pipe_wide_kernel<__VA_ARGS__>), grid, block, lds, stream, p); \
+    launch_kernel((attn_fwd_pipe_wide_kernel<__VA_ARGS__>), grid, block, lds, stream, ATTN_ARGS(p)); \
   } while (0)
       if (a.d == 128) LAUNCH_FWD(128, 4);
       else LAUNCH_FWD(128, 4, 96);
@@ -1244,9 +1256,9 @@ int attn_forward_mfma(const AttnArgs& a, hipStream_t stream) {
     }
     return check_launch("attn_fwd_dma");
   }
-  if (a.d <= 64) hipLaunchKernelGGL((attn_fwd_kernel<64>), grid, block, 0, stream, p);
-  else if (a.d <= 96) hipLaunchKernelGGL((attn_fwd_kernel<96>), grid, block, 0, stream, p);
-  else hipLaunchKernelGGL((attn_fwd_kernel<128>), grid, block, 0, stream, p);
+  if (a.d <= 64) launch_kernel((attn_fwd_kernel<64>), grid, block, 0, stream, ATTN_ARGS(p));
+  else if (a.d <= 96) launch_kernel((attn_fwd_kernel<96>), grid, block, 0, stream, ATTN_ARGS(p));
+  else launch_kernel((attn_fwd_kernel<128>), grid, block, 0, stream, ATTN_ARGS(p));
   return check_launch("attn_fwd_mfma");
 }
 
@@ -1260,14 +1272,14 @@ int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
     constexpr size_t lds_dkv = 4 * (2 * SwTile<64>::kBytes + 512);
     rc = raise_lds(attn_bwd_dkv_pipe_kernel<64, 4>, lds_dkv);
     if (rc) return rc;
-    hipLaunchKernelGGL((attn_bwd_dq_pipe_kernel<64, 4>), grid, block, 4 * 2 * SwTile<64>::kBytes, stream, p);
-    hipLaunchKernelGGL((attn_bwd_dkv_pipe_kernel<64, 4>), grid, block, lds_dkv, stream, p);
+    launch_kernel((attn_bwd_dq_pipe_kernel<64, 4>), grid, block, 4 * 2 * SwTile<64>::kBytes, stream, ATTN_ARGS(p));
+    launch_kernel((attn_bwd_dkv_pipe_kernel<64, 4>), grid, block, lds_dkv, stream, ATTN_ARGS(p));
     return check_launch("attn_bwd_pipe");
   }
   if (dma_ok(a) && a.d == 32) {
     constexpr size_t lds_dkv = 3 * (2 * SwTile<64>::kBytes + 512);
-    hipLaunchKernelGGL((attn_bwd_dq_dma2_kernel<64, 3, 32>), grid, block, 3 * 2 * SwTile<64>::kBytes, stream, p);
-    hipLaunchKernelGGL((attn_bwd_dkv_dma2_kernel<64, 3, 32>), grid, block, lds_dkv, stream, p);
+    launch_kernel((attn_bwd_dq_dma2_kernel<64, 3, 32>), grid, block, 3 * 2 * SwTile<64>::kBytes, stream, ATTN_ARGS(p));
+    launch_kernel((attn_bwd_dkv_dma2_kernel<64, 3, 32>), grid, block, lds_dkv, stream, ATTN_ARGS(p));
     return check_launch("attn_bwd_dma");
   }
   if (dma_ok(a)) {  // likewise: dQ first (it writes delta), then dK/dV
@@ -1277,8 +1289,8 @@ int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
   do {                                                                                               \
     rc = raise_lds(attn_bwd_dkv_dma_kernel<__VA_ARGS__>, lds_dkv);                                   \
     if (rc) return rc;                                                                               \
-    hipLaunchKernelGGL((attn_bwd_dq_dma_kernel<__VA_ARGS__>), grid, block, lds_dq, stream, p);       \
-    hipLaunchKernelGGL((attn_bwd_dkv_dma_kernel<__VA_ARGS__>), grid, block, lds_dkv, stream, p);     \
+    launch_kernel((attn_bwd_dq_dma_kernel<__VA_ARGS__>), grid, block, lds_dq, stream, ATTN_ARGS(p));       \
+    launch_kernel((attn_bwd_dkv_dma_kernel<__VA_ARGS__>), grid, block, lds_dkv, stream, ATTN_ARGS(p));     \
   } while (0)
       // Head dims 80 and 96 fit 256 registers (218 - 255, nothing spilled), so two workgroups share a CU: 118 -> 103 us
       // at d = 80, s = 1024, 64 (sequence, head) pairs.  Head dim 128 does not (72 - 92 bytes of scratch per lane and
@@ -1287,8 +1299,8 @@ int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
   do {                                                                                               \
     rc = raise_lds(attn_bwd_dkv_dma2_kernel<__VA_ARGS__>, lds_dkv);                                  \
     if (rc) return rc;                                                                               \
-    hipLaunchKernelGGL((attn_bwd_dq_dma2_kernel<__VA_ARGS__>), grid, block, lds_dq, stream, p);      \
-    hipLaunchKernelGGL((attn_bwd_dkv_dma2_kernel<__VA_ARGS__>), grid, block, lds_dkv, stream, p);    \
+    launch_kernel((attn_bwd_dq_dma2_kernel<__VA_ARGS__>), grid, block, lds_dq, stream, ATTN_ARGS(p));      \
+    launch_kernel((attn_bwd_dkv_dma2_kernel<__VA_ARGS__>), grid, block, lds_dkv, stream, ATTN_ARGS(p));    \
   } while (0)
       if (a.d == 128) LAUNCH_BWD(128, 2);
       else if (a.d == 96) LAUNCH_BWD2(128, 2, 96);
@@ -1301,14 +1313,14 @@ int attn_backward_mfma(const AttnArgs& a, hipStream_t stream) {
   rc = attn_delta(a, stream);
   if (rc) return rc;
   if (a.d <= 64) {
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<64>), grid, block, 0, stream, p);
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<64>), grid, block, 0, stream, p);
+    launch_kernel((attn_bwd_dkv_kernel<64>), grid, block, 0, stream, ATTN_ARGS(p));
+    launch_kernel((attn_bwd_dq_kernel<64>), grid, block, 0, stream, ATTN_ARGS(p));
   } else if (a.d <= 96) {
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<96>), grid, block, 0, stream, p);
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<96>), grid, block, 0, stream, p);
+    launch_kernel((attn_bwd_dkv_kernel<96>), grid, block, 0, stream, ATTN_ARGS(p));
+    launch_kernel((attn_bwd_dq_kernel<96>), grid, block, 0, stream, ATTN_ARGS(p));
   } else {
-    hipLaunchKernelGGL((attn_bwd_dkv_kernel<128>), grid, block, 0, stream, p);
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<128>), grid, block, 0, stream, p);
+    launch_kernel((attn_bwd_dkv_kernel<128>), grid, block, 0, stream, ATTN_ARGS(p));
+    launch_kernel((attn_bwd_dq_kernel<128>), grid, block, 0, stream, ATTN_ARGS(p));
   }
   return check_launch("attn_bwd_mfma");
 }

@@ -77,7 +77,8 @@ __device__ __forceinline__ void sum_parts(const float* parts, float scale, bf16*
 }
 
 template <int DP, int D>
-__global__ __launch_bounds__(NW * 64) void attn_fwd_split_kernel(AttnDev p, int pairs) {
+__global__ __launch_bounds__(NW * 64) void attn_fwd_split_kernel(int pairs, int /* tiles */, ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   using Tile = SwTile<DP>;
   constexpr int KS = D / 16, DT = (D + 31) / 32, STAGE = 2 * kTile32<DP>, LOADS = 2 * Tile::kInstr32;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -397,7 +398,8 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
 
 // dK / dV of every key tile, then dQ of every query tile: the longer work first.
 template <int DP, int D>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_split_kernel(AttnDev p, int pairs, int tiles) {
+__global__ __launch_bounds__(NW * 64) void attn_bwd_split_kernel(int pairs, int tiles, ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int per_side = pairs * tiles, side = (int)blockIdx.x >= per_side;
   int t, h, n;
@@ -419,8 +421,9 @@ int forward_t(const AttnArgs& a, hipStream_t stream) {
   static thread_local uint64_t raised = 0;
   constexpr size_t lds = lds_bytes<DP>(2 * kTile32<DP>);
   if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_fwd_split_kernel<DP, D>), lds, raised)) return rc;
+  const AttnDev p = to_dev(a);
   const int pairs = a.heads * a.b, tiles = (a.s + 31) / 32;
-  hipLaunchKernelGGL((attn_fwd_split_kernel<DP, D>), dim3(pairs * tiles), dim3(NW * 64), lds, stream, to_dev(a), pairs);
+  launch_kernel((attn_fwd_split_kernel<DP, D>), dim3(pairs * tiles), dim3(NW * 64), lds, stream, pairs, tiles, ATTN_ARGS(p));
   return check_launch("attn_fwd_split");
 }
 template <int DP, int D>
@@ -428,8 +431,9 @@ int backward_t(const AttnArgs& a, hipStream_t stream) {
   static thread_local uint64_t raised = 0;
   constexpr size_t lds = lds_bytes<DP>(kBwdStage<DP>);
   if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_bwd_split_kernel<DP, D>), lds, raised)) return rc;
+  const AttnDev p = to_dev(a);
   const int pairs = a.heads * a.b, tiles = (a.s + 31) / 32;
-  hipLaunchKernelGGL((attn_bwd_split_kernel<DP, D>), dim3(2 * pairs * tiles), dim3(NW * 64), lds, stream, to_dev(a), pairs, tiles);
+  launch_kernel((attn_bwd_split_kernel<DP, D>), dim3(2 * pairs * tiles), dim3(NW * 64), lds, stream, pairs, tiles, ATTN_ARGS(p));
   return check_launch("attn_bwd_split");
 }
 

@@ -442,10 +442,10 @@ int embed_forward(int dtype, const void* wte, const void* wpe, const int32_t* to
   const int rows = b * s;
   const dim3 grid((rows + kRowsPerBlock - 1) / kRowsPerBlock);
   if (dtype == HANAYO_BF16)
-    hipLaunchKernelGGL(embed_fwd_kernel<bf16>, grid, dim3(256), 0, stream, (const bf16*)wte, (const bf16*)wpe, tokens,
+    launch_kernel(embed_fwd_kernel<bf16>, grid, dim3(256), 0, stream, (const bf16*)wte, (const bf16*)wpe, tokens,
                        (bf16*)x, rows, s, H, vocab);
   else
-    hipLaunchKernelGGL(embed_fwd_kernel<float>, grid, dim3(256), 0, stream, (const float*)wte, (const float*)wpe, tokens,
+    launch_kernel(embed_fwd_kernel<float>, grid, dim3(256), 0, stream, (const float*)wte, (const float*)wpe, tokens,
                        (float*)x, rows, s, H, vocab);
   return check_launch("embed_forward");
 }
@@ -458,7 +458,7 @@ int embed_backward_t(const int32_t* tokens, const void* dx, float* d_wte, float*
   const size_t lds = (size_t)3 * H * sizeof(float);
   const int nv = (H + 511) / 512;
 #define LAUNCH(NV)                                                                                              \
-  hipLaunchKernelGGL((embed_bwd_token_kernel<T, NV>), dim3(rows), dim3(256), lds, stream, tokens, (const T*)dx, d_wte, \
+  launch_kernel((embed_bwd_token_kernel<T, NV>), dim3(rows), dim3(256), lds, stream, tokens, (const T*)dx, d_wte, \
                      rows, H, vocab)
   if (nv <= 1) LAUNCH(1);
   else if (nv <= 2) LAUNCH(2);
@@ -468,7 +468,7 @@ int embed_backward_t(const int32_t* tokens, const void* dx, float* d_wte, float*
   int rc = check_launch("embed_backward (tokens)");
   if (rc) return rc;
   const dim3 pgrid((unsigned)(((long)s * (H / 8) + 255) / 256));
-  hipLaunchKernelGGL(embed_bwd_pos_kernel<T>, pgrid, dim3(256), 0, stream, (const T*)dx, d_wpe, b, s, H);
+  launch_kernel(embed_bwd_pos_kernel<T>, pgrid, dim3(256), 0, stream, (const T*)dx, d_wpe, b, s, H);
   return check_launch("embed_backward (positions)");
 }
 }  // namespace
@@ -482,7 +482,7 @@ int embed_backward(int dtype, const int32_t* tokens, const void* dx, float* d_wt
 
 int list_labelled(const int32_t* labels, int rows, int vocab, int* live, int32_t* list, int32_t* slot, hipStream_t stream) {
   if (rows < 1 || vocab < 1) return set_error(HANAYO_EINVAL, "list_labelled: bad shape");
-  hipLaunchKernelGGL(list_labelled_kernel, dim3(1), dim3(1024), 0, stream, labels, rows, vocab, live, list, slot);
+  launch_kernel(list_labelled_kernel, dim3(1), dim3(1024), 0, stream, labels, rows, vocab, live, list, slot);
   return check_launch("list_labelled");
 }
 
@@ -490,9 +490,9 @@ int gather_rows(int dtype, const void* in, const int* live, const int32_t* list,
   if (rows < 1 || H < 8 || H % 8) return set_error(HANAYO_EINVAL, "gather_rows: bad shape");
   const dim3 grid((rows + kRowsPerBlock - 1) / kRowsPerBlock);
   if (dtype == HANAYO_BF16)
-    hipLaunchKernelGGL(gather_rows_kernel<bf16>, grid, dim3(256), 0, stream, (const bf16*)in, live, list, (bf16*)out, H);
+    launch_kernel(gather_rows_kernel<bf16>, grid, dim3(256), 0, stream, (const bf16*)in, live, list, (bf16*)out, H);
   else
-    hipLaunchKernelGGL(gather_rows_kernel<float>, grid, dim3(256), 0, stream, (const float*)in, live, list, (float*)out, H);
+    launch_kernel(gather_rows_kernel<float>, grid, dim3(256), 0, stream, (const float*)in, live, list, (float*)out, H);
   return check_launch("gather_rows");
 }
 
@@ -501,11 +501,11 @@ int scatter_rows(int dtype, const void* product, const int* live, const int32_t*
   if (rows < 1 || H < 8 || H % 8) return set_error(HANAYO_EINVAL, "scatter_rows: bad shape");
   const dim3 g((rows + kRowsPerBlock - 1) / kRowsPerBlock);
   if (dtype != HANAYO_BF16)
-    hipLaunchKernelGGL((scatter_rows_kernel<float, float>), g, dim3(256), 0, stream, (const float*)product, live, slot, grid, K, (float*)out, rows, H);
+    launch_kernel((scatter_rows_kernel<float, float>), g, dim3(256), 0, stream, (const float*)product, live, slot, grid, K, (float*)out, rows, H);
   else if (grid > 0)
-    hipLaunchKernelGGL((scatter_rows_kernel<bf16, float>), g, dim3(256), 0, stream, (const float*)product, live, slot, grid, K, (bf16*)out, rows, H);
+    launch_kernel((scatter_rows_kernel<bf16, float>), g, dim3(256), 0, stream, (const float*)product, live, slot, grid, K, (bf16*)out, rows, H);
   else
-    hipLaunchKernelGGL((scatter_rows_kernel<bf16, bf16>), g, dim3(256), 0, stream, (const bf16*)product, live, slot, grid, K, (bf16*)out, rows, H);
+    launch_kernel((scatter_rows_kernel<bf16, bf16>), g, dim3(256), 0, stream, (const bf16*)product, live, slot, grid, K, (bf16*)out, rows, H);
   return check_launch("scatter_rows");
 }
 
@@ -515,16 +515,16 @@ int softmax_xent(int dtype, void* logits, const int32_t* labels, const int* live
   if (dtype == HANAYO_BF16 && V > 2048 && V <= 1024 * 8 * 8) {
     const int nv = (V / 8 + 1023) / 1024;
     auto kern = nv <= 2 ? xent_row_kernel<2> : nv <= 4 ? xent_row_kernel<4> : nv <= 6 ? xent_row_kernel<6> : xent_row_kernel<8>;
-    hipLaunchKernelGGL(kern, dim3(rows), dim3(1024), 0, stream, (bf16*)logits, labels, live, list, loss_scale, nll, V);
+    launch_kernel(kern, dim3(rows), dim3(1024), 0, stream, (bf16*)logits, labels, live, list, loss_scale, nll, V);
   } else if (dtype == HANAYO_BF16)
-    hipLaunchKernelGGL(xent_kernel<bf16>, dim3(rows), dim3(256), 0, stream, (bf16*)logits, labels, live, list, loss_scale, nll, V);
+    launch_kernel(xent_kernel<bf16>, dim3(rows), dim3(256), 0, stream, (bf16*)logits, labels, live, list, loss_scale, nll, V);
   else
-    hipLaunchKernelGGL(xent_kernel<float>, dim3(rows), dim3(256), 0, stream, (float*)logits, labels, live, list, loss_scale, nll, V);
+    launch_kernel(xent_kernel<float>, dim3(rows), dim3(256), 0, stream, (float*)logits, labels, live, list, loss_scale, nll, V);
   return check_launch("softmax_xent");
 }
 
 int loss_finish(const float* nll, const int* live, float* loss, hipStream_t stream) {
-  hipLaunchKernelGGL(loss_finish_kernel, dim3(1), dim3(256), 0, stream, nll, live, loss);
+  launch_kernel(loss_finish_kernel, dim3(1), dim3(256), 0, stream, nll, live, loss);
   return check_launch("loss_finish");
 }
 
@@ -545,8 +545,8 @@ int adam(int dtype, const AdamArgs& g, hipStream_t stream) {
   for (int r = 0; r < 4; ++r) a.lo[r] = g.lo[r], a.hi[r] = g.hi[r];
   const size_t vec = g.count / 4, blocks = (vec + 255) / 256;
   if (blocks > 0x7fffffffu) return set_error(HANAYO_EUNSUPPORTED, "adam: too many elements");
-  if (dtype == HANAYO_BF16) hipLaunchKernelGGL(adam_kernel<bf16>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(adam_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  if (dtype == HANAYO_BF16) launch_kernel(adam_kernel<bf16>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
+  else launch_kernel(adam_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, stream, a);
   return check_launch("adam");
 }
 

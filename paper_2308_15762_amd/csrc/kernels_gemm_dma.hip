@@ -59,9 +59,6 @@ struct DmaGemmGroup {
   int first[kMaxGroup + 1];
   int count;
 };
-// What a launch passes: only weight gradients come in groups.
-template <int EPI>
-using DmaArgs = std::conditional_t<EPI == EPI_ACCUM_F32, DmaGemmGroup, DmaGemm>;
 
 // GELU in the epilogues: Phi (forward) and GELU' (input gradient of FC2) over [-8, 8) as kGeluN intervals of 1 / 128, each the
 // value at its left end and the rise to its right end; read with linear interpolation (error below 1e-5, far under bf16
@@ -193,20 +190,9 @@ struct Operand {
 };
 
 
+// wg: tile number within the problem
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
-__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(DmaArgs<EPI> args) {
-  DmaGemm p;
-  int wg = (int)blockIdx.x;  // tile number within the problem
-  if constexpr (EPI == EPI_ACCUM_F32) {
-    int gi = 0;
-#pragma unroll
-    for (int j = 1; j < kMaxGroup; ++j)
-      if (j < args.count && wg >= args.first[j]) gi = j;
-    p = args.prob[gi];
-    wg -= args.first[gi];
-  } else {
-    p = args;
-  }
+__device__ __forceinline__ void gemm_dma_body(DmaGemm p, int wg) {
   // A launch over rows counted on the device may have fewer workgroups than tiles (see launch): they take several each.
   // (By goto: with the tile's code in a function and a loop around it the other instances, which never loop, are scheduled
   // worse and one spills: 2048 x 16384 x 4096 with GELU' 222 -> 229 us.  With the goto only the 256 x 256 instance that loops
@@ -214,7 +200,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
   // us instead of 208.)
   constexpr bool kLoop = EDGE && EPI == EPI_NONE && !B_T;
   int step = 0, tiles_end = 0;
-  if (EDGE && p.live) {
+  if (EDGE && p.live_dim) {
     const int live = __builtin_amdgcn_readfirstlane(*p.live);
     if (live < 1) return;
     if (p.live_dim == LIVE_K) {
@@ -612,14 +598,38 @@ next_tile:
   }
 }
 
+// Only weight gradients come in groups.  What the first loads of a single problem depend on stands in the first 14 words of the
+// kernel's arguments, which are in scalar registers when it starts (see the build flags); live_dim stands above ldc.
+constexpr int kLdcBits = 28;
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
+__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(
+    const bf16* A, const bf16* B, void* C, const bf16* bias, int M, int N, int K, int lda, int ldb, int ldc_live, const bf16* aux,
+    bf16* aux_out, const int* live) {
+  DmaGemm p;
+  p.A = A; p.B = B; p.C = (bf16*)C; p.Cf = (float*)C; p.bias = bias; p.aux = aux; p.aux_out = aux_out;
+  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc_live & ((1 << kLdcBits) - 1);
+  p.colsum = nullptr; p.live = live; p.live_dim = ldc_live >> kLdcBits;
+  gemm_dma_body<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>(p, (int)blockIdx.x);
+}
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool EDGE>
+__global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_group_kernel(DmaGemmGroup grp) {
+  int gi = 0;
+#pragma unroll
+  for (int j = 1; j < kMaxGroup; ++j)
+    if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
+  gemm_dma_body<BM, BN, WGM, WGN, NSTAGE, true, true, EPI_ACCUM_F32, EDGE>(grp.prob[gi], (int)blockIdx.x - grp.first[gi]);
+}
+
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 int launch(DmaGemmGroup& grp, hipStream_t stream) {
   constexpr int NW = WGM * WGN;
   constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes) +
                          (EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU ? sizeof(GeluTable) : 0);
-  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>;
   static thread_local uint64_t raised = 0;
-  if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
+  const void* kern;
+  if constexpr (EPI == EPI_ACCUM_F32) kern = reinterpret_cast<const void*>(&gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, EDGE>);
+  else kern = reinterpret_cast<const void*>(&gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>);
+  if (const int rc = raise_lds(kern, lds, raised)) return rc;
   long tiles = 0;
   for (int i = 0; i < grp.count; ++i) {
     grp.first[i] = (int)tiles;
@@ -636,8 +646,14 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
     if (tiles > fit) tiles = fit;
   }
   for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
-  if constexpr (EPI == EPI_ACCUM_F32) hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, stream, grp);
-  else hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(NW * 64), lds, stream, grp.prob[0]);
+  const dim3 grid((unsigned)tiles), block(NW * 64);
+  if constexpr (EPI == EPI_ACCUM_F32) {
+    launch_kernel((gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, EDGE>), grid, block, lds, stream, grp);
+  } else {
+    const DmaGemm& p = grp.prob[0];
+    launch_kernel((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>), grid, block, lds, stream, p.A, p.B, (void*)p.C,
+                       p.bias, p.M, p.N, p.K, p.lda, p.ldb, p.ldc | p.live_dim << kLdcBits, p.aux, p.aux_out, p.live);
+  }
   return check_launch("gemm_dma");
 }
 
@@ -698,7 +714,7 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
   const long span_a = (long)(g.a_t ? kBK : bm) * g.lda * 2, span_b = (long)(g.b_t ? kBK : bn) * g.ldb * 2;
   // operands on 16-byte boundaries with every row of A and B on one too (those of C: see epilogue.h)
   const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
-  if (bits % 16 || g.lda % 8 || g.ldb % 8 || g.ldc % 4 || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
+  if (bits % 16 || g.lda % 8 || g.ldb % 8 || g.ldc % 4 || g.ldc >= 1 << kLdcBits || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
   if (whole_tiles(g, config)) return true;
   // edges: whole 16-byte vectors along every row
   return (g.a_t ? g.M : g.K) % 8 == 0 && (g.b_t ? g.N : g.K) % 8 == 0 && g.N % 8 == 0;
@@ -721,7 +737,7 @@ int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream
     p.bias = (const bf16*)g.bias; p.aux = (const bf16*)g.aux; p.aux_out = (bf16*)g.aux_out;
     p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
     p.colsum = g.b_t ? g.colsum : nullptr;
-    p.live = g.live; p.live_dim = g.live_dim;
+    p.live = g.live; p.live_dim = g.live ? g.live_dim : LIVE_NONE;
     edge = edge || g.live;
     if (g.live && g.live_dim == LIVE_M_SPLIT && (config != 7 || count != 1 || g.epi != EPI_STORE_F32))
       return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: a split contraction takes one problem of 256 x 256 tiles");

@@ -61,10 +61,6 @@ struct WaveGemmGroup {
   int first[kMaxGroup + 1];  // workgroups first[i] .. first[i + 1] - 1 are the tiles of problem i
   int count;
 };
-// What a launch passes: only weight gradients come in groups.  A single problem is passed by itself: its fields are where
-// the kernel expects them without a search, and a quarter of the bytes goes through the launch (1 us of host time).
-template <typename T, int EPI>
-using WaveArgs = std::conditional_t<EPI == EPI_ACCUM_F32, WaveGemmGroup<T>, WaveGemm<T>>;
 
 // VEC = elements of a 16-byte vector, BK = elements of a K tile (4 MFMA steps), Frag = what a lane feeds per step:
 // VEC contraction elements, 2 VEC per step over the two halves of the wavefront.
@@ -186,26 +182,14 @@ constexpr size_t wave_lds_bytes(int nst) {
 // other's waits) for launches with more tiles than CUs, two for launches of at most one tile per CU.  Even with one
 // stage the next tile's loads run under the MFMAs of this one: its fragments are in registers by then.
 template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
-__global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(WaveArgs<T, EPI> args) {
+__device__ __forceinline__ void gemm_wave_body(WaveGemm<T> p, int wg) {
   using P = Prec<T>;
   using OpA = WaveOperand<T, BM, A_T>;
   using OpB = WaveOperand<T, BN, B_T>;
   using Frag = typename P::Frag;
   constexpr int TM = BM / 32, TN = BN / 32, VEC = P::VEC, BK = P::BK;
   constexpr int STAGE = OpA::kBytes + OpB::kBytes, LOADS = OpA::kInstr + OpB::kInstr;
-  WaveGemm<T> p;
-  int wg = (int)blockIdx.x;
-  if constexpr (EPI == EPI_ACCUM_F32) {
-    int gi = 0;
-#pragma unroll
-    for (int j = 1; j < kMaxGroup; ++j)
-      if (j < args.count && wg >= args.first[j]) gi = j;
-    p = args.prob[gi];
-    wg -= args.first[gi];
-  } else {
-    p = args;
-  }
-  if (p.live) {
+  if (p.live_dim) {
     const int live = __builtin_amdgcn_readfirstlane(*p.live);
     if (live < 1) return;
     if (p.live_dim == LIVE_K) p.K = live;
@@ -445,14 +429,45 @@ __global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(WaveArgs<T, EPI> arg
   }
 }
 
+// Only weight gradients come in groups.  A single problem is passed by itself: its fields are where the kernel expects them
+// without a search, and a quarter of the bytes goes through the launch (1 us of host time).  The first 14 words of a kernel's
+// arguments are in scalar registers when it starts (see the build flags); what the first loads depend on stands there, and
+// live_dim above ldc, so that nothing at the start waits for the argument block in memory (0.3 us).
+constexpr int kLdcBits = 28;
+template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
+__global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(const T* A, const T* B, T* C, const T* bias, int M, int N, int K,
+                                                            int lda, int ldb, int ldc_live, const T* aux, T* aux_out,
+                                                            const int* live) {
+  WaveGemm<T> p;
+  p.A = A; p.B = B; p.C = C; p.Cf = nullptr; p.bias = bias; p.aux = aux; p.aux_out = aux_out;
+  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc_live & ((1 << kLdcBits) - 1);
+  p.colsum = nullptr; p.live = live; p.live_dim = ldc_live >> kLdcBits;
+  gemm_wave_body<T, BM, BN, NST, A_T, B_T, EPI>(p, (int)blockIdx.x);
+}
+template <typename T, int BM, int BN, int NST>
+__global__ __launch_bounds__(NW * 64) void gemm_wave_group_kernel(WaveGemmGroup<T> grp) {
+  int gi = 0;
+#pragma unroll
+  for (int j = 1; j < kMaxGroup; ++j)
+    if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
+  gemm_wave_body<T, BM, BN, NST, true, true, EPI_ACCUM_F32>(grp.prob[gi], (int)blockIdx.x - grp.first[gi]);
+}
+
 template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
 int launch(WaveGemmGroup<T>& grp, unsigned tiles, hipStream_t stream) {
   constexpr size_t lds = wave_lds_bytes<BM, BN>(NST);
-  auto kern = gemm_wave_kernel<T, BM, BN, NST, A_T, B_T, EPI>;
   static thread_local uint64_t raised = 0;
-  if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
-  if constexpr (EPI == EPI_ACCUM_F32) hipLaunchKernelGGL(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp);
-  else hipLaunchKernelGGL(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp.prob[0]);
+  if constexpr (EPI == EPI_ACCUM_F32) {
+    auto kern = gemm_wave_group_kernel<T, BM, BN, NST>;
+    if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
+    launch_kernel(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp);
+  } else {
+    auto kern = gemm_wave_kernel<T, BM, BN, NST, A_T, B_T, EPI>;
+    if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
+    const WaveGemm<T>& p = grp.prob[0];
+    launch_kernel(kern, dim3(tiles), dim3(NW * 64), lds, stream, p.A, p.B, p.C, p.bias, p.M, p.N, p.K, p.lda, p.ldb,
+                       p.ldc | p.live_dim << kLdcBits, p.aux, p.aux_out, p.live);
+  }
   return check_launch("gemm_wave");
 }
 
@@ -497,7 +512,7 @@ int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream) {
     p.bias = (const T*)g.bias; p.aux = (const T*)g.aux; p.aux_out = (T*)g.aux_out;
     p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
     p.colsum = g.epi == EPI_ACCUM_F32 ? g.colsum : nullptr;
-    p.live = g.live; p.live_dim = g.live_dim;
+    p.live = g.live; p.live_dim = g.live ? g.live_dim : LIVE_NONE;
     grp.first[i] = (int)tiles;
     tiles += tiles_of(&g, 1, edge);
   }
@@ -520,7 +535,7 @@ bool gemm_wave_supported(int dtype, const GemmArgs& g) {
   if (!combo || (g.colsum && g.epi != EPI_ACCUM_F32) || (g.live && g.live_dim == LIVE_M_SPLIT)) return false;
   const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
   return bits % 16 == 0 && (g.a_t ? g.M : g.K) % vec == 0 && (g.b_t ? g.N : g.K) % vec == 0 && g.N % vec == 0 && g.lda % vec == 0 &&
-         g.ldb % vec == 0 && g.ldc % 4 == 0 && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
+         g.ldb % vec == 0 && g.ldc % 4 == 0 && g.ldc < 1 << kLdcBits && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
 }
 
 int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream) {

@@ -115,7 +115,7 @@ int gemm_alu_t(const GemmArgs& g, hipStream_t stream) {
   const dim3 grid((unsigned)tiles), block(256);
 #define LAUNCH(E)                                                                                                    \
   case E:                                                                                                            \
-    hipLaunchKernelGGL((gemm_alu_kernel<T, E>), grid, block, 0, stream, (const T*)g.A, (const T*)g.B, g.M, g.N, g.K, \
+    launch_kernel((gemm_alu_kernel<T, E>), grid, block, 0, stream, (const T*)g.A, (const T*)g.B, g.M, g.N, g.K, \
                        g.lda, g.ldb, g.a_t, g.b_t, g.live, g.live_dim, ep);                                                          \
     break
   switch (g.epi) {
@@ -140,7 +140,7 @@ int gemm_alu(int dtype, const GemmArgs& g, hipStream_t stream) {
 int attn_delta(const AttnArgs& a, hipStream_t stream) {
   if (a.d % 8 || a.d > 128) return set_error(HANAYO_EUNSUPPORTED, "attn_delta: head dim %d", a.d);
   const long groups = (long)a.b * a.s * a.heads;
-  hipLaunchKernelGGL(attn_delta_kernel, dim3((unsigned)((groups + kDeltaGroups - 1) / kDeltaGroups)), dim3(256), 0, stream,
+  launch_kernel(attn_delta_kernel, dim3((unsigned)((groups + kDeltaGroups - 1) / kDeltaGroups)), dim3(256), 0, stream,
                      (const bf16*)a.ctx, (const bf16*)a.dctx, a.delta, groups, a.s, a.heads, a.d);
   return check_launch("attn_delta");
 }

@@ -46,8 +46,8 @@ struct Raw8<float> {
 template <typename T, int NV, bool FULL>
 __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, const T* __restrict__ gamma,
                                                      const T* __restrict__ beta, T* __restrict__ out,
-                                                     float2* __restrict__ stats, T* __restrict__ copy_out, int rows,
-                                                     int H, float eps) {
+                                                     float2* __restrict__ stats, int rows, int H, float eps,
+                                                     T* __restrict__ copy_out) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
   if (row >= rows) return;
@@ -119,8 +119,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T* __restrict__ x, co
 template <typename T, int RS, int RG, bool FULL>
 __global__ __launch_bounds__(RS * RG * 64) void ln_bwd_kernel(const T* __restrict__ dout, const T* __restrict__ x,
                                                               const T* __restrict__ gamma, const float2* __restrict__ stats,
-                                                              const T* __restrict__ addend, T* __restrict__ dz,
-                                                              float* __restrict__ partial, int rows, int H) {
+                                                              const T* __restrict__ addend, int rows, int H,
+                                                              T* __restrict__ dz, float* __restrict__ partial) {
   extern __shared__ float red[];                 // [RG][2 * H] for the column sums; before that the row-sum exchange
   float2* xch = reinterpret_cast<float2*>(red);  // [2][RG][RS]
   const int lane = threadIdx.x & 63;
@@ -307,8 +307,8 @@ int ln_forward_t(const void* x, const void* gamma, const void* beta, void* out, 
   const dim3 grid((T_ + kRowsPerBlock - 1) / kRowsPerBlock), block(256);
   const int nv = (H + 511) / 512;
 #define LAUNCH(NV, FULL)                                                                                              \
-  hipLaunchKernelGGL((ln_fwd_kernel<T, NV, FULL>), grid, block, 0, stream, (const T*)x, (const T*)gamma, (const T*)beta, \
-                     (T*)out, stats, (T*)copy_out, T_, H, eps)
+  launch_kernel((ln_fwd_kernel<T, NV, FULL>), grid, block, 0, stream, (const T*)x, (const T*)gamma, (const T*)beta, \
+                     (T*)out, stats, T_, H, eps, (T*)copy_out)
   if (H % 512 == 0) {  // every vector of every lane is inside the row
     switch (nv) {
       case 1: LAUNCH(1, true); break;
@@ -330,7 +330,7 @@ int ln_forward_t(const void* x, const void* gamma, const void* beta, void* out, 
 
 int launch_finalize(const float* partial, int rows, int ld, int n, float* out0, float* out1, int split, hipStream_t stream,
                     const char* what) {
-  hipLaunchKernelGGL(finalize_kernel, dim3((n + kFinalizeCols - 1) / kFinalizeCols), dim3(kFinalizeCols * kFinalizeGroups), 0,
+  launch_kernel(finalize_kernel, dim3((n + kFinalizeCols - 1) / kFinalizeCols), dim3(kFinalizeCols * kFinalizeGroups), 0,
                      stream, partial, rows, ld, n, out0, out1, split);
   return check_launch(what);
 }
@@ -347,11 +347,11 @@ int ln_backward_t(const void* dout, const void* x, const void* gamma, const floa
 #define LAUNCH(RS, RG)                                                                                                \
   do {                                                                                                                \
     if (H == 512 * RS)                                                                                                \
-      hipLaunchKernelGGL((ln_bwd_kernel<T, RS, RG, true>), dim3(blocks), dim3(RS * RG * 64), lds, stream, (const T*)dout, \
-                         (const T*)x, (const T*)gamma, stats, (const T*)addend, (T*)dz, partial, T_, H);              \
+      launch_kernel((ln_bwd_kernel<T, RS, RG, true>), dim3(blocks), dim3(RS * RG * 64), lds, stream, (const T*)dout, \
+                         (const T*)x, (const T*)gamma, stats, (const T*)addend, T_, H, (T*)dz, partial);              \
     else                                                                                                              \
-      hipLaunchKernelGGL((ln_bwd_kernel<T, RS, RG, false>), dim3(blocks), dim3(RS * RG * 64), lds, stream, (const T*)dout, \
-                         (const T*)x, (const T*)gamma, stats, (const T*)addend, (T*)dz, partial, T_, H);              \
+      launch_kernel((ln_bwd_kernel<T, RS, RG, false>), dim3(blocks), dim3(RS * RG * 64), lds, stream, (const T*)dout, \
+                         (const T*)x, (const T*)gamma, stats, (const T*)addend, T_, H, (T*)dz, partial);              \
   } while (0)
   switch (nv) {
     case 1: LAUNCH(1, 16); break;
@@ -379,7 +379,7 @@ int colsum_t(const void* in, int T_, int N, float* out, float* partial, hipStrea
   if (gy > 64) gy = 64;
   if (gy < 1) gy = 1;
   const dim3 grid((N + 255) / 256, gy);
-  hipLaunchKernelGGL((colsum_kernel<T>), grid, dim3(256), 0, stream, (const T*)in, T_, N, partial);
+  launch_kernel((colsum_kernel<T>), grid, dim3(256), 0, stream, (const T*)in, T_, N, partial);
   int rc = check_launch("colsum");
   if (rc) return rc;
   return launch_finalize(partial, gy, N, N, out, out, N, stream, "colsum finalize");
@@ -428,7 +428,7 @@ int finalize_group(const FinalizeJob* jobs, int count, hipStream_t stream) {
       if (batch.job[i].n > widest) widest = batch.job[i].n;
     }
     if (widest < 1) continue;
-    hipLaunchKernelGGL(finalize_group_kernel, dim3((widest + kFinalizeCols - 1) / kFinalizeCols, n),
+    launch_kernel(finalize_group_kernel, dim3((widest + kFinalizeCols - 1) / kFinalizeCols, n),
                        dim3(kFinalizeCols * kFinalizeGroups), 0, stream, batch);
     const int rc = check_launch("finalize_group");
     if (rc) return rc;
@@ -458,7 +458,7 @@ int copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t stream, int
   const size_t want = (n16 + 255) / 256;
   const size_t cap = max_workgroups > 0 ? (size_t)max_workgroups : (size_t)256 * 16;  // default: up to 16 workgroups per CU
   const unsigned blocks = (unsigned)(want < cap ? want : cap);
-  hipLaunchKernelGGL(copy_kernel, dim3(blocks), dim3(256), 0, stream, (const uint4*)src, (uint4*)dst, n16);
+  launch_kernel(copy_kernel, dim3(blocks), dim3(256), 0, stream, (const uint4*)src, (uint4*)dst, n16);
   return check_launch("copy");
 }
 
