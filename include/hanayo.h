@@ -376,12 +376,14 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
  * added inside a launch (a chunk's gradient accumulations keep their
  * list order).  Calls with lanes > 1 on one device are serialised on the host.
  *
- * The lanes are chosen by list scheduling with the schedule's own costs (forward 1, backward 2).
+ * The lanes are chosen by list scheduling with the schedule's own costs (forward 1, backward 2).  Of three or four lanes two
+ * are used where the tasks are small (ceil(T / 256) * ceil(F / 256) < 256): more are slower there.
  *
  * hanayo_executor_plan reports that plan without touching the GPU:
  *   lane  host [n]     lane of each task
- *   d, e  NULL, or the descriptors of a run with args->ends set: the plan then has the dependencies [4]
- *         below and counts the head's work (from the shapes) into the forward task of the last stage
+ *   d, e  NULL, or the descriptors of the run (d: the lanes it uses, see above; e, which needs d: a run with args->ends
+ *         set: the plan then has the dependencies [4] below and counts the head's work (from the shapes) into the
+ *         forward task of the last stage)
  *   deps  host [n][5]  indices of earlier tasks that task i waits for, -1 = none:
  *         [0] the local stage producing its input, [1] (B) its own forward,
  *         [2] (F) the backward that last read the stash entry it overwrites,

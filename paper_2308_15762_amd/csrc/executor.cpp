@@ -133,6 +133,17 @@ void plan_lanes(const hanayo_task* list, size_t n, int P, int W, int M, int rank
   }
 }
 
+// Lanes an executor uses of those it is given.  Tasks on different lanes meet at events, which cost the GPU about 10 us each
+// (a barrier packet and a signal between two queues), and smaller tasks meet more often.  Two lanes already cover each other's
+// launches there; the third and fourth pay where a task's own launches fill the chip only once and the others' tails fill in:
+// the line is 256 tiles of 256 x 256 in its widest product.  Steps with 4 and with 2 lanes, us: H = 512, T = 1024 1470 and
+// 1344; H = 768, T = 1527 2768 and 2605; H = 1024, T = 1024 2972 and 2775; H = 1024, T = 2048 8745 and 8549; above the line
+// H = 1024, T = 4096 25270 and 27665; H = 4096, T = 2048 164005 and 169271.  Results do not depend on it.
+int lanes_used(const Shape& sh, int lanes) {
+  const long tiles = (long)((sh.T + 255) / 256) * ((sh.F + 255) / 256);
+  return tiles < 256 && lanes > 2 ? 2 : lanes;
+}
+
 // Side streams and events, made once per device and kept: default priority, non-blocking.
 constexpr int kMaxLanes = 4;
 struct LaneResources {
@@ -306,6 +317,8 @@ int hanayo_executor_plan(const hanayo_task* list, size_t n, int P, int W, int M,
     if (rc) return rc;
     head_cost = head_cost_of(sh, *e);
   }
+  Shape used;
+  if (d && make_shape(d, used) == HANAYO_OK) lanes = lanes_used(used, lanes);
   LanePlan lp;
   plan_lanes(list, n, P, W, M, rank, lanes, e != nullptr && rank == 0, head_cost, pl, lp);
   for (size_t i = 0; i < n; ++i) {
@@ -366,8 +379,8 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
         return set_error(HANAYO_EINVAL, "executor: missing gradient buffer for mb %u chunk %d", tk.mb, tk.chunk);
     }
   }
-  const int lanes = a->lanes < 1 ? 1 : a->lanes;
-  if (lanes > kMaxLanes) return set_error(HANAYO_EINVAL, "executor: at most %d lanes", kMaxLanes);
+  if (a->lanes > kMaxLanes) return set_error(HANAYO_EINVAL, "executor: at most %d lanes", kMaxLanes);
+  const int lanes = a->lanes < 1 ? 1 : lanes_used(sh, a->lanes);
   LanePlan lp;
   plan_lanes(list, n, P, W, M, rank, lanes, en != nullptr, en ? head_cost_of(sh, en->desc) : 0.0, pl, lp);
   // a task records an event if a task on another lane waits for it
