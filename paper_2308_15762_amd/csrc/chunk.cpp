@@ -250,7 +250,11 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
   return colsum_add(dtype, g.B, g.K, g.N, g.colsum, g.colsum_scratch, stream);  // B is stored [K][ldb = N]
 }
 
-int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
+// A launch of few or small tiles takes jobs along: it leaves CUs idle, and one launch less is 2 to 3 us (a backward pass of one
+// block, T = 512, H = 256: 36.8 -> 34.6 us, two blocks, T = 777, H = 640: 183.9 -> 180.6).  Beside 256 x 256 tiles the jobs'
+// workgroups, which ask for the tiles' 128 KiB of LDS, hold up other lanes' kernels (four lanes, H = 4096: 0.6 % of a step).
+int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream, const FinalizeJob* jobs, int n_jobs, bool* taken) {
+  if (taken) *taken = false;
   if (count < 1 || count > 4) return set_error(HANAYO_EINVAL, "gemm_group: %d problems", count);
   bool alike = count == 1 || gs[0].epi == EPI_ACCUM_F32;  // the kernels take only weight gradients in groups
   for (int i = 0; i < count; ++i) {
@@ -260,12 +264,18 @@ int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream) {
     alike = alike && g.a_t == gs[0].a_t && g.b_t == gs[0].b_t && g.epi == gs[0].epi;
   }
   if (alike) {
-    if (const int edge = choose_wave_edge(dtype, gs, count)) return gemm_wave_group(dtype, gs, count, edge, stream);
+    if (const int edge = choose_wave_edge(dtype, gs, count)) {
+      if (taken) *taken = true;
+      return gemm_wave_group(dtype, gs, count, edge, stream, jobs, taken ? n_jobs : 0);
+    }
   }
   if (alike && dtype == HANAYO_BF16) {
     double cost;
     const int config = choose_dma_config(gs, count, g_gemm_sharing, &cost);
-    if (config >= 0) return gemm_dma_group(gs, count, config, stream);
+    if (config >= 0) {
+      if (taken) *taken = config != 7;
+      return gemm_dma_group(gs, count, config, stream, jobs, taken && *taken ? n_jobs : 0);
+    }
   }
   for (int i = 0; i < count; ++i) {
     const int rc = gemm(dtype, gs[i], stream);
@@ -333,17 +343,18 @@ int chunk_backward(const Shape& sh, const void* weights, float* grads, const voi
   char* ws = static_cast<char*>(workspace);
   const int T = sh.T, H = sh.H, F = sh.F;
   float* partial = reinterpret_cast<float*>(ws + WL.partial);
-  // Every LayerNorm backward leaves its partial gamma/beta sums in a slot of its own; one launch after the
-  // last block adds them all to the gradients.
+  // Every LayerNorm backward leaves its partial gamma/beta sums in a slot of its own; a block's weight-gradient launch
+  // adds its two LayerNorms' to the gradients, or one launch after the last block does it for all of them.
   std::vector<k::FinalizeJob> ln_jobs;
   ln_jobs.reserve(2 * (size_t)sh.nb);
-  auto ln_slot = [&]() { return reinterpret_cast<float*>(ws + WL.ln_partial + ln_jobs.size() * WL.ln_slot_bytes); };
+  size_t slot = 0;
+  auto ln_slot = [&]() { return reinterpret_cast<float*>(ws + WL.ln_partial + slot * WL.ln_slot_bytes); };
   auto ln_bwd = [&](const void* dout, const void* x, const void* gamma, const void* stats, const void* addend, void* dz,
                     float* dgamma, float* dbeta) {
     k::FinalizeJob job;
     const int rc = k::ln_backward_deferred(sh.dtype, dout, x, gamma, reinterpret_cast<const float2*>(stats), addend, dz,
                                            dgamma, dbeta, ln_slot(), T, H, st, &job);
-    if (rc == HANAYO_OK) ln_jobs.push_back(job);
+    if (rc == HANAYO_OK) ln_jobs.push_back(job), ++slot;
     return rc;
   };
   const void* dy_blk = dy;
@@ -399,7 +410,9 @@ int chunk_backward(const Shape& sh, const void* weights, float* grads, const voi
       // dx = da + dqkv Wqkv^T
       TRY(linear_bwd_input(sh, ws + WL.d_qkv, p.w[P_WQKV], dx_blk, H, 3 * H, k::EPI_ADD, ws + WL.d_h2, st));
     }
-    TRY(k::gemm_group(sh.dtype, dw, 4, st));
+    bool taken;
+    TRY(k::gemm_group(sh.dtype, dw, 4, st, ln_jobs.data() + ln_jobs.size() - 2, 2, &taken));
+    if (taken) ln_jobs.resize(ln_jobs.size() - 2);
     dy_blk = dx_blk;
   }
   return k::finalize_group(ln_jobs.data(), (int)ln_jobs.size(), st);

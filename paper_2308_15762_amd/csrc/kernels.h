@@ -40,9 +40,9 @@ int ln_forward(int dtype, const void* x, const void* gamma, const void* beta, vo
 int ln_backward(int dtype, const void* dout, const void* x, const void* gamma, const float2* stats, const void* addend,
                 void* dz, float* dgamma, float* dbeta, float* partial, int T, int H, hipStream_t stream);
 // The same with the last step left to the caller: dz is written, the gamma/beta sums stay as partial rows in
-// `partial` (kLnPartialRows * 2H floats, untouched until finalize_group has run) and *job says how to add them up.
-// finalize_group runs any number of such jobs, eight to a launch: one launch for all the LayerNorms of a chunk's
-// backward pass instead of one each.
+// `partial` (kLnPartialRows * 2H floats, untouched until the job has run) and *job says how to add them up.
+// gemm_group takes such jobs along in a launch of weight gradients; finalize_group runs any number of them, eight to a
+// launch.
 constexpr int kMaxFinalizeJobs = 8;
 struct FinalizeJob {
   const float* partial;  // [rows][ld]
@@ -113,7 +113,11 @@ __host__ __device__ inline int split_plan(int live, int tiles_n, int K, int grid
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream);
 // Up to 4 independent problems of one layout and epilogue; one launch where the tiled kernels allow
 // it (small problems then fill the chip together), otherwise one after the other.
-int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream);
+// `jobs` (at most kMaxJobs): partial rows that the launch may add up besides, in workgroups of their own; *taken says whether
+// it has, else finalize_group is left to the caller.  The sums are the same bits either way.
+constexpr int kMaxJobs = 2;
+int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream, const FinalizeJob* jobs = nullptr, int n_jobs = 0,
+               bool* taken = nullptr);
 
 // ---- attention ------------------------------------------------------------------
 // qkv is [b*s][3H] (Q | K | V, head j in columns j*d..), ctx [b*s][H], lse [b][heads][s].
@@ -142,11 +146,13 @@ bool gemm_dma_config_exists(int config);
 bool gemm_dma_supported(const GemmArgs& g, int config);
 void gemm_dma_tile(int config, int& bm, int& bn);
 int gemm_dma(const GemmArgs& g, int config, hipStream_t stream);
-int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream);
+int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream, const FinalizeJob* jobs = nullptr,
+                   int n_jobs = 0);
 // Tiles of edge x edge (64 or 32) whose contraction is split over the wavefronts of a workgroup: few tiles, ragged
 // extents, fp32.  Up to 4 problems of one layout and epilogue per launch; column sums are folded in.
 bool gemm_wave_supported(int dtype, const GemmArgs& g);
-int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream);
+int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream, const FinalizeJob* jobs = nullptr,
+                    int n_jobs = 0);
 // 7, 9, 10, 11 = force that direct-to-LDS configuration where it applies; 0 / 1 = the wavefront-split kernel with
 // 64 x 64 / 32 x 32 tiles where it applies; anything else = automatic choice
 void set_gemm_config(int config);

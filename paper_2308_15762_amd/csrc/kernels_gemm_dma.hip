@@ -24,6 +24,7 @@
 
 #include "device_util.h"
 #include "epilogue.h"
+#include "finalize.h"
 #include "kernels.h"
 
 namespace hanayo {
@@ -58,6 +59,8 @@ struct DmaGemmGroup {
   DmaGemm prob[kMaxGroup];
   int first[kMaxGroup + 1];
   int count;
+  FinalizeJob job[kMaxJobs];  // the workgroups behind the tiles: job_blocks of each of n_jobs jobs
+  int n_jobs, job_blocks;
 };
 
 // GELU in the epilogues: Phi (forward) and GELU' (input gradient of FC2) over [-8, 8) as kGeluN intervals of 1 / 128, each the
@@ -613,6 +616,12 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
 }
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool EDGE>
 __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_group_kernel(DmaGemmGroup grp) {
+  if ((int)blockIdx.x >= grp.first[kMaxGroup]) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int at = (int)blockIdx.x - grp.first[kMaxGroup], second = at >= grp.job_blocks;
+    finalize_columns<WGM * WGN * 64>(grp.job[second], at - second * grp.job_blocks, smem);
+    return;
+  }
   int gi = 0;
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
@@ -636,7 +645,7 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
     tiles += (long)((grp.prob[i].N + BN - 1) / BN) * ((grp.prob[i].M + BM - 1) / BM);
     if (grp.prob[i].live_dim == LIVE_M_SPLIT && tiles < kSplitGrid) tiles = kSplitGrid;
   }
-  if (tiles > 0x7fffffffL) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: too many tiles");
+  if (tiles > 0x7fff0000L) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: too many tiles");
   // Rows counted on the device: of the workgroups that all M rows would need, those past the count have nothing to do, but
   // each waits for a CU with room for its LDS (460 of 4096 rows x 30592 columns, 1680 of 1920 workgroups idle: 50 us; 31
   // for a launch of 460 rows).  Alone on the chip, as many workgroups as fit at once take the tiles in turn; next to other
@@ -646,10 +655,17 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
     if (tiles > fit) tiles = fit;
   }
   for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
-  const dim3 grid((unsigned)tiles), block(NW * 64);
+  const dim3 block(NW * 64);
   if constexpr (EPI == EPI_ACCUM_F32) {
+    grp.job_blocks = 0;
+    for (int i = 0; i < grp.n_jobs; ++i) {
+      const int blocks = finalize_blocks(grp.job[i], finalize_cols<NW * 64>());
+      if (blocks > grp.job_blocks) grp.job_blocks = blocks;
+    }
+    const dim3 grid((unsigned)(tiles + (long)grp.n_jobs * grp.job_blocks));
     launch_kernel((gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, EDGE>), grid, block, lds, stream, grp);
   } else {
+    const dim3 grid((unsigned)tiles);
     const DmaGemm& p = grp.prob[0];
     launch_kernel((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>), grid, block, lds, stream, p.A, p.B, (void*)p.C,
                        p.bias, p.M, p.N, p.K, p.lda, p.ldb, p.ldc | p.live_dim << kLdcBits, p.aux, p.aux_out, p.live);
@@ -721,11 +737,14 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
 }
 
 // The problems of a group share layout and epilogue (those of gs[0]); each must pass gemm_dma_supported.
-int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream) {
+int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
+  if (n_jobs < 0 || n_jobs > kMaxJobs || (n_jobs && gs[0].epi != EPI_ACCUM_F32)) return set_error(HANAYO_EINVAL, "gemm_dma: %d jobs", n_jobs);
   if (count < 1 || count > kMaxGroup) return set_error(HANAYO_EINVAL, "gemm_dma: group of %d", count);
   if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: only weight gradients in groups");
   DmaGemmGroup grp{};
   grp.count = count;
+  grp.n_jobs = n_jobs;
+  for (int i = 0; i < n_jobs; ++i) grp.job[i] = jobs[i];
   bool edge = false;
   for (int i = 0; i < count; ++i) {
     const GemmArgs& g = gs[i];

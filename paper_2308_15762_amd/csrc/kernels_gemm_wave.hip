@@ -27,6 +27,7 @@
 
 #include "device_util.h"
 #include "epilogue.h"
+#include "finalize.h"
 #include "kernels.h"
 
 namespace hanayo {
@@ -60,6 +61,8 @@ struct WaveGemmGroup {
   WaveGemm<T> prob[kMaxGroup];
   int first[kMaxGroup + 1];  // workgroups first[i] .. first[i + 1] - 1 are the tiles of problem i
   int count;
+  FinalizeJob job[kMaxJobs];  // the workgroups behind the tiles: job_blocks of each job
+  int job_blocks;
 };
 
 // VEC = elements of a 16-byte vector, BK = elements of a K tile (4 MFMA steps), Frag = what a lane feeds per step:
@@ -446,6 +449,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(const T* A, const T*
 }
 template <typename T, int BM, int BN, int NST>
 __global__ __launch_bounds__(NW * 64) void gemm_wave_group_kernel(WaveGemmGroup<T> grp) {
+  if ((int)blockIdx.x >= grp.first[kMaxGroup]) {
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const int at = (int)blockIdx.x - grp.first[kMaxGroup], second = at >= grp.job_blocks;
+    finalize_columns<NW * 64>(grp.job[second], at - second * grp.job_blocks, smem);
+    return;
+  }
   int gi = 0;
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
@@ -454,42 +463,42 @@ __global__ __launch_bounds__(NW * 64) void gemm_wave_group_kernel(WaveGemmGroup<
 }
 
 template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
-int launch(WaveGemmGroup<T>& grp, unsigned tiles, hipStream_t stream) {
+int launch(WaveGemmGroup<T>& grp, unsigned workgroups, hipStream_t stream) {
   constexpr size_t lds = wave_lds_bytes<BM, BN>(NST);
   static thread_local uint64_t raised = 0;
   if constexpr (EPI == EPI_ACCUM_F32) {
     auto kern = gemm_wave_group_kernel<T, BM, BN, NST>;
     if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
-    launch_kernel(kern, dim3(tiles), dim3(NW * 64), lds, stream, grp);
+    launch_kernel(kern, dim3(workgroups), dim3(NW * 64), lds, stream, grp);
   } else {
     auto kern = gemm_wave_kernel<T, BM, BN, NST, A_T, B_T, EPI>;
     if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
     const WaveGemm<T>& p = grp.prob[0];
-    launch_kernel(kern, dim3(tiles), dim3(NW * 64), lds, stream, p.A, p.B, p.C, p.bias, p.M, p.N, p.K, p.lda, p.ldb,
+    launch_kernel(kern, dim3(workgroups), dim3(NW * 64), lds, stream, p.A, p.B, p.C, p.bias, p.M, p.N, p.K, p.lda, p.ldb,
                        p.ldc | p.live_dim << kLdcBits, p.aux, p.aux_out, p.live);
   }
   return check_launch("gemm_wave");
 }
 
 template <typename T, int BM, int BN, int NST>
-int launch_layout(const GemmArgs& g, WaveGemmGroup<T>& grp, unsigned tiles, hipStream_t stream) {
+int launch_layout(const GemmArgs& g, WaveGemmGroup<T>& grp, unsigned workgroups, hipStream_t stream) {
   if (!g.a_t && g.b_t) {
     switch (g.epi) {
-      case EPI_NONE: return launch<T, BM, BN, NST, false, true, EPI_NONE>(grp, tiles, stream);
-      case EPI_BIAS: return launch<T, BM, BN, NST, false, true, EPI_BIAS>(grp, tiles, stream);
-      case EPI_BIAS_GELU: return launch<T, BM, BN, NST, false, true, EPI_BIAS_GELU>(grp, tiles, stream);
-      case EPI_BIAS_RES: return launch<T, BM, BN, NST, false, true, EPI_BIAS_RES>(grp, tiles, stream);
+      case EPI_NONE: return launch<T, BM, BN, NST, false, true, EPI_NONE>(grp, workgroups, stream);
+      case EPI_BIAS: return launch<T, BM, BN, NST, false, true, EPI_BIAS>(grp, workgroups, stream);
+      case EPI_BIAS_GELU: return launch<T, BM, BN, NST, false, true, EPI_BIAS_GELU>(grp, workgroups, stream);
+      case EPI_BIAS_RES: return launch<T, BM, BN, NST, false, true, EPI_BIAS_RES>(grp, workgroups, stream);
       default: break;
     }
   } else if (!g.a_t && !g.b_t) {
     switch (g.epi) {
-      case EPI_NONE: return launch<T, BM, BN, NST, false, false, EPI_NONE>(grp, tiles, stream);
-      case EPI_MUL_DGELU: return launch<T, BM, BN, NST, false, false, EPI_MUL_DGELU>(grp, tiles, stream);
-      case EPI_ADD: return launch<T, BM, BN, NST, false, false, EPI_ADD>(grp, tiles, stream);
+      case EPI_NONE: return launch<T, BM, BN, NST, false, false, EPI_NONE>(grp, workgroups, stream);
+      case EPI_MUL_DGELU: return launch<T, BM, BN, NST, false, false, EPI_MUL_DGELU>(grp, workgroups, stream);
+      case EPI_ADD: return launch<T, BM, BN, NST, false, false, EPI_ADD>(grp, workgroups, stream);
       default: break;
     }
   } else if (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32) {
-    return launch<T, BM, BN, NST, true, true, EPI_ACCUM_F32>(grp, tiles, stream);
+    return launch<T, BM, BN, NST, true, true, EPI_ACCUM_F32>(grp, workgroups, stream);
   }
   return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: layout/epilogue combination not built");
 }
@@ -501,7 +510,7 @@ long tiles_of(const GemmArgs* gs, int count, int edge) {
 }
 
 template <typename T>
-int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream) {
+int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
   WaveGemmGroup<T> grp{};
   grp.count = count;
   long tiles = 0;
@@ -517,10 +526,16 @@ int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream) {
     tiles += tiles_of(&g, 1, edge);
   }
   for (int i = count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
-  if (tiles > 0x7fffffffL) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: too many tiles");
-  if (edge == 32) return launch_layout<T, 32, 32, 2>(gs[0], grp, (unsigned)tiles, stream);
-  return tiles > 256 ? launch_layout<T, 64, 64, 1>(gs[0], grp, (unsigned)tiles, stream)
-                     : launch_layout<T, 64, 64, 2>(gs[0], grp, (unsigned)tiles, stream);
+  if (tiles > 0x7fff0000L) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: too many tiles");
+  for (int i = 0; i < n_jobs; ++i) {
+    grp.job[i] = jobs[i];
+    const int blocks = finalize_blocks(jobs[i], finalize_cols<NW * 64>());
+    if (blocks > grp.job_blocks) grp.job_blocks = blocks;
+  }
+  const unsigned workgroups = (unsigned)(tiles + (long)n_jobs * grp.job_blocks);
+  if (edge == 32) return launch_layout<T, 32, 32, 2>(gs[0], grp, workgroups, stream);
+  return tiles > 256 ? launch_layout<T, 64, 64, 1>(gs[0], grp, workgroups, stream)
+                     : launch_layout<T, 64, 64, 2>(gs[0], grp, workgroups, stream);
 }
 
 }  // namespace
@@ -538,13 +553,14 @@ bool gemm_wave_supported(int dtype, const GemmArgs& g) {
          g.ldb % vec == 0 && g.ldc % 4 == 0 && g.ldc < 1 << kLdcBits && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
 }
 
-int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream) {
+int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
+  if (n_jobs < 0 || n_jobs > kMaxJobs || (n_jobs && gs[0].epi != EPI_ACCUM_F32)) return set_error(HANAYO_EINVAL, "gemm_wave: %d jobs", n_jobs);
   if (count < 1 || count > kMaxGroup || (edge != 32 && edge != 64)) return set_error(HANAYO_EINVAL, "gemm_wave: group of %d", count);
   for (int i = 0; i < count; ++i)
     if (!gemm_wave_supported(dtype, gs[i]) || gs[i].a_t != gs[0].a_t || gs[i].b_t != gs[0].b_t || gs[i].epi != gs[0].epi)
       return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: shape not supported");
   if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: only weight gradients in groups");
-  return dtype == HANAYO_BF16 ? group_t<bf16>(gs, count, edge, stream) : group_t<float>(gs, count, edge, stream);
+  return dtype == HANAYO_BF16 ? group_t<bf16>(gs, count, edge, stream, jobs, n_jobs) : group_t<float>(gs, count, edge, stream, jobs, n_jobs);
 }
 
 }  // namespace k
