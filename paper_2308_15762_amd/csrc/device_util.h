@@ -51,16 +51,41 @@ __device__ __forceinline__ float ld(const bf16* p) { return (float)*p; }
 __device__ __forceinline__ void st(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st(bf16* p, float v) { *p = (bf16)v; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// Butterfly reductions over lanes l ^ 32, l ^ 16, ... l ^ 1 without the LDS crossbar that __shfl_xor goes through (about 100
+// cycles a step): the swaps exchange halves and 16-lane rows between two registers, and inside a row a rotation by 8 is l ^ 8,
+// after which lanes that differ by 8 agree and a rotation by 4 is as good as l ^ 4, and so on.  The same additions in the same
+// tree: the bits of the shuffles.  All 64 lanes have to be active.
+template <typename Op>
+__device__ __forceinline__ float reduce_halves(float v, Op op) {  // over l and l ^ 32
+  const unsigned u = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return op(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+template <int N, typename Op>
+__device__ __forceinline__ float reduce_rotated(float v, Op op) {
+  const int u = (int)__float_as_uint(v);
+  return op(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(u, u, 0x120 + N, 0xf, 0xf, false)));  // row_ror:N
 }
+template <typename Op>
+__device__ __forceinline__ float reduce_half(float v, Op op) {  // over the 32 lanes of each half
+  const unsigned u = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  v = reduce_rotated<8>(v, op);
+  v = reduce_rotated<4>(v, op);
+  v = reduce_rotated<2>(v, op);
+  return reduce_rotated<1>(v, op);
+}
+struct AddOp {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct MaxOp {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+__device__ __forceinline__ float halves_sum(float v) { return reduce_halves(v, AddOp()); }
+__device__ __forceinline__ float halves_max(float v) { return reduce_halves(v, MaxOp()); }
+__device__ __forceinline__ float wave_sum(float v) { return reduce_half(reduce_halves(v, AddOp()), AddOp()); }
+__device__ __forceinline__ float wave_max(float v) { return reduce_half(reduce_halves(v, MaxOp()), MaxOp()); }
 
 // Workgroup -> output tile, XCD-aware.  The dispatcher hands consecutive workgroup ids to the chip's
 // 8 XCDs in turn, and each XCD has an L2 of its own, so workgroup w runs on XCD w % 8 as that XCD's

@@ -280,7 +280,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(ATTN_F32_PARAMS) 
     float mloc = sc[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, sc[r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    mloc = halves_max(mloc);
     const float m_new = fmaxf(m, mloc);  // finite: the first key of every tile walked is allowed for every row
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2), shift = -m_new * c2;
     float rs = 0.f;
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_f32_kernel(ATTN_F32_PARAMS) 
       sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, shift));
       rs += sc[r];
     }
-    rs += __shfl_xor(rs, 32, 64);
+    rs = halves_sum(rs);
     lsum = lsum * alpha + rs;
     m = m_new;
 #pragma unroll
@@ -356,7 +356,7 @@ __device__ __forceinline__ void bwd_dq(const AttnF32& p, float* smem, int qt, in
 #pragma unroll
       for (int e = 0; e < 4; ++e) delta += c[e] * cf.v[kk][e];
     }
-  delta += __shfl_xor(delta, 32, 64);
+  delta = halves_sum(delta);
 
   f32x16 dq[DT];
 #pragma unroll
@@ -451,7 +451,7 @@ __device__ __forceinline__ void bwd_dkv(const AttnF32& p, float* smem, int kt, i
 #pragma unroll
       for (int e = 0; e < 4; ++e) delta += c[e] * cf.v[kk][e];  // cf is zero past d
     }
-    delta += __shfl_xor(delta, 32, 64);
+    delta = halves_sum(delta);
     f32x16 dp = mul_rows<DP, FULL>(cf, vf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {

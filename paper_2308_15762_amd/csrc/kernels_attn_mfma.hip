@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(ATTN_PARAMS) {
         mloc = fmaxf(mloc, v);
       }
     }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    mloc = halves_max(mloc);
     const float m_new = fmaxf(m, mloc);  // finite: key 0 is allowed for every row and comes first
     const float alpha = exp2f(m - m_new);
     float rs = 0.f;
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(ATTN_PARAMS) {
         sc[c][r] = e;
         rs += e;
       }
-    rs += __shfl_xor(rs, 32, 64);
+    rs = halves_sum(rs);
     lsum = lsum * alpha + rs;
     m = m_new;
 #pragma unroll
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256) void attn_fwd_dma_kernel(ATTN_PARAMS) {
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, sc[c][r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    mloc = halves_max(mloc);
     const float m_new = fmaxf(m, mloc);  // finite: key 0 is allowed for every row and comes first
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2);
     const float shift = -m_new * c2;
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(256) void attn_fwd_dma_kernel(ATTN_PARAMS) {
         sc[c][r] = e;
         rs += e;
       }
-    rs += __shfl_xor(rs, 32, 64);
+    rs = halves_sum(rs);
     lsum = lsum * alpha + rs;
     m = m_new;
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {  // the running maximum moved for some row
@@ -545,7 +545,7 @@ __device__ __forceinline__ void attn_fwd_pipe_body(const AttnDev& p) {
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, cur[c][r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    mloc = halves_max(mloc);
     const float m_new = fmaxf(m, mloc);  // finite: key 0 is allowed for every row and comes first
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2);
     const float shift = -m_new * c2;
@@ -558,7 +558,7 @@ __device__ __forceinline__ void attn_fwd_pipe_body(const AttnDev& p) {
         cur[c][r] = e;
         rs += e;
       }
-    rs += __shfl_xor(rs, 32, 64);
+    rs = halves_sum(rs);
     lsum = lsum * alpha + rs;
     m = m_new;
     __builtin_amdgcn_sched_barrier(0);
@@ -800,7 +800,7 @@ __device__ __forceinline__ void attn_bwd_dq_dma_body(const AttnDev& p) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) my_delta += (float)cf[kk][e] * (float)of[e];
   }
-  my_delta += __shfl_xor(my_delta, 32, 64);
+  my_delta = halves_sum(my_delta);
   if (q < p.s && half == 0) p.delta[stat] = my_delta;
   f32x16 dq[DT];
 #pragma unroll
@@ -1073,7 +1073,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int e = 0; e < 8; ++e) my_delta += (float)cf[kk][e] * (float)of[e];
   }
-  my_delta += __shfl_xor(my_delta, 32, 64);
+  my_delta = halves_sum(my_delta);
   if (q < p.s && half == 0) p.delta[stat] = my_delta;
   f32x16 dq[DT];
 #pragma unroll

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_split_kernel(int pairs, int 
     float mloc = sc[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, sc[r]);
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    mloc = halves_max(mloc);
     const float m_new = fmaxf(m, mloc);  // finite: the first key of every tile walked is allowed for every row
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2), shift = -m_new * c2;
     float rs = 0.f;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_split_kernel(int pairs, int 
       sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, shift));
       rs += sc[r];
     }
-    rs += __shfl_xor(rs, 32, 64);
+    rs = halves_sum(rs);
     lsum = lsum * alpha + rs;
     m = m_new;
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {
@@ -240,7 +240,7 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
 #pragma unroll
     for (int e = 0; e < 8; ++e) delta += (float)cf[kk][e] * (float)of[e];
   }
-  delta += __shfl_xor(delta, 32, 64);
+  delta = halves_sum(delta);
   f32x16 dq[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dq[dt] = zero16();
@@ -349,7 +349,7 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
 #pragma unroll
       for (int e = 0; e < 8; ++e) delta += (float)cr[e] * (float)of[kk][e];
     }
-    delta += __shfl_xor(delta, 32, 64);
+    delta = halves_sum(delta);
     if (half == 0) dlt_s[lane] = delta;  // read back below by the same wavefront: LDS operations of one keep their order
     asm volatile("" ::: "memory");
     const bool need_mask = (p.causal && q0 < k0 + 31) || k0 + 31 >= len || q0 + 31 >= p.s;
