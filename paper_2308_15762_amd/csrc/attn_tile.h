@@ -26,25 +26,6 @@ __device__ __forceinline__ bf16x8 pack_half(const f32x16& a, int t) {
   return o;
 }
 
-// The maximum that an online softmax subtracts follows the row's running maximum only once that is 2^kLazyMax ahead: exponents
-// then stay below 2^kLazyMax, which sums and products in fp32 and probabilities in bf16 (relative rounding) take as well, and the
-// accumulators are rescaled in a tile or two of a row instead of in nearly every one: with 32 rows to a wavefront one of them
-// has a new maximum in most tiles.
-constexpr float kLazyMax = 8.f;
-__device__ __forceinline__ float lazy_max(float m, float tile_max, float c2) { return (tile_max - m) * c2 > kLazyMax ? tile_max : m; }
-
-// The fragment with its signs flipped.
-__device__ __forceinline__ bf16x8 negated(bf16x8 v) {
-  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-  union {
-    bf16x8 f;
-    u32x4 u;
-  } x;
-  x.f = v;
-  x.u ^= 0x80008000u;
-  return x.f;
-}
-
 struct AttnDev {
   const bf16* qkv;
   const int32_t* valid_len;

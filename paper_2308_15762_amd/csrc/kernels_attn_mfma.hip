@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) void attn_fwd_dma_kernel(ATTN_PARAMS) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, sc[c][r]);
     mloc = halves_max(mloc);
-    const float m_new = lazy_max(m, mloc, c2);  // finite: key 0 is allowed for every row and comes first
+    const float m_new = fmaxf(m, mloc);  // finite: key 0 is allowed for every row and comes first
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2);
     const float shift = -m_new * c2;
     float rs = 0.f;
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(256) void attn_fwd_dma_kernel(ATTN_PARAMS) {
     rs = halves_sum(rs);
     lsum = lsum * alpha + rs;
     m = m_new;
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {  // the subtracted maximum moved for some row
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {  // the running maximum moved for some row
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -546,7 +546,7 @@ __device__ __forceinline__ void attn_fwd_pipe_body(const AttnDev& p) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) mloc = fmaxf(mloc, cur[c][r]);
     mloc = halves_max(mloc);
-    const float m_new = lazy_max(m, mloc, c2);  // finite: key 0 is allowed for every row and comes first
+    const float m_new = fmaxf(m, mloc);  // finite: key 0 is allowed for every row and comes first
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2);
     const float shift = -m_new * c2;
     float rs = 0.f;
@@ -562,7 +562,7 @@ __device__ __forceinline__ void attn_fwd_pipe_body(const AttnDev& p) {
     lsum = lsum * alpha + rs;
     m = m_new;
     __builtin_amdgcn_sched_barrier(0);
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {  // the subtracted maximum moved for some row
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f)) {  // the running maximum moved for some row
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -627,18 +627,6 @@ __global__ __launch_bounds__(256) void attn_fwd_pipe_wide_kernel(ATTN_PARAMS) {
   attn_fwd_pipe_body<DP, NST, D>(p);
 }
 
-// A value per query for this lane's 16 rows of a 32-query tile, as an MFMA's accumulator takes them.
-__device__ __forceinline__ f32x16 row_values(const float* lds, int half) {
-  f32x16 v;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const f32x4 x = *reinterpret_cast<const f32x4*>(lds + 8 * g + 4 * half);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[4 * g + e] = x[e];
-  }
-  return v;
-}
-
 template <int DP, int NST, int D = DP>
 __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
   using Tile = SwTile<DP>;
@@ -682,7 +670,7 @@ __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
     kf[kk] = frag_global(base + H + (size_t)key * ld3, key < p.s, kk, lane, p.d);
-    vf[kk] = negated(frag_global(base + 2 * H + (size_t)key * ld3, key < p.s, kk, lane, p.d));
+    vf[kk] = frag_global(base + 2 * H + (size_t)key * ld3, key < p.s, kk, lane, p.d);
   }
   f32x16 dk[DT], dv[DT];
 #pragma unroll
@@ -702,30 +690,29 @@ __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       if (p.causal && q0 + 32 * c + 31 < kw0) continue;  // all these queries precede the wavefront's keys
-      f32x16 sacc = zero16(), dp = row_values(dlt_s + 32 * c, half);
+      f32x16 sacc = zero16(), dp = zero16();
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Qs, fo, 32 * c, kk), kf[kk], sacc, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Cs, fo, 32 * c, kk), vf[kk], dp, 0, 0, 0);
       }
-      if ((p.causal && q0 + 32 * c < kw0 + 31) || kw0 + 31 >= len || q0 + 32 * c + 31 >= p.s) {  // masked scores give P = 0
-        asm volatile("");  // kept a branch: as selects the masks would cost every tile
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int qq = q0 + 32 * c + acc_row(r, half);
-          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sacc[r] = -INFINITY;
-        }
-      }
-      // P = 2^(c2 s - lse log2e), dS = P (dP - delta), where dp is delta - dP; lse of this lane's 16 queries comes as 4-vectors
+      // P = 2^(c2 s - lse log2e), dS = P (dP - delta); lse and delta of this lane's 16 queries come as 4-vectors
+      const bool need_mask = (p.causal && q0 + 32 * c < kw0 + 31) || kw0 + 31 >= len || q0 + 32 * c + 31 >= p.s;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + 32 * c + 8 * g + 4 * half);
+        const int ql = 32 * c + 8 * g + 4 * half;
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + ql);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(dlt_s + ql);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = 4 * g + e;
-          const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -l4[e] * kLog2e));
+          float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -l4[e] * kLog2e));
+          if (need_mask) {
+            const int qq = q0 + ql + e;
+            if (!(qq < p.s && key < len && (!p.causal || key <= qq))) pr = 0.f;
+          }
           sacc[r] = pr;
-          dp[r] *= -pr;
+          dp[r] = pr * (dp[r] - d4[e]);
         }
       }
 #pragma unroll
@@ -815,11 +802,9 @@ __device__ __forceinline__ void attn_bwd_dq_dma_body(const AttnDev& p) {
   }
   my_delta = halves_sum(my_delta);
   if (q < p.s && half == 0) p.delta[stat] = my_delta;
-  f32x16 dq[DT], less_delta;  // dP - delta comes out of products that start from -delta
+  f32x16 dq[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dq[dt] = zero16();
-#pragma unroll
-  for (int r = 0; r < 16; ++r) less_delta[r] = -my_delta;
 
   for (int t = 0; t < nt; ++t) {
     wait_tiles<LOADS>(min(NST - 2, nt - 1 - t));
@@ -831,22 +816,22 @@ __device__ __forceinline__ void attn_bwd_dq_dma_body(const AttnDev& p) {
     const char* Vs = Ks + Tile::kBytes;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      f32x16 sacc = zero16(), dp = less_delta;
+      f32x16 sacc = zero16(), dp = zero16();
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Ks, fo, 32 * c, kk), qf[kk], sacc, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Vs, fo, 32 * c, kk), cf[kk], dp, 0, 0, 0);
       }
-      if ((p.causal && k0 + 32 * c + 31 > qw0) || k0 + 32 * c + 32 > len) {  // masked scores give P = 0
-        asm volatile("");  // kept a branch: as selects the masks would cost every tile
+      const bool need_mask = (p.causal && k0 + 32 * c + 31 > qw0) || k0 + 32 * c + 32 > len;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+      for (int r = 0; r < 16; ++r) {
+        float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -my_lse2));
+        if (need_mask) {
           const int key = k0 + 32 * c + acc_row(r, half);
-          if (!(key < len && (!p.causal || key <= q))) sacc[r] = -INFINITY;
+          if (!(key < len && (!p.causal || key <= q))) pr = 0.f;
         }
+        dp[r] = pr * (dp[r] - my_delta);
       }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -my_lse2));
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
         const bf16x8 dsf = pack_half(dp, tt);
@@ -885,8 +870,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // dK / dV, software-pipelined in half tiles of 32 queries like attn_bwd_dq_pipe_kernel: the score
 // MFMAs of the next half tile (and this half's dP MFMAs) share a block with the exponentials, dS and
-// the dV / dK MFMAs of this one.  What the VALU would do per score besides an exponential and two products is left to the
-// MFMAs: they start from lse and from delta, on -scale K and -V, and end in lse - scale S and delta - dP.
+// the dV / dK MFMAs of this one.  Arithmetic is that of attn_bwd_dkv_dma_kernel.
 template <int DP, int NST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_pipe_kernel(ATTN_PARAMS) {
   const AttnDev p = ATTN_BLOCK;
@@ -907,8 +891,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const size_t stat0 = ((size_t)n * p.heads + h) * p.s;
   const int len = seq_len(p, n);
   const int k0 = kt * 128, kw0 = k0 + 32 * wave, key = kw0 + (lane & 31);
-  static_assert(DP == 64, "1 / sqrt(64) is a power of two");
-  constexpr float kScale = 0.125f;
+  const float scale = rsqrtf((float)p.d), c2 = scale * kLog2e;
 
   const int q_begin = (p.causal && k0 < len) ? (k0 / BQ) * BQ : 0;
   const int q_end = k0 < len ? p.s : 0;  // a tile of masked keys gets zero gradients
@@ -933,9 +916,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
   for (int kk = 0; kk < KS; ++kk) {
     kf[kk] = frag_global(base + H + (size_t)key * ld3, key < p.s, kk, lane, p.d);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) kf[kk][e] = (bf16)((float)kf[kk][e] * -kScale);  // a power of two: exact
-    vf[kk] = negated(frag_global(base + 2 * H + (size_t)key * ld3, key < p.s, kk, lane, p.d));
+    vf[kk] = frag_global(base + 2 * H + (size_t)key * ld3, key < p.s, kk, lane, p.d);
   }
   f32x16 dk[DT], dv[DT];
 #pragma unroll
@@ -945,10 +926,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   if (nt == 0) goto store;  // uniform over the workgroup
   {
-    // lse - scale S of the 32 queries of half c of tile t
+    // S of the 32 queries of half c of tile t
     auto scores = [&](int t, int c, f32x16& sc) {
       const char* Qs = smem + (t % NST) * STAGE;
-      sc = row_values(reinterpret_cast<const float*>(Qs + 2 * Tile::kBytes) + 32 * c, half);
+      sc = zero16();
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk)
         sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Qs, fo, 32 * c, kk), kf[kk], sc, 0, 0, 0);
@@ -963,7 +944,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int qq = q0 + acc_row(r, half);
-          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sc[r] = INFINITY;
+          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sc[r] = -INFINITY;
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -973,17 +954,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
       const char* Qs = smem + (t % NST) * STAGE;
       const char* Cs = Qs + Tile::kBytes;
-      f32x16 dp = row_values(reinterpret_cast<const float*>(Cs + Tile::kBytes) + 64 + 32 * c, half);
+      const float* lse_s = reinterpret_cast<const float*>(Cs + Tile::kBytes);
+      const float* dlt_s = lse_s + 64;
+      f32x16 dp = zero16();
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk)
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Cs, fo, 32 * c, kk), vf[kk], dp, 0, 0, 0);
       if (NEXT) scores(tn, cn, sc_n);
-      // P = exp(scale s - lse), dS = P (dP - delta)
+      // P = 2^(c2 s - lse log2e), dS = P (dP - delta); lse and delta of this lane's 16 queries come as 4-vectors
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(sc[r] * -kLog2e);
-        sc[r] = pr;
-        dp[r] *= -pr;
+      for (int g = 0; g < 4; ++g) {
+        const int ql = 32 * c + 8 * g + 4 * half;
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + ql);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(dlt_s + ql);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = 4 * g + e;
+          const float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -l4[e] * kLog2e));
+          sc[r] = pr;
+          dp[r] = pr * (dp[r] - d4[e]);
+        }
       }
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
@@ -1025,7 +1015,7 @@ store:
         bf16x4 a, b;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          a[e] = (bf16)(dk[dt][4 * g + e] * kScale);
+          a[e] = (bf16)(dk[dt][4 * g + e] * scale);
           b[e] = (bf16)dv[dt][4 * g + e];
         }
         *reinterpret_cast<bf16x4*>(out + H + col) = a;
@@ -1085,18 +1075,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
   my_delta = halves_sum(my_delta);
   if (q < p.s && half == 0) p.delta[stat] = my_delta;
-  f32x16 dq[DT], less_delta;  // dP - delta comes out of products that start from -delta
+  f32x16 dq[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dq[dt] = zero16();
-#pragma unroll
-  for (int r = 0; r < 16; ++r) less_delta[r] = -my_delta;
 
   // S (sc) and dP (dp) of the 32 keys of half c of tile t
   auto products = [&](int t, int c, f32x16& sc, f32x16& dp) {
     const char* Ks = smem + (t % NST) * STAGE;
     const char* Vs = Ks + Tile::kBytes;
     sc = zero16();
-    dp = less_delta;
+    dp = zero16();
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Ks, fo, 32 * c, kk), qf[kk], sc, 0, 0, 0);
@@ -1118,7 +1106,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (NEXT) products(tn, cn, sc_n, dp_n);
     const char* Ks = smem + (t % NST) * STAGE;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dp[r] *= __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -my_lse2));
+    for (int r = 0; r < 16; ++r) {
+      const float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -my_lse2));
+      dp[r] = pr * (dp[r] - my_delta);
+    }
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
       const bf16x8 dsf = pack_half(dp, tt);

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_split_kernel(int pairs, int 
 #pragma unroll
     for (int r = 1; r < 16; ++r) mloc = fmaxf(mloc, sc[r]);
     mloc = halves_max(mloc);
-    const float m_new = lazy_max(m, mloc, c2);  // finite: the first key of every tile walked is allowed for every row
+    const float m_new = fmaxf(m, mloc);  // finite: the first key of every tile walked is allowed for every row
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c2), shift = -m_new * c2;
     float rs = 0.f;
 #pragma unroll
