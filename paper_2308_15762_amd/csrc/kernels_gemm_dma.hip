@@ -63,52 +63,7 @@ struct DmaGemmGroup {
   int n_jobs, job_blocks;
 };
 
-// GELU in the epilogues: Phi (forward) and GELU' (input gradient of FC2) over [-8, 8) as kGeluN intervals of 1 / 128, each the
-// value at its left end and the rise to its right end; read with linear interpolation (error below 1e-5, far under bf16
-// rounding).  Computed by the compiler, Phi from one point to the next by its Taylor series about the left one (the term
-// after the last is below 1e-16), so that a workgroup only copies them into LDS, under the first K tiles.  Worked out with
-// erff by every workgroup between main loop and epilogue they cost 1.5 us of a tile: FC1 of 777 x 2560 x 640, 140 tiles,
-// 11.7 us a launch then and 10.1 now, 1527 x 3072 x 768 15.0 and 14.3; 1 us of 35 in 256 x 256 tiles, whose epilogue is
-// bound by what it stores.
-constexpr int kGeluN = 2048;
-struct GeluTable {
-  float at[kGeluN][2];
-};
-constexpr GeluTable gelu_table(bool grad) {
-  constexpr double h = 1.0 / 128.0;
-  // Phi and the density phi at k / 128, k = 0 .. 1024; phi(x + h) = phi(x) exp(-(x h + h h / 2))
-  double cdf[kGeluN / 2 + 1] = {0.5}, pdf[kGeluN / 2 + 1] = {0.39894228040143267794};
-  for (int k = 0; k < kGeluN / 2; ++k) {
-    const double x = k * h, e = -(x * h + 0.5 * h * h);
-    double term = 1.0, sum = 1.0;
-    for (int n = 1; n < 12; ++n) sum += term *= e / n;
-    pdf[k + 1] = pdf[k] * sum;
-    // derivatives of Phi: phi times the Hermite polynomials 1, -x, x^2 - 1, ...
-    double he0 = 1.0, he1 = x, step = h, rise = h, sign = -1.0;
-    for (int n = 2; n < 9; ++n) {
-      step *= h / n;
-      rise += sign * he1 * step;
-      sign = -sign;
-      const double he2 = x * he1 - (n - 1) * he0;
-      he0 = he1;
-      he1 = he2;
-    }
-    cdf[k + 1] = cdf[k] + pdf[k] * rise;
-  }
-  GeluTable t{};
-  float value[kGeluN + 1] = {};
-  for (int k = 0; k <= kGeluN; ++k) {
-    const int i = k - kGeluN / 2, a = i < 0 ? -i : i;
-    const double c = i < 0 ? 1.0 - cdf[a] : cdf[a];
-    value[k] = (float)(grad ? c + i * h * pdf[a] : c);
-  }
-  for (int k = 0; k < kGeluN; ++k) {
-    t.at[k][0] = value[k];
-    t.at[k][1] = value[k + 1] - value[k];
-  }
-  return t;
-}
-__device__ const GeluTable kPhiTable = gelu_table(false), kGeluGradTable = gelu_table(true);
+constexpr int kGeluN = 2048;  // intervals of the GELU epilogues' table
 
 constexpr int kBK = 64;       // K tile
 constexpr int KS = kBK / 32;  // MFMA steps per K tile
@@ -252,15 +207,30 @@ next_tile:
   const int nk = EDGE ? (p.K + kBK - 1) / kBK : p.K / kBK;
   const int k_tail = EDGE ? p.K - (nk - 1) * kBK : kBK;  // contraction elements of the last K tile
 
+  // GELU epilogues: Phi (forward) or GELU' (input gradient of FC2) comes from a table of kGeluN intervals over [-8, 8) behind
+  // the ring, made with erff and read with linear interpolation (error below 1e-5, far under bf16 rounding).  It is made
+  // while the first K tiles are on their way, each thread a run of neighbouring intervals, whose ends they share; between main
+  // loop and epilogue, every end twice, it held up each tile: FC1 / FC2's input gradient 777 x 2560 x 640 13.5 / 12.1 us a launch
+  // then and 12.5 / 11.0 now, 1527 x 3072 x 768 18.0 / 16.3 and 17.2 / 15.2, 4096 x 4096 x 1024 39.0 / 36.4 and 37.9 / 35.3.
   constexpr bool kGelu = EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU;
-  if constexpr (kGelu) {
-    const GeluTable* table = EPI == EPI_BIAS_GELU ? &kPhiTable : &kGeluGradTable;
-    constexpr int kParts = (int)sizeof(GeluTable) / 1024 / NW;
-    static_assert(kParts * NW * 1024 == (int)sizeof(GeluTable), "the table divides among the wavefronts");
+  float2* gelu_tab = reinterpret_cast<float2*>(smem + NSTAGE * STAGE_BYTES);
+  auto build_table = [&]() {
+    if constexpr (kGelu) {
+      constexpr int PER = kGeluN / (NW * 64);  // neighbouring intervals of a thread
+      auto value = [](int k) {
+        const float x = -8.f + (float)k * (1.f / 128.f);
+        return EPI == EPI_BIAS_GELU ? 0.5f * (1.0f + erff(x * 0.70710678118654752f)) : gelu_grad_f(x);
+      };
+      const int k0 = threadIdx.x * PER;
+      float left = value(k0);
 #pragma unroll
-    for (int i = 0; i < kParts; ++i)
-      dma16(table, (unsigned)((wave * kParts + i) * 1024 + lane * 16), lds0 + NSTAGE * STAGE_BYTES + (wave * kParts + i) * 1024);
-  }
+      for (int i = 0; i < PER; ++i) {
+        const float right = value(k0 + i + 1);
+        gelu_tab[k0 + i] = make_float2(left, right - left);
+        left = right;
+      }
+    }
+  };
 
   // Direct loads of one K tile.  The wavefront's i-th instruction for an operand covers the 64
   // slots q = wave * kPerWave + i of the tile; which rows that is goes into the lane's byte
@@ -442,14 +412,15 @@ next_tile:
         stay_inside_k(t == nk - 1);
         issue();
       }
-    if (kRest > 0 && nk >= NSTAGE) {
+    const bool filled = kRest > 0 && nk >= NSTAGE;
+    if (filled) {
       stay_inside_k(NSTAGE == nk);
 #pragma unroll
       for (int i = 0; i < kFirst; ++i) issue_part(i);
-      wait_vmcnt<(NSTAGE - 1) * LOADS - kRest>();
-    } else {
-      wait_tiles<LOADS>(min(NSTAGE - 1, nk - 1));
     }
+    build_table();
+    if (filled) wait_vmcnt<(NSTAGE - 1) * LOADS - kRest>();
+    else wait_tiles<LOADS>(min(NSTAGE - 1, nk - 1));
     if (nk == 1) clear_past_k();
     __syncthreads();
     colsum_tile(0);
@@ -494,9 +465,8 @@ next_tile:
   float* stage = reinterpret_cast<float*>(smem);
   constexpr int kBandRows = WGM * 32, kVecPerRow = BN / 8, kVecs = kBandRows * kVecPerRow;
   static_assert((size_t)kBandRows * EP * 4 <= (size_t)NSTAGE * STAGE_BYTES, "epilogue band must fit the load ring");
-  // GELU epilogues: 8 VALU operations and one LDS read per element instead of an exponential, a reciprocal and a
-  // polynomial, which at one workgroup per CU nothing else would overlap.
-  const float2* gelu_tab = reinterpret_cast<const float2*>(smem + NSTAGE * STAGE_BYTES);
+  // 8 VALU operations and one LDS read per element instead of an exponential, a reciprocal and a polynomial, which at one
+  // workgroup per CU nothing else would overlap.
   auto gelu_lookup = [&](float x) {
     const float t = fminf(fmaxf(fmaf(x, 128.f, 1024.f), 0.f), 2047.99f);
     const int k = (int)t;
@@ -633,7 +603,7 @@ template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int 
 int launch(DmaGemmGroup& grp, hipStream_t stream) {
   constexpr int NW = WGM * WGN;
   constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes) +
-                         (EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU ? sizeof(GeluTable) : 0);
+                         (EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU ? kGeluN * sizeof(float2) : 0);
   static thread_local uint64_t raised = 0;
   const void* kern;
   if constexpr (EPI == EPI_ACCUM_F32) kern = reinterpret_cast<const void*>(&gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, EDGE>);
