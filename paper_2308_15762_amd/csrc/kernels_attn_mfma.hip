@@ -627,6 +627,8 @@ __global__ __launch_bounds__(256) void attn_fwd_pipe_wide_kernel(ATTN_PARAMS) {
   attn_fwd_pipe_body<DP, NST, D>(p);
 }
 
+// us of the two backward launches with the masks as selects and as branches: d = 128, s = 2048, 32 pairs 236 and 188; d = 80, s = 1024,
+// 64 pairs 99 and 84; d = 96, 32 pairs 91 and 72; d = 32, 64 pairs 66 and 49.
 template <int DP, int NST, int D = DP>
 __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
   using Tile = SwTile<DP>;
@@ -696,8 +698,15 @@ __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Qs, fo, 32 * c, kk), kf[kk], sacc, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Cs, fo, 32 * c, kk), vf[kk], dp, 0, 0, 0);
       }
+      if ((p.causal && q0 + 32 * c < kw0 + 31) || kw0 + 31 >= len || q0 + 32 * c + 31 >= p.s) {  // masked scores give P = 0
+        asm volatile("");  // kept a branch: as selects the masks would cost every tile, half of the VALU's instructions
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int qq = q0 + 32 * c + acc_row(r, half);
+          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sacc[r] = -INFINITY;
+        }
+      }
       // P = 2^(c2 s - lse log2e), dS = P (dP - delta); lse and delta of this lane's 16 queries come as 4-vectors
-      const bool need_mask = (p.causal && q0 + 32 * c < kw0 + 31) || kw0 + 31 >= len || q0 + 32 * c + 31 >= p.s;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int ql = 32 * c + 8 * g + 4 * half;
@@ -706,11 +715,7 @@ __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = 4 * g + e;
-          float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -l4[e] * kLog2e));
-          if (need_mask) {
-            const int qq = q0 + ql + e;
-            if (!(qq < p.s && key < len && (!p.causal || key <= qq))) pr = 0.f;
-          }
+          const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -l4[e] * kLog2e));
           sacc[r] = pr;
           dp[r] = pr * (dp[r] - d4[e]);
         }
@@ -822,14 +827,17 @@ __device__ __forceinline__ void attn_bwd_dq_dma_body(const AttnDev& p) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Ks, fo, 32 * c, kk), qf[kk], sacc, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Vs, fo, 32 * c, kk), cf[kk], dp, 0, 0, 0);
       }
-      const bool need_mask = (p.causal && k0 + 32 * c + 31 > qw0) || k0 + 32 * c + 32 > len;
+      if ((p.causal && k0 + 32 * c + 31 > qw0) || k0 + 32 * c + 32 > len) {  // masked scores give P = 0
+        asm volatile("");  // kept a branch, as in the dK / dV kernel
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = k0 + 32 * c + acc_row(r, half);
+          if (!(key < len && (!p.causal || key <= q))) sacc[r] = -INFINITY;
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -my_lse2));
-        if (need_mask) {
-          const int key = k0 + 32 * c + acc_row(r, half);
-          if (!(key < len && (!p.causal || key <= q))) pr = 0.f;
-        }
+        const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -my_lse2));
         dp[r] = pr * (dp[r] - my_delta);
       }
 #pragma unroll

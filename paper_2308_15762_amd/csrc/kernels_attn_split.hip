@@ -29,8 +29,8 @@ constexpr int kTile32 = 32 * DP * 2;  // bytes of a 32-row tile
 template <int DP>
 constexpr int kPart = 32 * (DP + 4);  // floats of a wavefront's parked 32 x DP partial result
 template <int DP>
-constexpr size_t lds_bytes(int stage) {
-  const size_t ring = (size_t)NW * NST * stage, parts = (size_t)NW * kPart<DP> * 4 + NW * 32 * sizeof(float2);
+constexpr size_t lds_bytes(int stage, int stages = NST) {
+  const size_t ring = (size_t)NW * stages * stage, parts = (size_t)NW * kPart<DP> * 4 + NW * 32 * sizeof(float2);
   return ring > parts ? ring : parts;
 }
 
@@ -199,12 +199,19 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_split_kernel(int pairs, int 
 // of the query tile and its 32 deltas.
 template <int DP>
 constexpr int kBwdStage = 2 * kTile32<DP> + 512;
+// Stages of the backward kernel's rings.  One, and at most 256 registers, leave room for a second workgroup on a CU (for more
+// below d = 80), whose wavefronts cover the loads better than a second stage does: us with two and with one: d = 64, s = 256, 8
+// pairs 6.5 and 5.9; s = 509, 36 pairs, no mask 27.7 and 25.6; s = 1024, 8 heads 16.8 and 15.2; d = 32, s = 500, 8 heads 7.9 and 7.1; d =
+// 80, s = 1024, 4 heads 19.2 and 17.4; s = 777, 8 heads 19.2 and 18.7; s = 96, 16 pairs 6.5 and 6.4; d = 96, s = 384, 10 heads 12.1 and 11.6,
+// s = 700, 6 heads 17.4 and 18.0.  d = 128 does not fit 256 registers (s = 512, 8 heads 15.1 and 23.4).
+template <int D>
+constexpr int kBwdStages = D == 128 ? 2 : 1;
 
 // dQ of 32 query rows.
 template <int DP, int D>
 __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int h, int n) {
   using Tile = SwTile<DP>;
-  constexpr int KS = D / 16, DT = (D + 31) / 32, STAGE = kBwdStage<DP>, LOADS = 2 * Tile::kInstr32;
+  constexpr int KS = D / 16, DT = (D + 31) / 32, NB = kBwdStages<D>, STAGE = kBwdStage<DP>, LOADS = 2 * Tile::kInstr32;
   const unsigned lds0 = (unsigned)(unsigned long)((__attribute__((address_space(3))) char*)smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   typename Tile::Offsets fo;
@@ -215,16 +222,16 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
   const int kv_end = p.causal ? min(len, q0 + 32) : len;
   const int nt = (kv_end + 31) / 32, mine = nt > wave ? (nt - wave + NW - 1) / NW : 0;
   const float scale = rsqrtf((float)p.d), c2 = scale * kLog2e;
-  const unsigned ring = lds0 + wave * NST * STAGE;
-  const char* ring_ptr = smem + wave * NST * STAGE;
+  const unsigned ring = lds0 + wave * NB * STAGE;
+  const char* ring_ptr = smem + wave * NB * STAGE;
   auto issue = [&](int j) {
-    const unsigned st = ring + (unsigned)(j % NST) * STAGE;
+    const unsigned st = ring + (unsigned)(j % NB) * STAGE;
     const int k0 = (wave + j * NW) * 32;
     Tile::template issue32<D>(base + H, ld3, k0, p.s, st, lane);
     Tile::template issue32<D>(base + 2 * H, ld3, k0, p.s, st + kTile32<DP>, lane);
   };
 #pragma unroll
-  for (int j = 0; j < NST; ++j)
+  for (int j = 0; j < NB; ++j)
     if (j < mine) issue(j);
 
   const bool in = q < p.s;
@@ -245,9 +252,9 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) dq[dt] = zero16();
   for (int j = 0; j < mine; ++j) {
-    if (j + 1 < mine) wait_vmcnt<LOADS>();
+    if (NB > 1 && j + 1 < mine) wait_vmcnt<LOADS>();
     else wait_vmcnt<0>();
-    const char* Ks = ring_ptr + (j % NST) * STAGE;
+    const char* Ks = ring_ptr + (j % NB) * STAGE;
     const char* Vs = Ks + kTile32<DP>;
     const int k0 = (wave + j * NW) * 32;
     f32x16 sc = zero16(), dp = zero16();
@@ -256,14 +263,17 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
       sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Ks, fo, 0, kk), qf[kk], sc, 0, 0, 0);
       dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Vs, fo, 0, kk), cf[kk], dp, 0, 0, 0);
     }
-    const bool need_mask = (p.causal && k0 + 31 > q0) || k0 + 32 > len;
+    if ((p.causal && k0 + 31 > q0) || k0 + 32 > len) {  // masked scores give P = 0
+      asm volatile("");  // kept a branch: as selects the masks would cost every tile
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = k0 + acc_row(r, half);
+        if (!(key < len && (!p.causal || key <= q))) sc[r] = -INFINITY;
+      }
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -my_lse2));
-      if (need_mask) {
-        const int key = k0 + acc_row(r, half);
-        if (!(key < len && (!p.causal || key <= q))) pr = 0.f;
-      }
+      const float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -my_lse2));
       dp[r] = pr * (dp[r] - delta);
     }
 #pragma unroll
@@ -273,9 +283,9 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
       for (int dt = 0; dt < DT; ++dt)
         dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_cols(Ks, fo, 16 * tt, dt), dsf, dq[dt], 0, 0, 0);
     }
-    if (j + NST < mine) {
+    if (j + NB < mine) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      issue(j + NST);
+      issue(j + NB);
     }
   }
   __syncthreads();
@@ -289,7 +299,7 @@ __device__ __forceinline__ void bwd_dq(const AttnDev& p, char* smem, int qt, int
 template <int DP, int D>
 __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, int h, int n) {
   using Tile = SwTile<DP>;
-  constexpr int KS = D / 16, DT = (D + 31) / 32, STAGE = kBwdStage<DP>, LOADS = 2 * Tile::kInstr32 + 1;
+  constexpr int KS = D / 16, DT = (D + 31) / 32, NB = kBwdStages<D>, STAGE = kBwdStage<DP>, LOADS = 2 * Tile::kInstr32 + 1;
   const unsigned lds0 = (unsigned)(unsigned long)((__attribute__((address_space(3))) char*)smem);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), half = lane >> 5;
   typename Tile::Offsets fo;
@@ -304,17 +314,17 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
   const int t_begin = p.causal ? kt : 0;
   const int t_end = k0 < len ? (p.s + 31) / 32 : 0;  // a tile of masked keys gets zero gradients
   const int nt = t_end > t_begin ? t_end - t_begin : 0, mine = nt > wave ? (nt - wave + NW - 1) / NW : 0;
-  const unsigned ring = lds0 + wave * NST * STAGE;
-  char* ring_ptr = smem + wave * NST * STAGE;
+  const unsigned ring = lds0 + wave * NB * STAGE;
+  char* ring_ptr = smem + wave * NB * STAGE;
   auto issue = [&](int j) {
-    const unsigned st = ring + (unsigned)(j % NST) * STAGE;
+    const unsigned st = ring + (unsigned)(j % NB) * STAGE;
     const int q0 = (t_begin + wave + j * NW) * 32;
     Tile::template issue32<D>(base, ld3, q0, p.s, st, lane);
     Tile::template issue32<D>(dcb, H, q0, p.s, st + kTile32<DP>, lane);
     dma4(lse, (unsigned)(min(q0 + lane, p.s - 1) * 4), st + 2 * kTile32<DP>);
   };
 #pragma unroll
-  for (int j = 0; j < NST; ++j)
+  for (int j = 0; j < NB; ++j)
     if (j < mine) issue(j);
 
   bf16x8 kf[KS], vf[KS];
@@ -333,9 +343,9 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
     const int qr = min(q0 + (lane & 31), p.s - 1);
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) of[kk] = *reinterpret_cast<const bf16x8*>(ctb + (size_t)qr * H + kk * 16 + 8 * half);
-    if (j + 1 < mine) wait_vmcnt<LOADS + KS>();
+    if (NB > 1 && j + 1 < mine) wait_vmcnt<LOADS + KS>();
     else wait_vmcnt<KS>();
-    char* Qs = ring_ptr + (j % NST) * STAGE;
+    char* Qs = ring_ptr + (j % NB) * STAGE;
     const char* Cs = Qs + kTile32<DP>;
     const float* lse_s = reinterpret_cast<const float*>(Qs + 2 * kTile32<DP>);
     float* dlt_s = reinterpret_cast<float*>(Qs + 2 * kTile32<DP> + 256);
@@ -352,7 +362,14 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
     delta = halves_sum(delta);
     if (half == 0) dlt_s[lane] = delta;  // read back below by the same wavefront: LDS operations of one keep their order
     asm volatile("" ::: "memory");
-    const bool need_mask = (p.causal && q0 < k0 + 31) || k0 + 31 >= len || q0 + 31 >= p.s;
+    if ((p.causal && q0 < k0 + 31) || k0 + 31 >= len || q0 + 31 >= p.s) {  // masked scores give P = 0
+      asm volatile("");  // kept a branch: as selects the masks would cost every tile
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int qq = q0 + acc_row(r, half);
+        if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sc[r] = -INFINITY;
+      }
+    }
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int ql = 8 * g + 4 * half;
@@ -361,11 +378,7 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = 4 * g + e;
-        float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -l4[e] * kLog2e));
-        if (need_mask) {
-          const int qq = q0 + ql + e;
-          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) pr = 0.f;
-        }
+        const float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -l4[e] * kLog2e));
         sc[r] = pr;
         dp[r] = pr * (dp[r] - d4[e]);
       }
@@ -379,9 +392,9 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
         dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_cols(Qs, fo, 16 * tt, dt), dsf, dk[dt], 0, 0, 0);
       }
     }
-    if (j + NST < mine) {
+    if (j + NB < mine) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      issue(j + NST);
+      issue(j + NB);
     }
   }
   float* parts = reinterpret_cast<float*>(smem);
@@ -398,14 +411,25 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
 
 // dK / dV of every key tile, then dQ of every query tile: the longer work first.
 template <int DP, int D>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_split_kernel(int pairs, int tiles, ATTN_PARAMS) {
-  const AttnDev p = ATTN_BLOCK;
+__device__ __forceinline__ void bwd_split(const AttnDev& p, int pairs, int tiles) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int per_side = pairs * tiles, side = (int)blockIdx.x >= per_side;
   int t, h, n;
   place(p, (int)blockIdx.x - side * per_side, pairs, t, h, n);
   if (side) bwd_dq<DP, D>(p, smem, tiles - 1 - t, h, n);
   else bwd_dkv<DP, D>(p, smem, t, h, n);
+}
+template <int DP, int D>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_split_kernel(int pairs, int tiles, ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
+  bwd_split<DP, D>(p, pairs, tiles);
+}
+// The same in at most 256 registers, for two workgroups on a CU.
+template <int DP, int D>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_split2_kernel(int pairs, int tiles,
+                                                                                                          ATTN_PARAMS) {
+  const AttnDev p = ATTN_BLOCK;
+  bwd_split<DP, D>(p, pairs, tiles);
 }
 
 AttnDev to_dev(const AttnArgs& a) {
@@ -429,11 +453,14 @@ int forward_t(const AttnArgs& a, hipStream_t stream) {
 template <int DP, int D>
 int backward_t(const AttnArgs& a, hipStream_t stream) {
   static thread_local uint64_t raised = 0;
-  constexpr size_t lds = lds_bytes<DP>(kBwdStage<DP>);
-  if (const int rc = raise_lds(reinterpret_cast<const void*>(attn_bwd_split_kernel<DP, D>), lds, raised)) return rc;
+  constexpr size_t lds = lds_bytes<DP>(kBwdStage<DP>, kBwdStages<D>);
+  void (*kern)(int, int, ATTN_PARAMS);
+  if constexpr (kBwdStages<D> == 1) kern = attn_bwd_split2_kernel<DP, D>;
+  else kern = attn_bwd_split_kernel<DP, D>;
+  if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
   const AttnDev p = to_dev(a);
   const int pairs = a.heads * a.b, tiles = (a.s + 31) / 32;
-  launch_kernel((attn_bwd_split_kernel<DP, D>), dim3(2 * pairs * tiles), dim3(NW * 64), lds, stream, pairs, tiles, ATTN_ARGS(p));
+  launch_kernel(kern, dim3(2 * pairs * tiles), dim3(NW * 64), lds, stream, pairs, tiles, ATTN_ARGS(p));
   return check_launch("attn_bwd_split");
 }
 
