@@ -174,46 +174,59 @@ int choose_dma_config(const GemmArgs* gs, int count, double share, double* cost_
   return best;
 }
 
-// The same cost model for the wavefront-split kernel: the better tile edge and, in us, what it costs.  A round costs the K
-// tiles of its tiles plus an epilogue.  bf16: 0.178 us per 64 of K for 64 x 64 (four rounds of 4096 x 1024: 19 us at K =
-// 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix instructions (256 flop per clock and CU): a 32 x 32
+// The same cost model for the wavefront-split kernel: the better tile of the first `kinds` and, in us, what it costs.  A round
+// costs the K tiles of its tiles plus an epilogue.  bf16: 0.178 us per 64 of K for 64 x 64 (four rounds of 4096 x 1024: 19 us
+// at K = 1024, 54 at 4096), 0.075 for 32 x 32.  fp32 is bound by its matrix instructions (256 flop per clock and CU): a 32 x 32
 // tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
-int wave_edge(int dtype, const GemmArgs* gs, int count, double share, double* cost_us) {
-  static const struct { int edge; double per_k, epilogue, start; } kTiles[2][2] = {
-      {{64, 0.178 / 64, 1.0, 3.0}, {32, 0.075 / 64, 0.6, 2.5}}, {{64, 0.0154, 1.0, 3.0}, {32, 0.0044, 0.6, 2.5}}};
-  int best = 0;
-  for (const auto& t : kTiles[dtype == HANAYO_BF16 ? 0 : 1]) {
+//
+// In bf16 what a workgroup loads sets its pace, 44 bytes per clock and CU (16 KiB per 64 of K in 0.178 us): 96 x 64 tiles cost
+// 20 KiB, 32 x 64 tiles 12.  They are taken where the outputs then need one round of the CUs: us by the square tiles
+// and with all four, 1527 x 768 x 3072 19.3 and 15.3 (288 tiles of 64 x 64, 192 of 96 x 64), 700 x 1536 x 6144 35.3 and 25.1 (264 and
+// 192), 777 x 640 x 2560 11.4 and 7.8 (500 of 32 x 32, 250 of 32 x 64), 400 x 1024 x 4096 15.6 and 11.2, 1024 x 512 x 512 3.85 and
+// 3.64; at K = 256 two rounds of 32 x 32 are as fast (512 x 1024: 3.3 and 3.5 us).
+WaveTile wave_choice(int dtype, const GemmArgs* gs, int count, double share, int kinds, double* cost_us) {
+  struct Kind { WaveTile tile; double per_k, epilogue, start; };
+  static const Kind kBf16[] = {{WAVE_64x64, 0.178 / 64, 1.0, 3.0}, {WAVE_32x32, 0.075 / 64, 0.6, 2.5}, {WAVE_96x64, 0.2225 / 64, 1.3, 3.0},
+                               {WAVE_32x64, 0.13 / 64, 1.1, 2.7}};
+  static const Kind kFp32[] = {{WAVE_64x64, 0.0154, 1.0, 3.0}, {WAVE_32x32, 0.0044, 0.6, 2.5}};
+  const Kind* all = dtype == HANAYO_BF16 ? kBf16 : kFp32;
+  if (dtype != HANAYO_BF16 || gs[0].epi == EPI_ACCUM_F32) kinds = 2;
+  WaveTile best = WAVE_NONE;
+  for (int n = 0; n < kinds; ++n) {
+    const Kind& t = all[n];
+    int bm, bn;
+    wave_tile(t.tile, bm, bn);
     long tiles = 0;
     double k = 0.0;
     for (int i = 0; i < count; ++i) {
-      const long ti = (long)((gs[i].M + t.edge - 1) / t.edge) * ((gs[i].N + t.edge - 1) / t.edge);
+      const long ti = (long)((gs[i].M + bm - 1) / bm) * ((gs[i].N + bn - 1) / bn);
       tiles += ti;
       k += (double)ti * gs[i].K;
     }
     const double cost = t.start + rounds_of(tiles, share) * (k / tiles * t.per_k + t.epilogue);
-    if (!best || cost < *cost_us) best = t.edge, *cost_us = cost;
+    if (best == WAVE_NONE || cost < *cost_us) best = t.tile, *cost_us = cost;
   }
   return best;
 }
 
-// Tile edge of the wavefront-split kernel for these problems, 0 if it does not take them or a direct-to-LDS kernel is better.
-// That kernel adds a contraction in another order than the direct-to-LDS ones, which among themselves (and its two tile
-// edges among themselves) give the same bits.  An executor's results do not depend on its lanes, nor on what its plan
+// Tile of the wavefront-split kernel for these problems, WAVE_NONE if it does not take them or a direct-to-LDS kernel is better.
+// That kernel adds a contraction in another order than the direct-to-LDS ones, which among themselves (and its tiles
+// among themselves) give the same bits.  An executor's results do not depend on its lanes, nor on what its plan
 // expects of the other lanes, so between the two kinds the choice is made at one share for all of them.  Alone the split
 // kernel's many small tiles win up to K in the thousands; next to other lanes large tiles use the chip better.  us per
 // 16 x (forward, backward) of a block, share 0 / share 0.7, with 1, 2 and 4 lanes: H = 2048, T = 1024 8460 / 9248, 7996 /
 // 7507, 8343 / 7581; H = 1280, T = 1527 6445 / 6713, 5722 / 5373, 5994 / 5554; H = 512, T = 4096 4210 / 4202, 3274 / 3112,
 // 3404 / 3227.  Up to K = 1024 the time goes into start and epilogue, and nothing is won with lanes (H = 256, T = 2048:
 // 1597 / 1685, 1189 / 1201, 1241 / 1253).
-int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
+WaveTile choose_wave(int dtype, const GemmArgs* gs, int count) {
   if (dtype == HANAYO_BF16 && gemm_dma_config_exists(g_gemm_config)) {
     bool forced = true;  // a kernel that does not take these problems (or fp32) forces nothing
     for (int i = 0; i < count; ++i) forced = forced && gemm_dma_supported(gs[i], g_gemm_config);
-    if (forced) return 0;
+    if (forced) return WAVE_NONE;
   }
   for (int i = 0; i < count; ++i)
-    if (!gemm_wave_supported(dtype, gs[i])) return 0;
-  if (g_gemm_config == 0 || g_gemm_config == 1) return g_gemm_config == 0 ? 64 : 32;
+    if (!gemm_wave_supported(dtype, gs[i])) return WAVE_NONE;
+  if (g_gemm_config == 0 || g_gemm_config == 1) return g_gemm_config == 0 ? WAVE_64x64 : WAVE_32x32;
   double wave_cost, dma_cost;
   if (dtype == HANAYO_BF16) {
     double k = 0.0, outputs = 0.0;
@@ -223,10 +236,10 @@ int choose_wave_edge(int dtype, const GemmArgs* gs, int count) {
       k += n * gs[i].K;
     }
     const double share = g_in_lanes && k > 1024.0 * outputs ? 0.7 : 0.0;
-    wave_edge(dtype, gs, count, share, &wave_cost);
-    if (choose_dma_config(gs, count, share, &dma_cost) >= 0 && dma_cost <= wave_cost) return 0;
+    wave_choice(dtype, gs, count, share, 2, &wave_cost);  // by the square tiles, so that the line stays where it was
+    if (choose_dma_config(gs, count, share, &dma_cost) >= 0 && dma_cost <= wave_cost) return WAVE_NONE;
   }
-  return wave_edge(dtype, gs, count, g_gemm_sharing, &wave_cost);
+  return wave_choice(dtype, gs, count, g_gemm_sharing, 4, &wave_cost);
 }
 
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
@@ -238,7 +251,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
     const int rc = gemm(dtype, plain, stream);
     return rc ? rc : colsum_add(dtype, g.B, g.K, g.N, g.colsum, g.colsum_scratch, stream);
   }
-  if (const int edge = choose_wave_edge(dtype, &g, 1)) return gemm_wave_group(dtype, &g, 1, edge, stream);
+  if (const WaveTile tile = choose_wave(dtype, &g, 1)) return gemm_wave_group(dtype, &g, 1, tile, stream);
   if (dtype == HANAYO_BF16) {
     // the direct-to-LDS kernels fold the column sums into the GEMM
     double cost;
@@ -264,9 +277,9 @@ int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream, con
     alike = alike && g.a_t == gs[0].a_t && g.b_t == gs[0].b_t && g.epi == gs[0].epi;
   }
   if (alike) {
-    if (const int edge = choose_wave_edge(dtype, gs, count)) {
+    if (const WaveTile tile = choose_wave(dtype, gs, count)) {
       if (taken) *taken = true;
-      return gemm_wave_group(dtype, gs, count, edge, stream, jobs, taken ? n_jobs : 0);
+      return gemm_wave_group(dtype, gs, count, tile, stream, jobs, taken ? n_jobs : 0);
     }
   }
   if (alike && dtype == HANAYO_BF16) {

@@ -148,10 +148,16 @@ void gemm_dma_tile(int config, int& bm, int& bn);
 int gemm_dma(const GemmArgs& g, int config, hipStream_t stream);
 int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream, const FinalizeJob* jobs = nullptr,
                    int n_jobs = 0);
-// Tiles of edge x edge (64 or 32) whose contraction is split over the wavefronts of a workgroup: few tiles, ragged
-// extents, fp32.  Up to 4 problems of one layout and epilogue per launch; column sums are folded in.
+// Tiles whose contraction is split over the wavefronts of a workgroup: few tiles, ragged extents, fp32.  Up to 4 weight
+// gradients per launch; column sums are folded in.  The tiles among themselves give the same bits; WAVE_96x64 and WAVE_32x64
+// exist in bf16 and not for weight gradients.
+enum WaveTile { WAVE_NONE = 0, WAVE_64x64, WAVE_32x32, WAVE_96x64, WAVE_32x64 };
+inline void wave_tile(WaveTile t, int& bm, int& bn) {
+  bm = t == WAVE_64x64 ? 64 : t == WAVE_96x64 ? 96 : 32;
+  bn = t == WAVE_32x32 ? 32 : 64;
+}
 bool gemm_wave_supported(int dtype, const GemmArgs& g);
-int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream, const FinalizeJob* jobs = nullptr,
+int gemm_wave_group(int dtype, const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, const FinalizeJob* jobs = nullptr,
                     int n_jobs = 0);
 // 7, 9, 10, 11 = force that direct-to-LDS configuration where it applies; 0 / 1 = the wavefront-split kernel with
 // 64 x 64 / 32 x 32 tiles where it applies; anything else = automatic choice

@@ -498,19 +498,16 @@ int launch_layout(const GemmArgs& g, WaveGemmGroup<T>& grp, unsigned workgroups,
       default: break;
     }
   } else if (g.a_t && g.b_t && g.epi == EPI_ACCUM_F32) {
-    return launch<T, BM, BN, NST, true, true, EPI_ACCUM_F32>(grp, workgroups, stream);
+    if constexpr (BM == BN) return launch<T, BM, BN, NST, true, true, EPI_ACCUM_F32>(grp, workgroups, stream);
   }
   return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: layout/epilogue combination not built");
 }
 
-long tiles_of(const GemmArgs* gs, int count, int edge) {
-  long tiles = 0;
-  for (int i = 0; i < count; ++i) tiles += (long)((gs[i].M + edge - 1) / edge) * ((gs[i].N + edge - 1) / edge);
-  return tiles;
-}
 
 template <typename T>
-int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
+int group_t(const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
+  int bm, bn;
+  wave_tile(tile, bm, bn);
   WaveGemmGroup<T> grp{};
   grp.count = count;
   long tiles = 0;
@@ -523,7 +520,7 @@ int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream, const F
     p.colsum = g.epi == EPI_ACCUM_F32 ? g.colsum : nullptr;
     p.live = g.live; p.live_dim = g.live ? g.live_dim : LIVE_NONE;
     grp.first[i] = (int)tiles;
-    tiles += tiles_of(&g, 1, edge);
+    tiles += (long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
   }
   for (int i = count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
   if (tiles > 0x7fff0000L) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: too many tiles");
@@ -533,7 +530,13 @@ int group_t(const GemmArgs* gs, int count, int edge, hipStream_t stream, const F
     if (blocks > grp.job_blocks) grp.job_blocks = blocks;
   }
   const unsigned workgroups = (unsigned)(tiles + (long)n_jobs * grp.job_blocks);
-  if (edge == 32) return launch_layout<T, 32, 32, 2>(gs[0], grp, workgroups, stream);
+  if (tile == WAVE_32x32) return launch_layout<T, 32, 32, 2>(gs[0], grp, workgroups, stream);
+  if constexpr (sizeof(T) == 2) {
+    if (tile == WAVE_96x64)
+      return tiles > 256 ? launch_layout<T, 96, 64, 1>(gs[0], grp, workgroups, stream) : launch_layout<T, 96, 64, 2>(gs[0], grp, workgroups, stream);
+    if (tile == WAVE_32x64)
+      return tiles > 256 ? launch_layout<T, 32, 64, 1>(gs[0], grp, workgroups, stream) : launch_layout<T, 32, 64, 2>(gs[0], grp, workgroups, stream);
+  }
   return tiles > 256 ? launch_layout<T, 64, 64, 1>(gs[0], grp, workgroups, stream)
                      : launch_layout<T, 64, 64, 2>(gs[0], grp, workgroups, stream);
 }
@@ -553,14 +556,16 @@ bool gemm_wave_supported(int dtype, const GemmArgs& g) {
          g.ldb % vec == 0 && g.ldc % 4 == 0 && g.ldc < 1 << kLdcBits && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
 }
 
-int gemm_wave_group(int dtype, const GemmArgs* gs, int count, int edge, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
+int gemm_wave_group(int dtype, const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
   if (n_jobs < 0 || n_jobs > kMaxJobs || (n_jobs && gs[0].epi != EPI_ACCUM_F32)) return set_error(HANAYO_EINVAL, "gemm_wave: %d jobs", n_jobs);
-  if (count < 1 || count > kMaxGroup || (edge != 32 && edge != 64)) return set_error(HANAYO_EINVAL, "gemm_wave: group of %d", count);
+  if (count < 1 || count > kMaxGroup || tile == WAVE_NONE) return set_error(HANAYO_EINVAL, "gemm_wave: group of %d", count);
+  if (tile != WAVE_64x64 && tile != WAVE_32x32 && (dtype != HANAYO_BF16 || gs[0].epi == EPI_ACCUM_F32))
+    return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: tile not built");
   for (int i = 0; i < count; ++i)
     if (!gemm_wave_supported(dtype, gs[i]) || gs[i].a_t != gs[0].a_t || gs[i].b_t != gs[0].b_t || gs[i].epi != gs[0].epi)
       return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: shape not supported");
   if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: only weight gradients in groups");
-  return dtype == HANAYO_BF16 ? group_t<bf16>(gs, count, edge, stream, jobs, n_jobs) : group_t<float>(gs, count, edge, stream, jobs, n_jobs);
+  return dtype == HANAYO_BF16 ? group_t<bf16>(gs, count, tile, stream, jobs, n_jobs) : group_t<float>(gs, count, tile, stream, jobs, n_jobs);
 }
 
 }  // namespace k
