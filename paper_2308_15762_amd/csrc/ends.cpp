@@ -123,8 +123,7 @@ int head_loss(const Shape& sh, const hanayo_ends_desc* e, const void* lnf, const
     TRY(k::ln_forward(sh.dtype, y, gamma, gamma + (size_t)H * sh.esz, ws + L.hn, stats, nullptr, T, H, sh.eps, st));
     hn = ws + L.hn;
   }
-  TRY(k::list_labelled(labels, T, V, live, list, slot, st));
-  TRY(k::gather_rows(sh.dtype, hn, live, list, ws + L.hc, T, H, st));
+  TRY(k::gather_labelled(sh.dtype, labels, hn, T, V, H, ws + L.hc, live, list, slot, st));
   // logits[live][V] = hc[live][H] head[V][H]^T
   k::GemmArgs g{};
   g.A = ws + L.hc; g.B = head; g.C = ws + L.logits;
@@ -134,7 +133,6 @@ int head_loss(const Shape& sh, const hanayo_ends_desc* e, const void* lnf, const
   TRY(k::gemm(sh.dtype, g, st));
   // in place: logits -> gradient of loss_scale * loss w.r.t. the logits
   TRY(k::softmax_xent(sh.dtype, ws + L.logits, labels, live, list, loss_scale, nll, T, V, st));
-  TRY(k::loss_finish(nll, live, loss, st));
   // d_head[V][H] += dlogits[live][V]^T hc[live][H]
   k::GemmArgs gw{};
   gw.A = ws + L.logits; gw.B = ws + L.hc; gw.C = d_head;
@@ -155,7 +153,7 @@ int head_loss(const Shape& sh, const hanayo_ends_desc* e, const void* lnf, const
   } else {
     TRY(k::gemm(sh.dtype, gx, st));
   }
-  TRY(k::scatter_rows(sh.dtype, ws + L.product, live, slot, grid, V, e->final_ln ? static_cast<void*>(ws + L.d_hn) : dy, T, H, st));
+  TRY(k::scatter_rows(sh.dtype, ws + L.product, live, slot, grid, V, e->final_ln ? static_cast<void*>(ws + L.d_hn) : dy, T, H, nll, loss, st));
   if (e->final_ln)
     TRY(k::ln_backward(sh.dtype, ws + L.d_hn, y, lnf, stats, nullptr, dy, d_lnf, d_lnf + H,
                        reinterpret_cast<float*>(ws + L.partial), T, H, st));

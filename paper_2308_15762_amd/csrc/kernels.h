@@ -182,17 +182,14 @@ int embed_forward(int dtype, const void* wte, const void* wpe, const int32_t* to
 // d_wte[tokens[n][i]][:] += dx[n][i][:] (fixed order, no atomics); d_wpe[i][:] += sum_n dx[n][i][:].
 int embed_backward(int dtype, const int32_t* tokens, const void* dx, float* d_wte, float* d_wpe, int b, int s, int H,
                    int vocab, hipStream_t stream);
-// The rows whose label lies inside [0, vocab), in order: live[0] = their number n, list[0..n) = the rows, slot[row] =
-// the row's place in the list or -1.
-int list_labelled(const int32_t* labels, int rows, int vocab, int* live, int32_t* list, int32_t* slot, hipStream_t stream);
-// out[i][:] = in[list[i]][:] for i < live[0]
-int gather_rows(int dtype, const void* in, const int* live, const int32_t* list, void* out, int rows, int H, hipStream_t stream);
+// The rows whose label lies inside [0, vocab), in order: live[0] = their number n, list[0..n) = the rows, slot[row] = the row's
+// place in the list or -1; out[i][:] = in[list[i]][:].
+int gather_labelled(int dtype, const int32_t* labels, const void* in, int rows, int vocab, int H, void* out, int* live, int32_t* list,
+                    int32_t* slot, hipStream_t stream);
 // In place on logits [live][V], whose row i belongs to label labels[list[i]]: the gradient of loss_scale * (mean of the
 // rows' negative log-likelihoods); nll[i] = the row's negative log-likelihood.
 int softmax_xent(int dtype, void* logits, const int32_t* labels, const int* live, const int32_t* list, float loss_scale,
                  float* nll, int rows, int V, hipStream_t stream);
-// loss[0] = sum(nll[0..live)) / live (0 if live is 0).
-int loss_finish(const float* nll, const int* live, float* loss, hipStream_t stream);
 struct AdamArgs {
   void* params;   // storage type, updated
   float* master;  // bf16 storage: fp32 copy of the parameters, updated; ignored for fp32 storage
@@ -212,8 +209,9 @@ int adam(int dtype, const AdamArgs& a, hipStream_t stream);
 
 // out[row][:] = row slot[row] of the [live][H] product (zeros where slot is -1).  grid > 0: the product is the sum of the
 // fp32 slices of split_plan(live, tiles_n, K, grid), else it is stored whole in the storage type.
+// Also loss[0] = sum(nll[0..live)) / live (0 if live is 0).
 int scatter_rows(int dtype, const void* product, const int* live, const int32_t* slot, int grid, int K, void* out, int rows, int H,
-                 hipStream_t stream);
+                 const float* nll, float* loss, hipStream_t stream);
 
 // ---- misc ------------------------------------------------------------------------
 // max_workgroups > 0 caps the grid: a copy that uses only a few CUs and so runs at a chosen fraction of the
