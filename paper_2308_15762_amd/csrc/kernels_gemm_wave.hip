@@ -8,6 +8,10 @@
 // shorter than with an output split.  A 64 x 64 tile then costs one fragment read per MFMA, half of what four
 // wavefronts of 32 x 32 each would read.  The partial tiles are added in a fixed order through LDS at the end.
 //
+// What a workgroup loads sets its pace (44 bytes per clock and CU), so a launch is as long as the busiest CU's loads: tiles
+// of 96 x 64 and 32 x 64 (bf16; not for weight gradients, whose operands run the other way) fill the gaps between 64 x 64 and
+// 32 x 32 where these need a second round of the CUs (see wave_choice in chunk.cpp).
+//
 // Measured (us per launch, MI355X): bf16 512 x 256 x 1024: 11.6 in one 128 x 128 tile per 8 CUs, 4.1 here; bf16 weight
 // gradient 1024 x 1024 x 2048: 26.5 and 12.3; bf16 1527 x 768 x 3072, which only the ALU kernel took: 551 and 20.4;
 // fp32 256 x 256 x 1024: 206 on the ALU and 8.1, 2048 x 1024 x 1024: 103 TFLOP/s of the 157 that fp32 MFMAs issue at.

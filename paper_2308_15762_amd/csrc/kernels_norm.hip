@@ -244,8 +244,8 @@ __global__ __launch_bounds__(kFinalizeCols * kFinalizeGroups) void finalize_kern
   }
 }
 
-// Several finaliser jobs in one launch (blockIdx.y = job): the gamma/beta sums of all the LayerNorms of a
-// chunk's backward pass, whose partial rows wait in slots of their own until the pass is over.
+// Several finaliser jobs in one launch (blockIdx.y = job): the gamma/beta sums of the LayerNorms of a chunk's backward pass
+// that no weight-gradient launch has taken along (finalize.h).
 struct FinalizeJobs {
   FinalizeJob job[kMaxFinalizeJobs];
 };
