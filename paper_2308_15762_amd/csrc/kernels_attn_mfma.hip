@@ -627,8 +627,8 @@ __global__ __launch_bounds__(256) void attn_fwd_pipe_wide_kernel(ATTN_PARAMS) {
   attn_fwd_pipe_body<DP, NST, D>(p);
 }
 
-// us of the two backward launches with the masks as selects and as branches: d = 128, s = 2048, 32 pairs 236 and 188; d = 80, s = 1024,
-// 64 pairs 99 and 84; d = 96, 32 pairs 91 and 72; d = 32, 64 pairs 66 and 49.
+// us of the two backward launches with the masks as selects and as branches: d = 128, s = 2048, 32 pairs 236 and 186; d = 80, s = 1024,
+// 64 pairs 99 and 83; d = 96, 32 pairs 91 and 70; d = 32, 64 pairs 66 and 49.
 template <int DP, int NST, int D = DP>
 __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
   using Tile = SwTile<DP>;
@@ -698,27 +698,26 @@ __device__ __forceinline__ void attn_bwd_dkv_dma_body(const AttnDev& p) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Qs, fo, 32 * c, kk), kf[kk], sacc, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Cs, fo, 32 * c, kk), vf[kk], dp, 0, 0, 0);
       }
-      if ((p.causal && q0 + 32 * c < kw0 + 31) || kw0 + 31 >= len || q0 + 32 * c + 31 >= p.s) {  // masked scores give P = 0
-        asm volatile("");  // kept a branch: as selects the masks would cost every tile, half of the VALU's instructions
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int qq = q0 + 32 * c + acc_row(r, half);
-          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sacc[r] = -INFINITY;
-        }
-      }
       // P = 2^(c2 s - lse log2e), dS = P (dP - delta); lse and delta of this lane's 16 queries come as 4-vectors
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int ql = 32 * c + 8 * g + 4 * half;
-        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + ql);
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(dlt_s + ql);
+        const f32x4 l4 = *reinterpret_cast<const f32x4*>(lse_s + 32 * c + 8 * g + 4 * half);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = 4 * g + e;
-          const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -l4[e] * kLog2e));
-          sacc[r] = pr;
-          dp[r] = pr * (dp[r] - d4[e]);
+        for (int e = 0; e < 4; ++e) sacc[4 * g + e] = __builtin_amdgcn_exp2f(fmaf(sacc[4 * g + e], c2, -l4[e] * kLog2e));
+      }
+      if ((p.causal && q0 + 32 * c < kw0 + 31) || kw0 + 31 >= len || q0 + 32 * c + 31 >= p.s) {
+        asm volatile("");  // kept a branch: as selects the masks would cost every tile, half of the VALU's instructions
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {  // P and not the score: a query whose log-sum-exp is NaN must not reach keys behind the mask
+          const int qq = q0 + 32 * c + acc_row(r, half);
+          if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sacc[r] = 0.f;
         }
+      }
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(dlt_s + 32 * c + 8 * g + 4 * half);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dp[4 * g + e] = sacc[4 * g + e] * (dp[4 * g + e] - d4[e]);
       }
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
@@ -827,19 +826,18 @@ __device__ __forceinline__ void attn_bwd_dq_dma_body(const AttnDev& p) {
         sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Ks, fo, 32 * c, kk), qf[kk], sacc, 0, 0, 0);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Tile::frag_rows(Vs, fo, 32 * c, kk), cf[kk], dp, 0, 0, 0);
       }
-      if ((p.causal && k0 + 32 * c + 31 > qw0) || k0 + 32 * c + 32 > len) {  // masked scores give P = 0
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sacc[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -my_lse2));
+      if ((p.causal && k0 + 32 * c + 31 > qw0) || k0 + 32 * c + 32 > len) {
         asm volatile("");  // kept a branch, as in the dK / dV kernel
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = k0 + 32 * c + acc_row(r, half);
-          if (!(key < len && (!p.causal || key <= q))) sacc[r] = -INFINITY;
+          if (!(key < len && (!p.causal || key <= q))) sacc[r] = 0.f;
         }
       }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[r], c2, -my_lse2));
-        dp[r] = pr * (dp[r] - my_delta);
-      }
+      for (int r = 0; r < 16; ++r) dp[r] = sacc[r] * (dp[r] - my_delta);
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt) {
         const bf16x8 dsf = pack_half(dp, tt);

@@ -362,14 +362,7 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
     delta = halves_sum(delta);
     if (half == 0) dlt_s[lane] = delta;  // read back below by the same wavefront: LDS operations of one keep their order
     asm volatile("" ::: "memory");
-    if ((p.causal && q0 < k0 + 31) || k0 + 31 >= len || q0 + 31 >= p.s) {  // masked scores give P = 0
-      asm volatile("");  // kept a branch: as selects the masks would cost every tile
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int qq = q0 + acc_row(r, half);
-        if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sc[r] = -INFINITY;
-      }
-    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int ql = 8 * g + 4 * half;
@@ -381,6 +374,14 @@ __device__ __forceinline__ void bwd_dkv(const AttnDev& p, char* smem, int kt, in
         const float pr = __builtin_amdgcn_exp2f(fmaf(sc[r], c2, -l4[e] * kLog2e));
         sc[r] = pr;
         dp[r] = pr * (dp[r] - d4[e]);
+      }
+    }
+    if ((p.causal && q0 < k0 + 31) || k0 + 31 >= len || q0 + 31 >= p.s) {
+      asm volatile("");  // kept a branch: as selects the masks would cost every tile
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {  // P and dS themselves: a query whose log-sum-exp or delta is NaN must not reach keys behind the mask
+        const int qq = q0 + acc_row(r, half);
+        if (!(qq < p.s && key < len && (!p.causal || key <= qq))) sc[r] = dp[r] = 0.f;
       }
     }
 #pragma unroll
