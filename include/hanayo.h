@@ -604,6 +604,12 @@ int hanayo_op_copy(void* dst, const void* src, size_t bytes, void* hip_stream);
    and executor calls dispatch, and nothing for other threads. */
 int hanayo_op_gemm_config(int config);
 
+/* Which kernel hanayo_op_gemm would run these arguments on (operands on 16-byte boundaries, no column sums), under the calling
+   thread's setting and without touching the GPU: *kernel = a number of hanayo_op_gemm_config, 12 / 13 = the kernel whose
+   wavefronts split the contraction with 96x64 / 32x64 tiles, or 14 = the kernel without matrix instructions that takes whatever the
+   others do not.  Refuses what hanayo_op_gemm refuses. */
+int hanayo_op_gemm_kernel(int dtype, int M, int N, int K, int lda, int ldb, int ldc, int a_t, int b_t, int epilogue, int* kernel);
+
 /* out = LN(x) over the last dimension; stats[t] = (mean, rstd) as two floats;
    copy_out (may be NULL) receives a copy of x. */
 int hanayo_op_layernorm_forward(int dtype, const void* x, const void* gamma, const void* beta, void* out,

@@ -198,11 +198,14 @@ WaveTile wave_choice(int dtype, const GemmArgs* gs, int count, double share, int
     wave_tile(t.tile, bm, bn);
     long tiles = 0;
     double k = 0.0;
+    bool ok = true;
     for (int i = 0; i < count; ++i) {
+      ok = ok && gemm_wave_tile_fits(t.tile, dtype, gs[i]);
       const long ti = (long)((gs[i].M + bm - 1) / bm) * ((gs[i].N + bn - 1) / bn);
       tiles += ti;
       k += (double)ti * gs[i].K;
     }
+    if (!ok) continue;
     const double cost = t.start + rounds_of(tiles, share) * (k / tiles * t.per_k + t.epilogue);
     if (best == WAVE_NONE || cost < *cost_us) best = t.tile, *cost_us = cost;
   }
@@ -240,6 +243,19 @@ WaveTile choose_wave(int dtype, const GemmArgs* gs, int count) {
     if (choose_dma_config(gs, count, share, &dma_cost) >= 0 && dma_cost <= wave_cost) return WAVE_NONE;
   }
   return wave_choice(dtype, gs, count, g_gemm_sharing, 4, &wave_cost);
+}
+
+int gemm_kernel(int dtype, const GemmArgs& g) {
+  switch (choose_wave(dtype, &g, 1)) {
+    case WAVE_64x64: return 0;
+    case WAVE_32x32: return 1;
+    case WAVE_96x64: return 12;
+    case WAVE_32x64: return 13;
+    case WAVE_NONE: break;
+  }
+  double cost;
+  const int config = dtype == HANAYO_BF16 ? choose_dma_config(&g, 1, g_gemm_sharing, &cost) : -1;
+  return config >= 0 ? config : 14;
 }
 
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {

@@ -111,6 +111,8 @@ __host__ __device__ inline int split_plan(int live, int tiles_n, int K, int grid
   return (K + per - 1) / per;
 }
 int gemm(int dtype, const GemmArgs& g, hipStream_t stream);
+// The kernel that gemm would run this problem on, by the numbers of hanayo_op_gemm_kernel.
+int gemm_kernel(int dtype, const GemmArgs& g);
 // Up to 4 independent problems of one layout and epilogue; one launch where the tiled kernels allow
 // it (small problems then fill the chip together), otherwise one after the other.
 // `jobs` (at most kMaxJobs): partial rows that the launch may add up besides, in workgroups of their own; *taken says whether
@@ -157,6 +159,7 @@ inline void wave_tile(WaveTile t, int& bm, int& bn) {
   bn = t == WAVE_32x32 ? 32 : 64;
 }
 bool gemm_wave_supported(int dtype, const GemmArgs& g);
+bool gemm_wave_tile_fits(WaveTile t, int dtype, const GemmArgs& g);  // of a supported problem: lane offsets within 31 bits
 int gemm_wave_group(int dtype, const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, const FinalizeJob* jobs = nullptr,
                     int n_jobs = 0);
 // 7, 9, 10, 11 = force that direct-to-LDS configuration where it applies; 0 / 1 = the wavefront-split kernel with

@@ -560,13 +560,20 @@ bool gemm_wave_supported(int dtype, const GemmArgs& g) {
          g.ldb % vec == 0 && g.ldc % 4 == 0 && g.ldc < 1 << kLdcBits && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
 }
 
+// A lane's offset reaches over the tile's rows where they are contiguous along the contraction; 64 rows are always within bounds.
+bool gemm_wave_tile_fits(WaveTile t, int dtype, const GemmArgs& g) {
+  int bm, bn;
+  wave_tile(t, bm, bn);
+  return g.a_t || bm <= 64 || (long)bm * g.lda * (dtype == HANAYO_BF16 ? 2 : 4) < (1L << 31);
+}
+
 int gemm_wave_group(int dtype, const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
   if (n_jobs < 0 || n_jobs > kMaxJobs || (n_jobs && gs[0].epi != EPI_ACCUM_F32)) return set_error(HANAYO_EINVAL, "gemm_wave: %d jobs", n_jobs);
   if (count < 1 || count > kMaxGroup || tile == WAVE_NONE) return set_error(HANAYO_EINVAL, "gemm_wave: group of %d", count);
   if (tile != WAVE_64x64 && tile != WAVE_32x32 && (dtype != HANAYO_BF16 || gs[0].epi == EPI_ACCUM_F32))
     return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: tile not built");
   for (int i = 0; i < count; ++i)
-    if (!gemm_wave_supported(dtype, gs[i]) || gs[i].a_t != gs[0].a_t || gs[i].b_t != gs[0].b_t || gs[i].epi != gs[0].epi)
+    if (!gemm_wave_supported(dtype, gs[i]) || !gemm_wave_tile_fits(tile, dtype, gs[i]) || gs[i].a_t != gs[0].a_t || gs[i].b_t != gs[0].b_t || gs[i].epi != gs[0].epi)
       return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: shape not supported");
   if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: only weight gradients in groups");
   return dtype == HANAYO_BF16 ? group_t<bf16>(gs, count, tile, stream, jobs, n_jobs) : group_t<float>(gs, count, tile, stream, jobs, n_jobs);

@@ -71,6 +71,20 @@ int hanayo_op_gemm_config(int config) {
   return HANAYO_OK;
 }
 
+int hanayo_op_gemm_kernel(int dtype, int M, int N, int K, int lda, int ldb, int ldc, int a_t, int b_t, int epilogue, int* kernel) {
+  if (int rc = check_dtype(dtype)) return rc;
+  if (!kernel) return set_error(HANAYO_EINVAL, "op_gemm_kernel: NULL pointer");
+  const char any = 0;  // stands for the operands until the arguments have been checked
+  const hanayo_gemm_problem q = {&any, &any, const_cast<char*>(&any), &any, &any, const_cast<char*>(&any),
+                                 M, N, K, lda, ldb, ldc, nullptr, nullptr};
+  k::GemmArgs g;
+  if (int rc = fill_gemm(q, a_t, b_t, epilogue, g)) return rc;
+  g.A = g.B = g.bias = g.aux = nullptr;
+  g.C = g.aux_out = nullptr;
+  *kernel = k::gemm_kernel(dtype, g);
+  return HANAYO_OK;
+}
+
 int hanayo_op_layernorm_forward(int dtype, const void* x, const void* gamma, const void* beta, void* out, float* stats,
                                 void* copy_out, int rows, int hidden, float eps, void* hip_stream) {
   if (int rc = check_dtype(dtype)) return rc;

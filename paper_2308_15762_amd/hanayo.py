@@ -109,7 +109,7 @@ EXPORTS = ("hanayo_strerror", "hanayo_last_error", "hanayo_stage_rank", "hanayo_
            "hanayo_stash_bytes", "hanayo_workspace_bytes", "hanayo_act_bytes", "hanayo_chunk_forward",
            "hanayo_chunk_backward", "hanayo_stash_arena_bytes", "hanayo_stash_arena_bytes_input",
            "hanayo_recompute_scratch_bytes", "hanayo_executor_run", "hanayo_executor_plan", "hanayo_pipeline_run", "hanayo_replay", "hanayo_actions", "hanayo_replay_actions", "hanayo_pipeline_run_actions", "hanayo_device_info",
-           "hanayo_op_gemm", "hanayo_op_gemm_group", "hanayo_op_gemm_config", "hanayo_op_copy", "hanayo_op_layernorm_forward", "hanayo_op_layernorm_backward", "hanayo_op_layernorm_backward_static", "hanayo_op_colsum_add",
+           "hanayo_op_gemm", "hanayo_op_gemm_group", "hanayo_op_gemm_config", "hanayo_op_gemm_kernel", "hanayo_op_copy", "hanayo_op_layernorm_forward", "hanayo_op_layernorm_backward", "hanayo_op_layernorm_backward_static", "hanayo_op_colsum_add",
            "hanayo_op_attention_forward", "hanayo_op_attention_backward",
            "hanayo_embed_forward", "hanayo_embed_backward", "hanayo_head_workspace_bytes", "hanayo_head_loss",
            "hanayo_adam_step", "hanayo_chunk_adam_step", "hanayo_ends_workspace_bytes")
@@ -434,6 +434,13 @@ def hanayo_op_copy(dst, src, nbytes, stream=None):
 
 def hanayo_op_gemm_config(config):
     _check(_lib.hanayo_op_gemm_config(int(config)))
+
+
+def hanayo_op_gemm_kernel(dtype, M, N, K, lda, ldb, ldc, a_t, b_t, epilogue):
+    """The number of the kernel that hanayo_op_gemm would use (no GPU needed)."""
+    out = ctypes.c_int()
+    _check(_lib.hanayo_op_gemm_kernel(dtype, M, N, K, lda, ldb, ldc, int(a_t), int(b_t), epilogue, ctypes.byref(out)))
+    return out.value
 
 
 def hanayo_op_layernorm_forward(dtype, x, gamma, beta, out, stats, copy_out, rows, hidden, eps, stream=None):

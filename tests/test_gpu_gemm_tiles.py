@@ -36,3 +36,24 @@ def test_tiles_give_the_same_bits(layout, M, N, K):
             assert (got[0][0].float() - exact).norm() <= 3e-3 * exact.norm()   # bf16 storage: 2^-9 of every element
         for other in got[1:]:
             assert torch.equal(got[0][0], other[0]) and torch.equal(got[0][1], other[1]), epi
+
+
+def strided(rows, cols, ld, values):
+    """`values` in rows `ld` elements apart."""
+    room = torch.empty((rows - 1) * ld + cols, dtype=torch.bfloat16, device="cuda")
+    view = torch.as_strided(room, (rows, cols), (ld, 1))
+    view.copy_(values)
+    return room, view
+
+
+# the last stride whose 96 rows a lane's offset reaches, the first that it does not (64-row tiles take it), the last for 64 rows
+@pytest.mark.parametrize("lda", [(2 ** 31 - 1) // 192 // 8 * 8, (2 ** 31 - 1) // 192 // 8 * 8 + 8, (2 ** 31 - 1) // 128 // 8 * 8])
+def test_rows_far_apart(lda):
+    M, N, K = 200, 5000, 1024
+    g = torch.Generator(device="cuda").manual_seed(5)
+    draw = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
+    A, B, want, got = draw(M, K), draw(K, N), draw(M, N), draw(M, N)
+    wide, _ = strided(M, K, lda, A)
+    hn.hanayo_op_gemm(hn.BF16, A, B, want, M, N, K, K, N, N, False, True, hn.EPI_NONE)
+    hn.hanayo_op_gemm(hn.BF16, wide, B, got, M, N, K, lda, N, N, False, True, hn.EPI_NONE)
+    assert torch.equal(want, got)
