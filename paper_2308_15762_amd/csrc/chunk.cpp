@@ -180,10 +180,13 @@ int choose_dma_config(const GemmArgs* gs, int count, double share, double* cost_
 // tile costs a quarter of a 64 x 64 one and 15 % (more loads per flop).
 //
 // In bf16 what a workgroup loads sets its pace, 44 bytes per clock and CU (16 KiB per 64 of K in 0.178 us): 96 x 64 tiles cost
-// 20 KiB, 32 x 64 tiles 12.  They are taken where the outputs then need one round of the CUs: us by the square tiles
+// 20 KiB, 32 x 64 tiles 12.  They fill the gaps where the square tiles need one round more.  us by the square tiles
 // and with all four, 1527 x 768 x 3072 19.3 and 15.3 (288 tiles of 64 x 64, 192 of 96 x 64), 700 x 1536 x 6144 35.3 and 25.1 (264 and
 // 192), 777 x 640 x 2560 11.4 and 7.8 (500 of 32 x 32, 250 of 32 x 64), 400 x 1024 x 4096 15.6 and 11.2, 1024 x 512 x 512 3.85 and
-// 3.64; at K = 256 two rounds of 32 x 32 are as fast (512 x 1024: 3.3 and 3.5 us).
+// 3.64; at K = 256 two rounds of 32 x 32 are as fast (512 x 1024: 3.3 and 3.5 us).  A 96 x 64 workgroup parks 104 KiB of partial
+// tiles and so has a CU to itself: more than 256 of them, with nothing to cover a tile's start and end, are slower than the
+// square ones (1025 x 3632 x 1360, 627 tiles: 31.4 against 27.0).  Of 32 x 64 a CU holds three (32 x 30592 x 512, 478 tiles: 6.98
+// against 7.36).
 WaveTile wave_choice(int dtype, const GemmArgs* gs, int count, double share, int kinds, double* cost_us) {
   struct Kind { WaveTile tile; double per_k, epilogue, start; };
   static const Kind kBf16[] = {{WAVE_64x64, 0.178 / 64, 1.0, 3.0}, {WAVE_32x32, 0.075 / 64, 0.6, 2.5}, {WAVE_96x64, 0.2225 / 64, 1.3, 3.0},
@@ -205,7 +208,7 @@ WaveTile wave_choice(int dtype, const GemmArgs* gs, int count, double share, int
       tiles += ti;
       k += (double)ti * gs[i].K;
     }
-    if (!ok) continue;
+    if (!ok || (t.tile == WAVE_96x64 && tiles > 256)) continue;
     const double cost = t.start + rounds_of(tiles, share) * (k / tiles * t.per_k + t.epilogue);
     if (best == WAVE_NONE || cost < *cost_us) best = t.tile, *cost_us = cost;
   }

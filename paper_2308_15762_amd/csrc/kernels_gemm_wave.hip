@@ -10,7 +10,7 @@
 //
 // What a workgroup loads sets its pace (44 bytes per clock and CU), so a launch is as long as the busiest CU's loads: tiles
 // of 96 x 64 and 32 x 64 (bf16; not for weight gradients, whose operands run the other way) fill the gaps between 64 x 64 and
-// 32 x 32 where these need a second round of the CUs (see wave_choice in chunk.cpp).
+// 32 x 32 where these need one round of the CUs more (see wave_choice in chunk.cpp).
 //
 // Measured (us per launch, MI355X): bf16 512 x 256 x 1024: 11.6 in one 128 x 128 tile per 8 CUs, 4.1 here; bf16 weight
 // gradient 1024 x 1024 x 2048: 26.5 and 12.3; bf16 1527 x 768 x 3072, which only the ALU kernel took: 551 and 20.4;
@@ -536,8 +536,7 @@ int group_t(const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, co
   const unsigned workgroups = (unsigned)(tiles + (long)n_jobs * grp.job_blocks);
   if (tile == WAVE_32x32) return launch_layout<T, 32, 32, 2>(gs[0], grp, workgroups, stream);
   if constexpr (sizeof(T) == 2) {
-    if (tile == WAVE_96x64)
-      return tiles > 256 ? launch_layout<T, 96, 64, 1>(gs[0], grp, workgroups, stream) : launch_layout<T, 96, 64, 2>(gs[0], grp, workgroups, stream);
+    if (tile == WAVE_96x64) return launch_layout<T, 96, 64, 2>(gs[0], grp, workgroups, stream);  // one to a CU either way
     if (tile == WAVE_32x64)
       return tiles > 256 ? launch_layout<T, 32, 64, 1>(gs[0], grp, workgroups, stream) : launch_layout<T, 32, 64, 2>(gs[0], grp, workgroups, stream);
   }

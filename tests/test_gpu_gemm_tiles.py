@@ -11,11 +11,13 @@ pytestmark = pytest.mark.gpu
 LAYOUTS = {"fwd": ([hn.EPI_NONE, hn.EPI_BIAS, hn.EPI_BIAS_GELU, hn.EPI_BIAS_RES], True), "dx": ([hn.EPI_NONE, hn.EPI_MUL_DGELU, hn.EPI_ADD], False)}
 
 
-# 96 x 64: 192 tiles, whole and ragged, one row into the last tile, K below and past a K tile; 32 x 64: 250 tiles, N ending
-# inside a tile, 256 and 264 tiles of it; 64 and less: the square tiles
+# (test_host_gemm_choice.py holds which tile these go to.)  96 x 64: 192 tiles, whole and ragged, one row into the last tile, K below
+# and past a K tile, 256 tiles and one tile row more (square again); 32 x 64: 250 tiles, N ending inside a tile, 256, few rows, 478 (the
+# instance with one stage); 264 tiles of 32 x 64 would be 64 x 64; 64 and less: the square tiles
 @pytest.mark.parametrize("layout", list(LAYOUTS))
 @pytest.mark.parametrize("M, N, K", [(1536, 768, 1024), (1527, 768, 3072), (1441, 760, 2056), (700, 1536, 1608), (777, 640, 2560), (769, 632, 520),
-                                     (1024, 512, 2048), (33 * 32, 512, 1032), (96, 3840, 1288), (1, 5120, 1280), (31, 72, 264)])
+                                     (1024, 512, 2048), (33 * 32, 512, 1032), (96, 3840, 1288), (1, 5120, 1280), (31, 72, 264),
+                                     (1536, 1024, 1024), (1537, 1024, 1024), (1025, 3632, 1360), (128, 4096, 1544), (32, 30592, 512)])
 def test_tiles_give_the_same_bits(layout, M, N, K):
     epis, b_t = LAYOUTS[layout]
     g = torch.Generator(device="cuda").manual_seed(M + N + K)

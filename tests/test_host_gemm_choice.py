@@ -35,3 +35,16 @@ def test_lane_offsets_stay_within_31_bits(b_t):
     last = (2 ** 31 - 1) // (64 * 2) // 8 * 8
     assert choice(M, N, K, lda=last, b_t=b_t) in (WAVE_64x64, WAVE_32x32, WAVE_32x64)
     assert choice(M, N, K, lda=last + 8, b_t=b_t) not in (WAVE_64x64, WAVE_32x32, WAVE_32x64, WAVE_96x64)
+
+
+@pytest.mark.parametrize("b_t", [True, False])
+@pytest.mark.parametrize("M, N, K, kernel", [
+    (1536, 768, 1024, WAVE_96x64), (1527, 768, 3072, WAVE_96x64), (1441, 760, 2056, WAVE_96x64), (700, 1536, 1608, WAVE_96x64),
+    (777, 640, 2560, WAVE_32x64), (769, 632, 520, WAVE_32x64), (1024, 512, 2048, WAVE_32x64), (96, 3840, 1288, WAVE_32x64),
+    (33 * 32, 512, 1032, WAVE_64x64), (1, 5120, 1280, WAVE_32x32), (31, 72, 264, WAVE_32x32),
+    # a 96 x 64 workgroup has a CU to itself: one round of them at most
+    (1536, 1024, 1024, WAVE_96x64), (1537, 1024, 1024, WAVE_64x64), (1025, 3632, 1360, WAVE_64x64),
+    # of 32 x 64 a CU holds several
+    (128, 4096, 1544, WAVE_32x64), (32, 30592, 512, WAVE_32x64)])
+def test_tile_of_few_rows(M, N, K, kernel, b_t):
+    assert choice(M, N, K, b_t=b_t) == kernel
