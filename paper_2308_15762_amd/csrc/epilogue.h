@@ -32,6 +32,11 @@ __device__ __forceinline__ void store8_row(bf16* p, const float (&v)[8]) {
   *reinterpret_cast<bf16x8_row*>(p) = a;
 }
 
+// The distance between rows of C, a multiple of 4, and the kind of counted dimension in one kernel argument, for every distance.
+inline unsigned pack_ldc(int ldc, int live_dim) { return (unsigned)ldc >> 2 | (unsigned)live_dim << 29; }
+__device__ __forceinline__ int ldc_of(unsigned packed) { return (int)((packed & 0x1fffffffu) << 2); }
+__device__ __forceinline__ int live_dim_of(unsigned packed) { return (int)(packed >> 29); }
+
 // One output element (m, n) with accumulator value `acc`.
 template <typename T, int EPI>
 __device__ __forceinline__ void epilogue_one(const EpiParams<T>& p, int m, int n, float acc) {

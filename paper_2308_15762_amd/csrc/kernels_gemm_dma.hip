@@ -572,16 +572,15 @@ next_tile:
 }
 
 // Only weight gradients come in groups.  What the first loads of a single problem depend on stands in the first 14 words of the
-// kernel's arguments, which are in scalar registers when it starts (see the build flags); live_dim stands above ldc.
-constexpr int kLdcBits = 28;
+// kernel's arguments, which are in scalar registers when it starts (see the build flags); live_dim stands beside ldc.
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(
-    const bf16* A, const bf16* B, void* C, const bf16* bias, int M, int N, int K, int lda, int ldb, int ldc_live, const bf16* aux,
+    const bf16* A, const bf16* B, void* C, const bf16* bias, int M, int N, int K, int lda, int ldb, unsigned ldc_live, const bf16* aux,
     bf16* aux_out, const int* live) {
   DmaGemm p;
   p.A = A; p.B = B; p.C = (bf16*)C; p.Cf = (float*)C; p.bias = bias; p.aux = aux; p.aux_out = aux_out;
-  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc_live & ((1 << kLdcBits) - 1);
-  p.colsum = nullptr; p.live = live; p.live_dim = ldc_live >> kLdcBits;
+  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc_of(ldc_live);
+  p.colsum = nullptr; p.live = live; p.live_dim = live_dim_of(ldc_live);
   gemm_dma_body<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>(p, (int)blockIdx.x);
 }
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool EDGE>
@@ -638,7 +637,7 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
     const dim3 grid((unsigned)tiles);
     const DmaGemm& p = grp.prob[0];
     launch_kernel((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>), grid, block, lds, stream, p.A, p.B, (void*)p.C,
-                       p.bias, p.M, p.N, p.K, p.lda, p.ldb, p.ldc | p.live_dim << kLdcBits, p.aux, p.aux_out, p.live);
+                       p.bias, p.M, p.N, p.K, p.lda, p.ldb, pack_ldc(p.ldc, p.live_dim), p.aux, p.aux_out, p.live);
   }
   return check_launch("gemm_dma");
 }
@@ -700,7 +699,7 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
   const long span_a = (long)(g.a_t ? kBK : bm) * g.lda * 2, span_b = (long)(g.b_t ? kBK : bn) * g.ldb * 2;
   // operands on 16-byte boundaries with every row of A and B on one too (those of C: see epilogue.h)
   const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
-  if (bits % 16 || g.lda % 8 || g.ldb % 8 || g.ldc % 4 || g.ldc >= 1 << kLdcBits || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
+  if (bits % 16 || g.lda % 8 || g.ldb % 8 || g.ldc % 4 || span_a >= (1L << 31) || span_b >= (1L << 31)) return false;
   if (whole_tiles(g, config)) return true;
   // edges: whole 16-byte vectors along every row
   return (g.a_t ? g.M : g.K) % 8 == 0 && (g.b_t ? g.N : g.K) % 8 == 0 && g.N % 8 == 0;

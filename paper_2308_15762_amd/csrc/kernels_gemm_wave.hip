@@ -439,16 +439,15 @@ __device__ __forceinline__ void gemm_wave_body(WaveGemm<T> p, int wg) {
 // Only weight gradients come in groups.  A single problem is passed by itself: its fields are where the kernel expects them
 // without a search, and a quarter of the bytes goes through the launch (1 us of host time).  The first 14 words of a kernel's
 // arguments are in scalar registers when it starts (see the build flags); what the first loads depend on stands there, and
-// live_dim above ldc, so that nothing at the start waits for the argument block in memory (0.3 us).
-constexpr int kLdcBits = 28;
+// live_dim with ldc, so that nothing at the start waits for the argument block in memory (0.3 us).
 template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(const T* A, const T* B, T* C, const T* bias, int M, int N, int K,
-                                                            int lda, int ldb, int ldc_live, const T* aux, T* aux_out,
+                                                            int lda, int ldb, unsigned ldc_live, const T* aux, T* aux_out,
                                                             const int* live) {
   WaveGemm<T> p;
   p.A = A; p.B = B; p.C = C; p.Cf = nullptr; p.bias = bias; p.aux = aux; p.aux_out = aux_out;
-  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc_live & ((1 << kLdcBits) - 1);
-  p.colsum = nullptr; p.live = live; p.live_dim = ldc_live >> kLdcBits;
+  p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc_of(ldc_live);
+  p.colsum = nullptr; p.live = live; p.live_dim = live_dim_of(ldc_live);
   gemm_wave_body<T, BM, BN, NST, A_T, B_T, EPI>(p, (int)blockIdx.x);
 }
 template <typename T, int BM, int BN, int NST>
@@ -479,7 +478,7 @@ int launch(WaveGemmGroup<T>& grp, unsigned workgroups, hipStream_t stream) {
     if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
     const WaveGemm<T>& p = grp.prob[0];
     launch_kernel(kern, dim3(workgroups), dim3(NW * 64), lds, stream, p.A, p.B, p.C, p.bias, p.M, p.N, p.K, p.lda, p.ldb,
-                       p.ldc | p.live_dim << kLdcBits, p.aux, p.aux_out, p.live);
+                       pack_ldc(p.ldc, p.live_dim), p.aux, p.aux_out, p.live);
   }
   return check_launch("gemm_wave");
 }
@@ -556,7 +555,7 @@ bool gemm_wave_supported(int dtype, const GemmArgs& g) {
   if (!combo || (g.colsum && g.epi != EPI_ACCUM_F32) || (g.live && g.live_dim == LIVE_M_SPLIT)) return false;
   const uintptr_t bits = (uintptr_t)g.A | (uintptr_t)g.B | (uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.aux | (uintptr_t)g.aux_out;
   return bits % 16 == 0 && (g.a_t ? g.M : g.K) % vec == 0 && (g.b_t ? g.N : g.K) % vec == 0 && g.N % vec == 0 && g.lda % vec == 0 &&
-         g.ldb % vec == 0 && g.ldc % 4 == 0 && g.ldc < 1 << kLdcBits && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
+         g.ldb % vec == 0 && g.ldc % 4 == 0 && (long)64 * g.lda * esz < (1L << 31) && (long)64 * g.ldb * esz < (1L << 31);
 }
 
 // A lane's offset reaches over the tile's rows where they are contiguous along the contraction; 64 rows are always within bounds.

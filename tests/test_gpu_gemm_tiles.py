@@ -59,3 +59,21 @@ def test_rows_far_apart(lda):
     hn.hanayo_op_gemm(hn.BF16, A, B, want, M, N, K, K, N, N, False, True, hn.EPI_NONE)
     hn.hanayo_op_gemm(hn.BF16, wide, B, got, M, N, K, lda, N, N, False, True, hn.EPI_NONE)
     assert torch.equal(want, got)
+
+
+# 2^28 elements between rows of C and beyond, on both kinds of kernel (9: 128 x 128 tiles loaded straight into LDS)
+@pytest.mark.parametrize("config", [0, 9])
+@pytest.mark.parametrize("ldc, M", [(2 ** 28, 5), (2 ** 28 + 4, 5), (2 ** 31 - 4, 2)])
+def test_rows_of_the_output_far_apart(ldc, M, config):
+    N, K = 136, 264
+    g = torch.Generator(device="cuda").manual_seed(6)
+    draw = lambda *s: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)  # noqa: E731
+    A, B, want = draw(M, K), draw(K, N), draw(M, N)
+    room, view = strided(M, N, ldc, draw(M, N))
+    hn.hanayo_op_gemm_config(config)
+    try:
+        hn.hanayo_op_gemm(hn.BF16, A, B, want, M, N, K, K, N, N, False, True, hn.EPI_NONE)
+        hn.hanayo_op_gemm(hn.BF16, A, B, room, M, N, K, K, N, ldc, False, True, hn.EPI_NONE)
+    finally:
+        hn.hanayo_op_gemm_config(-1)
+    assert torch.equal(want, view)

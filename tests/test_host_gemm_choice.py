@@ -48,3 +48,13 @@ def test_lane_offsets_stay_within_31_bits(b_t):
     (128, 4096, 1544, WAVE_32x64), (32, 30592, 512, WAVE_32x64)])
 def test_tile_of_few_rows(M, N, K, kernel, b_t):
     assert choice(M, N, K, b_t=b_t) == kernel
+
+
+@pytest.mark.parametrize("M, N, K, epilogue, a_t", [(1536, 768, 1024, hn.EPI_NONE, False), (64, 64, 64, hn.EPI_BIAS, False), (4096, 4096, 1024, hn.EPI_BIAS_GELU, False),
+                                                    (1024, 1024, 512, hn.EPI_ACCUM_F32, True), (4096, 4096, 4096, hn.EPI_ACCUM_F32, True)])
+def test_rows_of_the_output_may_be_any_distance_apart(M, N, K, epilogue, a_t):
+    for dtype in (hn.BF16, hn.FP32):
+        near = choice(M, N, K, epilogue=epilogue, a_t=a_t, dtype=dtype)
+        assert near != ALU
+        for ldc in (2 ** 28 - 4, 2 ** 28, 2 ** 31 - 4):
+            assert choice(M, N, K, ldc=ldc, epilogue=epilogue, a_t=a_t, dtype=dtype) == near
