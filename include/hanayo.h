@@ -376,12 +376,13 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
  * added inside a launch (a chunk's gradient accumulations keep their
  * list order).  Calls with lanes > 1 on one device are serialised on the host.
  *
- * The lanes are chosen by list scheduling with the schedule's own costs (forward 1, backward 2).  Of three or four lanes two
- * are used where the tasks are small (ceil(T / 256) * ceil(F / 256) < 256): more are slower there.
+ * The lanes are chosen by list scheduling with the schedule's own costs (forward 1, backward 2).  Of three or four lanes a rank
+ * of at most four chunks uses two where its tasks are small (with N = max(F, 3H): fewer than 256 tiles of 256 x 256 in a
+ * T x N product and fewer than 512 in an H x N one) and more would not shorten that schedule by a fifth: more are slower there.
  *
  * hanayo_executor_plan reports that plan without touching the GPU:
  *   lane  host [n]     lane of each task
- *   d, e  NULL, or the descriptors of the run (d: the lanes it uses, see above; e, which needs d: a run with args->ends
+ *   d, e  NULL, or the descriptors of the run (d: whether its tasks are small, see above; e, which needs d: a run with args->ends
  *         set: the plan then has the dependencies [4] below and counts the head's work (from the shapes) into the
  *         forward task of the last stage)
  *   deps  host [n][5]  indices of earlier tasks that task i waits for, -1 = none:

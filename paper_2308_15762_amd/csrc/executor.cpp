@@ -20,6 +20,7 @@
 
 #include <array>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "ends.h"
@@ -58,11 +59,15 @@ int make_plan(const hanayo_task* list, size_t n, int W, Plan& pl) {
   return HANAYO_OK;
 }
 
+constexpr int kMaxLanes = 4;
+
 // What a task must wait for besides the tasks before it on its own lane.
 enum { DEP_INPUT, DEP_FORWARD, DEP_SLOT, DEP_GRADS, DEP_ENDS, N_DEPS };
 struct LanePlan {
+  int lanes = 1;
   std::vector<int32_t> lane;
   std::vector<std::array<int32_t, N_DEPS>> dep;  // task indices, -1 = none
+  std::vector<double> cost, done;                // in forward tasks: what a task costs, when it ends
   std::vector<float> busy;                       // lanes the plan expects to be busy while the task runs (average, >= 1)
 };
 
@@ -75,17 +80,22 @@ struct LanePlan {
 //   DEP_GRADS    (backward) the previous backward of the same chunk: one accumulation at a time
 //   DEP_ENDS     (with the model's ends: forward of the last stage, backward of stage 0) the previous task that
 //                added to the gradients of the embedding tables and the head, which may be one table
-// head_cost: with ends, what the head and loss add to the forward task of the last stage, in forward tasks.
-void plan_lanes(const hanayo_task* list, size_t n, int P, int W, int M, int rank, int lanes, bool ends, double head_cost,
-                const Plan& pl, LanePlan& lp) {
+// head_cost: with ends, what the head and loss add to the forward task of the last stage, in forward tasks.  Returns the plan's
+// length.
+double schedule_lanes(const hanayo_task* list, size_t n, int P, int W, int M, int rank, int lanes, bool ends, double head_cost,
+                      const Plan& pl, LanePlan& lp) {
   const int nchunk = chunks_per_rank(W), S = nchunk * P;
+  lp.lanes = lanes;
   lp.lane.assign(n, 0);
   lp.dep.assign(n, {-1, -1, -1, -1, -1});
   int32_t last_ends = -1;
   std::vector<int32_t> f_at((size_t)M * nchunk, -1), b_at((size_t)M * nchunk, -1), last_b(nchunk, -1);
   std::vector<std::vector<int32_t>> slot_reader(nchunk);
   for (int c = 0; c < nchunk; ++c) slot_reader[c].assign(pl.per_chunk[c], -1);
-  std::vector<double> done(n, 0.0), lane_free(lanes, 0.0), cost(n, 0.0);
+  std::vector<double> lane_free(lanes, 0.0);
+  std::vector<double>&done = lp.done, &cost = lp.cost;
+  done.assign(n, 0.0);
+  cost.assign(n, 0.0);
   for (size_t i = 0; i < n; ++i)
     cost[i] = (list[i].kind == HANAYO_F ? 1.0 : 2.0) + (ends && list[i].kind == HANAYO_F && (int)list[i].stage == S - 1 ? head_cost : 0.0);
   for (size_t i = 0; i < n; ++i) {
@@ -118,34 +128,61 @@ void plan_lanes(const hanayo_task* list, size_t n, int P, int W, int M, int rank
     lp.lane[i] = best;
     done[i] = lane_free[best] = best_start + cost[i];
   }
+  double length = 0.0;
+  for (double end : lane_free)
+    if (end > length) length = end;
+  return length;
+}
+
+// Are the tasks small: no product of a micro-batch with 256 tiles of 256 x 256, no weight gradient with 512?
+bool small_tasks(const Shape& sh) {
+  auto tiles = [](int m, int n) { return (long)((m + 255) / 256) * ((n + 255) / 256); };
+  const int widest = sh.F > 3 * sh.H ? sh.F : 3 * sh.H;
+  return tiles(sh.T, widest) < 256 && tiles(sh.H, widest) < 512;
+}
+
+// The plan a run uses: on all the lanes it is given, or on two of them.  Tasks on different lanes meet at events, which cost
+// the GPU about 10 us each (a barrier packet and a signal between two queues), and lanes that the list cannot keep busy only
+// add such meetings: a chunk's backward tasks run one after the other, so a rank of two chunks rarely has work for more than
+// two lanes.  The plan's own clock tells: small tasks of a rank of at most four chunks use two lanes unless more shorten the
+// plan by a fifth.  us of a step with two / with four lanes, the four's plan taking so many parts of the two's:
+//   0.96 (two chunks, rank 0): fp32 H = 256, T = 256 495 / 565; bf16 H = 256, T = 512 880 / 960; H = 512, T = 1024 1260 / 1410; H = 1024,
+//     T = 1024 2605 / 2760, T = 2048 4120 / 4200, T = 3072 5380 / 5465, T = 3840 6340 / 6345; H = 2048, T = 1024 7310 / 7430; H = 2560, T = 1024
+//     10660 / 10660; fp32 H = 512, T = 1024 4075 / 4130, H = 1024, T = 2048 12760 / 12870
+//   0.9 - 0.94 (one chunk, GPipe and 1F1B): H = 512, T = 1024 771 / 871 and 738 / 818; H = 1024, T = 2048 2350 / 2453 and 2317 / 2395
+//   0.86 (two chunks, two micro-batches): H = 256, T = 512 253 / 294; H = 1024, T = 1024 684 / 729, T = 2048 1085 / 1099
+//   0.82 - 0.99 (four chunks, a head of 4096 to 50304 columns, which orders their ends): H = 256, T = 512 1110 / 1238 to 1540 / 1641; H = 512,
+//     T = 1024 1733 / 1830 to 2950 / 3020; H = 1024, T = 2048 5440 / 5460 to 8410 / 8550, 2 blocks 10000 / 10000, 10920 / 10720, 12900 / 13115
+//   0.77 (two chunks, last rank): H = 256, T = 512 1002 / 1061; H = 512, T = 1024 1269 / 1236; H = 1024, T = 1024 2707 / 2697, T = 2048 4201 /
+//     4076
+//   0.51 (four chunks): H = 256, T = 512 1950 / 2005; H = 512, T = 1024 2570 / 2375; H = 1024, T = 1024 2 blocks 11260 / 10200, T = 2048 8520 /
+//     7510; H = 2048, T = 1024 14670 / 12960; H = 4096, T = 512 2 blocks 31700 / 28300
+//   0.95, but eight chunks (H = 512, T = 1024, a head of 50304 columns): 4300 / 3990
+// Larger tasks gain from all lanes, whose tails fill in, or lose nothing: 0.96 with H = 4096, T = 512 16450 / 16220, H = 3072, T = 1024
+// 14600 / 14320, H = 1024, T = 4096 6930 / 6870.  Results do not depend on it.
+void plan_lanes(const hanayo_task* list, size_t n, int P, int W, int M, int rank, const Shape* sh, int lanes, bool ends,
+                double head_cost, const Plan& pl, LanePlan& lp) {
+  const double length = schedule_lanes(list, n, P, W, M, rank, lanes, ends, head_cost, pl, lp);
+  if (lanes > 2 && chunks_per_rank(W) <= kMaxLanes && sh && small_tasks(*sh)) {
+    LanePlan two;
+    if (length > 0.8 * schedule_lanes(list, n, P, W, M, rank, 2, ends, head_cost, pl, two)) lp = std::move(two);
+  }
   // In the plan's own clock, how many lanes work during each task: the overlap of its interval
   // with every task's, over its length.
   lp.busy.assign(n, 1.0f);
   for (size_t i = 0; i < n; ++i) {
-    const double ci = cost[i], si = done[i] - ci;
+    const double ci = lp.cost[i], si = lp.done[i] - ci;
     double overlap = 0.0;
     for (size_t j = 0; j < n; ++j) {
-      const double sj = done[j] - cost[j];
-      const double lo = si > sj ? si : sj, hi = done[i] < done[j] ? done[i] : done[j];
+      const double sj = lp.done[j] - lp.cost[j];
+      const double lo = si > sj ? si : sj, hi = lp.done[i] < lp.done[j] ? lp.done[i] : lp.done[j];
       if (hi > lo) overlap += hi - lo;
     }
     lp.busy[i] = (float)(overlap / ci);
   }
 }
 
-// Lanes an executor uses of those it is given.  Tasks on different lanes meet at events, which cost the GPU about 10 us each
-// (a barrier packet and a signal between two queues), and smaller tasks meet more often.  Two lanes already cover each other's
-// launches there; the third and fourth pay where a task's own launches fill the chip only once and the others' tails fill in:
-// the line is 256 tiles of 256 x 256 in its widest product.  Steps with 4 and with 2 lanes, us: H = 512, T = 1024 1470 and
-// 1344; H = 768, T = 1527 2768 and 2605; H = 1024, T = 1024 2972 and 2775; H = 1024, T = 2048 8745 and 8549; above the line
-// H = 1024, T = 4096 25270 and 27665; H = 4096, T = 2048 164005 and 169271.  Results do not depend on it.
-int lanes_used(const Shape& sh, int lanes) {
-  const long tiles = (long)((sh.T + 255) / 256) * ((sh.F + 255) / 256);
-  return tiles < 256 && lanes > 2 ? 2 : lanes;
-}
-
 // Side streams and events, made once per device and kept: default priority, non-blocking.
-constexpr int kMaxLanes = 4;
 struct LaneResources {
   int device = -1;
   hipStream_t side[kMaxLanes - 1] = {};
@@ -317,10 +354,10 @@ int hanayo_executor_plan(const hanayo_task* list, size_t n, int P, int W, int M,
     if (rc) return rc;
     head_cost = head_cost_of(sh, *e);
   }
-  Shape used;
-  if (d && make_shape(d, used) == HANAYO_OK) lanes = lanes_used(used, lanes);
+  Shape tasks_of;
   LanePlan lp;
-  plan_lanes(list, n, P, W, M, rank, lanes, e != nullptr && rank == 0, head_cost, pl, lp);
+  plan_lanes(list, n, P, W, M, rank, d && make_shape(d, tasks_of) == HANAYO_OK ? &tasks_of : nullptr, lanes, e != nullptr && rank == 0,
+             head_cost, pl, lp);
   for (size_t i = 0; i < n; ++i) {
     lane[i] = lp.lane[i];
     for (int k = 0; k < N_DEPS; ++k) deps[i * N_DEPS + k] = lp.dep[i][k];
@@ -380,9 +417,9 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
     }
   }
   if (a->lanes > kMaxLanes) return set_error(HANAYO_EINVAL, "executor: at most %d lanes", kMaxLanes);
-  const int lanes = a->lanes < 1 ? 1 : lanes_used(sh, a->lanes);
   LanePlan lp;
-  plan_lanes(list, n, P, W, M, rank, lanes, en != nullptr, en ? head_cost_of(sh, en->desc) : 0.0, pl, lp);
+  plan_lanes(list, n, P, W, M, rank, &sh, a->lanes < 1 ? 1 : a->lanes, en != nullptr, en ? head_cost_of(sh, en->desc) : 0.0, pl, lp);
+  const int lanes = lp.lanes;
   // a task records an event if a task on another lane waits for it
   std::vector<char> signals(n, 0);
   for (size_t i = 0; i < n; ++i)

@@ -141,6 +141,26 @@ def test_kernel_choice_does_not_depend_on_lanes(hidden, heads, seq, mb, causal):
             assert torch.equal(a, b)
 
 
+# four chunks of small tasks, ragged and whole, fp32; two chunks of tasks above the line up to which a rank of two chunks uses two lanes
+@pytest.mark.parametrize("hidden,heads,seq,mb,chunks,dtype", [(640, 8, 777, 1, 4, "bf16"), (1024, 16, 512, 2, 4, "bf16"), (256, 4, 96, 2, 4, "fp32"),
+                                                              (1024, 16, 1025, 4, 2, "bf16")])
+def test_three_and_four_lanes_give_the_bits_of_one(hidden, heads, seq, mb, chunks, dtype):
+    """Lists that do keep three and four lanes busy, so that the load expected of the other lanes takes part in the choice of tiles."""
+    wl = W["gpt_1024_bf16"].scaled(hidden=hidden, heads=heads, ffn=4 * hidden, seq=seq, mb=mb, n_blocks=1, P=4, W=chunks // 2, M=4, dtype=dtype)
+    runs = []
+    for lanes, mode in ((1, hn.STASH_FULL), (3, hn.STASH_FULL), (4, hn.STASH_FULL), (3, hn.STASH_INPUT), (4, hn.STASH_INPUT)):
+        gpu = GpuRank(wl, 0, lanes=lanes, stash_mode=mode)
+        assert len(set(hn.hanayo_executor_plan(gpu.tasks, wl.P, wl.W, wl.M, 0, lanes, gpu.desc)[0].tolist())) == lanes
+        gpu.run()
+        torch.cuda.synchronize()
+        runs.append([t.clone() for t in gpu.act_out + gpu.grad_out] + [g.cpu().numpy() for g in gpu.grads])
+    n = len(runs[0]) - chunks
+    for other in runs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(runs[0][:n], other[:n]))
+        for a, b in zip(runs[0][n:], other[n:]):   # the order of the bias gradients' sums depends on the tile
+            assert perr(b, a) <= 1e-5
+
+
 @pytest.mark.parametrize("lanes", [1, 3])
 @pytest.mark.parametrize("name", ["tiny_gpt_fp32_rank0", "gpt_1024_sched_small", "bert_sched_small"])
 def test_input_only_stash_recomputes_to_the_same_result(name, lanes):

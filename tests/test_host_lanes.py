@@ -1,22 +1,60 @@
-"""How many of its lanes the executor uses, by the size of a chunk's products (no GPU)."""
+"""How many of its lanes the executor uses: by what they shorten the list's schedule and by the size of a chunk's products (no GPU)."""
 
 import pytest
 
 from paper_2308_15762_amd import hanayo as hn
 
 
-@pytest.mark.parametrize("tokens, ffn, most", [
-    (4096, 4096, 4),          # 16 x 16 tiles of 256 x 256
-    (4096 - 256, 4096, 2),    # 15 x 16
-    (4096 - 255, 4096, 4),    # 15 whole tile rows and one more row
-    (128, 1024, 2),
-    (2048, 10240, 4),
+def lanes_used(tasks, P, W, M, rank, lanes, desc):
+    """The lanes of the plan, which is the plan for that many lanes without a look at the tasks' size."""
+    lane, deps = hn.hanayo_executor_plan(tasks, P, W, M, rank, lanes, desc)
+    used = len(set(lane.tolist()))
+    want, want_deps = hn.hanayo_executor_plan(tasks, P, W, M, rank, used)
+    assert (lane == want).all() and (deps == want_deps).all()
+    return used
+
+
+def chunk(tokens, hidden=256, ffn=1024, dtype=hn.BF16):
+    return hn.make_desc(1, hidden, hidden // 8, ffn, tokens, 1, hn.PRE_LN, hn.MASK_CAUSAL, dtype)
+
+
+@pytest.mark.parametrize("dtype", [hn.BF16, hn.FP32])
+@pytest.mark.parametrize("P, W, M, rank, most", [
+    (4, 2, 8, 0, 4), (4, 2, 8, 3, 4), (4, 2, 2, 0, 4), (2, 2, 4, 0, 4), (8, 4, 4, 0, 4),   # four chunks and more: half the time of two lanes
+    (4, 1, 8, 0, 2), (2, 1, 4, 0, 2), (4, 1, 2, 0, 2), (8, 1, 16, 0, 2),                   # two chunks: up to a seventh
+    (4, 1, 8, 1, 4), (4, 1, 8, 2, 4), (4, 1, 8, 3, 4),                                     # the same on other ranks: a quarter and more
 ])
-def test_small_tasks_use_two_lanes(tokens, ffn, most):
-    tasks = hn.hanayo_schedule(4, 2, 8, 0)
-    desc = hn.make_desc(1, 256, 4, ffn, tokens, 1, hn.PRE_LN, hn.MASK_CAUSAL, hn.BF16)
+def test_small_tasks_use_the_lanes_that_shorten_the_list(P, W, M, rank, most, dtype):
+    tasks = hn.hanayo_schedule(P, W, M, rank)
+    for lanes in (1, 2, 4):
+        assert lanes_used(tasks, P, W, M, rank, lanes, chunk(512, dtype=dtype)) == min(lanes, most)
+
+
+def test_the_head_counts():
+    """The tasks with the head's gradients run one after the other: of four chunks' lanes only two are worth while, of eight chunks' all."""
+    for W, most in ((2, 2), (4, 4)):
+        tasks = hn.hanayo_schedule(4, W, 4, 0)
+        for lanes in (1, 2, 3, 4):
+            lane, _ = hn.hanayo_executor_plan(tasks, 4, W, 4, 0, lanes, chunk(512), hn.EndsDesc(16384, 512, 1))
+            assert len(set(lane.tolist())) == min(lanes, most)
+
+
+@pytest.mark.parametrize("scheme", [hn.SCHEME_GPIPE, hn.SCHEME_1F1B])
+def test_one_chunk_uses_two_lanes(scheme):
+    tasks = hn.hanayo_schedule_scheme(scheme, 4, 0, 8, 0)
     for lanes in (1, 2, 3, 4):
-        lane, deps = hn.hanayo_executor_plan(tasks, 4, 2, 8, 0, lanes, desc)
-        want, want_deps = hn.hanayo_executor_plan(tasks, 4, 2, 8, 0, min(lanes, most))
-        assert (lane == want).all() and (deps == want_deps).all()
-        assert len(set(lane.tolist())) == min(lanes, most)
+        assert lanes_used(tasks, 4, 0, 8, 0, lanes, chunk(512)) == min(lanes, 2)
+
+
+@pytest.mark.parametrize("tokens, hidden, ffn, most", [
+    (4096, 256, 4096, 4),          # 16 x 16 tiles of 256 x 256
+    (4096 - 256, 256, 4096, 2),    # 15 x 16
+    (4096 - 255, 256, 4096, 4),    # 15 whole tile rows and one more row
+    (4096, 1368, 3648, 4),         # Q, K and V are the wider product: 4104 columns, 17 tiles
+    (512, 2560, 10240, 2),         # weight gradients of 400 tiles
+    (512, 3072, 12288, 4),         # of 576
+])
+def test_tasks_are_small_up_to_a_line(tokens, hidden, ffn, most):
+    tasks = hn.hanayo_schedule(4, 1, 8, 0)
+    for lanes in (1, 2, 3, 4):
+        assert lanes_used(tasks, 4, 1, 8, 0, lanes, chunk(tokens, hidden, ffn)) == min(lanes, most)

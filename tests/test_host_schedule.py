@@ -145,17 +145,18 @@ def _accesses(P, W, rank, tasks, slot, lane, ends=False):
     return out
 
 
+@pytest.mark.parametrize("seq", [128, 2048])   # small tasks, for which a rank of two chunks uses two lanes; large ones
 @pytest.mark.parametrize("ends", [False, True])
 @pytest.mark.parametrize("lanes", [1, 2, 3, 4])
 @pytest.mark.parametrize("P,W,M", [(2, 1, 4), (4, 2, 8), (4, 1, 16), (8, 4, 12), (3, 2, 5), (1, 2, 3), (5, 3, 2)])
-def test_lane_plan_orders_every_conflict(P, W, M, lanes, ends):
+def test_lane_plan_orders_every_conflict(P, W, M, lanes, ends, seq):
     """Any two tasks that touch one buffer, at least one of them writing, are ordered by the plan's
     event waits together with the in-order execution of each lane."""
     for rank in range(P):
         tasks = hn.hanayo_schedule(P, W, M, rank)
         n = len(tasks)
-        desc = hn.make_desc(2, 256, 4, 1024, 128, 2, hn.PRE_LN, hn.MASK_CAUSAL, hn.BF16)
-        lane, deps = hn.hanayo_executor_plan(tasks, P, W, M, rank, lanes, desc, hn.EndsDesc(4096, 128, 1) if ends else None)
+        desc = hn.make_desc(2, 256, 4, 4096 if seq > 128 else 1024, seq, 2, hn.PRE_LN, hn.MASK_CAUSAL, hn.BF16)
+        lane, deps = hn.hanayo_executor_plan(tasks, P, W, M, rank, lanes, desc, hn.EndsDesc(4096, seq, 1) if ends else None)
         assert lane.min() >= 0 and lane.max() < lanes
         assert ends and rank == 0 or (deps[:, 4] == -1).all()
         _, _, slot = S.stash_plan(S.schedule(P, W, M, rank), W)
@@ -178,6 +179,8 @@ def test_lane_plan_orders_every_conflict(P, W, M, lanes, ends):
                     assert before[i] >> j & 1, "tasks %d and %d share %s unordered" % (j, i, (wj & (ri | wi)) | (rj & wi))
         if lanes > 1 and P >= 2 and M >= 4:
             assert len(set(lane.tolist())) > 1   # the plan does use more than one lane
+            # and all of them for large tasks, or where there are more than four chunks (of 16 tasks no more than two run at a time)
+            assert len(set(lane.tolist())) == lanes or (seq == 128 and W <= 2) or (P, W, M) == (2, 1, 4)
 
 
 def test_lane_plan_rejects_bad_arguments():
