@@ -588,7 +588,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
   if ((int)blockIdx.x >= grp.first[kMaxGroup]) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int at = (int)blockIdx.x - grp.first[kMaxGroup], second = at >= grp.job_blocks;
-    finalize_columns<WGM * WGN * 64>(grp.job[second], at - second * grp.job_blocks, smem);
+    finalize_columns<WGM * WGN * 64, 4>(grp.job[second], at - second * grp.job_blocks, smem);
     return;
   }
   int gi = 0;
@@ -628,7 +628,7 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   if constexpr (EPI == EPI_ACCUM_F32) {
     grp.job_blocks = 0;
     for (int i = 0; i < grp.n_jobs; ++i) {
-      const int blocks = finalize_blocks(grp.job[i], finalize_cols<NW * 64>());
+      const int blocks = finalize_blocks(grp.job[i], finalize_cols<NW * 64, 4>());
       if (blocks > grp.job_blocks) grp.job_blocks = blocks;
     }
     const dim3 grid((unsigned)(tiles + (long)grp.n_jobs * grp.job_blocks));

@@ -455,7 +455,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_wave_group_kernel(WaveGemmGroup<
   if ((int)blockIdx.x >= grp.first[kMaxGroup]) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int at = (int)blockIdx.x - grp.first[kMaxGroup], second = at >= grp.job_blocks;
-    finalize_columns<NW * 64>(grp.job[second], at - second * grp.job_blocks, smem);
+    finalize_columns<NW * 64, 4>(grp.job[second], at - second * grp.job_blocks, smem);
     return;
   }
   int gi = 0;
@@ -529,7 +529,7 @@ int group_t(const GemmArgs* gs, int count, WaveTile tile, hipStream_t stream, co
   if (tiles > 0x7fff0000L) return set_error(HANAYO_EUNSUPPORTED, "gemm_wave: too many tiles");
   for (int i = 0; i < n_jobs; ++i) {
     grp.job[i] = jobs[i];
-    const int blocks = finalize_blocks(jobs[i], finalize_cols<NW * 64>());
+    const int blocks = finalize_blocks(jobs[i], finalize_cols<NW * 64, 4>());
     if (blocks > grp.job_blocks) grp.job_blocks = blocks;
   }
   const unsigned workgroups = (unsigned)(tiles + (long)n_jobs * grp.job_blocks);

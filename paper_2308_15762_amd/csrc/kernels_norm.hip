@@ -8,6 +8,7 @@
 #include <atomic>
 
 #include "device_util.h"
+#include "finalize.h"
 #include "kernels.h"
 
 namespace hanayo {
@@ -217,58 +218,24 @@ __global__ __launch_bounds__(RS * RG * 64) void ln_bwd_kernel(const T* __restric
   }
 }
 
-// out[c] += sum_r partial[r][c] for c in [0, n), without atomics and in a fixed order: a workgroup owns 32
-// columns; its 32 row groups each run down every 32nd partial row (32 lanes x 4 bytes = one 128-byte line per
-// row; with 256 partial rows that is 8 loads per thread, all in flight at once), the group sums are added in
-// order through LDS, and one thread per column adds the total to `out`.
-// Columns >= split go to out1[c - split].  The same bits every run.
-constexpr int kFinalizeCols = 32, kFinalizeGroups = 32;
-__global__ __launch_bounds__(kFinalizeCols * kFinalizeGroups) void finalize_kernel(const float* __restrict__ partial, int rows, int ld, int n,
-                                                       float* __restrict__ out0, float* __restrict__ out1, int split) {
-  __shared__ float red[kFinalizeGroups][kFinalizeCols];
-  const int cl = threadIdx.x % kFinalizeCols, rg = threadIdx.x / kFinalizeCols;
-  const int c = blockIdx.x * kFinalizeCols + cl;
-  float t = 0.f;
-  if (c < n) {
-#pragma unroll 8
-    for (int r = rg; r < rows; r += kFinalizeGroups) t += partial[(size_t)r * ld + c];
-  }
-  red[rg][cl] = t;
-  __syncthreads();
-  if (rg == 0 && c < n) {
-    float total = 0.f;
-#pragma unroll
-    for (int g = 0; g < kFinalizeGroups; ++g) total += red[g][cl];
-    float* dst = c < split ? out0 + c : out1 + (c - split);
-    *dst += total;
-  }
+// Adding up partial rows (see finalize.h).
+constexpr int kFinalizeThreads = 1024, kFinalizeCols = finalize_cols<kFinalizeThreads, 1>();
+__global__ __launch_bounds__(kFinalizeThreads) void finalize_kernel(const float* __restrict__ partial, int rows, int ld, int n,
+                                                                    float* __restrict__ out0, float* __restrict__ out1, int split) {
+  __shared__ float red[32][32];
+  finalize_columns<kFinalizeThreads, 1>(FinalizeJob{partial, rows, ld, n, out0, out1, split}, blockIdx.x, red);
 }
 
 // Several finaliser jobs in one launch (blockIdx.y = job): the gamma/beta sums of the LayerNorms of a chunk's backward pass
-// that no weight-gradient launch has taken along (finalize.h).
+// that no weight-gradient launch has taken along.
 struct FinalizeJobs {
   FinalizeJob job[kMaxFinalizeJobs];
 };
-__global__ __launch_bounds__(kFinalizeCols * kFinalizeGroups) void finalize_group_kernel(FinalizeJobs jobs) {
+__global__ __launch_bounds__(kFinalizeThreads) void finalize_group_kernel(FinalizeJobs jobs) {
+  __shared__ float red[32][32];
   const FinalizeJob j = jobs.job[blockIdx.y];
   if ((int)blockIdx.x * kFinalizeCols >= j.n) return;  // uniform over the workgroup: jobs may differ in width
-  __shared__ float red[kFinalizeGroups][kFinalizeCols];
-  const int cl = threadIdx.x % kFinalizeCols, rg = threadIdx.x / kFinalizeCols;
-  const int c = blockIdx.x * kFinalizeCols + cl;
-  float t = 0.f;
-  if (c < j.n) {
-#pragma unroll 8
-    for (int r = rg; r < j.rows; r += kFinalizeGroups) t += j.partial[(size_t)r * j.ld + c];
-  }
-  red[rg][cl] = t;
-  __syncthreads();
-  if (rg == 0 && c < j.n) {
-    float total = 0.f;
-#pragma unroll
-    for (int g = 0; g < kFinalizeGroups; ++g) total += red[g][cl];
-    float* dst = c < j.split ? j.out0 + c : j.out1 + (c - j.split);
-    *dst += total;
-  }
+  finalize_columns<kFinalizeThreads, 1>(j, blockIdx.x, red);
 }
 
 // ------------------------------------------------------------------ column sums
@@ -330,7 +297,7 @@ int ln_forward_t(const void* x, const void* gamma, const void* beta, void* out, 
 
 int launch_finalize(const float* partial, int rows, int ld, int n, float* out0, float* out1, int split, hipStream_t stream,
                     const char* what) {
-  launch_kernel(finalize_kernel, dim3((n + kFinalizeCols - 1) / kFinalizeCols), dim3(kFinalizeCols * kFinalizeGroups), 0,
+  launch_kernel(finalize_kernel, dim3((n + kFinalizeCols - 1) / kFinalizeCols), dim3(kFinalizeThreads), 0,
                      stream, partial, rows, ld, n, out0, out1, split);
   return check_launch(what);
 }
@@ -429,7 +396,7 @@ int finalize_group(const FinalizeJob* jobs, int count, hipStream_t stream) {
     }
     if (widest < 1) continue;
     launch_kernel(finalize_group_kernel, dim3((widest + kFinalizeCols - 1) / kFinalizeCols, n),
-                       dim3(kFinalizeCols * kFinalizeGroups), 0, stream, batch);
+                       dim3(kFinalizeThreads), 0, stream, batch);
     const int rc = check_launch("finalize_group");
     if (rc) return rc;
   }
