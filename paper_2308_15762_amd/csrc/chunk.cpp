@@ -193,7 +193,7 @@ WaveTile wave_choice(int dtype, const GemmArgs* gs, int count, double share, int
                                {WAVE_32x64, 0.13 / 64, 1.1, 2.7}};
   static const Kind kFp32[] = {{WAVE_64x64, 0.0154, 1.0, 3.0}, {WAVE_32x32, 0.0044, 0.6, 2.5}};
   const Kind* all = dtype == HANAYO_BF16 ? kBf16 : kFp32;
-  if (dtype != HANAYO_BF16 || gs[0].epi == EPI_ACCUM_F32) kinds = 2;
+  if (dtype != HANAYO_BF16 || gs[0].epi == EPI_ACCUM_F32 || count > 1) kinds = 2;  // groups and weight gradients: square tiles
   WaveTile best = WAVE_NONE;
   for (int n = 0; n < kinds; ++n) {
     const Kind& t = all[n];
@@ -288,7 +288,7 @@ int gemm(int dtype, const GemmArgs& g, hipStream_t stream) {
 int gemm_group(int dtype, const GemmArgs* gs, int count, hipStream_t stream, const FinalizeJob* jobs, int n_jobs, bool* taken) {
   if (taken) *taken = false;
   if (count < 1 || count > 4) return set_error(HANAYO_EINVAL, "gemm_group: %d problems", count);
-  bool alike = count == 1 || gs[0].epi == EPI_ACCUM_F32;  // the kernels take only weight gradients in groups
+  bool alike = true;
   for (int i = 0; i < count; ++i) {
     const GemmArgs& g = gs[i];
     if (g.M < 1 || g.N < 1 || g.K < 1) return set_error(HANAYO_EINVAL, "gemm: empty problem");

@@ -150,9 +150,9 @@ void gemm_dma_tile(int config, int& bm, int& bn);
 int gemm_dma(const GemmArgs& g, int config, hipStream_t stream);
 int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream, const FinalizeJob* jobs = nullptr,
                    int n_jobs = 0);
-// Tiles whose contraction is split over the wavefronts of a workgroup: few tiles, ragged extents, fp32.  Up to 4 weight
-// gradients per launch; column sums are folded in.  The tiles among themselves give the same bits; WAVE_96x64 and WAVE_32x64
-// exist in bf16 and not for weight gradients.
+// Tiles whose contraction is split over the wavefronts of a workgroup: few tiles, ragged extents, fp32.  Up to 4 problems
+// per launch; column sums are folded in.  The tiles among themselves give the same bits; WAVE_96x64 and WAVE_32x64
+// exist in bf16, for single problems that are no weight gradients.
 enum WaveTile { WAVE_NONE = 0, WAVE_64x64, WAVE_32x32, WAVE_96x64, WAVE_32x64 };
 inline void wave_tile(WaveTile t, int& bm, int& bn) {
   bm = t == WAVE_64x64 ? 64 : t == WAVE_96x64 ? 96 : 32;

@@ -571,8 +571,8 @@ next_tile:
   }
 }
 
-// Only weight gradients come in groups.  What the first loads of a single problem depend on stands in the first 14 words of the
-// kernel's arguments, which are in scalar registers when it starts (see the build flags); live_dim stands beside ldc.
+// A single product, unless it is a weight gradient, is passed by itself: what its first loads depend on stands in the first 14 words of
+// the kernel's arguments, which are in scalar registers when it starts (see the build flags); live_dim stands beside ldc.
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_kernel(
     const bf16* A, const bf16* B, void* C, const bf16* bias, int M, int N, int K, int lda, int ldb, unsigned ldc_live, const bf16* aux,
@@ -583,9 +583,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
   p.colsum = nullptr; p.live = live; p.live_dim = live_dim_of(ldc_live);
   gemm_dma_body<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>(p, (int)blockIdx.x);
 }
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool EDGE>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
 __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_dma_group_kernel(DmaGemmGroup grp) {
-  if ((int)blockIdx.x >= grp.first[kMaxGroup]) {
+  if (EPI == EPI_ACCUM_F32 && (int)blockIdx.x >= grp.first[kMaxGroup]) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int at = (int)blockIdx.x - grp.first[kMaxGroup], second = at >= grp.job_blocks;
     finalize_columns<WGM * WGN * 64, 4>(grp.job[second], at - second * grp.job_blocks, smem);
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll
   for (int j = 1; j < kMaxGroup; ++j)
     if (j < grp.count && (int)blockIdx.x >= grp.first[j]) gi = j;
-  gemm_dma_body<BM, BN, WGM, WGN, NSTAGE, true, true, EPI_ACCUM_F32, EDGE>(grp.prob[gi], (int)blockIdx.x - grp.first[gi]);
+  gemm_dma_body<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>(grp.prob[gi], (int)blockIdx.x - grp.first[gi]);
 }
 
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, bool A_T, bool B_T, int EPI, bool EDGE>
@@ -603,11 +603,6 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   constexpr int NW = WGM * WGN;
   constexpr size_t lds = (size_t)NSTAGE * (Operand<BM, A_T, NW>::kBytes + Operand<BN, B_T, NW>::kBytes) +
                          (EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU ? kGeluN * sizeof(float2) : 0);
-  static thread_local uint64_t raised = 0;
-  const void* kern;
-  if constexpr (EPI == EPI_ACCUM_F32) kern = reinterpret_cast<const void*>(&gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, EDGE>);
-  else kern = reinterpret_cast<const void*>(&gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>);
-  if (const int rc = raise_lds(kern, lds, raised)) return rc;
   long tiles = 0;
   for (int i = 0; i < grp.count; ++i) {
     grp.first[i] = (int)tiles;
@@ -625,19 +620,27 @@ int launch(DmaGemmGroup& grp, hipStream_t stream) {
   }
   for (int i = grp.count; i <= kMaxGroup; ++i) grp.first[i] = (int)tiles;
   const dim3 block(NW * 64);
-  if constexpr (EPI == EPI_ACCUM_F32) {
-    grp.job_blocks = 0;
-    for (int i = 0; i < grp.n_jobs; ++i) {
-      const int blocks = finalize_blocks(grp.job[i], finalize_cols<NW * 64, 4>());
-      if (blocks > grp.job_blocks) grp.job_blocks = blocks;
+  if constexpr (EPI != EPI_STORE_F32) {
+    if (EPI == EPI_ACCUM_F32 || grp.count > 1) {
+      auto kern = gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>;
+      static thread_local uint64_t raised = 0;
+      if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
+      grp.job_blocks = 0;
+      for (int i = 0; i < grp.n_jobs; ++i) {
+        const int blocks = finalize_blocks(grp.job[i], finalize_cols<NW * 64, 4>());
+        if (blocks > grp.job_blocks) grp.job_blocks = blocks;
+      }
+      launch_kernel(kern, dim3((unsigned)(tiles + (long)grp.n_jobs * grp.job_blocks)), block, lds, stream, grp);
+      return check_launch("gemm_dma");
     }
-    const dim3 grid((unsigned)(tiles + (long)grp.n_jobs * grp.job_blocks));
-    launch_kernel((gemm_dma_group_kernel<BM, BN, WGM, WGN, NSTAGE, EDGE>), grid, block, lds, stream, grp);
-  } else {
-    const dim3 grid((unsigned)tiles);
+  }
+  if constexpr (EPI != EPI_ACCUM_F32) {
+    auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>;
+    static thread_local uint64_t raised = 0;
+    if (const int rc = raise_lds(reinterpret_cast<const void*>(kern), lds, raised)) return rc;
     const DmaGemm& p = grp.prob[0];
-    launch_kernel((gemm_dma_kernel<BM, BN, WGM, WGN, NSTAGE, A_T, B_T, EPI, EDGE>), grid, block, lds, stream, p.A, p.B, (void*)p.C,
-                       p.bias, p.M, p.N, p.K, p.lda, p.ldb, pack_ldc(p.ldc, p.live_dim), p.aux, p.aux_out, p.live);
+    launch_kernel(kern, dim3((unsigned)tiles), block, lds, stream, p.A, p.B, (void*)p.C, p.bias, p.M, p.N, p.K, p.lda, p.ldb,
+                  pack_ldc(p.ldc, p.live_dim), p.aux, p.aux_out, p.live);
   }
   return check_launch("gemm_dma");
 }
@@ -709,7 +712,6 @@ bool gemm_dma_supported(const GemmArgs& g, int config) {
 int gemm_dma_group(const GemmArgs* gs, int count, int config, hipStream_t stream, const FinalizeJob* jobs, int n_jobs) {
   if (n_jobs < 0 || n_jobs > kMaxJobs || (n_jobs && gs[0].epi != EPI_ACCUM_F32)) return set_error(HANAYO_EINVAL, "gemm_dma: %d jobs", n_jobs);
   if (count < 1 || count > kMaxGroup) return set_error(HANAYO_EINVAL, "gemm_dma: group of %d", count);
-  if (count > 1 && gs[0].epi != EPI_ACCUM_F32) return set_error(HANAYO_EUNSUPPORTED, "gemm_dma: only weight gradients in groups");
   DmaGemmGroup grp{};
   grp.count = count;
   grp.n_jobs = n_jobs;
