@@ -377,8 +377,9 @@ int hanayo_executor_run(const hanayo_task* list, size_t n, const hanayo_exec_arg
  * list order).  Calls with lanes > 1 on one device are serialised on the host.
  *
  * The lanes are chosen by list scheduling with the schedule's own costs (forward 1, backward 2).  Of three or four lanes a rank
- * of at most four chunks uses two where its tasks are small (with N = max(F, 3H): fewer than 256 tiles of 256 x 256 in a
- * T x N product and fewer than 512 in an H x N one) and more would not shorten that schedule by a fifth: more are slower there.
+ * of at most four chunks uses fewer where its tasks are small (with N = max(F, 3H): fewer than 256 tiles of 256 x 256 in a
+ * T x N product and fewer than 512 in an H x N one): two unless all shorten that schedule by 2 and by an eighth (a fifth with
+ * args->ends or where a block's forward pass is below 5 us at the rates of large products), else the fewest within a twentieth of the shortest schedule.
  *
  * hanayo_executor_plan reports that plan without touching the GPU:
  *   lane  host [n]     lane of each task

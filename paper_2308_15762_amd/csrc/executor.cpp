@@ -141,31 +141,50 @@ bool small_tasks(const Shape& sh) {
   return tiles(sh.T, widest) < 256 && tiles(sh.H, widest) < 512;
 }
 
-// The plan a run uses: on all the lanes it is given, or on two of them.  Tasks on different lanes meet at events, which cost
+// Is a block's forward pass shorter than its launches, 5 us at the rates that large products reach?
+bool launch_bound(const Shape& sh) {
+  const double flop = 4.0 * sh.T * sh.H * (2.0 * sh.H + sh.F);
+  return flop < 5e-6 * (sh.dtype == HANAYO_BF16 ? 1.39e15 : 1.57e14);
+}
+
+// The plan a run uses: on all the lanes it is given, or on fewer.  Tasks on different lanes meet at events, which cost
 // the GPU about 10 us each (a barrier packet and a signal between two queues), and lanes that the list cannot keep busy only
 // add such meetings: a chunk's backward tasks run one after the other, so a rank of two chunks rarely has work for more than
-// two lanes.  The plan's own clock tells: small tasks of a rank of at most four chunks use two lanes unless more shorten the
-// plan by a fifth.  us of a step with two / with four lanes, the four's plan taking so many parts of the two's:
-//   0.96 (two chunks, rank 0): fp32 H = 256, T = 256 495 / 565; bf16 H = 256, T = 512 880 / 960; H = 512, T = 1024 1260 / 1410; H = 1024,
-//     T = 1024 2605 / 2760, T = 2048 4120 / 4200, T = 3072 5380 / 5465, T = 3840 6340 / 6345; H = 2048, T = 1024 7310 / 7430; H = 2560, T = 1024
-//     10660 / 10660; fp32 H = 512, T = 1024 4075 / 4130, H = 1024, T = 2048 12760 / 12870
-//   0.9 - 0.94 (one chunk, GPipe and 1F1B): H = 512, T = 1024 771 / 871 and 738 / 818; H = 1024, T = 2048 2350 / 2453 and 2317 / 2395
-//   0.86 (two chunks, two micro-batches): H = 256, T = 512 253 / 294; H = 1024, T = 1024 684 / 729, T = 2048 1085 / 1099
-//   0.82 - 0.99 (four chunks, a head of 4096 to 50304 columns, which orders their ends): H = 256, T = 512 1110 / 1238 to 1540 / 1641; H = 512,
-//     T = 1024 1733 / 1830 to 2950 / 3020; H = 1024, T = 2048 5440 / 5460 to 8410 / 8550, 2 blocks 10000 / 10000, 10920 / 10720, 12900 / 13115
-//   0.77 (two chunks, last rank): H = 256, T = 512 1002 / 1061; H = 512, T = 1024 1269 / 1236; H = 1024, T = 1024 2707 / 2697, T = 2048 4201 /
-//     4076
-//   0.51 (four chunks): H = 256, T = 512 1950 / 2005; H = 512, T = 1024 2570 / 2375; H = 1024, T = 1024 2 blocks 11260 / 10200, T = 2048 8520 /
-//     7510; H = 2048, T = 1024 14670 / 12960; H = 4096, T = 512 2 blocks 31700 / 28300
-//   0.95, but eight chunks (H = 512, T = 1024, a head of 50304 columns): 4300 / 3990
-// Larger tasks gain from all lanes, whose tails fill in, or lose nothing: 0.96 with H = 4096, T = 512 16450 / 16220, H = 3072, T = 1024
-// 14600 / 14320, H = 1024, T = 4096 6930 / 6870.  Results do not depend on it.
+// two lanes.  The plan's own clock tells.  Small tasks of a rank of at most four chunks use two lanes unless all of them shorten
+// the plan by two forward tasks and an eighth, or a fifth with the model's ends, whose tasks wait for each other, and where
+// launches are all there is to a task; then they use the fewest that come within a twentieth of the shortest plan.  us of a step
+// with two / three / four lanes, the plans of three and four taking so many parts of the two's (P, W, M, rank; F = 4 H):
+//   0.96 0.96 (4, 1, 8, 0)  bf16 H = 256, T = 512 965 / 1046 / 1043; H = 512, T = 1024 1258 / 1299 / 1365; H = 1024, T = 2048 4188 / 4192 / 4212;
+//                           T = 3840 6340 / - / 6345; fp32 H = 256, T = 256 999 / 1055 / 1064; H = 768, T = 334 3518 / 3531 / 3618
+//   0.9  0.9  (one chunk, GPipe)  bf16 H = 512, T = 1024 771 / - / 871; H = 1024, T = 2048 2350 / - / 2453
+//   0.92 0.83 (4, 1, 4, 2)  bf16 H = 256, T = 512 366 / 393 / 389; H = 640, T = 777 764 / 773 / 745; H = 1024, T = 2048 2037 / 2073 / 2017;
+//                           fp32 H = 768, T = 334 1687 / 1693 / 1666; H = 1024, T = 64, 2 blocks 2231 / 2098 / 2212
+//   0.88 0.83 (8, 1, 8, 5)  bf16 H = 256, T = 512 904 / 981 / 930; H = 512, T = 512, 3 blocks 2810 / 2924 / 2779; H = 1024, T = 2048 4056 / 4048 /
+//                           3986; fp32 H = 768, T = 334 3346 / 3216 / 3289; H = 1024, T = 64, 2 blocks 4371 / 4043 / 4294
+//   0.86 0.86 (4, 1, 4, 3)  bf16 H = 512, T = 1024 654 / 676 / 692; H = 640, T = 777 830 / 811 / 834; H = 1024, T = 2048 2235 / 2153 / 2184;
+//                           fp32 H = 256, T = 256 583 / 611 / 607; H = 768, T = 334 1834 / 1728 / 1808; H = 512, T = 1024 2097 / 2037 / 2078
+//   0.83 0.83 (4, 1, 2, 1: 6 and 5 forward tasks)  bf16 H = 512, T = 1024 312 / 360 / 356; H = 1024, T = 1024 669 / 699 / 686; fp32 H = 768, T = 334
+//                           848 / 842 / 868
+//   0.83 0.75 (4, 1, 8, 2)  bf16 H = 256, T = 512 905 / 992 / 1010; H = 640, T = 777 1540 / 1450 / 1394; H = 1024, T = 2048 4073 / 4022 / 3876;
+//                           fp32 H = 256, T = 256 1003 / 1123 / 1127; H = 768, T = 334 3439 / 3169 / 3156
+//   0.77 0.77 (4, 1, 8, 3)  bf16 H = 256, T = 512 1175 / 1190 / 1213; H = 1024, T = 2048 4266 / 4064 / 4128; fp32 H = 512, T = 256 1569 / 1421 / 1470;
+//                           H = 1024, T = 64, 2 blocks 4614 / 4118 / 4287
+//   0.72 0.51 (4, 2, 8, 0)  bf16 H = 256, T = 512 1950 / - / 2005; H = 512, T = 1024 2570 / - / 2375; H = 1024, T = 2048 8520 / - / 7510; H = 2048, T =
+//                           1024 14670 / - / 12960
+//   0.83 0.83 (4, 2, 4, 0, a head of 4096 columns)  bf16 H = 1024, T = 1024 3498 / 3594 / 3592
+//   eight chunks, 0.95 (H = 512, T = 1024, a head of 50304 columns): 4300 / - / 3990
+// Larger tasks gain from all lanes, whose tails fill in, or lose nothing: 0.96 with H = 4096, T = 512 16450 / - / 16220, H = 3072, T = 1024
+// 14600 / - / 14320, H = 1024, T = 4096 6930 / - / 6870.  Results do not depend on it.
 void plan_lanes(const hanayo_task* list, size_t n, int P, int W, int M, int rank, const Shape* sh, int lanes, bool ends,
                 double head_cost, const Plan& pl, LanePlan& lp) {
   const double length = schedule_lanes(list, n, P, W, M, rank, lanes, ends, head_cost, pl, lp);
   if (lanes > 2 && chunks_per_rank(W) <= kMaxLanes && sh && small_tasks(*sh)) {
-    LanePlan two;
-    if (length > 0.8 * schedule_lanes(list, n, P, W, M, rank, 2, ends, head_cost, pl, two)) lp = std::move(two);
+    LanePlan two, three;
+    const double by_two = schedule_lanes(list, n, P, W, M, rank, 2, ends, head_cost, pl, two);
+    if (by_two - length < 2.0 || length > (ends || launch_bound(*sh) ? 0.8 : 0.88) * by_two)
+      lp = std::move(two);
+    else if (lanes > 3 && schedule_lanes(list, n, P, W, M, rank, 3, ends, head_cost, pl, three) <= 1.05 * length)
+      lp = std::move(three);
   }
   // In the plan's own clock, how many lanes work during each task: the overlap of its interval
   // with every task's, over its length.

@@ -439,9 +439,9 @@ __device__ __forceinline__ void gemm_wave_body(WaveGemm<T> p, int wg) {
 // Weight gradients come with others of theirs and with jobs, other products in groups only where a caller sends them so: a single
 // one is passed by itself.  Its fields are where the kernel expects them without a search, and a quarter of the bytes goes
 // through the launch (1 us of host time).  Groups: four of 512 x 512 x 512 with a bias 5.3 us, one after the other 14.2; two of 2048 x
-// 1024 x 1024 13.4 and 18.3.  The first 14 words of a kernel's
-// arguments are in scalar registers when it starts (see the build flags); what the first loads depend on stands there, and
-// live_dim with ldc, so that nothing at the start waits for the argument block in memory (0.3 us).
+// 1024 x 1024 13.4 and 18.3.  The first 14 words of a kernel's arguments are in scalar registers when it starts (see the build
+// flags); what the first loads depend on stands there, and live_dim with ldc, so that nothing at the start waits for the argument
+// block in memory (0.3 us).
 template <typename T, int BM, int BN, int NST, bool A_T, bool B_T, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemm_wave_kernel(const T* A, const T* B, T* C, const T* bias, int M, int N, int K,
                                                             int lda, int ldb, unsigned ldc_live, const T* aux, T* aux_out,

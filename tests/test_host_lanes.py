@@ -22,12 +22,30 @@ def chunk(tokens, hidden=256, ffn=1024, dtype=hn.BF16):
 @pytest.mark.parametrize("P, W, M, rank, most", [
     (4, 2, 8, 0, 4), (4, 2, 8, 3, 4), (4, 2, 2, 0, 4), (2, 2, 4, 0, 4), (8, 4, 4, 0, 4),   # four chunks and more: half the time of two lanes
     (4, 1, 8, 0, 2), (2, 1, 4, 0, 2), (4, 1, 2, 0, 2), (8, 1, 16, 0, 2),                   # two chunks: up to a seventh
-    (4, 1, 8, 1, 4), (4, 1, 8, 2, 4), (4, 1, 8, 3, 4),                                     # the same on other ranks: a quarter and more
+    (4, 1, 8, 1, 4), (4, 1, 8, 2, 4), (4, 1, 8, 3, 3),                                     # the same on other ranks: a quarter and more
 ])
 def test_small_tasks_use_the_lanes_that_shorten_the_list(P, W, M, rank, most, dtype):
+    """Three where the fourth lane would not shorten the list further."""
     tasks = hn.hanayo_schedule(P, W, M, rank)
     for lanes in (1, 2, 4):
-        assert lanes_used(tasks, P, W, M, rank, lanes, chunk(512, dtype=dtype)) == min(lanes, most)
+        assert lanes_used(tasks, P, W, M, rank, lanes, chunk(512, hidden=64, ffn=256, dtype=dtype)) == min(lanes, most)
+
+
+@pytest.mark.parametrize("P, M, rank, given, launch_bound, otherwise", [
+    (4, 4, 3, 3, 2, 3), (4, 4, 3, 4, 2, 3),      # 14 forward tasks' time on two lanes, 12 on three and on four
+    (8, 8, 5, 3, 2, 3), (8, 8, 5, 4, 2, 3),      # 24, 21, 20
+    (4, 4, 2, 3, 2, 2), (4, 4, 2, 4, 2, 4),      # 12, 11, 10
+    (4, 8, 2, 3, 2, 3), (4, 8, 2, 4, 4, 4),      # 24, 20, 18
+    (4, 2, 1, 4, 2, 2),                          # 6, 5, 5: too little to win
+    (4, 4, 0, 3, 2, 2), (2, 4, 1, 4, 2, 2),      # 14, 13, 13; 14 on any
+])
+def test_the_line_follows_the_tasks_time(P, M, rank, given, launch_bound, otherwise):
+    """Two chunks: tasks whose launches are all there is to them (5 us a block) need more of a gain for a third lane."""
+    tasks = hn.hanayo_schedule(P, 1, M, rank)
+    # 24 T H^2 operations: 4.63 and 5.00 us at 1.39 PFLOP/s in bf16, 4.81 and 5.21 us at 157 TFLOP/s in fp32
+    for tokens, hidden, dtype, want in ((1024, 512, hn.BF16, launch_bound), (1106, 512, hn.BF16, otherwise), (480, 256, hn.FP32, launch_bound),
+                                        (520, 256, hn.FP32, otherwise)):
+        assert lanes_used(tasks, P, 1, M, rank, given, chunk(tokens, hidden, 4 * hidden, dtype)) == want
 
 
 def test_the_head_counts():
@@ -37,6 +55,9 @@ def test_the_head_counts():
         for lanes in (1, 2, 3, 4):
             lane, _ = hn.hanayo_executor_plan(tasks, 4, W, 4, 0, lanes, chunk(512), hn.EndsDesc(16384, 512, 1))
             assert len(set(lane.tolist())) == min(lanes, most)
+    # less than a fifth, whatever the tasks' time: 30, 25 and 25 forward tasks' time with this head
+    tasks = hn.hanayo_schedule(4, 2, 4, 0)
+    assert len(set(hn.hanayo_executor_plan(tasks, 4, 2, 4, 0, 4, chunk(1024, 1024, 4096), hn.EndsDesc(4096, 1024, 1))[0].tolist())) == 2
 
 
 @pytest.mark.parametrize("scheme", [hn.SCHEME_GPIPE, hn.SCHEME_1F1B])
