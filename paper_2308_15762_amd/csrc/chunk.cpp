@@ -220,10 +220,9 @@ WaveTile wave_choice(int dtype, const GemmArgs* gs, int count, double share, int
 // among themselves) give the same bits.  An executor's results do not depend on its lanes, nor on what its plan
 // expects of the other lanes, so between the two kinds the choice is made at one share for all of them.  Alone the split
 // kernel's many small tiles win up to K in the thousands; next to other lanes large tiles use the chip better.  us per
-// 16 x (forward, backward) of a block, share 0 / share 0.7, with 1, 2 and 4 lanes: H = 2048, T = 1024 8460 / 9248, 7996 /
-// 7507, 8343 / 7581; H = 1280, T = 1527 6445 / 6713, 5722 / 5373, 5994 / 5554; H = 512, T = 4096 4210 / 4202, 3274 / 3112,
-// 3404 / 3227.  Up to K = 1024 the time goes into start and epilogue, and nothing is won with lanes (H = 256, T = 2048:
-// 1597 / 1685, 1189 / 1201, 1241 / 1253).
+// 16 x (forward, backward) of a block, share 0 / share 0.7, with 1 and 2 lanes: H = 2048, T = 1024 8460 / 9248, 7996 / 7507;
+// H = 1280, T = 1527 6445 / 6713, 5722 / 5373; H = 512, T = 4096 4210 / 4202, 3274 / 3112.  Up to K = 1024 the time goes into start
+// and epilogue, and nothing is won with lanes (H = 256, T = 2048: 1597 / 1685, 1189 / 1201).
 WaveTile choose_wave(int dtype, const GemmArgs* gs, int count) {
   if (dtype == HANAYO_BF16 && gemm_dma_config_exists(g_gemm_config)) {
     bool forced = true;  // a kernel that does not take these problems (or fp32) forces nothing

@@ -28,7 +28,7 @@ bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) 
 // The head works on the labelled rows only (a bidirectional model labels about one position in seven): their hidden
 // states are gathered, and the three GEMMs, the loss and their gradients run over `live` rows, a number that stays on
 // the device.  Measured (MI355X), bidirectional, T = 4096, H = 1024, V = 30592, 460 labelled rows: 828 us over all rows,
-// 209 over these (of which 72 add to d_head, 250 MB read and written; the row list takes 5, the gather 5, the scatter 15).
+// 200 over these (of which 72 add to d_head, 250 MB read and written; listing and gathering the rows take 6, the scatter 15).
 // Tiles are chosen for T rows, whatever their share: over all rows 825 - 877 us, over these 160, 244, 462 and 825 us for 0.2,
 // 15, 50 and 100 % labelled; T = 2048, H = 4096, V = 50304 2279 - 2522 us and 625, 827, 1391, 2365.
 struct HeadLayout {

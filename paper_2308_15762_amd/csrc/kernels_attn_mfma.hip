@@ -1185,7 +1185,7 @@ bool dma_ok(const AttnArgs& a) {
 //   no mask, d = 80: s = 256 96 10.2 / 28.9 and 11.1 / 24.5; s = 512 96 16.7 / 46.2 and 16.5 / 35.7; s = 1024 128 29.6 / 83.1 and
 //                    27.4 / 74.6, 192 30.3 / 84.8 and 39.3 / 113
 // Next to other lanes idle CUs are not lost and only the shorter chain counts, so the lines lie lower, the same ones for every
-// lane count (the kernels do not give the same bits).  Change of a step with 4 lanes, forward / backward split, %:
+// lane count (the kernels do not give the same bits).  Change of a step with all of 4 lanes in use, forward / backward split, %:
 //   causal, d = 64:  s = 512 128 -0.9 / -2.5, 192 +0.9 / +1.9; s = 2048 128 -2.2 / -10.6
 //   causal, d = 80:  s = 128 32 -2.7 / -5.9, 64 +0.3 / -0.1 (with 2 lanes -0.1 / +1.6); s = 512 96 -0.6 / -1.6, 128 +1.3 / +3.7; s = 2048 128 -1.5 / -3.1
 //   no mask, d = 64: s = 512 96 -0.8 / -1.3, 128 +0.8 / +3.1;  d = 80: s = 512 64 -2.2 / -2.9, 96 +2.4 / +0.3, 128 +3.2 / +7.4

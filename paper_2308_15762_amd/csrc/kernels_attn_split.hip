@@ -202,8 +202,10 @@ constexpr int kBwdStage = 2 * kTile32<DP> + 512;
 // Stages of the backward kernel's rings.  One, and at most 256 registers, leave room for a second workgroup on a CU (for more
 // below d = 80), whose wavefronts cover the loads better than a second stage does: us with two and with one: d = 64, s = 256, 8
 // pairs 6.5 and 5.9; s = 509, 36 pairs, no mask 27.7 and 25.6; s = 1024, 8 heads 16.8 and 15.2; d = 32, s = 500, 8 heads 7.9 and 7.1; d =
-// 80, s = 1024, 4 heads 19.2 and 17.4; s = 777, 8 heads 19.2 and 18.7; s = 96, 16 pairs 6.5 and 6.4; d = 96, s = 384, 10 heads 12.1 and 11.6,
-// s = 700, 6 heads 17.4 and 18.0.  d = 128 does not fit 256 registers (s = 512, 8 heads 15.1 and 23.4).
+// 80, s = 1024, 4 heads 19.2 and 17.4; s = 777, 8 heads 19.2 and 18.7; s = 96, 16 pairs 6.5 and 6.4; d = 96, s = 384, 10 heads 10.6 and 10.0,
+// s = 1024, 4 and 8 heads 19.5 and 18.0, 25.3 and 21.6, s = 700, 6 heads, no mask 25.3 and 17.8.  A few more workgroups than CUs under a
+// causal mask go the other way, the last ones being short: d = 96, s = 700, 6 heads 16.2 and 16.5, s = 600, 8 heads 14.6 and 15.4; twice the
+// kernels for that are not worth it.  d = 128 does not fit 256 registers (s = 512, 8 heads 15.1 and 23.4).
 template <int D>
 constexpr int kBwdStages = D == 128 ? 2 : 1;
 

@@ -212,6 +212,10 @@ next_tile:
   // while the first K tiles are on their way, each thread a run of neighbouring intervals, whose ends they share; between main
   // loop and epilogue, every end twice, it held up each tile: FC1 / FC2's input gradient 777 x 2560 x 640 13.5 / 12.1 us a launch
   // then and 12.5 / 11.0 now, 1527 x 3072 x 768 18.0 / 16.3 and 17.2 / 15.2, 4096 x 4096 x 1024 39.0 / 36.4 and 37.9 / 35.3.
+  // Its 16 KiB stand behind the ring instead of in it: 256 x 256 tiles take 144 KiB and, as before, all registers of a CU; 256 x 128
+  // tiles 160, beside which only kernels without LDS run; 128 x 128 tiles 80 (two on a CU, as before) and, with three stages, 112, beside
+  // which another lane's 64 KiB no longer fit.  Steps of 18 shapes with two to four lanes, H = 512 - 2560, take 0.98 - 1.005 of
+  // the time with the table in the ring.
   constexpr bool kGelu = EPI == EPI_BIAS_GELU || EPI == EPI_MUL_DGELU;
   float2* gelu_tab = reinterpret_cast<float2*>(smem + NSTAGE * STAGE_BYTES);
   auto build_table = [&]() {
