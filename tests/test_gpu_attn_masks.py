@@ -1,5 +1,6 @@
-"""bf16 attention backward: a masked (query, key) pair has probability zero whatever the query's log-sum-exp holds, so a row whose
-softmax went wrong (NaN, minus infinity) reaches no gradient of the keys that the mask keeps from it."""
+"""bf16 attention backward: a masked (query, key) pair has probability zero whatever the query's log-sum-exp holds (NaN, minus infinity),
+so that alone reaches no gradient of the keys that the mask keeps from the query.  (An output or output gradient that is not
+finite still does, as zero times NaN in dK; and at head dim 64 the 128-row kernels mask the scores before the exponential.)"""
 
 import pytest
 import torch
